@@ -1,0 +1,502 @@
+"""What a training program has this library do, as cases to be timed: one mini-batch of one pipeline stage.
+
+A pass is gradient reset, forward and backward of every micro-batch and, where the stage groups them, the weight
+gradients, through the C ABI's functions as the binding names them.  The program around it is an ordinary one: it
+keeps its parameters, their gradients and the input gradients each in one flat buffer (what an optimizer or an
+all-reduce would walk over), creates the stage once and calls it with device pointers.
+
+Six model shapes, with the sizes of the repository's workloads and ranges around them:
+  mlp        two-branch perceptron in fp32: launch latency, the smallest calls
+  towers     feature towers of unequal input widths, merged (several micro-batches a step: every schedule)
+  transformer   pre-LN transformer branches, mean pool, merged head, cross-entropy
+  recommender   embedding bags summed, dot interaction, MLPs, fp32 tables beside bf16 layers
+  concat        embedding bags concatenated next to wide dense branches
+  hetero        eight branches of five widths and three depths, from one row to several hundred
+
+Schedules, as the benchmark and the pipeline use them:
+  plain         fw_j, bw_j in turn on one stream, weight gradients accumulated by every backward pass
+  grouped       the same with the weight gradients of all layers in one launch behind the backward pass
+  two_streams   1F1B with two micro-batches in flight, forward and backward passes on two streams
+  graph         kFkB with every micro-batch in flight, two lanes, group launches, one captured HIP graph
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2406_17145_amd import binding as B
+
+DEV = "cuda:0"
+TORCH_TYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "i32": torch.int32}
+MODELS = ("mlp", "towers", "transformer", "recommender", "concat", "hetero")
+
+
+def listed():
+    return [
+        # the smallest call that is made in earnest: a step of 4 x 8 fp32 samples, all launch latency
+        dict(name="mlp_f32_8x4", model="mlp", b=8, n_micro=4, schedule="plain", branches=2, d_in=64, d_hid=128, d_out=64),
+        # feature towers as the benchmark runs them: few rows, weights streamed, replayed from a graph
+        dict(name="towers_64x8_graph", model="towers", b=64, n_micro=8, schedule="graph", widths="942,3820,2048,1",
+             hidden=1000, depth=3, act="gelu"),
+        # the same stage in a 1F1B pipeline with a larger micro-batch: eager, accumulating in every backward pass
+        dict(name="towers_512x4_1f1b", model="towers", b=512, n_micro=4, schedule="two_streams", widths="942,3820,2048,1",
+             hidden=1000, depth=3, act="gelu"),
+        # the paper's width: seven towers of four 4096-wide layers, half a billion parameters
+        dict(name="towers_wide_512", model="towers", b=512, n_micro=1, schedule="grouped",
+             widths="4096,4096,4096,4096,4096,4096,4096", hidden=4096, depth=4, act="gelu"),
+        # the benchmark's headline stage
+        dict(name="transformer_4x512", model="transformer", b=4, n_micro=1, schedule="grouped", branches=4, layers=2,
+             d_model=1024, d_ff=4096, seq=512, head_out=1024, classes=1000),
+        # the paper's depth: four branches of eight layers over sequences of 256, the largest step
+        dict(name="transformer_deep_8x256", model="transformer", b=8, n_micro=1, schedule="grouped", branches=4, layers=8,
+             d_model=1024, d_ff=4096, seq=256, head_out=1024, classes=1000),
+        # a small transformer stage with ragged sizes, two micro-batches accumulated
+        dict(name="transformer_ragged_3x100", model="transformer", b=3, n_micro=2, schedule="plain", branches=2, layers=2,
+             d_model=256, d_ff=1000, seq=100, head_out=200, classes=37),
+        # recommendation stage: 26 tables of 100 000 rows, bags of 20
+        dict(name="recommender_2048", model="recommender", b=2048, n_micro=1, schedule="grouped", dense=13, bottom="512,256,128",
+             tables=26, rows=100000, dim=128, bag=20, ragged=False, top="1024,1024,512,256,1", act="gelu"),
+        # bags of 0 to 12 rows, odd batch, accumulation over three micro-batches
+        dict(name="recommender_ragged_300x3", model="recommender", b=300, n_micro=3, schedule="plain", dense=13, bottom="100,64",
+             tables=9, rows=20000, dim=64, bag=12, ragged=True, top="200,100,1", act="relu"),
+        # the paper's recommendation shape: million-row tables, bags of 100 rows concatenated, 4096-wide layers
+        dict(name="concat_256", model="concat", b=256, n_micro=1, schedule="grouped", n_dense=7, width=4096, depth=4, tables=7,
+             rows=1000000, dim=64, bag=100, top="4096,4096,1", act="gelu"),
+        # the heterogeneous stage with a single sample: every weight read for one row
+        dict(name="hetero_1", model="hetero", b=1, n_micro=1, schedule="grouped", branches=8, base=256, out=512, loss=True),
+        # the same as a stage in the middle of a pipeline: outputs handed on, output gradients received
+        dict(name="hetero_128_mid", model="hetero", b=128, n_micro=1, schedule="grouped", branches=8, base=256, out=512, loss=False),
+    ]
+
+
+def draw(rng):
+    def log(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    def one():
+        model = rng.choice(MODELS)
+        n_micro = rng.randint(1, 4)
+        sched = rng.choice(["plain", "grouped", "two_streams"])
+        if model == "mlp":
+            return dict(model=model, b=log(1, 64), n_micro=n_micro, schedule=rng.choice(["plain", "two_streams"]),
+                        branches=rng.randint(2, 4), d_in=log(16, 300), d_hid=log(16, 400), d_out=log(8, 200))
+        if model == "towers":
+            if rng.random() < 0.5:
+                n_micro, sched = rng.choice([4, 6, 8]), "graph"
+            hidden = log(200, 4096)
+            n = rng.randint(2, 7)
+            same = rng.random() < 0.3
+            widths = [hidden] * n if same else [log(1, 4096) for _ in range(n)]
+            return dict(model=model, b=log(8, 1024), n_micro=n_micro, schedule=sched, widths=",".join(map(str, widths)),
+                        hidden=hidden, depth=rng.randint(2, 4), act="gelu")
+        if model == "transformer":
+            d = 64 * log(2, 16)
+            return dict(model=model, b=log(1, 8), n_micro=rng.randint(1, 2), schedule=sched, branches=rng.randint(1, 4),
+                        layers=rng.randint(1, 8), d_model=d, d_ff=rng.choice([4 * d, 2 * d, log(200, 4096)]), seq=log(24, 512),
+                        head_out=log(64, 1024), classes=log(10, 1500))
+        if model == "recommender":
+            dim, b = rng.choice([16, 32, 64, 128]), log(64, 4096)
+            # (ReLU only with few rows: among millions of pre-activations some are so close to zero that the order of a
+            # sum decides their mask, and the gradient of that sample's row with it)
+            return dict(model=model, b=b, n_micro=n_micro, schedule=rng.choice(["plain", "grouped"]), dense=13,
+                        bottom="%d,%d" % (log(32, 512), dim), tables=rng.randint(2, 26), rows=log(1000, 100000), dim=dim,
+                        bag=log(1, 40), ragged=rng.random() < 0.5, top="%d,%d,1" % (log(64, 1024), log(32, 1024)),
+                        act="relu" if b <= 512 else "gelu")
+        if model == "concat":
+            width = log(256, 4096)
+            return dict(model=model, b=log(16, 512), n_micro=1, schedule=rng.choice(["plain", "grouped"]), n_dense=rng.randint(1, 7),
+                        width=width, depth=rng.randint(1, 4), tables=rng.randint(2, 7), rows=log(10000, 1000000), dim=64,
+                        bag=log(4, 100), top="%d,1" % log(256, 4096), act="gelu")
+        return dict(model=model, b=log(1, 512), n_micro=n_micro, schedule=rng.choice(["plain", "grouped"]), branches=rng.randint(3, 8),
+                    base=rng.choice([64, 128, 200, 256]), out=log(64, 512), loss=rng.random() < 0.5)
+
+    most = max(_cost(c) for c in listed())
+    while True:
+        c = one()
+        if _cost(c) <= most:
+            return c
+
+
+# ---- the operator graphs -------------------------------------------------------------------------------------
+class _Graph:
+    def __init__(self):
+        self.ops = []
+
+    def add(self, kind, inputs=(), **kw):
+        self.ops.append(dict(kind=kind, inputs=list(inputs), **kw))
+        return len(self.ops) - 1
+
+    def input(self, features, dtype, **kw):
+        return self.add("input", out_features=features, dtype=dtype, seq_len=kw.pop("seq_len", 1), rows_extra=kw.pop("rows_extra", 0),
+                        role=kw.pop("role", "data"), **kw)
+
+    def linear(self, x, k, n, act="none", dtype="bf16", out_dtype=None):
+        return self.add("linear", (x,), in_features=k, out_features=n, act=act, bias=True, dtype=dtype, out_dtype=out_dtype or dtype)
+
+    def mlp(self, x, k, widths, act):
+        """Layers of the given widths; the last one emits an fp32 logit when it is one column wide."""
+        for j, w in enumerate(widths):
+            last = j == len(widths) - 1 and w == 1
+            x = self.linear(x, k, w, "none" if last else act, out_dtype="f32" if last else None)
+            k = w
+        return x, k
+
+    def bags(self, c, concat):
+        out = []
+        for _ in range(c["tables"]):
+            idx = self.input(c["bag"], "i32", role="indices", rows=c["rows"], ragged=bool(c.get("ragged")))
+            off = self.input(1, "i32", rows_extra=1, role="offsets", of=idx)
+            kw = dict(num_rows=c["rows"], bag_size=c["bag"], dtype="bf16")
+            if concat:
+                out.append(self.add("embedding_bag_concat", (idx, off), in_features=c["dim"], out_features=c["bag"] * c["dim"], **kw))
+            else:
+                out.append(self.add("embedding_bag_sum", (idx, off), out_features=c["dim"], **kw))
+        return out
+
+
+def _ints(text):
+    return [int(v) for v in text.split(",")]
+
+
+def _ops(c):
+    g = _Graph()
+    total = c["b"] * c["n_micro"]
+    if c["model"] == "mlp":
+        outs = []
+        for _ in range(c["branches"]):
+            h = g.linear(g.input(c["d_in"], "f32"), c["d_in"], c["d_hid"], "relu", "f32")
+            outs.append(g.linear(h, c["d_hid"], c["d_out"], "none", "f32"))
+        w = c["d_out"] * c["branches"]
+        y = g.add("concat", outs, out_features=w, dtype="f32")
+        g.add("loss_mse", (y, g.input(w, "f32", role="target", draw="normal")), loss_scale=0.5 / (total * w))
+    elif c["model"] == "towers":
+        outs = [g.mlp(g.input(w, "bf16"), w, [c["hidden"]] * c["depth"], c["act"])[0] for w in _ints(c["widths"])]
+        w = c["hidden"] * len(outs)
+        h = g.linear(g.add("concat", outs, out_features=w, dtype="bf16"), w, c["hidden"], c["act"])
+        y = g.linear(h, c["hidden"], 1, out_dtype="f32")
+        g.add("loss_mse", (y, g.input(1, "f32", role="target", draw="uniform")), loss_scale=1.0 / total)
+    elif c["model"] == "transformer":
+        d, s = c["d_model"], c["seq"]
+        kw = dict(out_features=d, dtype="bf16")
+        pooled = []
+        for _ in range(c["branches"]):
+            x = g.input(d, "bf16", seq_len=s)
+            for _ in range(c["layers"]):
+                a = g.add("layernorm", (x,), eps=1e-5, seq_len=s, **kw)
+                o = g.add("attention", (g.linear(a, d, 3 * d),), heads=d // 64, seq_len=s, **kw)
+                h = g.add("add", (x, g.linear(o, d, d)), **kw)
+                f = g.linear(g.add("layernorm", (h,), eps=1e-5, seq_len=s, **kw), d, c["d_ff"], "gelu")
+                x = g.add("add", (h, g.linear(f, c["d_ff"], d)), **kw)
+            pooled.append(g.add("meanpool", (x,), seq_len=s, **kw))
+        w = d * c["branches"]
+        h = g.linear(g.add("concat", pooled, out_features=w, dtype="bf16"), w, c["head_out"])
+        z = g.linear(h, c["head_out"], c["classes"], out_dtype="f32")
+        g.add("loss_ce", (z, g.input(1, "i32", role="target", draw="label", classes=c["classes"])), loss_scale=1.0 / total)
+    elif c["model"] == "recommender":
+        vec = g.mlp(g.input(c["dense"], "bf16", draw="lognormal"), c["dense"], _ints(c["bottom"]), c["act"])[0]
+        vecs = [vec] + g.bags(c, False)
+        n = len(vecs)
+        x = g.add("concat", vecs, out_features=c["dim"] * n, dtype="bf16")
+        w = c["dim"] + n * (n - 1) // 2
+        z, _ = g.mlp(g.add("dot_interact", (x,), in_features=c["dim"], out_features=w, dtype="bf16"), w, _ints(c["top"]), c["act"])
+        g.add("loss_bce", (z, g.input(1, "f32", role="target", draw="click")), loss_scale=1.0 / total)
+    elif c["model"] == "concat":
+        outs = [g.mlp(g.input(c["width"], "bf16"), c["width"], [c["width"]] * c["depth"], c["act"])[0] for _ in range(c["n_dense"])]
+        outs += g.bags(c, True)
+        w = c["n_dense"] * c["width"] + c["tables"] * c["bag"] * c["dim"]
+        z, _ = g.mlp(g.add("concat", outs, out_features=w, dtype="bf16"), w, _ints(c["top"]), c["act"])
+        g.add("loss_bce", (z, g.input(1, "f32", role="target", draw="click")), loss_scale=1.0 / total)
+    else:
+        outs = []
+        for i in range(c["branches"]):
+            w = c["base"] * 2 ** (i % 5)
+            x = g.mlp(g.input(w, "bf16"), w, [w] * (2 + i % 3), "gelu")[0]
+            outs.append(g.linear(x, w, c["out"]))
+        w = c["out"] * c["branches"]
+        x = g.add("concat", outs, out_features=w, dtype="bf16")
+        y = g.linear(x, w, w, out_dtype="f32" if c["loss"] else "bf16")
+        if c["loss"]:
+            g.add("loss_mse", (y, g.input(w, "f32", role="target", draw="normal")), loss_scale=1.0 / (total * w))
+    return g.ops
+
+
+def _rows(ops, b):
+    """Rows of every operator's output."""
+    rows = []
+    for op in ops:
+        if op["kind"] == "input":
+            rows.append(b * op["seq_len"] + op["rows_extra"])
+        elif op["kind"] in ("meanpool", "embedding_bag_sum", "embedding_bag_concat"):
+            rows.append(b)
+        else:
+            rows.append(rows[op["inputs"][0]])
+    return rows
+
+
+def _out_type(op):
+    return op.get("out_dtype", op.get("dtype"))
+
+
+def _is_output(ops, i):
+    return not ops[i]["kind"].startswith("loss") and ops[i]["kind"] != "input" and not any(i in op["inputs"] for op in ops)
+
+
+# ---- preparation ----------------------------------------------------------------------------------------------
+def _flat(shapes, dtype):
+    """One buffer and a view of it per shape; every view starts on a 128-byte line."""
+    sizes = [-(-math.prod(s) // 64) * 64 for s in shapes]
+    buf = torch.zeros(max(1, sum(sizes)), dtype=dtype, device=DEV)
+    views, at = [], 0
+    for s, n in zip(shapes, sizes):
+        views.append(buf[at:at + math.prod(s)].view(s))
+        at += n
+    return buf, views
+
+
+def _param_shapes(op):
+    """(matrix shape or None, vector lengths): matrices have padded rows."""
+    k = op["kind"]
+    if k == "linear":
+        return (op["out_features"], B.gpp_ld(op["in_features"])), [op["out_features"]]
+    if k == "layernorm":
+        return None, [op["out_features"]] * 2
+    if k.startswith("embedding_bag"):
+        return (op["num_rows"], B.gpp_ld(op["in_features"] if k.endswith("concat") else op["out_features"])), []
+    return None, []
+
+
+class Program:
+    """One stage with its parameters, gradients and a mini-batch of inputs on the GPU."""
+
+    def __init__(self, case, seed):
+        self.handle = None
+        self.case, self.ops = case, _ops(case)
+        ops, b, n_micro = self.ops, case["b"], case["n_micro"]
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        self._parameters(gen)
+        sched = case["schedule"]
+        flags = {"plain": 0, "two_streams": 0, "grouped": B.FLAG_GROUPED_DW,
+                 "graph": B.FLAG_GROUPED_DW | B.FLAG_SHARED_GPU | B.flag_group_launches(2)}[sched]
+        slots = {"plain": 1, "grouped": 1, "two_streams": min(2, n_micro), "graph": n_micro}[sched]
+        self.desc, self.keep = B.build_desc(ops, b, slots, flags, self.param_ptrs, self.grad_ptrs)
+        n_ws = B.gpp_stage_workspace_bytes(self.desc)
+        self.ws = torch.empty(n_ws + 256, dtype=torch.uint8, device=DEV)
+        self.handle = B.gpp_stage_create(self.desc, (self.ws.data_ptr() + 255) // 256 * 256, n_ws)
+        self._tensors(gen, _rows(ops, b))
+        self.tasks = B.gpp_schedule_tasks(n_micro, slots * b, 1 if sched == "two_streams" else slots, b)
+        self.graph = None
+        if sched in ("two_streams", "graph"):
+            self.streams = [torch.cuda.Stream(device=DEV) for _ in range(2)]
+        if sched == "graph":
+            self._enqueue()
+            torch.cuda.synchronize()
+            self.graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(self.graph):
+                self._enqueue()
+
+    def _parameters(self, gen):
+        """Weights N(0, 1/fan_in), small biases, LayerNorm gains around one, table rows U(-0.01, 0.01); padding columns zero."""
+        mats, tabs, vecs = [], [], []
+        for i, op in enumerate(self.ops):
+            m, v = _param_shapes(op)
+            if m:
+                (tabs if op["kind"].startswith("embedding") else mats).append((i, m))
+            vecs += [(i, (n,)) for n in v]
+        f32 = self.case["model"] == "mlp"
+        _, p_mats = _flat([s for _, s in mats], torch.float32 if f32 else torch.bfloat16)
+        _, p_vecs = _flat([s for _, s in vecs], torch.float32)
+        _, p_tabs = _flat([s for _, s in tabs], torch.float32)
+        self.grad_weights, g_mats = _flat([s for _, s in mats], torch.float32)
+        self.grad_vectors, g_vecs = _flat([s for _, s in vecs], torch.float32)
+        self.grad_tables, g_tabs = _flat([s for _, s in tabs], torch.float32) if tabs else (None, [])
+        self.params = (p_mats, p_vecs, p_tabs)
+        self.param_ptrs, self.grad_ptrs = {}, {}
+        for group, ps, gs in ((mats, p_mats, g_mats), (tabs, p_tabs, g_tabs), (vecs, p_vecs, g_vecs)):
+            for (i, _), p, g in zip(group, ps, gs):
+                op = self.ops[i]
+                if op["kind"] == "linear" and p.dim() == 2:
+                    p[:, :op["in_features"]].normal_(0.0, op["in_features"] ** -0.5, generator=gen)
+                elif p.dim() == 2:
+                    p[:, :op["in_features"] if op["kind"].endswith("concat") else op["out_features"]].uniform_(-0.01, 0.01, generator=gen)
+                else:
+                    p.normal_(1.0 if op["kind"] == "layernorm" and i not in self.param_ptrs else 0.0, 0.02, generator=gen)
+                self.param_ptrs.setdefault(i, []).append(p.data_ptr())
+                self.grad_ptrs.setdefault(i, []).append(g.data_ptr())
+        for d in (self.param_ptrs, self.grad_ptrs):
+            for v in d.values():
+                v.extend([None] * (2 - len(v)))
+
+    def _tensors(self, gen, rows):
+        ops, n_micro = self.ops, self.case["n_micro"]
+        ins = [i for i, op in enumerate(ops) if op["kind"] == "input"]
+        outs = [i for i in range(len(ops)) if _is_output(ops, i)]
+        perms, cdf = {}, {}
+        self.inputs = []
+        for _ in range(n_micro):
+            mb = []
+            for i in ins:
+                mb.append(self._input(gen, ops[i], i, rows[i], perms, cdf))
+            self.inputs.append(mb)
+        floats = [i for i in ins if ops[i]["role"] == "data"]
+        kind = TORCH_TYPE[ops[floats[0]]["dtype"]]
+        self.grad_inputs, g_in = _flat([(rows[i], ops[i]["out_features"]) for i in floats] * n_micro, kind)
+        self.outputs, self.grad_outputs, out_views, gout_views = None, None, [], []
+        if outs:
+            shapes = [(rows[i], ops[i]["out_features"]) for i in outs] * n_micro
+            self.outputs, out_views = _flat(shapes, TORCH_TYPE[_out_type(ops[outs[0]])])
+            self.grad_outputs, gout_views = _flat(shapes, TORCH_TYPE[_out_type(ops[outs[0]])])
+            for v in gout_views:
+                v.normal_(0.0, 1.0 / math.sqrt(v.numel() * n_micro), generator=gen)
+        self.losses, loss_views = _flat([(1,)] * n_micro, torch.float32)
+        self.io = []
+        for j, mb in enumerate(self.inputs):
+            gi = iter(g_in[j * len(floats):(j + 1) * len(floats)])
+            part = slice(j * len(outs), (j + 1) * len(outs))
+            self.io.append(([t.data_ptr() for t in mb], [t.data_ptr() for t in out_views[part]], loss_views[j].data_ptr(),
+                            [t.data_ptr() for t in gout_views[part]] or None,
+                            [next(gi).data_ptr() if i in floats else None for i in ins]))
+
+    def _input(self, gen, op, i, rows, perms, cdf):
+        n, role = op["out_features"], op["role"]
+        if role == "indices":          # bounded Zipf(1.05) ranks, permuted per table
+            r = op["rows"]
+            if r not in cdf:
+                c = np.cumsum(np.arange(1, r + 1, dtype=np.float64) ** -1.05)
+                cdf[r] = torch.from_numpy(c / c[-1]).to(DEV)
+            if i not in perms:
+                perms[i] = torch.randperm(r, generator=gen, device=DEV).to(torch.int32)
+            u = torch.rand((rows, n), generator=gen, device=DEV, dtype=torch.float64)
+            return perms[i][torch.searchsorted(cdf[r], u).clamp_(max=r - 1)].contiguous()
+        if role == "offsets":          # full bags, or lengths 0 .. bag_size
+            src = self.ops[op["of"]]
+            bag = src["out_features"]
+            if src["ragged"]:
+                lens = torch.randint(0, bag + 1, (rows - 1,), generator=gen, device=DEV)
+            else:
+                lens = torch.full((rows - 1,), bag, device=DEV)
+            return torch.cat([torch.zeros(1, dtype=torch.int64, device=DEV), lens.cumsum(0)]).to(torch.int32).view(rows, 1)
+        how = op.get("draw", "normal")
+        if how == "label":
+            return torch.randint(0, op["classes"], (rows, n), generator=gen, device=DEV, dtype=torch.int32)
+        t = torch.empty((rows, n), dtype=torch.float32, device=DEV)
+        if how == "normal":
+            t.normal_(0.0, 1.0, generator=gen)
+        elif how == "lognormal":
+            t.log_normal_(0.0, 1.0, generator=gen)
+        elif how == "uniform":
+            t.uniform_(0.0, 1.0, generator=gen)
+        else:                          # "click": 3 % positives
+            t.copy_(torch.rand((rows, n), generator=gen, device=DEV) < 0.03)
+        return t.to(TORCH_TYPE[op["dtype"]])
+
+    def _enqueue(self):
+        h, main = self.handle, torch.cuda.current_stream()
+        sched = self.case["schedule"]
+        if sched in ("plain", "grouped"):
+            s = main.cuda_stream
+            B.gpp_stage_grad_reset(h, s)
+            for ins, outs, loss, gouts, gins in self.io:
+                B.gpp_stage_forward(h, 0, ins, outs, loss, s)
+                B.gpp_stage_backward(h, 0, gouts, gins, s)
+                if sched == "grouped":
+                    B.gpp_stage_backward_weights(h, s)
+            return
+        for s in self.streams:
+            s.wait_stream(main)
+        raw = [s.cuda_stream for s in self.streams]
+        if sched == "graph" and all(B.gpp_stage_lanes(h)):    # (some widths have layers that no lanes are allowed with)
+            self.marshalled = B.gpp_stage_run_schedule_lanes(h, self.tasks, self.io, raw, raw)
+        else:
+            self.marshalled = B.gpp_stage_run_schedule(h, self.tasks, self.io, raw[0], raw[1])
+        for s in self.streams:
+            main.wait_stream(s)
+
+    def step(self):
+        if self.graph is not None:
+            self.graph.replay()
+        else:
+            self._enqueue()
+        out = dict(losses=self.losses, grad_inputs=self.grad_inputs, grad_weights=self.grad_weights, grad_vectors=self.grad_vectors)
+        if self.outputs is not None:
+            del out["losses"]
+            out["outputs"] = self.outputs
+        if self.grad_tables is not None:
+            out["grad_tables"] = self.grad_tables
+        return out
+
+    def __del__(self):
+        if self.handle is not None and torch is not None:      # (at interpreter exit the modules may be gone first)
+            torch.cuda.synchronize()
+            B.gpp_stage_destroy(self.handle)
+            self.handle = None
+
+
+def prepare(case, seed):
+    return Program(case, seed)
+
+
+def run(state):
+    return state.step()
+
+
+# ---- what a pass cannot do without ------------------------------------------------------------------------------
+def _distinct_rows(n_rows, draws):
+    """Expected number of distinct rows among `draws` bounded-Zipf(1.05) indices."""
+    p = np.arange(1, n_rows + 1, dtype=np.float64) ** -1.05
+    return float(-np.expm1(draws * np.log1p(-p / p.sum())).sum())
+
+
+def work(case):
+    """Bytes: parameters and inputs read once, gradients, input gradients and outputs written once.  Flops: the three
+    products of every Linear, the six of attention (two forward, four backward)."""
+    ops = _ops(case)
+    rows = _rows(ops, case["b"])
+    m = case["n_micro"]
+    by = fl = 0.0
+    for i, op in enumerate(ops):
+        k, es = op["kind"], 4 if _out_type(op) in ("f32", "i32") else 2
+        if k == "input":
+            by += m * rows[i] * op["out_features"] * (2 * es if op["role"] == "data" else es)
+        elif k == "linear":
+            p = op["in_features"] * op["out_features"]
+            by += p * ((4 if op["dtype"] == "f32" else 2) + 4) + 8 * op["out_features"]
+            fl += m * 6.0 * rows[i] * p
+        elif k == "layernorm":
+            by += 16 * op["out_features"]
+        elif k == "attention":
+            fl += m * 12.0 * case["b"] * op["seq_len"] ** 2 * op["out_features"]
+        elif k.startswith("embedding_bag"):
+            share = 0.5 if case.get("ragged") else 1.0
+            n = int(m * case["b"] * op["bag_size"] * share)
+            by += 8 * _distinct_rows(op["num_rows"], n) * (op["in_features"] if k.endswith("concat") else op["out_features"])
+        if _is_output(ops, i):
+            by += 2 * m * rows[i] * op["out_features"] * es
+    return dict(bytes=by, flops=fl)
+
+
+def _cost(case):
+    """Rough seconds of a pass, to keep drawn cases below the largest listed one."""
+    ops = _ops(case)
+    w = 0.0
+    rows = _rows(ops, case["b"])
+    for i, op in enumerate(ops):
+        if op["kind"] == "linear":
+            p = op["in_features"] * op["out_features"]
+            w += p * 12 / 4e12 + case["n_micro"] * (6.0 * max(rows[i], 64) * p / 7e14 + 1e-6)
+        elif op["kind"].startswith("embedding_bag"):
+            w += case["n_micro"] * case["b"] * op["bag_size"] * 3e-10
+    return w
+
+
+def tolerance(case):
+    """Measured: every listed case and some drawn ones through the other GEMM kernels of the library, whose sums run in
+    another order (bf16), and against the fp64 oracle (fp32); four times the largest difference, per model.  `max` is over
+    the root mean square of a whole flat buffer, whose tensors differ in scale."""
+    return {
+        "mlp": {"rel": 2e-6, "max": 2e-5},                      # 3e-7, 2e-6 (small sums: a little more than four times)
+        "towers": {"rel": 0.02, "max": 0.99},                   # 5.9e-3, 0.28
+        "transformer": {"rel": 0.03, "max": 0.99},              # 9.1e-3, 0.30
+        "recommender": {"rel": 0.012, "max": 0.7},              # 3.1e-3, 0.18
+        "concat": {"rel": 0.02, "max": 0.99},                   # 5.7e-3, 0.55
+        "hetero": {"rel": 0.015, "max": 0.3},                   # 3.8e-3, 0.07
+    }[case["model"]]
