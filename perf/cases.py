@@ -268,12 +268,15 @@ def _param_shapes(op):
 class Program:
     """One stage with its parameters, gradients and a mini-batch of inputs on the GPU."""
 
-    def __init__(self, case, seed):
+    def __init__(self, case, seed, stage=True):
         self.handle = None
         self.case, self.ops = case, _ops(case)
         ops, b, n_micro = self.ops, case["b"], case["n_micro"]
         gen = torch.Generator(device=DEV).manual_seed(seed)
         self._parameters(gen)
+        if not stage:
+            self._tensors(gen, _rows(ops, b))
+            return
         sched = case["schedule"]
         flags = {"plain": 0, "two_streams": 0, "grouped": B.FLAG_GROUPED_DW,
                  "graph": B.FLAG_GROUPED_DW | B.FLAG_SHARED_GPU | B.flag_group_launches(2)}[sched]
@@ -309,7 +312,7 @@ class Program:
         self.grad_weights, g_mats = _flat([s for _, s in mats], torch.float32)
         self.grad_vectors, g_vecs = _flat([s for _, s in vecs], torch.float32)
         self.grad_tables, g_tabs = _flat([s for _, s in tabs], torch.float32) if tabs else (None, [])
-        self.params = (p_mats, p_vecs, p_tabs)
+        self.params = ((mats, p_mats), (vecs, p_vecs), (tabs, p_tabs))
         self.param_ptrs, self.grad_ptrs = {}, {}
         for group, ps, gs in ((mats, p_mats, g_mats), (tabs, p_tabs, g_tabs), (vecs, p_vecs, g_vecs)):
             for (i, _), p, g in zip(group, ps, gs):
@@ -340,6 +343,7 @@ class Program:
         floats = [i for i in ins if ops[i]["role"] == "data"]
         kind = TORCH_TYPE[ops[floats[0]]["dtype"]]
         self.grad_inputs, g_in = _flat([(rows[i], ops[i]["out_features"]) for i in floats] * n_micro, kind)
+        self.float_inputs, self.output_ops = floats, outs
         self.outputs, self.grad_outputs, out_views, gout_views = None, None, [], []
         if outs:
             shapes = [(rows[i], ops[i]["out_features"]) for i in outs] * n_micro
@@ -347,6 +351,7 @@ class Program:
             self.grad_outputs, gout_views = _flat(shapes, TORCH_TYPE[_out_type(ops[outs[0]])])
             for v in gout_views:
                 v.normal_(0.0, 1.0 / math.sqrt(v.numel() * n_micro), generator=gen)
+        self.gout_views = gout_views
         self.losses, loss_views = _flat([(1,)] * n_micro, torch.float32)
         self.io = []
         for j, mb in enumerate(self.inputs):
@@ -437,6 +442,102 @@ def prepare(case, seed):
 
 def run(state):
     return state.step()
+
+
+# ---- the same pass in 64 bits -------------------------------------------------------------------------------------
+def exact(case, seed):
+    """What `run` returns, by plain torch in float64: no storage step between the operators, gradients by autograd."""
+    prog = Program(case, seed, stage=False)
+    ops, b, f64 = prog.ops, case["b"], torch.float64
+    par, views = {}, []
+    for group, tensors in prog.params:
+        mine = []
+        for (i, _), t in zip(group, tensors):
+            mine.append(t.to(f64).requires_grad_())
+            par.setdefault(i, []).append(mine[-1])
+        views.append(mine)
+    ins = [i for i, op in enumerate(ops) if op["kind"] == "input"]
+    losses, outputs, grad_inputs = [], [], []
+    n_out = len(prog.output_ops)
+    for j, mb in enumerate(prog.inputs):
+        val = {i: t.to(f64) if t.is_floating_point() else t.long() for i, t in zip(ins, mb)}
+        leaves = [val[i].requires_grad_() for i in prog.float_inputs]
+        loss = None
+        for i, op in enumerate(ops):
+            if op["kind"] == "input" or op["kind"].startswith("loss"):
+                continue
+            val[i] = _exact_op(op, [val[k] for k in op["inputs"]], par.get(i), b)
+        ends, seeds = [], []
+        for op in ops:
+            if op["kind"].startswith("loss"):
+                loss = _exact_loss(op, val[op["inputs"][0]], val[op["inputs"][1]])
+                ends.append(loss)
+                seeds.append(torch.ones_like(loss))
+        for k, i in enumerate(prog.output_ops):
+            ends.append(val[i])
+            seeds.append(prog.gout_views[j * n_out + k].to(f64))
+            outputs.append(val[i].detach())
+        torch.autograd.backward(ends, seeds)
+        losses.append(None if loss is None else loss.detach().view(1))
+        grad_inputs += [t.grad if t.grad is not None else torch.zeros_like(t) for t in leaves]
+
+    def flat(tensors):
+        buf, parts = _flat([tuple(t.shape) for t in tensors], f64)
+        for v, t in zip(parts, tensors):
+            v.copy_(t)
+        return buf
+
+    def grads(tensors):
+        return flat([t.grad for t in tensors])
+
+    out = dict(losses=None if losses[0] is None else flat(losses), grad_inputs=flat(grad_inputs), grad_weights=grads(views[0]),
+               grad_vectors=grads(views[1]))
+    if prog.output_ops:
+        del out["losses"]
+        out["outputs"] = flat(outputs)
+    if views[2]:
+        out["grad_tables"] = grads(views[2])
+    return out
+
+
+def _exact_op(op, src, par, b):
+    F = torch.nn.functional
+    k, n = op["kind"], op.get("out_features")
+    x = src[0]
+    if k == "linear":
+        z = x @ par[0][:, :op["in_features"]].T + par[1]
+        return {"none": lambda t: t, "relu": torch.relu, "gelu": F.gelu}[op["act"]](z)
+    if k == "layernorm":
+        return F.layer_norm(x, (n,), par[0], par[1], op["eps"])
+    if k == "attention":
+        q, kk, v = (t.reshape(b, op["seq_len"], op["heads"], -1).transpose(1, 2).contiguous() for t in x.chunk(3, dim=1))
+        p = torch.softmax(q @ kk.transpose(2, 3).contiguous() / math.sqrt(q.shape[-1]), dim=-1)
+        return (p @ v).transpose(1, 2).reshape(x.shape[0], n)
+    if k == "add":
+        return x + src[1]
+    if k == "meanpool":
+        return x.view(b, op["seq_len"], n).mean(dim=1)
+    if k == "concat":
+        return torch.cat(src, dim=1)
+    if k == "dot_interact":
+        t = x.view(x.shape[0], -1, op["in_features"])
+        pairs = torch.tril_indices(t.shape[1], t.shape[1], -1, device=x.device)
+        return torch.cat([t[:, 0], (t @ t.transpose(1, 2).contiguous())[:, pairs[0], pairs[1]]], dim=1)
+    idx, off = x.reshape(-1), src[1].reshape(-1)
+    bag, dim = op["bag_size"], op["in_features"] if k == "embedding_bag_concat" else n
+    slot = torch.arange(bag, device=idx.device)
+    at, held = off[:-1, None] + slot, slot < (off[1:] - off[:-1])[:, None]
+    rows = par[0][:, :dim][idx[torch.where(held, at, 0)]] * held[..., None]
+    return rows.reshape(rows.shape[0], -1) if k == "embedding_bag_concat" else rows.sum(dim=1)
+
+
+def _exact_loss(op, y, t):
+    F = torch.nn.functional
+    if op["kind"] == "loss_mse":
+        return op["loss_scale"] * ((y - t) ** 2).sum()
+    if op["kind"] == "loss_ce":
+        return op["loss_scale"] * F.cross_entropy(y, t.view(-1), reduction="sum")
+    return op["loss_scale"] * F.binary_cross_entropy_with_logits(y, t, reduction="sum")
 
 
 # ---- what a pass cannot do without ------------------------------------------------------------------------------
