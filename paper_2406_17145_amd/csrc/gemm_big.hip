@@ -491,22 +491,20 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
 
   void *Cout = FORM == FORM_DW ? p.C : result_ptr(p, ext);
   if (Cout == nullptr) return;
-  // ---- epilogue.  Tiles inside the matrix whose rows are 16-byte aligned go through LDS and touch
-  // memory in whole 16-byte pieces of rows (each wave has a private block; the operand tiles are dead:
-  // the k-loop and the bias sums ended with a barrier); the rest keeps the accumulator layout.
+  // ---- epilogue.  Where all rows are 16-byte aligned it goes through LDS and touches memory in whole 16-byte
+  // pieces of rows (each wave has a private block; the operand tiles are dead: the k-loop and the bias sums ended
+  // with a barrier); other results (fp32 outputs among them) keep the accumulator layout.
   static_assert(C::NW * epi_lds_floats<WTN>() * 4 <= C::LDS_ELEMS * 2, "epilogue blocks do not fit the operand LDS");
-  if (m0 + BM <= p.M && n0 + BN <= p.N) {
-    // (also for a plain bias / cast epilogue: rows in 16-byte pieces beat the accumulator layout's 2-byte pieces
-    // sixteen rows apart -- 4 x [2048 x 4096 x 1024] forward 78 -> 75.5 us, a one-k-step launch of the same output
-    // 29 -> 26 us.  While the stores were flat instructions, which count on the LDS wait counter as well, it
-    // was the other way round: 87 against 95 us)
-    if (epi_lds_ok(p, Cout, FORM)) {
-      if (FORM == FORM_DW && do_bias) __syncthreads();   // the bias sums were read from LDS after the last barrier
-      epilogue_wave_lds<FORM, WTM, WTN>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw,
-                                        (float *)lds + wave * epi_lds_floats<WTN>());
-    } else {
-      epilogue_wave<FORM, false, WTM, WTN>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw);
-    }
+  const bool inside = m0 + BM <= p.M && n0 + BN <= p.N;
+  // (also for a plain bias / cast epilogue: rows in 16-byte pieces beat the accumulator layout's 2-byte pieces
+  // sixteen rows apart -- 4 x [2048 x 4096 x 1024] forward 78 -> 75.5 us, a one-k-step launch of the same output
+  // 29 -> 26 us.  While the stores were flat instructions, which count on the LDS wait counter as well, it
+  // was the other way round: 87 against 95 us)
+  if (epi_lds_ok(p, Cout, FORM)) {
+    if (FORM == FORM_DW && do_bias) __syncthreads();   // the bias sums were read from LDS after the last barrier
+    float *stage = (float *)lds + wave * epi_lds_floats<WTN>();
+    if (inside) epilogue_wave_lds<FORM, false, WTM, WTN, GROUP>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
+    else epilogue_wave_lds<FORM, true, WTM, WTN, GROUP>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
   } else {
     epilogue_wave<FORM, true, WTM, WTN>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw);
   }
@@ -533,26 +531,15 @@ __global__ __launch_bounds__(256, 3) void k_gemm_mid(const GemmProb *__restrict_
   big_tile_body<FORM, 2, 2, 2, 2, 1, 1>(p, t.m0, t.n0, lds, accumulate_dw, ext);
 }
 
-// backward-weight over a group of stash slots (see big_tile_body)
-template <int WTM, int WTN, int NS>
-__global__ __launch_bounds__(512) void k_gemm_big_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
-                                                           int accumulate_dw, SlotGroup grp) {
-  typedef BigCfg<FORM_DW, 2, 4, WTM, WTN, 2> C;
-  __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
-  // (bands of four tile rows: one workgroup per compute unit, 32 tiles in flight per XCD as a 4 x 8 block; seven
-  // [4096 x 4096] gradients over 2048 rows: 3226 -> 2684 us)
-  const BigTile t = big_locate<C::BM, C::BN, 4>(probs, n, total_blocks);
-  const GemmProb p = probs[t.pi];
-  ExtPtrs none;
-  big_tile_body<FORM_DW, 2, 4, WTM, WTN, 2, NS, true>(p, t.m0, t.n0, lds, accumulate_dw, none, grp);
-}
+// backward-weight over a group of stash slots (see big_tile_body).
 // Tile order of the grouped weight gradient: bands of eight tile rows.  Its launch holds thousands of 128 x 128 tiles,
 // 128 of them in flight per XCD; numbered column by column these are 32 rows x 4 columns of a [4096 x 1024] gradient
 // (36 operand panels of 512 KB through a 4 MB L2), in bands 8 x 16 (24 panels).  Measured on the transformer stage's
 // launch of all layers: 497-505 -> 483 us (bands of 4: 497, of 16: 487 scaled to the same box).
 constexpr int DW_BAND = 8;
 // (four workgroups per compute unit: 40 KB of LDS and 128 registers each; with three the transformer stage's launch
-// is 6 % slower)
+// is 6 % slower.  The tile for every size: 256 x 256 outputs per workgroup of eight waves, alone on its compute unit,
+// exposes its 256 KB of stores -- seven [4096 x 4096] gradients over 256 / 2048 rows 127 / 467 us against 100 / 410)
 __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
                                                               int accumulate_dw, SlotGroup grp) {
   typedef BigCfg<FORM_DW, 2, 2, 2, 2, 1> C;
@@ -578,29 +565,50 @@ bool gemm_big_supported(const GemmProb &p) {
   if (a_rows * p.lda * 2 >= 0xffffff00ll || b_rows * p.ldb * 2 >= 0xffffff00ll) return false;
   return true;
 }
-// Tile shape for a launch: 256 (256 x 256, eight waves), 128 (128 x 256, eight waves), 64 (128 x 128,
-// four waves, three workgroups per compute unit), or 0 when the smaller tile kernel should run it.
-// `tiles256` / `tiles128`: 256 x 256 / 128 x 256 tiles of the whole launch.  The eight-wave kernels
-// hold one workgroup per compute unit, so they win only when every one of the 256 compute units gets
-// the same whole number of tiles; in between, the co-resident small tiles do.  Measured, 4 branches of
-// [2048 x N] outputs with contraction K, microseconds for tile 256 / 128 / 64:
-//   forward N 4096 K 1024 (512 / 1024 tiles): 87 / 95 / 90      N 3072 K 1024 (384 / 768): 77 / 71 / 66
-//   forward N 1024 K 4096 (128 / 256):       127 / 88 / 92      N 1024 K 1024 (128 / 256): 39 / 26 / 26
-//   backward-weight [3072 x 1024], 2048 rows (192 / 384): 81 / 90 / 71     [1024 x 1024] (64 / 128): 73 / 46 / 38
-int gemm_big_tile_rows(int form, int maxM, int maxN, int64_t launch_elems, int tiles256, int tiles128) {
-  constexpr int CUS = 256;
-  if (maxM < 128 || maxN < 128) return 0;
-  if (launch_elems < (int64_t)128 * 128 * 128) return 0;
-  if (maxM >= 256 && maxN >= 256 && tiles256 >= CUS && tiles256 % CUS == 0) return 256;
-  // forward with the two-batch direct loop: a last round that still fills half of the compute units beats the
-  // co-resident small tiles (4 x [2048 x 3072 x 1024], 384 tiles: 70 against 74 us)
-  if (form == FORM_FWD && maxM >= 256 && maxN >= 256 && tiles256 >= CUS && tiles256 % CUS >= CUS / 2) return 256;
-  if (maxN >= 256 && tiles128 == CUS) return 128;
-  // the single-buffer small tiles hide their load latency only behind co-resident workgroups: with
-  // fewer tiles than compute units (a lone [2048 x 1024 x 1024] problem: 28 us against 20 us) they lose
-  // to the ring-buffered tile kernel
-  if (2 * tiles128 < CUS) return 0;
-  return 64;
+// Tile shape for a launch: 256 (256 x 256, eight waves), 128 (128 x 256, eight waves; forward only), 64 (128 x 128,
+// four waves, three workgroups per compute unit), or 0 for the kernel whose waves split the contraction over 64 x 64
+// blocks.  Whatever takes least by the estimates below, which are microseconds fitted to launches with operands from
+// memory, 1 to 7 records of M 64 .. 2048, N and K 1000 .. 4096: K / 64 k-steps, workgroups as counted in `c`.
+//   256 x 256: one workgroup per compute unit, rounds of 256.       4 x [2048 x 4096 x 1024] 87 forward, 91 backward-data
+//   128 x 256: the same with half the work in a workgroup.          7 x [256 x 4096 x 4096] forward 81 (256: 104, 64: 92, 0: 151)
+//   128 x 128: 1, 2 or 3 per compute unit; a partial round is partly hidden under the full ones.
+//                                                                   7 x [256 x 4096 x 4096] backward-data 87 (256: 127, 0: 159)
+//   64 x 64:   at a few workgroups per compute unit.                4 x [512 x 1000 x 3820] 48 (256: 96, 128: 65, 64: 72)
+// 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218; a lone [512 x 4096 x 4096]: 95, 62, 72, 45.
+// The estimates are within 20 % of what was measured, so the 64 x 64 blocks, whose time depends least on the rest of
+// the shape, are left only for an estimate 10 % below theirs.
+int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64) {
+  constexpr float CUS = 256.0f;
+  const float nk = (float)cdiv(max_k, GB_BK);
+  const bool fwd = form == FORM_FWD;
+  auto rounds = [&](float tiles, auto cost) {          // rounds of one workgroup per compute unit
+    const float full = floorf(tiles / CUS), part = tiles / CUS - full;
+    return full * cost(1.0f) + (full == 0.0f || part > 0.01f ? cost(part) : 0.0f);
+  };
+  auto t256 = [&](float fill) { return fwd ? 10.0f + 8.0f * fill + (1.35f + 0.2f * fill) * nk : 12.0f + 4.0f * fill + 1.82f * nk; };
+  auto t128 = [&](float fill) { return 9.0f + 4.0f * fill + 0.95f * nk; };
+  auto mid = [&](float tiles) {
+    auto level = [&](float per_cu) {                   // workgroups that share a compute unit
+      const float fixed = per_cu <= 1.0f ? 9.0f : (per_cu <= 2.0f ? 13.5f : 16.0f);
+      const float step = per_cu <= 1.0f ? 1.06f : (per_cu <= 2.0f ? 1.13f : 1.55f);
+      return fixed - (fwd ? 0.0f : 3.0f) + step * nk;
+    };
+    const float full = floorf(tiles / (3.0f * CUS)), rest = tiles / CUS - 3.0f * full;
+    if (full == 0.0f) return level(rest);
+    return full * level(3.0f) + (rest > 0.01f ? 0.6f * level(rest) : 0.0f);
+  };
+  float best = blocks64 ? 0.9f * (3.0f + fmaxf(1.0f, c.t64 / CUS) * (3.2f + 0.30f * nk)) : 1e30f;
+  int rows = blocks64 ? 0 : 64;
+  auto take = [&](int r, float t) {
+    if (t < best) {
+      best = t;
+      rows = r;
+    }
+  };
+  take(64, mid(c.t128));
+  take(256, rounds(c.t256, t256));
+  if (fwd) take(128, rounds(c.t128x256, t128));
+  return rows;
 }
 int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n) {
   const int bn = tile_rows == 64 ? 128 : 256, bm = tile_rows == 64 ? 128 : tile_rows;
@@ -608,46 +616,34 @@ int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n) {
   return cdiv(M, bm) * cdiv(N, bn);
 }
 
-template <int FORM>
-static void launch_big_form(const GemmProb *probs, int n, int blocks, int acc, int tile_rows, int direct, const ExtPtrs &ext,
-                            hipStream_t s) {
-  const dim3 g(blocks), b(512);
-  // direct: the forward form on both eight-wave tiles, backward-data on the 256 x 256 tile (its a operand is
-  // k-contiguous); backward-weight always stages through registers
-  constexpr int P256 = FORM == FORM_DW ? 0 : 2, P128 = FORM == FORM_FWD ? 1 : 0;
-  if constexpr (P256 != 0) {
-    if (tile_rows == 256 && direct) {
-      hipLaunchKernelGGL((k_gemm_big<FORM, 4, 2, 2, P256, 2>), g, b, 0, s, probs, n, blocks, acc, ext);
-      return;
-    }
-  }
-  if constexpr (P128 != 0) {
-    if (tile_rows == 128 && direct) {
-      hipLaunchKernelGGL((k_gemm_big<FORM, 2, 2, 2, P128, 3>), g, b, 0, s, probs, n, blocks, acc, ext);
-      return;
-    }
-  }
-  if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM, 4, 2, 2, 0, 2>), g, b, 0, s, probs, n, blocks, acc, ext);
-  else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM, 2, 2, 2, 0, 2>), g, b, 0, s, probs, n, blocks, acc, ext);
-  else hipLaunchKernelGGL((k_gemm_mid<FORM>), g, dim3(256), 0, s, probs, n, blocks, acc, ext);
-}
 // direct != 0: operands straight into LDS where the form has such a loop (every record must pass
 // gemm_big_direct_ok); the other launches stage through registers
+template <int FORM>
+static void launch_big_form(const GemmProb *probs, int n, int blocks, int tile_rows, int direct, const ExtPtrs &ext, hipStream_t s) {
+  const dim3 g(blocks), b(512);
+  if (tile_rows == 256 && direct) hipLaunchKernelGGL((k_gemm_big<FORM, 4, 2, 2, 2, 2>), g, b, 0, s, probs, n, blocks, 0, ext);
+  else if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM, 4, 2, 2, 0, 2>), g, b, 0, s, probs, n, blocks, 0, ext);
+  else hipLaunchKernelGGL((k_gemm_mid<FORM>), g, dim3(256), 0, s, probs, n, blocks, 0, ext);
+}
 void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, int direct,
                      const ExtPtrs &ext, hipStream_t s) {
   if (total_blocks <= 0) return;
-  if (form == FORM_FWD) launch_big_form<FORM_FWD>(probs, n, total_blocks, accumulate_dw, tile_rows, direct, ext, s);
-  else if (form == FORM_DX) launch_big_form<FORM_DX>(probs, n, total_blocks, accumulate_dw, tile_rows, direct, ext, s);
-  else launch_big_form<FORM_DW>(probs, n, total_blocks, accumulate_dw, tile_rows, direct, ext, s);
+  const dim3 g(total_blocks);
+  if (form == FORM_FWD && tile_rows == 128) {
+    if (direct) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 2, 1, 3>), g, dim3(512), 0, s, probs, n, total_blocks, 0, ext);
+    else hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 2, 0, 2>), g, dim3(512), 0, s, probs, n, total_blocks, 0, ext);
+  } else if (form == FORM_FWD) {
+    launch_big_form<FORM_FWD>(probs, n, total_blocks, tile_rows, direct, ext, s);
+  } else if (form == FORM_DX) {
+    launch_big_form<FORM_DX>(probs, n, total_blocks, tile_rows, direct, ext, s);
+  } else {
+    hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, ext);
+  }
 }
 
-void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, const SlotGroup &grp,
-                          hipStream_t s) {
+void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, const SlotGroup &grp, hipStream_t s) {
   if (total_blocks <= 0 || grp.n <= 0) return;
-  const dim3 g(total_blocks), b(512);
-  if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big_dw_group<4, 2, 2>), g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
-  else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big_dw_group<2, 2, 2>), g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
-  else hipLaunchKernelGGL(k_gemm_mid_dw_group, dim3(total_blocks), dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, grp);
+  hipLaunchKernelGGL(k_gemm_mid_dw_group, dim3(total_blocks), dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, grp);
 }
 
 }  // namespace gpp

@@ -309,7 +309,13 @@ __device__ __forceinline__ void epilogue_wave(const GemmProb &p, void *Cout, con
 // a lane then owns 8 consecutive columns of a row, every optional operand (residual / gradient
 // addend, stashed derivative or mask source, old gradient) is one or two 16-byte loads, the result
 // one 16-byte store (two for fp32), and the loads of a 32-row block are all requested before the
-// first is used.  For tiles that lie inside the matrix, with 16-byte aligned rows everywhere.
+// first is used.  Needs 16-byte aligned rows everywhere (epi_lds_ok).
+// CHECK: the tile sticks out of the matrix.  Loads stay unconditional -- a lane beyond the matrix reads its last
+// row, or the row's first chunk -- and only the stores are predicated; the one chunk of a row that straddles the
+// last column (N no multiple of 8; whole in memory, since rows are padded to 16 bytes) is stored by elements.
+// (On the accumulator layout a predicate in front of every 2-byte load and store made each of them a memory round
+// trip of its own: a 384-row backward-data launch of 256 x 256 tiles, K 4096, took 148 us against 120 us at 512
+// rows, a [1000 x 256] weight gradient over 300 rows twice the time of a [1024 x 256] one.)
 constexpr int EPI_LDS_PAD = 4;   // floats: keeps rows 16-byte aligned and spreads them over the banks
 template <int TJ>
 constexpr int epi_lds_floats() { return 32 * (32 * TJ + EPI_LDS_PAD); }
@@ -337,15 +343,20 @@ __device__ __forceinline__ u32x4 pack_bf16x8(const float (&v)[8]) {
   return u;
 }
 
-template <int FORM, int TI, int TJ>
+template <int FORM, bool CHECK, int TI, int TJ, bool STREAM = false>
 __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout, const f32x16 (&acc)[TI][TJ], int wr0, int wc0,
                                                   int lane, int accumulate_dw, float *stage) {
   constexpr int COLS = 32 * TJ, ST = COLS + EPI_LDS_PAD;
   constexpr int LPR = COLS / 8, RPI = 64 / LPR, ITS = 32 / RPI;   // lanes per row, rows per step, steps per block
   const int rl = lane / LPR, c8 = (lane % LPR) * 8;
-  const int col = wc0 + c8;
+  const bool col_ok = !CHECK || wc0 + c8 < p.N, whole = !CHECK || wc0 + c8 + 8 <= p.N;
+  const int col = col_ok ? wc0 + c8 : 0;
+  auto rows = [&](int r) { return CHECK ? min(r, p.M - 1) : r; };       // row a load may touch
   float bias[8] = {};
-  if (FORM == FORM_FWD && p.bias) {
+  if (FORM == FORM_FWD && p.bias && !whole) {      // (a bias vector has no padding to read)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bias[e] = p.bias[min(col + e, p.N - 1)];
+  } else if (FORM == FORM_FWD && p.bias) {
     const float4 b0 = *(const float4 *)(p.bias + col), b1 = *(const float4 *)(p.bias + col + 4);
     bias[0] = b0.x; bias[1] = b0.y; bias[2] = b0.z; bias[3] = b0.w;
     bias[4] = b1.x; bias[5] = b1.y; bias[6] = b1.z; bias[7] = b1.w;
@@ -360,6 +371,17 @@ __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout,
   const uint16_t *resp = use_res ? (const uint16_t *)p.res : (const uint16_t *)Cout;
   const uint16_t *auxp = aux_in ? (const uint16_t *)p.aux : (const uint16_t *)Cout;
   const int64_t ldr = use_res ? p.ldres : 0, lda = aux_in ? p.ldaux : 0;
+  auto put = [&](uint16_t *o, int row, const float (&v)[8]) {
+    if (CHECK && (!col_ok || row >= p.M)) return;
+    const u32x4 u = pack_bf16x8(v);
+    if (whole) {
+      *(u32x4 *)o = u;
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (col + e < p.N) o[e] = (uint16_t)(u[e / 2] >> (16 * (e & 1)));
+  };
 #pragma unroll
   for (int i = 0; i < TI; ++i) {
     // accumulators of the 32-row block -> LDS, in their own layout (a half-wave writes 32 consecutive floats)
@@ -370,31 +392,44 @@ __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout,
     __builtin_amdgcn_wave_barrier();
     const int row0 = wr0 + 32 * i + rl;
     if (FORM == FORM_DW) {
-      float4 old[ITS][2];
-      float *c = (float *)Cout + (int64_t)row0 * p.ldc + col;
+      // fp32 rows: a lane takes FOUR columns, so that one instruction of a wave covers whole rows of the block
+      // (256 contiguous bytes of each); with eight columns per lane every store covered every other 16 bytes of a
+      // row, and the L2 had to put the lines together.  STREAM: a gradient that no pass adds to any more goes past
+      // the caches, which keep the operand panels instead (seven [4096 x 4096] gradients over 512 rows: 178 us with
+      // eight columns per lane, 167 with four, 137 streamed; over 2048 rows 454, 440, 410)
+      constexpr int LPR4 = COLS / 4, RPI4 = 64 / LPR4, ITS4 = 32 / RPI4;
+      const int rl4 = lane / LPR4, c4 = (lane % LPR4) * 4, row4 = wr0 + 32 * i + rl4;
+      const bool in4 = !CHECK || wc0 + c4 < p.N, whole4 = !CHECK || wc0 + c4 + 4 <= p.N;
+      const int col4 = in4 ? wc0 + c4 : 0;
+      float *c = (float *)Cout + col4;
+      float4 old[ITS4];
       if (accumulate_dw) {
 #pragma unroll
-        for (int t = 0; t < ITS; ++t) {
-          old[t][0] = *(const float4 *)(c + (int64_t)t * RPI * p.ldc);
-          old[t][1] = *(const float4 *)(c + (int64_t)t * RPI * p.ldc + 4);
-        }
+        for (int t = 0; t < ITS4; ++t) old[t] = *(const float4 *)(c + (int64_t)rows(row4 + RPI4 * t) * p.ldc);
       }
 #pragma unroll
-      for (int t = 0; t < ITS; ++t) {
-        float4 v0 = *(const float4 *)(stage + (rl + RPI * t) * ST + c8), v1 = *(const float4 *)(stage + (rl + RPI * t) * ST + c8 + 4);
-        if (accumulate_dw) {
-          v0 = make_float4(old[t][0].x + v0.x, old[t][0].y + v0.y, old[t][0].z + v0.z, old[t][0].w + v0.w);
-          v1 = make_float4(old[t][1].x + v1.x, old[t][1].y + v1.y, old[t][1].z + v1.z, old[t][1].w + v1.w);
+      for (int t = 0; t < ITS4; ++t) {
+        float4 v = *(const float4 *)(stage + (rl4 + RPI4 * t) * ST + c4);
+        if (accumulate_dw) v = make_float4(old[t].x + v.x, old[t].y + v.y, old[t].z + v.z, old[t].w + v.w);
+        float *o = c + (int64_t)(row4 + RPI4 * t) * p.ldc;
+        if (CHECK && (!in4 || row4 + RPI4 * t >= p.M)) continue;
+        if (whole4) {
+          typedef float f32x4 __attribute__((ext_vector_type(4)));
+          if (STREAM && !accumulate_dw) __builtin_nontemporal_store((f32x4){v.x, v.y, v.z, v.w}, (f32x4 *)o);
+          else *(float4 *)o = v;
+        } else {
+          const float e4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (col4 + e < p.N) o[e] = e4[e];
         }
-        *(float4 *)(c + (int64_t)t * RPI * p.ldc) = v0;
-        *(float4 *)(c + (int64_t)t * RPI * p.ldc + 4) = v1;
       }
     } else {
       u32x4 res_raw[ITS], aux_raw[ITS];
 #pragma unroll
       for (int t = 0; t < ITS; ++t) {
-        res_raw[t] = *(const u32x4 *)(resp + (int64_t)(row0 + RPI * t) * ldr + col);
-        aux_raw[t] = *(const u32x4 *)(auxp + (int64_t)(row0 + RPI * t) * lda + col);
+        res_raw[t] = *(const u32x4 *)(resp + (int64_t)rows(row0 + RPI * t) * ldr + col);
+        aux_raw[t] = *(const u32x4 *)(auxp + (int64_t)rows(row0 + RPI * t) * lda + col);
       }
 #pragma unroll
       for (int t = 0; t < ITS; ++t) {
@@ -414,7 +449,7 @@ __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout,
           } else if (p.act == ACT_GELU) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) gelu_both(v[e], v[e], d[e]);
-            if (aux_out) *(u32x4 *)((uint16_t *)p.aux + (int64_t)(row0 + RPI * t) * p.ldaux + col) = pack_bf16x8(d);
+            if (aux_out) put((uint16_t *)p.aux + (int64_t)(row0 + RPI * t) * p.ldaux + col, row0 + RPI * t, d);
           }
           if (use_res) {
 #pragma unroll
@@ -435,7 +470,7 @@ __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout,
             }
           }
         }
-        *(u32x4 *)((uint16_t *)Cout + (int64_t)(row0 + RPI * t) * p.ldc + col) = pack_bf16x8(v);
+        put((uint16_t *)Cout + (int64_t)(row0 + RPI * t) * p.ldc + col, row0 + RPI * t, v);
       }
     }
     __builtin_amdgcn_wave_barrier();   // the block is free again

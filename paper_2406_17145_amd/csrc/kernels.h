@@ -213,8 +213,9 @@ int gemm_generic_tiles(int M, int N, int *tiles_n);
 int gemm_mfma_group_tile(int form, int maxM, int maxN);
 int gemm_mfma_tiles_for(int tile, int M, int N, int *tiles_n);
 int gemm_mfma_partial_floats(int tile);
-// large-tile kernels: 256 x 256 or 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
-// 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64)
+// large-tile kernels: 256 x 256 or (forward) 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
+// 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64; backward-weight
+// has this tile only)
 void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, int direct,
                      const ExtPtrs &ext, hipStream_t s);
 bool gemm_big_supported(const GemmProb &p);
@@ -225,9 +226,14 @@ struct SlotGroup {
   int32_t first = 0, n = 1, total = 1, pad = 0;
   int64_t stride = 0;
 };
-void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, const SlotGroup &grp,
-                          hipStream_t s);
-int gemm_big_tile_rows(int form, int maxM, int maxN, int64_t launch_elems, int tiles256, int tiles128);
+void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, const SlotGroup &grp, hipStream_t s);
+// Workgroups of a launch per output block shape.  Records with a shorter contraction than the launch's longest count
+// for the share of it that they have.
+struct GemmTileCounts {
+  float t256 = 0, t128x256 = 0, t128 = 0, t64 = 0;     // 256 x 256, 128 x 256, 128 x 128, 64 x 64
+};
+// forward / backward-data; `blocks64`: the 64 x 64 kernel (0) is a choice
+int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64);
 int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n);
 // backward-weight for small weight matrices and many rows: 64 x 64 tiles, the contraction split over the waves
 void launch_gemm_dw_ksplit(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, hipStream_t s);

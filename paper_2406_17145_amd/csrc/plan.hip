@@ -698,7 +698,8 @@ struct Emitter {
           dw_ksplit = true;
         }
       }
-      if (!dx.empty() && !dw.empty() && row_tiles > 0 && !(pl.flags & 2)) {
+      // (not where backward-data alone is a launch for the large tiles)
+      if (!dx.empty() && !dw.empty() && row_tiles > 0 && !(pl.flags & 2) && large_tile(dx, FORM_DX, row_tiles) == 0) {
         int blocks = 0, col_tiles = 2;
         skinny_pick_tiles(dx, row_tiles, col_tiles, false);
         for (auto &r : dx) {
@@ -744,17 +745,9 @@ struct Emitter {
           }
           if (use_mfma) tile = gemm_mfma_group_tile(form, max_m, max_n);
           // few rows: the weight-streaming kernel (forward and backward-data only)
-          int row_tiles = (use_mfma && form != FORM_DW) ? gemm_skinny_row_tiles(max_m) : 0;
-          // many rows but a small launch (fewer 128 x 128 tiles than compute units, e.g. the MLPs of the
-          // recommendation workload at 2048 rows): the tiled kernels would run one workgroup on half of
-          // the compute units with a barrier per k-step; the kernel whose waves split the contraction
-          // covers the matrix with 64-row blocks instead (measured at [2048 x 1024 x 1024]: 14.8 us
-          // against 20.7 us forward, 15.4 against 26.7 backward-data)
-          if (use_mfma && form != FORM_DW && row_tiles == 0 && !(pl.flags & 2)) {
-            int64_t elems = 0;
-            for (auto &r : g) elems += (int64_t)r.M * r.N;
-            if (elems < (int64_t)128 * 128 * 256) row_tiles = 2;
-          }
+          int row_tiles = (use_mfma && form != FORM_DW) ? few_rows(g) : 0;
+          int tile_rows = (use_mfma && form != FORM_DW) ? large_tile(g, form, row_tiles) : 0;
+          if (tile_rows > 0) row_tiles = 0;
           if (row_tiles > 0) {
             int blocks = 0, col_tiles = 2;
             // (group launches cover several micro-batches: the launch is large without the smaller row tile, and
@@ -776,58 +769,19 @@ struct Emitter {
             if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
             continue;
           }
-          // many rows and columns: the large-tile kernel
-          if (use_mfma && !(pl.flags & 2)) {
-            bool ok = true;
-            int64_t elems = 0;
-            int tiles256 = 0, tiles128 = 0;
-            for (auto &r : g) {
-              ok = ok && gemm_big_supported(r);
-              elems += (int64_t)r.M * r.N;
-              tiles256 += ((r.M + 255) / 256) * ((r.N + 255) / 256);
-              tiles128 += ((r.M + 127) / 128) * ((r.N + 255) / 256);
-            }
-            int tile_rows = ok ? gemm_big_tile_rows(form, max_m, max_n, elems, tiles256, tiles128) : 0;
-            if (tile_rows > 0) {
-              // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source):
-              // the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident
-              // 128 x 128 workgroups hide them behind each other's k-loops (measured cold on 4 x [2048 x 4096 x 1024]
-              // with the GELU derivative: 119 -> 106 us)
-              if (form == FORM_DX && tile_rows == 256) {
-                bool second = true;
-                for (auto &r : g) second = second && r.act != ACT_NONE;
-                if (second) tile_rows = 64;
-              }
-              // operands copied straight into LDS (software-pipelined loops of the eight-wave tiles) where the
-              // a operand is k-contiguous and the tile has such a loop: forward on both tiles (4 x [2048 x 4096 x
-              // 1024] cold: 83 staged, 82 plain direct loop, 78 pipelined), backward-data on the 256 x 256 tile
-              // (4 x [2048 x 4096 x 4096]: 336 staged, 297 pipelined; on the 128 x 256 tile the two 8-byte transposing
-              // reads per fragment of W keep the staged loop ahead: 96 against 112 us)
-              bool direct = form == FORM_FWD || (form == FORM_DX && tile_rows == 256);
-              for (auto &r : g) direct = direct && gemm_big_direct_ok(r);
-              int blocks = 0;
-              for (auto &r : g) {
-                r.blk_begin = blocks;
-                r.split_k = 1;
-                blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
-              }
-              Step &s = add_step(K_GEMM_BIG, push_table(g), (int)g.size(), blocks);
-              s.a0 = direct ? 1 : 0;
-              s.a1 = form;
-              s.a2 = tile_rows;
-              if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
-              continue;
-            }
-          }
-          // backward-weight with a long contraction and too few 128 x 128 tiles to fill the chip:
-          // small tiles, the contraction split over the waves of each workgroup
           if (use_mfma && form == FORM_DW && !(pl.flags & 2)) {
             int tiles128 = 0, min_k = 1 << 30;
+            bool ok = true;
             for (auto &r : g) {
               tiles128 += gemm_mfma_tiles_for(128, r.M, r.N, nullptr);
               min_k = std::min(min_k, r.K);
+              ok = ok && gemm_big_supported(r);
             }
-            if (min_k >= 512 && tiles128 < 192) {
+            // backward-weight with a long contraction and too few 128 x 128 tiles to fill the chip: small tiles, the
+            // contraction split over the waves of each workgroup; the longer the contraction, the more tiles it takes
+            // to fill in otherwise (2 x [1000 x 256] over 512 / 1200 rows: 9.5 / 13.0 us against 10.1 / 18.1 with
+            // 128 x 128 tiles; 4 x [1000 x 1000]: 35.9 / 53.5 against 16.4 / 28.1)
+            if (min_k >= 512 && tiles128 < std::min(192, 32 + min_k / 16)) {
               int blocks = 0;
               for (auto &r : g) {
                 r.blk_begin = blocks;
@@ -837,6 +791,31 @@ struct Emitter {
               add_step(K_GEMM_DW_KSPLIT, push_table(g), (int)g.size(), blocks);
               continue;
             }
+            // every other one runs on the co-resident 128 x 128 tiles, whatever its size (2 x [1000 x 256] over 300
+            // rows: 7.9 us against 10.4 with the ring-buffered 128 x 128 tiles and 10.7 with 64 x 64; [100 x 64]: 7.2
+            // against 10.0 and 7.1)
+            if (ok) tile_rows = 64;
+          }
+          // the large-tile kernels
+          if (tile_rows > 0) {
+            // operands copied straight into LDS (software-pipelined loops of the eight-wave tiles) where the
+            // a operand is k-contiguous and the tile has such a loop: forward on both tiles (4 x [2048 x 4096 x
+            // 1024] cold: 83 staged, 82 plain direct loop, 78 pipelined), backward-data on the 256 x 256 tile
+            // (4 x [2048 x 4096 x 4096]: 336 staged, 297 pipelined)
+            bool direct = form == FORM_FWD || (form == FORM_DX && tile_rows == 256);
+            for (auto &r : g) direct = direct && gemm_big_direct_ok(r);
+            int blocks = 0;
+            for (auto &r : g) {
+              r.blk_begin = blocks;
+              r.split_k = 1;
+              blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
+            }
+            Step &s = add_step(K_GEMM_BIG, push_table(g), (int)g.size(), blocks);
+            s.a0 = direct ? 1 : 0;
+            s.a1 = form;
+            s.a2 = tile_rows;
+            if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
+            continue;
           }
           int launch_tiles = 0;
           if (use_mfma)
@@ -870,6 +849,56 @@ struct Emitter {
           if (use_mfma && wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
         }
     recs.clear();
+  }
+
+  // Few rows, or a small launch (fewer 128 x 128 tiles than compute units, e.g. the MLPs of the recommendation workload
+  // at 2048 rows, where the tiled kernels would run one workgroup on half of the compute units with a barrier per
+  // k-step: [2048 x 1024 x 1024] 14.8 us against 20.7 us forward, 15.4 against 26.7 backward-data): row tile of the
+  // kernel whose waves split the contraction, 0 for other launches.
+  int few_rows(const std::vector<GemmProb> &g) const {
+    int max_m = 0;
+    int64_t elems = 0;
+    for (auto &r : g) {
+      max_m = std::max(max_m, r.M);
+      elems += (int64_t)r.M * r.N;
+    }
+    const int row_tiles = gemm_skinny_row_tiles(max_m);
+    return row_tiles == 0 && !(pl.flags & 2) && elems < (int64_t)128 * 128 * 256 ? 2 : row_tiles;
+  }
+  // Large-tile kernel of a forward / backward-data launch (rows of its tile), or 0: the kernel above, or where that is
+  // not meant for the launch either, the small tiles.  Up to 64 rows a tile would be half padding.  Where launches
+  // share the GPU (flag bit 4) the few-row kernel stays wherever it is meant to run: its workgroups fit beside those of
+  // another stream, and group launches, which give the same results bit by bit as single ones, know no other kernel.
+  int large_tile(const std::vector<GemmProb> &g, int form, int few) const {
+    if (pl.flags & 2) return 0;
+    int max_m = 0, max_n = 0, max_k = 0;
+    for (auto &r : g) {
+      if (!gemm_big_supported(r)) return 0;
+      max_m = std::max(max_m, r.M);
+      max_n = std::max(max_n, r.N);
+      max_k = std::max(max_k, r.K);
+    }
+    if (few > 0 && (max_m <= 64 || (pl.flags & 16) || pl.group_lanes > 0)) return 0;
+    GemmTileCounts c;
+    auto tiles = [](const GemmProb &r, int bm, int bn) { return (float)(((r.M + bm - 1) / bm) * ((r.N + bn - 1) / bn)); };
+    for (auto &r : g) {
+      const float share = (float)r.K / (float)max_k;
+      c.t256 += share * tiles(r, 256, 256);
+      c.t128x256 += share * tiles(r, 128, 256);
+      c.t128 += share * tiles(r, 128, 128);
+      c.t64 += share * tiles(r, 64, 64);
+    }
+    int rows = gemm_big_tile_rows(form, max_k, c, few > 0);
+    // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source) behind a short
+    // contraction: the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident
+    // 128 x 128 workgroups hide them behind each other's k-loops (4 x [2048 x 4096 x 1024] with the GELU derivative
+    // inside a step: 119 -> 106 us; with a contraction of 4096 the large tile stays ahead, 260 against 296 us)
+    if (form == FORM_DX && rows == 256 && max_k <= 1024) {
+      bool second = true;
+      for (auto &r : g) second = second && r.act != ACT_NONE;
+      if (second) rows = 64;
+    }
+    return rows;
   }
 
   // Tile shape of a few-row launch: `row_tiles` comes in as the largest row tile the rows allow.  The
@@ -1808,29 +1837,15 @@ void Emitter::backward() {
   steps = &pl.dwg;
   steps->clear();
   if (!dw_group.empty()) {
-    // (a launch of their own for the largest layers with 256 x 256 tiles, which win on those shapes alone --
-    // 98 against 112 us on 4 x [4096 x 1024] over 2048 rows -- measured no faster for the step: 515 against
-    // 502 us for the transformer stage; one launch lets the co-resident tiles of all layers fill each other's tails)
-    int64_t elems = 0;
-    int tiles256 = 0, tiles128 = 0, max_m = 0, max_n = 0;
-    for (auto &r : dw_group) {
-      elems += (int64_t)r.M * r.N;
-      tiles256 += ((r.M + 255) / 256) * ((r.N + 255) / 256);
-      tiles128 += ((r.M + 127) / 128) * ((r.N + 255) / 256);
-      max_m = std::max(max_m, r.M);
-      max_n = std::max(max_n, r.N);
-    }
-    int tile_rows = gemm_big_tile_rows(FORM_DW, max_m, max_n, elems, tiles256, tiles128);
-    if (tile_rows == 0) tile_rows = 64;
+    // (one launch lets the co-resident tiles of all layers fill each other's tails)
     int blocks = 0;
     for (auto &r : dw_group) {
       r.blk_begin = blocks;
       r.split_k = 1;
-      blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
+      blocks += gemm_big_tiles_for(64, r.M, r.N, &r.tiles_n);
     }
     // (contraction-major operands: staged through registers, see emit_gemms)
-    Step &sg = add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
-    sg.a2 = tile_rows;
+    add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
   }
   steps = &pl.bwd;
 }

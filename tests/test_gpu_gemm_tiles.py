@@ -1,0 +1,56 @@
+"""The GEMM kernels' tile shapes at sizes where they can go wrong: every output tile of the large kernels, matrices that end inside
+a tile in rows, in columns and inside a 16-byte chunk of a row, gradients that are stored and gradients that are added to."""
+import numpy as np
+import pytest
+
+from paper_2406_17145_amd import binding as B
+from paper_2406_17145_amd import workloads as W
+from tests.parity_util import compare, run_gpu, run_oracle
+from tests.test_gpu_schedule import _run
+
+pytestmark = pytest.mark.gpu
+
+
+def _chain(rows, widths, acts, branches, n_micro, dtype=W.BF16):
+    """`branches` chains of Linear layers over the given widths, side by side, a squared loss on all of them."""
+    g = W._Graph()
+    outs = []
+    for _ in range(branches):
+        x = g.input(widths[0], dtype)
+        for k, n, act in zip(widths, widths[1:], acts):
+            x = g.linear(x, k, n, act, dtype)
+        outs.append(x)
+    y, total = outs[0], widths[-1] * branches
+    if branches > 1:
+        y = g.add("concat", outs, out_features=total, dtype=dtype)
+    t = g.input(total, W.F32, role="target")
+    g.add("loss_mse", (y, t), loss_scale=1.0 / (rows * n_micro * total))
+    rng = np.random.Generator(np.random.PCG64(rows + total))
+    params = W._draw_params(g.ops, rng)
+    for p in params.values():
+        p["b"] = 0.1 * rng.standard_normal(p["b"].shape).astype(np.float32)
+    batches = W._draw_batches(g.ops, rows, n_micro, rng, {})
+    return W.Workload("gemm_tiles", g.ops, rows, n_micro, params, batches, 2e-2 if dtype == W.BF16 else 1e-4)
+
+
+# The bar is that of bf16 storage with fp32 accumulation: the oracle rounds at the same places, so what is left is the order of
+# fp32 sums and results that fall on the other side of a rounding boundary.
+@pytest.mark.parametrize("rows,widths,acts,branches", [
+    (2000, (128, 2056, 136), ("gelu", "none"), 2),        # 256 x 256 forward, ragged in both directions
+    (1900, (1904, 136, 2000), ("none", "gelu"), 2),       # 256 x 256 backward-data into 1904 columns
+    (250, (520, 2056, 520), ("gelu", "gelu"), 9),         # 128 x 256 forward, a last row tile of 122 rows
+    (129, (1000, 1500, 1000), ("gelu", "gelu"), 7),       # one row more than a tile
+    (300, (203, 333, 70), ("gelu", "none"), 3),           # columns that end inside a 16-byte chunk
+    (65, (64, 128, 8), ("gelu", "none"), 1),              # smallest launch with a choice of kernels
+    (700, (600, 2000, 72), ("gelu", "none"), 1),
+])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_tiles_of_every_shape(rows, widths, acts, branches, grouped):
+    wl = _chain(rows, widths, acts, branches, 2)          # (ungrouped: the second micro-batch adds to the gradients of the first)
+    print(f"[case] rows={rows} widths={widths} branches={branches} grouped={grouped}", flush=True)
+    if grouped:
+        _, res, grads = _run(wl, 2, 2, False, flags=B.FLAG_GROUPED_DW)
+    else:
+        res, grads = run_gpu(wl)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="gemm_tiles")
