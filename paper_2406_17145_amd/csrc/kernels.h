@@ -205,11 +205,12 @@ struct StageFlags {
 };
 
 // ---- launch entry points (defined next to the kernels) -------------------------
-void launch_gemm_generic(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int in_dtype, hipStream_t s);
+void launch_gemm_generic(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int in_dtype, int tile, hipStream_t s);
 void launch_gemm_mfma(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile,
                       const ExtPtrs &ext, hipStream_t s);
 // tile geometry used by the planner to count workgroups
-int gemm_generic_tiles(int M, int N, int *tiles_n);
+int gemm_generic_tiles(int tile, int M, int N, int *tiles_n);
+int gemm_generic_tile(int tiles64);
 int gemm_mfma_group_tile(int form, int maxM, int maxN);
 int gemm_mfma_tiles_for(int tile, int M, int N, int *tiles_n);
 int gemm_mfma_partial_floats(int tile);

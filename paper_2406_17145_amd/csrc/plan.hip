@@ -818,6 +818,11 @@ struct Emitter {
             continue;
           }
           int launch_tiles = 0;
+          if (!use_mfma) {
+            int tiles64 = 0;
+            for (auto &r : g) tiles64 += gemm_generic_tiles(64, r.M, r.N, nullptr);
+            tile = gemm_generic_tile(tiles64);
+          }
           if (use_mfma)
             for (auto &r : g) launch_tiles += gemm_mfma_tiles_for(tile, r.M, r.N, nullptr);
           int64_t part_off = 0, cnt_off = 0;
@@ -825,7 +830,7 @@ struct Emitter {
             r.blk_begin = blocks;
             r.split_k = 1;
             if (!use_mfma) {
-              blocks += gemm_generic_tiles(r.M, r.N, &r.tiles_n);
+              blocks += gemm_generic_tiles(tile, r.M, r.N, &r.tiles_n);
               continue;
             }
             const int tiles = gemm_mfma_tiles_for(tile, r.M, r.N, &r.tiles_n);
@@ -1480,7 +1485,10 @@ void Emitter::backward() {
           w.K = (int32_t)nd.rows;           // contraction over the micro-batch rows
           w.in_dtype = d.param_dtype;
           // on the matrix-core path the bias gradient rides along in the backward-weight launch
-          bool fuse_db = d.has_bias && !(pl.flags & 1) && w.in_dtype == DT_BF16 && gemm_mfma_supported(w);
+          // (the generic kernel sums what it multiplies too: fp32 layers, whose operand is the stored gradient itself;
+          // two launches of a [8 x 128 x 64] perceptron's backward pass less)
+          bool fuse_db = d.has_bias && ((!(pl.flags & 1) && w.in_dtype == DT_BF16 && gemm_mfma_supported(w)) ||
+                                        (w.in_dtype == DT_F32 && nd.gout.dtype == DT_F32));
           // grouped weight gradients: this record waits for the launch that contracts over every slot of
           // a group of backward passes (both operands sit at the same offsets in every slot)
           const bool grouped = (pl.flags & 4) && !(pl.flags & 1) && w.in_dtype == DT_BF16 && gemm_big_supported(w) &&
