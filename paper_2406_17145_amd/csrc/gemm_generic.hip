@@ -183,9 +183,6 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const GemmProb *__restrict
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
 
-  // backward-weight tiles of the first column block also sum the rows of dZ^T they stream: the bias gradient
-  const bool do_bias = p.form == FORM_DW && p.bias != nullptr && n0 == 0;
-  float bsum = 0.0f;
   for (int k0 = 0; k0 < p.K; k0 += GK) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -213,15 +210,23 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const GemmProb *__restrict
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
     }
-    if (do_bias && t < GT) {
-#pragma unroll
-      for (int kk = 0; kk < GK; ++kk) bsum += As[kk][t];
-    }
     __syncthreads();
   }
-  if (do_bias && t < GT && m0 + t < p.M) {
-    GPP_G float *db = (GPP_G float *)p.bias + m0 + t;
-    *db = accumulate_dw ? *db + bsum : bsum;
+  // backward-weight tiles of the first column block also sum the columns of dZ, the bias gradient: four row groups, in
+  // a loop of its own (a test for it inside the loop above doubled the time of every launch)
+  if (p.form == FORM_DW && p.bias != nullptr && n0 == 0) {
+    float bsum = 0.0f;
+    const int bi = min(m0 + (t & (GT - 1)), p.M - 1);
+#pragma unroll 4
+    for (int k = t / GT; k < p.K; k += 256 / GT) bsum += to_f32<T>(A[(int64_t)k * sak + bi]);
+    float *red = &As[0][0];
+    red[t] = bsum;
+    __syncthreads();
+    if (t < GT && m0 + t < p.M) {
+      const float total = (red[t] + red[GT + t]) + (red[2 * GT + t] + red[3 * GT + t]);
+      GPP_G float *db = (GPP_G float *)p.bias + m0 + t;
+      *db = accumulate_dw ? *db + total : total;
+    }
   }
 
 #pragma unroll
