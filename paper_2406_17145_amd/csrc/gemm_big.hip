@@ -18,6 +18,8 @@
 // swizzled LDS tiles, with the LDS reads software-pipelined under the MFMAs).  The three forms and the two
 // LDS layouts (k-contiguous rows read with b128, contraction-major rows read with the transposing read) are
 // those of the smaller tile kernel.
+#include <algorithm>
+
 #include "gemm_tile_body.h"
 
 namespace gpp {
@@ -184,13 +186,13 @@ struct BigTile {
 // GM > 0: the tiles of a record are numbered in bands of GM tile rows, column by column inside a band, so that
 // the tiles in flight on an XCD form a block that is about as wide as it is high (fewest distinct operand panels
 // per tile); GM = 0: whole columns of tiles one after the other.
+__device__ __forceinline__ int big_spread(int total_blocks) {
+  const int bid = blockIdx.x, xcd = bid & 7, idx = bid >> 3, per = total_blocks >> 3, rem = total_blocks & 7;
+  return xcd * per + min(xcd, rem) + idx;
+}
 template <int BM, int BN, int GM = 0>
 __device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs, int n, int total_blocks) {
-  int bid = blockIdx.x;
-  {
-    const int xcd = bid & 7, idx = bid >> 3, per = total_blocks >> 3, rem = total_blocks & 7;
-    bid = xcd * per + min(xcd, rem) + idx;
-  }
+  const int bid = big_spread(total_blocks);
   BigTile t;
   t.pi = find_prob(probs, n, bid);
   const int tile = bid - probs[t.pi].blk_begin;
@@ -216,7 +218,9 @@ __device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs
 // the other -- the weight gradient of a group of backward passes in one pass over the accumulator.
 // Both operands live in the slots at the same offsets: slot g of the group is `grp.stride` bytes times
 // its slot number behind slot 0, whose addresses the record holds.
-template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, int NS, bool GROUP = false, int PIPE = 0>
+//
+// PARTIAL (forward): the record covers a slice of a contraction; its result is that slice's sum, stored as plain fp32.
+template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, int NS, bool GROUP = false, int PIPE = 0, bool PARTIAL = false>
 __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0, uint16_t *lds, int accumulate_dw,
                                               const ExtPtrs &ext, const SlotGroup grp = SlotGroup()) {
   static_assert(!GROUP || FORM == FORM_DW, "only the weight gradient contracts over a group of slots");
@@ -496,6 +500,12 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   // with a barrier); other results (fp32 outputs among them) keep the accumulator layout.
   static_assert(C::NW * epi_lds_floats<WTN>() * 4 <= C::LDS_ELEMS * 2, "epilogue blocks do not fit the operand LDS");
   const bool inside = m0 + BM <= p.M && n0 + BN <= p.N;
+  if constexpr (PARTIAL) {      // fp32 rows as a gradient's (the planner's buffer has whole, aligned rows)
+    float *stage = (float *)lds + wave * epi_lds_floats<WTN>();
+    if (inside) epilogue_wave_lds<FORM_DW, false, WTM, WTN>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, 0, stage);
+    else epilogue_wave_lds<FORM_DW, true, WTM, WTN>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, 0, stage);
+    return;
+  }
   // (also for a plain bias / cast epilogue: rows in 16-byte pieces beat the accumulator layout's 2-byte pieces
   // sixteen rows apart -- 4 x [2048 x 4096 x 1024] forward 78 -> 75.5 us, a one-k-step launch of the same output
   // 29 -> 26 us.  While the stores were flat instructions, which count on the LDS wait counter as well, it
@@ -518,6 +528,73 @@ __global__ __launch_bounds__(512) void k_gemm_big(const GemmProb *__restrict__ p
   const BigTile t = big_locate<C::BM, C::BN>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
   big_tile_body<FORM, 2, 4, WTM, WTN, BUFS, NS, false, PIPE>(p, t.m0, t.n0, lds, accumulate_dw, ext);
+}
+
+// Forward with a long contraction and few output tiles (the layer behind a merge of many branches): `split_k` workgroups
+// share an output tile of 128 x 256, each sums a slice of the contraction into its own fp32 matrix, and the launch behind
+// this one adds the slices in order and finishes the result.  The workgroups of one slice follow each other, so an XCD
+// works on few slices and its L2 sees a tile row of that slice's operands once.  [512 x 4096 x 28672]: 211 us on
+// the 64 x 64 blocks, 124 + 12 here; [256 x 4096 x 73472]: 292 and 176 + 10.
+__global__ __launch_bounds__(512) void k_gemm_big_split(const GemmProb *__restrict__ probs, int total_blocks) {
+  typedef BigCfg<FORM_FWD, 2, 4, 2, 2, 3, true> C;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
+  const int w = big_spread(total_blocks);
+  GemmProb p = probs[0];
+  const int tiles = total_blocks / p.split_k, split = w / tiles, tile = w - split * tiles, tiles_m = cdiv(p.M, C::BM);
+  const int slice = cdiv(cdiv(p.K, GB_BK), p.split_k) * GB_BK, k0 = split * slice;     // (every slice holds some of the contraction)
+  p.A = (const GPP_G uint16_t *)p.A + k0;
+  p.B = (const GPP_G uint16_t *)p.B + k0;
+  p.K = min(slice, p.K - k0);
+  p.ldc = split_sum_ld(p.N);
+  p.C = p.partial + (int64_t)split * p.M * p.ldc;
+  p.c_ext = 0;
+  ExtPtrs none;
+  big_tile_body<FORM_FWD, 2, 4, 2, 2, 3, 2, false, 1, true>(p, (tile % tiles_m) * C::BM, (tile / tiles_m) * C::BN, lds, 0, none);
+}
+// sum of the slices in order, then what the forward epilogue does; a thread takes four columns of a row
+__global__ __launch_bounds__(256) void k_split_sum(const GemmProb *__restrict__ probs, ExtPtrs ext) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const GemmProb p = probs[0];
+  void *Cout = result_ptr(p, ext);
+  if (Cout == nullptr) return;
+  const int ld = (int)split_sum_ld(p.N), quads = ld / 4;
+  const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int row = (int)(at / quads), col = (int)(at - (int64_t)row * quads) * 4;
+  if (row >= p.M || col >= p.N) return;
+  const GPP_G float *src = p.partial + (int64_t)row * ld + col;
+  const int64_t step = (int64_t)p.M * ld;
+  float v[4] = {0.0f, 0.0f, 0.0f, 0.0f}, d[4];
+  for (int q = 0; q < p.split_k; q += 4) {
+    f32x4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = *(const GPP_G f32x4 *)(src + (int64_t)min(q + u, p.split_k - 1) * step);   // (loads without a branch)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += q + u < p.split_k ? x[u][e] : 0.0f;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int c = min(col + e, p.N - 1);
+    if (p.bias) v[e] += p.bias[c];
+    d[e] = act_stash(v[e], p.act);
+    v[e] = act_apply(v[e], p.act);
+    if (p.res) v[e] += load_as_f32(p.res, p.res_dtype, (int64_t)row * p.ldres + c);
+  }
+  auto put = [&](void *dst, int dtype, int64_t ldd, const float (&o)[4]) {
+    const int64_t i = (int64_t)row * ldd + col;
+    if (dtype == DT_BF16 && col + 4 <= p.N && (ldd & 3) == 0 && ((uintptr_t)dst & 7) == 0) {
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      *(u32x2 *)((uint16_t *)dst + i) = (u32x2){(uint32_t)f32_to_bf16_bits(o[0]) | ((uint32_t)f32_to_bf16_bits(o[1]) << 16),
+                                                (uint32_t)f32_to_bf16_bits(o[2]) | ((uint32_t)f32_to_bf16_bits(o[3]) << 16)};
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col + e < p.N) store_from_f32(dst, dtype, i + e, o[e]);
+  };
+  if (p.act == ACT_GELU && p.aux) put((void *)p.aux, p.aux_dtype, p.ldaux, d);
+  put(Cout, p.c_dtype, p.ldc, v);
 }
 
 // 128 x 128 tile, 2 x 2 waves of 64 x 64, one LDS buffer, three waves per SIMD
@@ -577,7 +654,7 @@ bool gemm_big_supported(const GemmProb &p) {
 // 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218; a lone [512 x 4096 x 4096]: 95, 62, 72, 45.
 // The estimates are within 20 % of what was measured, so the 64 x 64 blocks, whose time depends least on the rest of
 // the shape, are left only for an estimate 10 % below theirs.
-int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64) {
+int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, float *us) {
   constexpr float CUS = 256.0f;
   const float nk = (float)cdiv(max_k, GB_BK);
   const bool fwd = form == FORM_FWD;
@@ -608,7 +685,19 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
   take(64, mid(c.t128));
   take(256, rounds(c.t256, t256));
   if (fwd) take(128, rounds(c.t128x256, t128));
+  *us = best;
   return rows;
+}
+// Slices of a lone forward record's contraction (0: not split): as many workgroups as compute units, slices of at least 16
+// k-steps, where one round of them and the pass over the slices (written and read once, 4 TB/s, and a launch) take 15 %
+// less than the kernel chosen otherwise, by the estimates above.
+int gemm_big_split(int M, int N, int K, float us) {
+  const int tiles = cdiv(M, 128) * cdiv(N, 256), nk = cdiv(K, GB_BK);
+  int s = std::min(std::min(16, 256 / tiles), nk / 16);
+  if (s < 2) return 0;
+  s = cdiv(nk, cdiv(nk, s));                            // no slice without k-steps
+  const float t = 13.0f + 0.95f * (float)cdiv(nk, s) + 8.0f + (float)M * (float)N * 8.0f * (float)s / 4e6f;
+  return s >= 2 && t < 0.85f * us ? s : 0;
 }
 int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n) {
   const int bn = tile_rows == 64 ? 128 : 256, bm = tile_rows == 64 ? 128 : tile_rows;
@@ -639,6 +728,13 @@ void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumul
   } else {
     hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, ext);
   }
+}
+
+void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, const ExtPtrs &ext, hipStream_t s) {
+  if (total_blocks <= 0) return;
+  hipLaunchKernelGGL(k_gemm_big_split, dim3(total_blocks), dim3(512), 0, s, probs, total_blocks);
+  const int64_t threads = (int64_t)M * (split_sum_ld(N) / 4);
+  hipLaunchKernelGGL(k_split_sum, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s, probs, ext);
 }
 
 void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, const SlotGroup &grp, hipStream_t s) {

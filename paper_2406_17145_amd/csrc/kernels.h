@@ -234,7 +234,12 @@ struct GemmTileCounts {
   float t256 = 0, t128x256 = 0, t128 = 0, t64 = 0;     // 256 x 256, 128 x 256, 128 x 128, 64 x 64
 };
 // forward / backward-data; `blocks64`: the 64 x 64 kernel (0) is a choice
-int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64);
+// (*us: the estimate of the choice)
+int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, float *us);
+// forward over slices of the contraction: slices (0: none), row stride of their fp32 sums [slices][M][ld], and the two launches
+int gemm_big_split(int M, int N, int K, float us);
+inline __host__ __device__ int64_t split_sum_ld(int N) { return (N + 63) / 64 * 64; }
+void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, const ExtPtrs &ext, hipStream_t s);
 int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n);
 // backward-weight for small weight matrices and many rows: 64 x 64 tiles, the contraction split over the waves
 void launch_gemm_dw_ksplit(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, hipStream_t s);

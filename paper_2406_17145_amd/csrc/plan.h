@@ -29,7 +29,7 @@ enum Kern : int32_t {
   K_ELT, K_GEMM_GENERIC, K_GEMM_MFMA, K_COLSUM, K_LN_FWD, K_LN_BWD, K_LN_BWD_PARAMS, K_ATTN_FWD, K_ATTN_DQ,
   K_ATTN_DKV, K_POOL, K_EMB_FWD, K_EMB_BWD, K_INTERACT_FWD, K_INTERACT_BWD, K_LOSS_FWD, K_LOSS_BWD, K_LOSS_SUM,
   K_GEMM_SKINNY, K_GEMM_BWD_MERGED, K_LOSS_FWD_SMALL, K_GEMM_BIG, K_GEMM_DW_KSPLIT, K_GEMM_DW_GROUP, K_FORK, K_JOIN,
-  K_HEAD_LOSS
+  K_HEAD_LOSS, K_GEMM_SPLIT
 };
 enum ExtKind : int32_t { EXT_NONE = 0, EXT_INPUTS, EXT_OUTPUTS, EXT_GRAD_OUTPUTS, EXT_GRAD_INPUTS };
 
@@ -71,6 +71,7 @@ struct Plan {
   std::vector<int> input_ops, output_ops, loss_ops;
   int64_t micro_batch = 0;
   int32_t slots = 1, flags = 0;
+  int64_t slot_data_bytes = 0, split_bytes = 0;   // a slot: its tensors, then the fp32 sums of a forward GEMM's slices
   int64_t slot_bytes = 0, shared_bytes = 0, table_bytes = 0, tmp_bytes = 0;
   int64_t gemm_partial_bytes = 0, gemm_counter_bytes = 0;   // split-K partial tiles and arrival counters
   int64_t off_flags = 0, off_tables = 0, off_group_tables = 0, off_slots = 0, off_shared = 0, total_bytes = 0;

@@ -367,12 +367,13 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
     loss_parts = (int)parts;
     loss_scalars = alloc(SP_SLOT, 1, std::max<int64_t>(1, parts), DT_F32);
   }
-  slot_bytes = align_up(slot_top, 256);
+  slot_data_bytes = align_up(slot_top, 256);
   shared_bytes = align_up(shared_top, 256);
   return GPP_OK;
 }
 
 void Plan::layout() {
+  slot_bytes = slot_data_bytes + split_bytes;
   off_flags = 0;
   off_tables = 256;
   off_group_tables = align_up(off_tables + (int64_t)slots * table_bytes, 256);
@@ -396,6 +397,7 @@ struct Emitter {
   std::vector<int> gstate;
   std::vector<Buf> gaddend;
   std::vector<char> dz_ready;
+  int64_t split_need = 0;               // the same of the forward GEMM over slices of its contraction (per slot)
   int64_t part_need = 0, cnt_need = 0;  // split-K scratch high-water marks over all launches
   std::vector<LnProb> ln_fold_later;    // LayerNorm parameter folds of the whole backward pass (see backward())
   std::vector<GemmProb> dw_group;   // backward-weight records left to the launch over a group of slots
@@ -746,8 +748,22 @@ struct Emitter {
           if (use_mfma) tile = gemm_mfma_group_tile(form, max_m, max_n);
           // few rows: the weight-streaming kernel (forward and backward-data only)
           int row_tiles = (use_mfma && form != FORM_DW) ? few_rows(g) : 0;
-          int tile_rows = (use_mfma && form != FORM_DW) ? large_tile(g, form, row_tiles) : 0;
+          int slices = 0;
+          int tile_rows = (use_mfma && form != FORM_DW) ? large_tile(g, form, row_tiles, &slices) : 0;
           if (tile_rows > 0) row_tiles = 0;
+          if (slices > 1) {     // (the sums live in the slot: passes of different micro-batches may overlap)
+            GemmProb &r = g[0];
+            r.blk_begin = 0;
+            r.split_k = slices;
+            r.partial = (float *)(ws + pl.off_slots + (int64_t)slot * pl.slot_bytes + pl.slot_data_bytes);
+            split_need = std::max(split_need, align_up(slices * r.M * split_sum_ld(r.N) * 4, 256));
+            Step &s = add_step(K_GEMM_SPLIT, push_table(g), 1, gemm_big_tiles_for(128, r.M, r.N, &r.tiles_n) * slices);
+            s.a1 = r.M;
+            s.a2 = r.N;
+            s.launches = 2;
+            if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
+            continue;
+          }
           if (row_tiles > 0) {
             int blocks = 0, col_tiles = 2;
             // (group launches cover several micro-batches: the launch is large without the smaller row tile, and
@@ -874,7 +890,8 @@ struct Emitter {
   // not meant for the launch either, the small tiles.  Up to 64 rows a tile would be half padding.  Where launches
   // share the GPU (flag bit 4) the few-row kernel stays wherever it is meant to run: its workgroups fit beside those of
   // another stream, and group launches, which give the same results bit by bit as single ones, know no other kernel.
-  int large_tile(const std::vector<GemmProb> &g, int form, int few) const {
+  // *slices: > 1 when a lone forward record had better be summed over that many slices of its contraction.
+  int large_tile(const std::vector<GemmProb> &g, int form, int few, int *slices = nullptr) const {
     if (pl.flags & 2) return 0;
     int max_m = 0, max_n = 0, max_k = 0;
     for (auto &r : g) {
@@ -893,7 +910,10 @@ struct Emitter {
       c.t128 += share * tiles(r, 128, 128);
       c.t64 += share * tiles(r, 64, 64);
     }
-    int rows = gemm_big_tile_rows(form, max_k, c, few > 0);
+    float us = 0.0f;
+    int rows = gemm_big_tile_rows(form, max_k, c, few > 0, &us);
+    if (slices && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16) && gemm_big_direct_ok(g[0]))
+      *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, us);
     // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source) behind a short
     // contraction: the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident
     // 128 x 128 workgroups hide them behind each other's k-loops (4 x [2048 x 4096 x 1024] with the GELU derivative
@@ -1870,6 +1890,7 @@ gpp_status_t Plan::emit(int slot, char *ws) {
   tmp_bytes = std::max<int64_t>(tmp_bytes, em.shared_tmp_top);
   gemm_partial_bytes = std::max<int64_t>(gemm_partial_bytes, em.part_need);
   gemm_counter_bytes = std::max<int64_t>(gemm_counter_bytes, em.cnt_need);
+  split_bytes = std::max<int64_t>(split_bytes, em.split_need);
   return GPP_OK;
 }
 

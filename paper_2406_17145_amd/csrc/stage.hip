@@ -80,7 +80,7 @@ static void *g_static_ptr[STATIC_MAX_DEVICES] = {nullptr};          // per devic
 static const gpp_stage *g_static_owner[STATIC_MAX_DEVICES] = {nullptr};   // per device: the stage that holds it
 
 static bool gemm_step(const Step &sp) {
-  return sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_SKINNY || sp.kern == K_GEMM_BWD_MERGED ||
+  return sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_SPLIT || sp.kern == K_GEMM_SKINNY || sp.kern == K_GEMM_BWD_MERGED ||
          sp.kern == K_GEMM_DW_KSPLIT || sp.kern == K_GEMM_DW_GROUP;
 }
 
@@ -88,6 +88,7 @@ static bool gemm_step(const Step &sp) {
 static int step_tag(const Step &sp, bool backward) {
   switch (sp.kern) {
     case K_GEMM_MFMA: return 1 + sp.a1;                    // 1 fwd, 2 dx, 3 dw
+    case K_GEMM_SPLIT: return 28;
     case K_GEMM_BIG: return 28 + sp.a1;                    // 28 fwd, 29 dx, 30 dw
     case K_GEMM_SKINNY: return 25 + sp.a1;                 // 25 fwd, 26 dx
     case K_GEMM_BWD_MERGED: return 27;
@@ -453,6 +454,7 @@ static gpp_status_t run_steps(gpp_stage *st, const std::vector<Step> &steps, int
         if (!grp) return fail(GPP_ERR_UNSUPPORTED, "internal: group launch without a group");
         launch_gemm_dw_group((const GemmProb *)tab, sp.n, sp.blocks, accumulate, *grp, s);
         break;
+      case K_GEMM_SPLIT: launch_gemm_split((const GemmProb *)tab, sp.blocks, sp.a1, sp.a2, ext, s); break;
       case K_GEMM_SKINNY: launch_gemm_skinny((const GemmProb *)tab, sp.n, sp.blocks, sp.a1, sp.a2, sp.a0, sp.a3, ext, s); break;
       case K_GEMM_BWD_MERGED: launch_gemm_bwd_merged((const GemmProb *)tab, sp.n, sp.blocks, sp.a2, sp.a1, accumulate, ext, s); break;
       case K_HEAD_LOSS: {   // always runs: it also writes the prediction and two gradients

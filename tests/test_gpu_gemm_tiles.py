@@ -43,6 +43,8 @@ def _chain(rows, widths, acts, branches, n_micro, dtype=W.BF16):
     (300, (203, 333, 70), ("gelu", "none"), 3),           # columns that end inside a 16-byte chunk
     (65, (64, 128, 8), ("gelu", "none"), 1),              # smallest launch with a choice of kernels
     (700, (600, 2000, 72), ("gelu", "none"), 1),
+    (130, (20008, 523, 64), ("gelu", "none"), 1),         # sums over 16 slices of the contraction, the last one shorter
+    (100, (9000, 1000), ("none",), 1),                    # the same into an output of the stage
 ])
 @pytest.mark.parametrize("grouped", [False, True])
 def test_tiles_of_every_shape(rows, widths, acts, branches, grouped):
