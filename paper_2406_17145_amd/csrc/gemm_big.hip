@@ -470,7 +470,17 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
     }
   } else {
     fetch(ra[0], rb[0], 0);
+    const bool ragged = FORM != FORM_DW && (p.K & 7) != 0;     // the contraction ends inside a chunk of k-contiguous rows
     for (int kt = 0; kt < nk; ++kt) {
+      if (ragged && kt + 1 == nk) {                            // clear what lies beyond it (row padding)
+        const int k = kt * GB_BK + (tid & 7) * 8;
+#pragma unroll
+        for (int q = 0; q < RegsA::PER_THREAD; ++q) ra[0].v[q] = chunk_clear_tail(ra[0].v[q], k, p.K);
+        if (!B_TR) {
+#pragma unroll
+          for (int q = 0; q < RegsB::PER_THREAD; ++q) rb[0].v[q] = chunk_clear_tail(rb[0].v[q], k, p.K);
+        }
+      }
       to_lds(ra[0], rb[0], 0);
       __syncthreads();
       if (kt + 1 < nk) fetch(ra[0], rb[0], kt + 1);
@@ -628,8 +638,8 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
 }
 
 // ---- host side -------------------------------------------------------------------------
-// The kernels take a problem when the chunks of its k-contiguous operands are whole (contraction
-// length a multiple of 8) and the matrices fit the 32-bit buffer offsets.
+// The kernels take a problem when its matrices fit the 32-bit buffer offsets; the eight-wave ones also need whole chunks
+// of k-contiguous operands (contraction length a multiple of 8).
 // Direct loads move whole, aligned 16-byte chunks: rows and base pointers of both operands must be 16-byte
 // aligned (the planner pads leading dimensions to 64 elements, so only unusual callers fail this).
 bool gemm_big_direct_ok(const GemmProb &p) {
@@ -637,7 +647,6 @@ bool gemm_big_direct_ok(const GemmProb &p) {
 }
 bool gemm_big_supported(const GemmProb &p) {
   if (!gemm_mfma_supported(p)) return false;
-  if (p.form != FORM_DW && (p.K & 7)) return false;
   const int64_t a_rows = p.form == FORM_DW ? p.K : p.M, b_rows = p.form == FORM_FWD ? p.N : p.K;
   if (a_rows * p.lda * 2 >= 0xffffff00ll || b_rows * p.ldb * 2 >= 0xffffff00ll) return false;
   return true;
@@ -652,9 +661,10 @@ bool gemm_big_supported(const GemmProb &p) {
 //                                                                   7 x [256 x 4096 x 4096] backward-data 87 (256: 127, 0: 159)
 //   64 x 64:   at a few workgroups per compute unit.                4 x [512 x 1000 x 3820] 48 (256: 96, 128: 65, 64: 72)
 // 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218; a lone [512 x 4096 x 4096]: 95, 62, 72, 45.
+// `whole_chunks`: every contraction length is a multiple of 8.
 // The estimates are within 20 % of what was measured, so the 64 x 64 blocks, whose time depends least on the rest of
 // the shape, are left only for an estimate 10 % below theirs.
-int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, float *us) {
+int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, bool whole_chunks, float *us) {
   constexpr float CUS = 256.0f;
   const float nk = (float)cdiv(max_k, GB_BK);
   const bool fwd = form == FORM_FWD;
@@ -683,8 +693,8 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
     }
   };
   take(64, mid(c.t128));
-  take(256, rounds(c.t256, t256));
-  if (fwd) take(128, rounds(c.t128x256, t128));
+  if (whole_chunks) take(256, rounds(c.t256, t256));
+  if (whole_chunks && fwd) take(128, rounds(c.t128x256, t128));
   *us = best;
   return rows;
 }

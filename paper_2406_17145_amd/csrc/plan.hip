@@ -256,8 +256,11 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
         m.val_parent = i;
         m.val_col = col;
       }
-      // (a concatenated embedding bag reads its gradient as a dense [b * bag_size, d] matrix: own buffer)
-      if (sole && m.gdtype == c.gdtype && m.wants_grad && m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
+      // (a concatenated embedding bag reads its gradient as a dense [b * bag_size, d] matrix: own buffer.  A Linear whose
+      // slice does not start on 16 bytes gets a copy of its gradient: on the slice itself its two GEMMs would not run
+      // on the matrix cores -- five [951 x 2036 x 2036] layers: 690 us each for both, the copy 30)
+      const bool aligned = m.d.kind != GPP_OP_LINEAR || c.gdtype != DT_BF16 || col % 8 == 0;
+      if (sole && aligned && m.gdtype == c.gdtype && m.wants_grad && m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
         m.gout_parent = i;
         m.gout_col = col;
       }
@@ -893,12 +896,13 @@ struct Emitter {
   // *slices: > 1 when a lone forward record had better be summed over that many slices of its contraction.
   int large_tile(const std::vector<GemmProb> &g, int form, int few, int *slices = nullptr) const {
     if (pl.flags & 2) return 0;
-    int max_m = 0, max_n = 0, max_k = 0;
+    int max_m = 0, max_k = 0;
+    bool whole = true;
     for (auto &r : g) {
       if (!gemm_big_supported(r)) return 0;
       max_m = std::max(max_m, r.M);
-      max_n = std::max(max_n, r.N);
       max_k = std::max(max_k, r.K);
+      whole = whole && r.K % 8 == 0;
     }
     if (few > 0 && (max_m <= 64 || (pl.flags & 16) || pl.group_lanes > 0)) return 0;
     GemmTileCounts c;
@@ -911,8 +915,8 @@ struct Emitter {
       c.t64 += share * tiles(r, 64, 64);
     }
     float us = 0.0f;
-    int rows = gemm_big_tile_rows(form, max_k, c, few > 0, &us);
-    if (slices && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16) && gemm_big_direct_ok(g[0]))
+    int rows = gemm_big_tile_rows(form, max_k, c, few > 0, whole, &us);
+    if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16) && gemm_big_direct_ok(g[0]))
       *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, us);
     // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source) behind a short
     // contraction: the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident

@@ -41,6 +41,7 @@ def _chain(rows, widths, acts, branches, n_micro, dtype=W.BF16):
     (250, (520, 2056, 520), ("gelu", "gelu"), 9),         # 128 x 256 forward, a last row tile of 122 rows
     (129, (1000, 1500, 1000), ("gelu", "gelu"), 7),       # one row more than a tile
     (300, (203, 333, 70), ("gelu", "none"), 3),           # columns that end inside a 16-byte chunk
+    (700, (1203, 333, 1207), ("gelu", "gelu"), 4),        # contractions that end inside a chunk, slices of a merge off 16 bytes
     (65, (64, 128, 8), ("gelu", "none"), 1),              # smallest launch with a choice of kernels
     (700, (600, 2000, 72), ("gelu", "none"), 1),
     (130, (20008, 523, 64), ("gelu", "none"), 1),         # sums over 16 slices of the contraction, the last one shorter
