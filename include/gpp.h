@@ -418,6 +418,13 @@ int32_t gpp_stage_num_outputs(const gpp_stage_t *stage);
 /* op id of the i-th input / output; -1 if out of range */
 int32_t gpp_stage_input_op(const gpp_stage_t *stage, int32_t i);
 int32_t gpp_stage_output_op(const gpp_stage_t *stage, int32_t i);
+/* The grouped launches that a stage of this descriptor consists of, one line each in the order of issue: the pass
+ * (forward, backward, weights), the profile tag of the kernel, its records and workgroups, and for GEMM kernels that
+ * have a choice the rows of their output tile and the slices of their contraction (0: none), as
+ *   forward gemm_big_fwd records=7 blocks=224 tile=256 slices=0
+ * Host-only: needs no GPU, parameter pointers are not looked at.  text: HOST, zero-terminated; GPP_ERR_INVALID_ARG if
+ * `capacity` bytes do not hold it. */
+gpp_status_t gpp_stage_describe(const gpp_stage_desc_t *desc, char *text, size_t capacity);
 /* number of kernel launches of one forward (backward = 0) / backward (1) / grouped weight-gradient (2) call */
 int32_t gpp_stage_num_launches(const gpp_stage_t *stage, int32_t backward);
 /* Integer artefacts of the last backward of embedding op `op`: DEVICE pointers into the workspace.

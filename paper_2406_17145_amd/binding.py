@@ -60,7 +60,7 @@ EXPORTS = [
     "gpp_stage_embedding_sort_result", "gpp_last_error", "gpp_stage_profile_enable", "gpp_stage_profile_read",
     "gpp_profile_tag_name", "gpp_compute_in_flight", "gpp_assign_schedules", "gpp_schedule_tasks",
     "gpp_stage_run_schedule", "gpp_stage_memory", "gpp_stage_backward_weights", "gpp_stage_info", "gpp_stage_io_info",
-    "gpp_stage_run_schedule_lanes", "gpp_stage_lanes", "gpp_stage_group_launches",
+    "gpp_stage_run_schedule_lanes", "gpp_stage_lanes", "gpp_stage_group_launches", "gpp_stage_describe",
     "gpp_partition", "gpp_partition_search", "gpp_pipeline_workspace_bytes", "gpp_pipeline_create", "gpp_pipeline_run", "gpp_pipeline_destroy",
 ]
 GPP_PROFILE_TAGS = 32
@@ -133,6 +133,7 @@ def load():
                                                  C.POINTER(vp), i32]
     lib.gpp_stage_lanes.restype, lib.gpp_stage_lanes.argtypes = i32, [vp, C.POINTER(i32), C.POINTER(i32)]
     lib.gpp_stage_group_launches.restype, lib.gpp_stage_group_launches.argtypes = i32, [vp, C.POINTER(i32), C.POINTER(i32)]
+    lib.gpp_stage_describe.restype, lib.gpp_stage_describe.argtypes = i32, [C.POINTER(StageDesc), C.c_char_p, C.c_size_t]
     lib.gpp_stage_memory.restype, lib.gpp_stage_memory.argtypes = i32, [vp] + [C.POINTER(C.c_size_t)] * 3
     lib.gpp_stage_info.restype = i32
     lib.gpp_stage_info.argtypes = [vp, C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
@@ -436,6 +437,17 @@ def gpp_partition_search(n_ops, edges, b_values, t, w, a, k_values, n_devices, m
     n = ns.value
     return dict(stage_of_op=list(stage_of), devices=list(dev)[:n], in_flight=list(inf)[:n], b=list(sb)[:n], k=list(sk)[:n],
                 bottleneck=tps.value, dp_states=states.value)
+
+
+def gpp_stage_describe(desc):
+    """The launches of a stage: one dict each with pass, kernel (its profile tag), records, blocks, tile and slices."""
+    buf = C.create_string_buffer(1 << 20)
+    _check(load().gpp_stage_describe(C.byref(desc), buf, len(buf)))
+    out = []
+    for line in buf.value.decode().splitlines():
+        p, kernel, *fields = line.split()
+        out.append({"pass": p, "kernel": kernel, **{k: int(v) for k, v in (f.split("=") for f in fields)}})
+    return out
 
 
 def gpp_stage_memory(handle):

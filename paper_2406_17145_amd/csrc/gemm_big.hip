@@ -701,9 +701,9 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
 // Slices of a lone forward record's contraction (0: not split): as many workgroups as compute units, slices of at least 16
 // k-steps, where one round of them and the pass over the slices (written and read once, 4 TB/s, and a launch) take 15 %
 // less than the kernel chosen otherwise, by the estimates above.
-int gemm_big_split(int M, int N, int K, float us) {
+int gemm_big_split(int M, int N, int K, int64_t most, float us) {
   const int tiles = cdiv(M, 128) * cdiv(N, 256), nk = cdiv(K, GB_BK);
-  int s = std::min(std::min(16, 256 / tiles), nk / 16);
+  int s = (int)std::min<int64_t>(std::min(std::min(16, 256 / tiles), nk / 16), most);
   if (s < 2) return 0;
   s = cdiv(nk, cdiv(nk, s));                            // no slice without k-steps
   const float t = 13.0f + 0.95f * (float)cdiv(nk, s) + 8.0f + (float)M * (float)N * 8.0f * (float)s / 4e6f;

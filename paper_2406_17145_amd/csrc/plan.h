@@ -71,7 +71,10 @@ struct Plan {
   std::vector<int> input_ops, output_ops, loss_ops;
   int64_t micro_batch = 0;
   int32_t slots = 1, flags = 0;
-  int64_t slot_data_bytes = 0, split_bytes = 0;   // a slot: its tensors, then the fp32 sums of a forward GEMM's slices
+  // Memory that no forward pass of a slot has a use for: the gradient buffers that the backward pass writes (space, offset,
+  // bytes).  The fp32 sums of a forward GEMM over slices of its contraction live there, see Emitter::forward_scratch.
+  Buf fwd_scratch;
+  int64_t fwd_scratch_bytes = 0;
   int64_t slot_bytes = 0, shared_bytes = 0, table_bytes = 0, tmp_bytes = 0;
   int64_t gemm_partial_bytes = 0, gemm_counter_bytes = 0;   // split-K partial tiles and arrival counters
   int64_t off_flags = 0, off_tables = 0, off_group_tables = 0, off_slots = 0, off_shared = 0, total_bytes = 0;

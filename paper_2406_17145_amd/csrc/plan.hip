@@ -322,7 +322,20 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
     // grouped weight gradients read dZ of several in-flight micro-batches at once: a copy per slot
     nd.gout = alloc((flags & 4) ? SP_SLOT : SP_SHARED, nd.rows, nd.feat, nd.gdtype);
   };
+  // first the gradients that a forward launch may write (a loss's prediction, the input of a one-column head in front of
+  // it), then the others: nothing of these is alive during a forward pass of their slot.  Shared ones belong to a stage's
+  // only slot, or may be in use by another slot's backward pass on another stream.
+  for (int i = 0; i < n; ++i)
+    if (nodes[i].is_loss) {
+      const int y = nodes[i].in[0];
+      alloc_gout(y);
+      if (nodes[y].d.kind == GPP_OP_LINEAR && nodes[y].feat == 1) alloc_gout(nodes[y].in[0]);
+    }
+  const int64_t slot_mark = slot_top, shared_mark = shared_top;
   for (int i = 0; i < n; ++i) alloc_gout(i);
+  fwd_scratch.space = slots == 1 && !(flags & 4) ? SP_SHARED : SP_SLOT;
+  fwd_scratch.off = fwd_scratch.space == SP_SLOT ? slot_mark : shared_mark;
+  fwd_scratch_bytes = (fwd_scratch.space == SP_SLOT ? slot_top : shared_top) - fwd_scratch.off;
   for (int i = 0; i < n; ++i) {
     Node &nd = nodes[i];
     const gpp_op_desc_t &d = nd.d;
@@ -370,13 +383,12 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
     loss_parts = (int)parts;
     loss_scalars = alloc(SP_SLOT, 1, std::max<int64_t>(1, parts), DT_F32);
   }
-  slot_data_bytes = align_up(slot_top, 256);
+  slot_bytes = align_up(slot_top, 256);
   shared_bytes = align_up(shared_top, 256);
   return GPP_OK;
 }
 
 void Plan::layout() {
-  slot_bytes = slot_data_bytes + split_bytes;
   off_flags = 0;
   off_tables = 256;
   off_group_tables = align_up(off_tables + (int64_t)slots * table_bytes, 256);
@@ -400,7 +412,6 @@ struct Emitter {
   std::vector<int> gstate;
   std::vector<Buf> gaddend;
   std::vector<char> dz_ready;
-  int64_t split_need = 0;               // the same of the forward GEMM over slices of its contraction (per slot)
   int64_t part_need = 0, cnt_need = 0;  // split-K scratch high-water marks over all launches
   std::vector<LnProb> ln_fold_later;    // LayerNorm parameter folds of the whole backward pass (see backward())
   std::vector<GemmProb> dw_group;   // backward-weight records left to the launch over a group of slots
@@ -427,6 +438,12 @@ struct Emitter {
     if (steps == &pl.fwd) pl.fwd_shared = true;
     else if (steps == &pl.bwd) pl.bwd_shared = true;
     return ws + pl.off_shared + b.off;
+  }
+  // (not through ptr(): as shared memory it is used by a stage with one slot only, whose forward passes never overlap
+  // with anything)
+  char *forward_scratch() const {
+    const Buf &b = pl.fwd_scratch;
+    return ws + (b.space == SP_SLOT ? pl.off_slots + (int64_t)slot * pl.slot_bytes : pl.off_shared) + b.off;
   }
   template <typename T>
   int64_t push_table(const std::vector<T> &recs) {
@@ -754,12 +771,11 @@ struct Emitter {
           int slices = 0;
           int tile_rows = (use_mfma && form != FORM_DW) ? large_tile(g, form, row_tiles, &slices) : 0;
           if (tile_rows > 0) row_tiles = 0;
-          if (slices > 1) {     // (the sums live in the slot: passes of different micro-batches may overlap)
+          if (slices > 1) {
             GemmProb &r = g[0];
             r.blk_begin = 0;
             r.split_k = slices;
-            r.partial = (float *)(ws + pl.off_slots + (int64_t)slot * pl.slot_bytes + pl.slot_data_bytes);
-            split_need = std::max(split_need, align_up(slices * r.M * split_sum_ld(r.N) * 4, 256));
+            r.partial = (float *)forward_scratch();
             Step &s = add_step(K_GEMM_SPLIT, push_table(g), 1, gemm_big_tiles_for(128, r.M, r.N, &r.tiles_n) * slices);
             s.a1 = r.M;
             s.a2 = r.N;
@@ -893,7 +909,8 @@ struct Emitter {
   // not meant for the launch either, the small tiles.  Up to 64 rows a tile would be half padding.  Where launches
   // share the GPU (flag bit 4) the few-row kernel stays wherever it is meant to run: its workgroups fit beside those of
   // another stream, and group launches, which give the same results bit by bit as single ones, know no other kernel.
-  // *slices: > 1 when a lone forward record had better be summed over that many slices of its contraction.
+  // *slices: > 1 when a lone forward record had better be summed over that many slices of its contraction (no more than
+  // have their sums in the memory that a forward pass may overwrite: a stage needs no workspace for them).
   int large_tile(const std::vector<GemmProb> &g, int form, int few, int *slices = nullptr) const {
     if (pl.flags & 2) return 0;
     int max_m = 0, max_k = 0;
@@ -917,7 +934,7 @@ struct Emitter {
     float us = 0.0f;
     int rows = gemm_big_tile_rows(form, max_k, c, few > 0, whole, &us);
     if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16) && gemm_big_direct_ok(g[0]))
-      *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, us);
+      *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, pl.fwd_scratch_bytes / (g[0].M * split_sum_ld(g[0].N) * 4), us);
     // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source) behind a short
     // contraction: the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident
     // 128 x 128 workgroups hide them behind each other's k-loops (4 x [2048 x 4096 x 1024] with the GELU derivative
@@ -1894,7 +1911,6 @@ gpp_status_t Plan::emit(int slot, char *ws) {
   tmp_bytes = std::max<int64_t>(tmp_bytes, em.shared_tmp_top);
   gemm_partial_bytes = std::max<int64_t>(gemm_partial_bytes, em.part_need);
   gemm_counter_bytes = std::max<int64_t>(gemm_counter_bytes, em.cnt_need);
-  split_bytes = std::max<int64_t>(split_bytes, em.split_need);
   return GPP_OK;
 }
 

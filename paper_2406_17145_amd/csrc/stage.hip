@@ -171,6 +171,29 @@ gpp_status_t gpp_stage_workspace_bytes(const gpp_stage_desc_t *desc, size_t *byt
   return GPP_OK;
 }
 
+gpp_status_t gpp_stage_describe(const gpp_stage_desc_t *desc, char *text, size_t capacity) {
+  if (!text || capacity == 0) return fail(GPP_ERR_INVALID_ARG, "text is null or has no room");
+  Plan pl;
+  gpp_status_t st = build_plan(desc, pl);
+  if (st != GPP_OK) return fail(st, pl.error);
+  std::string out;
+  const std::vector<Step> *lists[3] = {&pl.fwd, &pl.bwd, &pl.dwg};
+  static const char *const names[3] = {"forward", "backward", "weights"};
+  for (int l = 0; l < 3; ++l)
+    for (const Step &sp : *lists[l]) {
+      char line[160];
+      int tile = 0, slices = 0;
+      if (sp.kern == K_GEMM_GENERIC || sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG) tile = sp.a2;
+      if (sp.kern == K_GEMM_SPLIT) slices = ((const GemmProb *)(pl.blob.data() + sp.table_off))->split_k;
+      snprintf(line, sizeof(line), "%s %s records=%d blocks=%d tile=%d slices=%d\n", names[l], kTagNames[step_tag(sp, l == 1)], sp.n,
+               sp.blocks, tile, slices);
+      out += line;
+    }
+  if (out.size() + 1 > capacity) return fail(GPP_ERR_INVALID_ARG, "text needs " + std::to_string(out.size() + 1) + " bytes");
+  memcpy(text, out.c_str(), out.size() + 1);
+  return GPP_OK;
+}
+
 // workspace == nullptr: take the static workspace of the current device (gpp_stage_create_static)
 static gpp_status_t stage_create(const gpp_stage_desc_t *desc, void *workspace, size_t workspace_bytes, gpp_stage_t **out) {
   if (!out) return fail(GPP_ERR_INVALID_ARG, "out is null");

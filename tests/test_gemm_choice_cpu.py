@@ -1,0 +1,56 @@
+"""Which GEMM kernels a stage's plan holds and what workspace it needs, from the library's own planner (no GPU): the sizes at
+which a rule of the dispatch changes its answer."""
+import pytest
+
+from paper_2406_17145_amd import binding as B
+from paper_2406_17145_amd import workloads as W
+
+
+def desc(ops, rows, slots=1, flags=0):
+    return B.build_desc(ops, rows, slots, flags)
+
+
+def plan(ops, rows, slots=1, flags=0):
+    d, keep = desc(ops, rows, slots, flags)
+    return B.gpp_stage_describe(d)
+
+
+def layers(rows, k, n, branches=1, act="none", dtype=W.BF16, loss=False, out_dtype=None, grad=True):
+    """`branches` Linear layers side by side over inputs of their own; a loss over the first one's output, or stage outputs."""
+    g = W._Graph()
+    for _ in range(branches):
+        y = g.linear(g.input(k, dtype) if grad else g.input(k, dtype, role="fixed"), k, n, act, dtype, out_dtype=out_dtype)
+    if loss:
+        g.add("loss_mse", (y, g.input(n, W.F32, role="target")), loss_scale=1.0 / (rows * n))
+    return g.ops
+
+
+def line(n):
+    return -(-n // 256) * 256
+
+
+@pytest.mark.parametrize("rows,k,n", [(128, 20480, 4096), (256, 16384, 1024), (100, 16000, 1000)])
+@pytest.mark.parametrize("slots,flags", [(1, 0), (1, B.FLAG_GROUPED_DW), (4, 0), (4, B.FLAG_GROUPED_DW)])
+@pytest.mark.parametrize("grad", [True, False])
+def test_sums_over_slices_need_no_workspace(rows, k, n, slots, flags, grad):
+    """A stage of one layer holds, per slot, the input, the output and the target, and per slot or once both gradients: the sums
+    of a contraction over slices add nothing (what is left are launch tables of a few kilobytes)."""
+    ops = layers(rows, k, n, loss=True, grad=grad)
+    d, keep = desc(ops, rows, slots, flags)
+    ld = B.gpp_ld
+    values = line(rows * ld(k) * 2) + line(rows * ld(n) * 2) + line(rows * ld(n) * 4)
+    grads = line(rows * ld(n) * 2) + (line(rows * ld(k) * 2) if grad else 0)
+    need = slots * (values + (grads if flags else 0)) + (0 if flags else grads)
+    assert need < B.gpp_stage_workspace_bytes(d) < need + (32 << 10) * slots
+
+
+def test_sums_over_slices_fit_the_gradients_they_lie_over():
+    def slices(ops, rows, slots, flags):
+        return [p["slices"] for p in plan(ops, rows, slots, flags) if p["kernel"] == "gemm_big_fwd"]
+    wide = layers(256, 20480, 1024, loss=True)
+    for slots, flags in ((1, 0), (1, B.FLAG_GROUPED_DW), (3, B.FLAG_GROUPED_DW)):
+        (s,) = slices(wide, 256, slots, flags)
+        assert 2 <= s and s * 256 * 1024 * 4 <= 256 * 20480 * 2     # (the input's gradient buffer)
+    # gradients that the slots share may be in use by another micro-batch; without an input gradient there is nothing to lie over
+    assert not any(slices(wide, 256, 2, 0))
+    assert not any(slices(layers(256, 20480, 1024, loss=True, grad=False), 256, 1, B.FLAG_GROUPED_DW))

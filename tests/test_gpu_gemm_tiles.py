@@ -33,6 +33,50 @@ def _chain(rows, widths, acts, branches, n_micro, dtype=W.BF16):
     return W.Workload("gemm_tiles", g.ops, rows, n_micro, params, batches, 2e-2 if dtype == W.BF16 else 1e-4)
 
 
+def _plan(wl, slots=1, flags=0):
+    d, keep = B.build_desc(wl.ops, wl.micro_batch, slots, flags)
+    return B.gpp_stage_describe(d)
+
+
+# What the second launch of a layer over slices of its contraction does to the sum of the slices: every activation, a residual
+# addend, both storage types, a result of the stage, a result inside a merge buffer (on 16 bytes, on 8, on 2).  The sums lie over
+# the slot's gradient buffers, so the backward pass that follows finds arbitrary bits in every row's padding.
+@pytest.mark.parametrize("kind", ["none", "relu", "gelu", "f32", "residual", "output", "merge_0", "merge_12", "merge_13"])
+@pytest.mark.parametrize("slots,flags", [(1, 0), (1, B.FLAG_GROUPED_DW), (2, B.FLAG_GROUPED_DW)])
+def test_sums_over_slices(kind, slots, flags):
+    rows, k, n, n_micro = 100, 16000, 1000, 3
+    g = W._Graph()
+    act = kind if kind in ("relu", "gelu") else "none"
+    y = g.linear(g.input(k, W.BF16), k, n, act, W.BF16, out_dtype=W.F32 if kind == "f32" else None)
+    if kind == "residual":
+        y = g.add("add", (y, g.input(n, W.BF16)), out_features=n, dtype=W.BF16)
+    if kind.startswith("merge"):
+        col = int(kind[6:])
+        parts = ([g.input(col, W.BF16)] if col else []) + [y]
+        m = g.add("concat", parts, out_features=col + n, dtype=W.BF16)
+        y, n = g.linear(m, col + n, 40, "gelu", W.BF16), 40
+    if kind != "output":
+        g.add("loss_mse", (y, g.input(n, W.F32, role="target")), loss_scale=1.0 / (rows * n_micro * n))
+    rng = np.random.Generator(np.random.PCG64(len(kind)))
+    params = W._draw_params(g.ops, rng)
+    for p in params.values():
+        p["b"] = 0.1 * rng.standard_normal(p["b"].shape).astype(np.float32)
+    wl = W.Workload("gemm_tiles", g.ops, rows, n_micro, params, W._draw_batches(g.ops, rows, n_micro, rng, {}), 2e-2)
+    gouts = [{y: W.round_to_bf16(rng.standard_normal((rows, n)).astype(np.float32))} for _ in range(n_micro)] if kind == "output" else None
+    print(f"[case] slices {kind} slots={slots} flags={flags}", flush=True)
+    assert [p["slices"] > 1 for p in _plan(wl, slots, flags) if p["kernel"] == "gemm_big_fwd"] == [True]
+    _, res, grads = _run(wl, slots, 1, slots > 1, slots=slots, flags=flags, gouts=gouts)
+    stage, ref = run_oracle(wl, gouts)
+    compare(wl, res, grads, stage, ref, label=f"gemm_tiles slices {kind}")
+
+
+def test_sums_over_slices_in_the_static_workspace():
+    wl = _chain(256, (16384, 1024), ("gelu",), 1, 2)
+    assert max(p["slices"] for p in _plan(wl)) > 1
+    st = B.Stage(wl.ops, wl.micro_batch, wl.params, static_workspace=True)
+    st.close()
+
+
 # The bar is that of bf16 storage with fp32 accumulation: the oracle rounds at the same places, so what is left is the order of
 # fp32 sums and results that fall on the other side of a rounding boundary.
 @pytest.mark.parametrize("rows,widths,acts,branches", [
