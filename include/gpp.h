@@ -160,14 +160,20 @@ int64_t gpp_ld(int64_t features);
 
 /* Bytes of workspace a stage needs (activation stash for every slot, backward
  * scratch, launch tables, sort buffers).  Host-only: needs no GPU.  Validates
- * the descriptor (parameter pointers are not looked at). */
+ * the descriptor (parameter pointers are not looked at).
+ * Part of it is not strictly needed: a bf16 LINEAR that a CONCAT places at a
+ * column that is no multiple of 8 gets a copy of its output gradient
+ * (rows * gpp_ld(out_features) * 2 bytes, per stash slot under flag bit 2).
+ * Creation takes a workspace that only lacks these copies and runs such layers
+ * on the gradient in place, with kernels that are several times slower. */
 gpp_status_t gpp_stage_workspace_bytes(const gpp_stage_desc_t *desc, size_t *bytes);
 
 /* Validates G_i (C1: it must be a DAG; shapes must agree), plans the grouped
  * launches and copies the launch tables into the workspace (synchronous
  * copies; the only calls of this library that synchronise are create,
  * destroy-free-of-device-work and sync_status).  `workspace` is DEVICE memory
- * of at least gpp_stage_workspace_bytes bytes, 256-byte aligned, owned by the
+ * of at least gpp_stage_workspace_bytes bytes (or without the copies described
+ * there; the message of GPP_ERR_WORKSPACE names the least), 256-byte aligned, owned by the
  * caller and reserved for this stage until destroy.  Its content is cleared. */
 gpp_status_t gpp_stage_create(const gpp_stage_desc_t *desc, void *workspace, size_t workspace_bytes,
                               gpp_stage_t **out);

@@ -71,6 +71,9 @@ struct Plan {
   std::vector<int> input_ops, output_ops, loss_ops;
   int64_t micro_batch = 0;
   int32_t slots = 1, flags = 0;
+  // Linear layers merged at a column off 16 bytes: their gradient is copied out of the merge's (gout_copies: the stage has
+  // some), or read in place (no_copies, set before analyse(): the workspace is too small for the copies)
+  bool gout_copies = false, no_copies = false;
   // Memory that no forward pass of a slot has a use for: the gradient buffers that the backward pass writes (space, offset,
   // bytes).  The fp32 sums of a forward GEMM over slices of its contraction live there, see Emitter::forward_scratch.
   Buf fwd_scratch;

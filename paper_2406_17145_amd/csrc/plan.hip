@@ -260,9 +260,13 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
       // slice does not start on 16 bytes gets a copy of its gradient: on the slice itself its two GEMMs would not run
       // on the matrix cores -- five [951 x 2036 x 2036] layers: 690 us each for both, the copy 30)
       const bool aligned = m.d.kind != GPP_OP_LINEAR || c.gdtype != DT_BF16 || col % 8 == 0;
-      if (sole && aligned && m.gdtype == c.gdtype && m.wants_grad && m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
-        m.gout_parent = i;
-        m.gout_col = col;
+      if (sole && m.gdtype == c.gdtype && m.wants_grad && m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
+        if (aligned || no_copies) {
+          m.gout_parent = i;
+          m.gout_col = col;
+        } else {
+          gout_copies = true;
+        }
       }
       col += m.feat;
     }
@@ -447,7 +451,7 @@ struct Emitter {
   }
   template <typename T>
   int64_t push_table(const std::vector<T> &recs) {
-    int64_t off = align_up((int64_t)pl.blob.size(), 64);
+    int64_t off = align_up((int64_t)pl.blob.size(), 16);
     pl.blob.resize(off + recs.size() * sizeof(T));
     if (!recs.empty()) memcpy(pl.blob.data() + off, recs.data(), recs.size() * sizeof(T));
     return off;

@@ -152,14 +152,18 @@ int64_t gpp_ld(int64_t features) { return (features + 63) / 64 * 64; }
 
 const char *gpp_last_error(void) { return g_last_error.c_str(); }
 
-static gpp_status_t build_plan(const gpp_stage_desc_t *desc, Plan &pl) {
+// `room`: bytes of workspace there are; a plan that needs more and holds gradient copies is made again without them
+static gpp_status_t build_plan(const gpp_stage_desc_t *desc, Plan &pl, size_t room = SIZE_MAX) {
   gpp_status_t st = pl.analyse(desc);
   if (st != GPP_OK) return st;
   pl.layout();
   st = pl.emit(0, nullptr);  // sizing pass: table and temporary sizes
   if (st != GPP_OK) return st;
   pl.layout();
-  return GPP_OK;
+  if ((size_t)pl.total_bytes <= room || !pl.gout_copies) return GPP_OK;
+  pl = Plan();
+  pl.no_copies = true;
+  return build_plan(desc, pl, room);
 }
 
 gpp_status_t gpp_stage_workspace_bytes(const gpp_stage_desc_t *desc, size_t *bytes) {
@@ -216,7 +220,7 @@ static gpp_status_t stage_create(const gpp_stage_desc_t *desc, void *workspace, 
   }
   gpp_stage *st = new (std::nothrow) gpp_stage();
   if (!st) return fail(GPP_ERR_INVALID_ARG, "out of host memory");
-  gpp_status_t rc = build_plan(desc, st->plan);
+  gpp_status_t rc = build_plan(desc, st->plan, workspace_bytes);
   if (rc != GPP_OK) {
     std::string e = st->plan.error;
     delete st;

@@ -6,6 +6,7 @@ import pytest
 from paper_2406_17145_amd import binding as B
 from paper_2406_17145_amd import workloads as W
 from tests.parity_util import compare, run_gpu, run_oracle
+from tests.test_gemm_choice_cpu import least_workspace
 from tests.test_gpu_schedule import _run
 
 pytestmark = pytest.mark.gpu
@@ -101,6 +102,22 @@ def test_tiles_of_every_shape(rows, widths, acts, branches, grouped):
         res, grads = run_gpu(wl)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="gemm_tiles")
+
+
+# A workspace that lacks only the gradient copies of a merge off 16 bytes: the stage runs on the gradients in place.
+@pytest.mark.parametrize("act", ["relu", "gelu"])
+@pytest.mark.parametrize("slots,flags", [(1, 0), (2, B.FLAG_GROUPED_DW)])
+def test_merge_off_16_bytes_without_room_for_the_copies(act, slots, flags, monkeypatch):
+    wl = _chain(300, (120, 77, 203), (act, act), 3, 2)
+    least = least_workspace(wl.ops, wl.micro_batch, slots, flags)
+    assert least < B.gpp_stage_workspace_bytes(B.build_desc(wl.ops, wl.micro_batch, slots, flags)[0])
+    print(f"[case] merge off 16 bytes {act} slots={slots} flags={flags}", flush=True)
+    stage, ref = run_oracle(wl)
+    for room in (None, least):
+        if room:
+            monkeypatch.setattr(B, "gpp_stage_workspace_bytes", lambda d: room)
+        _, res, grads = _run(wl, slots, 1, slots > 1, slots=slots, flags=flags)
+        compare(wl, res, grads, stage, ref, label="gemm_tiles merge off 16 bytes")
 
 
 # fp32: the small tiles (32 x 32, contraction in steps of 64, split over four waves) around their edges, and the first launch that
