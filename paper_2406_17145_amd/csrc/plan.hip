@@ -258,8 +258,9 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
       }
       // (a concatenated embedding bag reads its gradient as a dense [b * bag_size, d] matrix: own buffer.  A Linear whose
       // slice does not start on 16 bytes gets a copy of its gradient: on the slice itself its two GEMMs would not run
-      // on the matrix cores -- five [951 x 2036 x 2036] layers: 690 us each for both, the copy 30)
-      const bool aligned = m.d.kind != GPP_OP_LINEAR || c.gdtype != DT_BF16 || col % 8 == 0;
+      // on the matrix cores -- five [951 x 2036 x 2036] layers: 690 us each for both, the copy 30; nor do they with a copy
+      // under flag bit 0)
+      const bool aligned = m.d.kind != GPP_OP_LINEAR || c.gdtype != DT_BF16 || col % 8 == 0 || (flags & 1);
       if (sole && m.gdtype == c.gdtype && m.wants_grad && m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
         if (aligned || no_copies) {
           m.gout_parent = i;

@@ -88,3 +88,13 @@ def test_gradient_copies_of_a_merge_are_not_insisted_on(slots, flags):
     aligned = merged(500, (104, 96, 104, 40))
     d, keep = desc(aligned, rows, slots, flags)
     assert B.gpp_stage_workspace_bytes(d) == least_workspace(aligned, rows, slots, flags)
+
+
+@pytest.mark.parametrize("flags", [B.FLAG_FORCE_GENERIC_GEMM, B.FLAG_FORCE_GENERIC_GEMM | B.FLAG_GROUPED_DW])
+def test_no_gradient_copies_without_matrix_cores(flags):
+    ops, rows = merged(500, (100, 100, 105, 40)), 500
+    d, keep = desc(ops, rows, 2, flags)
+    assert B.gpp_stage_workspace_bytes(d) == least_workspace(ops, rows, 2, flags)
+    # one element-wise launch of the backward pass ingests the output gradients, one applies the derivatives, one returns the
+    # input gradients
+    assert len([p for p in B.gpp_stage_describe(d) if p["pass"] == "backward" and p["kernel"] == "elt_bwd"]) == 3
