@@ -52,7 +52,7 @@ struct GemmProb {
 // ---- 2-D copy / convert / accumulate / activation backward --------------
 // dst[r,c] = cvt(src[r,c]) (+ addend[r,c]); rows x cols elements.
 // mode 1 (act backward, in place on dst): dst[r,c] = dst[r,c] * act'(src[r,c])
-// mode 2 (add): dst = src + addend
+// mode 2 (copy with act backward): dst[r,c] = src[r,c] * act'(addend[r,c])
 struct EltProb {
   const GPP_G void *src;
   GPP_G void *dst;

@@ -17,10 +17,11 @@ int elt_blocks(int rows, int cols) {
 // every load of a thread requested before its first store: a run-time type test or a bounds branch in
 // front of each load makes the wave wait for the previous load, and the copy then pays one memory
 // latency per element instead of one per thread.  Elements beyond the end re-read the last element.
-template <int SD, int DD>
+// MASK: times the derivative from the bf16 matrix p.addend on the way.
+template <int SD, int DD, bool MASK = false>
 __device__ __forceinline__ void elt_copy_body(const EltProb &p, const void *src, void *dst, uint32_t base, uint32_t total) {
   constexpr int IT = ELT_PER_BLOCK / 256;
-  float v[IT];
+  float v[IT], m[IT];
   uint32_t di[IT];
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -29,6 +30,11 @@ __device__ __forceinline__ void elt_copy_body(const EltProb &p, const void *src,
     const int64_t si = (int64_t)r * p.ld_src + c;
     di[it] = r * (uint32_t)p.ld_dst + c;
     v[it] = SD == DT_BF16 ? bf16_bits_to_f32(((const uint16_t *)src)[si]) : ((const float *)src)[si];
+    if (MASK) m[it] = bf16_bits_to_f32(((const uint16_t *)p.addend)[(int64_t)r * p.ld_add + c]);
+  }
+  if (MASK) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) v[it] *= act_grad(m[it], p.act);
   }
 #pragma unroll
   for (int it = 0; it < IT; ++it)
@@ -71,8 +77,10 @@ __global__ __launch_bounds__(256) void k_elt(const EltProb *__restrict__ probs, 
   if (!src || !dst) return;
   const int64_t total = (int64_t)p.rows * p.cols;
   const int64_t base = (int64_t)(blockIdx.x - p.blk_begin) * ELT_PER_BLOCK;
-  if (p.mode == 0 && !p.addend && p.src_dtype != DT_I32 && p.dst_dtype != DT_I32 && total < (1ll << 31) &&
-      (int64_t)p.rows * p.ld_dst < (1ll << 32)) {
+  const bool small = total < (1ll << 31) && (int64_t)p.rows * p.ld_dst < (1ll << 32);
+  if (p.mode == 2 && small && p.src_dtype == DT_BF16 && p.dst_dtype == DT_BF16 && p.add_dtype == DT_BF16)
+    return elt_copy_body<DT_BF16, DT_BF16, true>(p, src, dst, (uint32_t)base, (uint32_t)total);
+  if (p.mode == 0 && !p.addend && p.src_dtype != DT_I32 && p.dst_dtype != DT_I32 && small) {
     const bool sb = p.src_dtype == DT_BF16, db = p.dst_dtype == DT_BF16;
     if (sb && db && elt_vec_ok(p, src, dst, 2)) return elt_copy_vec_body<2>(p, src, dst, (uint32_t)base, (uint32_t)total);
     if (!sb && !db && elt_vec_ok(p, src, dst, 4)) return elt_copy_vec_body<4>(p, src, dst, (uint32_t)base, (uint32_t)total);
@@ -96,7 +104,8 @@ __global__ __launch_bounds__(256) void k_elt(const EltProb *__restrict__ probs, 
       store_from_f32(dst, p.dst_dtype, di, g * act_grad(load_as_f32(src, p.src_dtype, si), p.act));
     } else {
       float v = load_as_f32(src, p.src_dtype, si);
-      if (p.addend) v += load_as_f32(p.addend, p.add_dtype, (int64_t)r * p.ld_add + c);
+      if (p.mode == 2) v *= act_grad(load_as_f32(p.addend, p.add_dtype, (int64_t)r * p.ld_add + c), p.act);
+      else if (p.addend) v += load_as_f32(p.addend, p.add_dtype, (int64_t)r * p.ld_add + c);
       store_from_f32(dst, p.dst_dtype, di, v);
     }
   }

@@ -1425,12 +1425,12 @@ void Emitter::backward() {
 
   auto mask_source = [&](const Node &p) -> Buf { return p.d.act == GPP_ACT_GELU_ERF ? p.aux : p.val; };
   // every member of concat `c` is a ReLU layer stored in place whose only consumer is the concat and
-  // whose gradient is a view of the concat's gradient
+  // whose gradient is a view of the concat's gradient or a copy of its slice of it
   auto concat_relu_members = [&](int c) -> bool {
     for (int m : N[c].in) {
       const Node &mm = N[m];
       if (mm.d.kind != GPP_OP_LINEAR || mm.d.act != GPP_ACT_RELU || mm.users.size() != 1 || mm.val_parent != c ||
-          mm.gout_parent != c || mm.fused_add >= 0 || dz_ready[m])
+          (mm.gout_parent >= 0 ? mm.gout_parent != c : mm.gdtype != N[c].gdtype) || mm.fused_add >= 0 || dz_ready[m])
         return false;
     }
     return true;
@@ -1478,28 +1478,28 @@ void Emitter::backward() {
       flush_post();
     }
 
-    // 2. complete the gradients of this level's operators
+    // 2. complete the gradients of this level's operators: the copy of a gradient that was passed through applies the
+    // activation's derivative on the way, other gradients are multiplied in place.  One launch: what is multiplied in
+    // place is a buffer or a merge's column slice of its operator's own, no copy reads it.
     std::vector<int> live;
     {
-      std::vector<EltProb> copies, masks;
+      std::vector<EltProb> recs;
       for (int i : pl.by_level[L]) {
         Node &nd = N[i];
         if (nd.is_loss || !nd.wants_grad) continue;
-        if (nd.gout_parent < 0 && gstate[i] == G_ADDEND) {
-          copies.push_back(elt(gaddend[i], nd.gout, nd.rows, nd.feat));
-          gstate[i] = G_WRITTEN;
-        }
+        const bool mask = nd.d.kind == GPP_OP_LINEAR && nd.d.act != GPP_ACT_NONE && !dz_ready[i];
+        const bool copy = nd.gout_parent < 0 && gstate[i] == G_ADDEND;
+        if (copy) gstate[i] = G_WRITTEN;
         if (state_of(i) != G_WRITTEN) continue;  // no gradient reaches this operator
         live.push_back(i);
-        if (nd.d.kind == GPP_OP_LINEAR && nd.d.act != GPP_ACT_NONE && !dz_ready[i]) {
-          EltProb e = elt(mask_source(nd), nd.gout, nd.rows, nd.feat);
-          e.mode = 1;
-          e.act = nd.d.act;
-          masks.push_back(e);
-        }
+        if (!copy && !mask) continue;
+        EltProb e = elt(copy ? gaddend[i] : mask_source(nd), nd.gout, nd.rows, nd.feat);
+        if (copy && mask) with_addend(e, mask_source(nd));
+        e.mode = !mask ? 0 : copy ? 2 : 1;
+        e.act = nd.d.act;
+        recs.push_back(e);
       }
-      emit_elt(copies);
-      emit_elt(masks);
+      emit_elt(recs);
     }
 
     // 3. per-kind grouped backward launches

@@ -98,3 +98,14 @@ def test_no_gradient_copies_without_matrix_cores(flags):
     # one element-wise launch of the backward pass ingests the output gradients, one applies the derivatives, one returns the
     # input gradients
     assert len([p for p in B.gpp_stage_describe(d) if p["pass"] == "backward" and p["kernel"] == "elt_bwd"]) == 3
+
+
+def test_activation_of_a_copied_gradient_costs_no_launch():
+    """Launches of the backward pass between the merged layer's GEMMs and the branches': one that copies and multiplies (GELU),
+    none but the copies where the merged layer has applied the derivative of every branch (ReLU)."""
+    for act in ("gelu", "relu"):
+        steps = [p for p in plan(merged(500, (100, 100, 105, 40), act), 500) if p["pass"] == "backward"]
+        elt = [p["records"] for p in steps if p["kernel"] == "elt_bwd"]
+        # output gradients in; two copies, and in place the other two; input gradients that no GEMM stored itself
+        assert elt[:2] == [1, 4 if act == "gelu" else 2]
+        assert len(elt) <= 3
