@@ -219,8 +219,10 @@ __device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs
 // Both operands live in the slots at the same offsets: slot g of the group is `grp.stride` bytes times
 // its slot number behind slot 0, whose addresses the record holds.
 //
+// STREAM (backward-weight): stored gradients go past the caches, see epilogue_wave_lds.
 // PARTIAL (forward): the record covers a slice of a contraction; its result is that slice's sum, stored as plain fp32.
-template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, int NS, bool GROUP = false, int PIPE = 0, bool PARTIAL = false>
+template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, int NS, bool GROUP = false, int PIPE = 0, bool PARTIAL = false,
+          bool STREAM = false>
 __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0, uint16_t *lds, int accumulate_dw,
                                               const ExtPtrs &ext, const SlotGroup grp = SlotGroup()) {
   static_assert(!GROUP || FORM == FORM_DW, "only the weight gradient contracts over a group of slots");
@@ -523,8 +525,8 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   if (epi_lds_ok(p, Cout, FORM)) {
     if (FORM == FORM_DW && do_bias) __syncthreads();   // the bias sums were read from LDS after the last barrier
     float *stage = (float *)lds + wave * epi_lds_floats<WTN>();
-    if (inside) epilogue_wave_lds<FORM, false, WTM, WTN, GROUP>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
-    else epilogue_wave_lds<FORM, true, WTM, WTN, GROUP>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
+    if (inside) epilogue_wave_lds<FORM, false, WTM, WTN, STREAM>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
+    else epilogue_wave_lds<FORM, true, WTM, WTN, STREAM>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
   } else {
     epilogue_wave<FORM, true, WTM, WTN>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw);
   }
@@ -627,6 +629,7 @@ constexpr int DW_BAND = 8;
 // (four workgroups per compute unit: 40 KB of LDS and 128 registers each; with three the transformer stage's launch
 // is 6 % slower.  The tile for every size: 256 x 256 outputs per workgroup of eight waves, alone on its compute unit,
 // exposes its 256 KB of stores -- seven [4096 x 4096] gradients over 256 / 2048 rows 127 / 467 us against 100 / 410)
+template <bool STREAM>
 __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
                                                               int accumulate_dw, SlotGroup grp) {
   typedef BigCfg<FORM_DW, 2, 2, 2, 2, 1> C;
@@ -634,7 +637,7 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
   const BigTile t = big_locate<C::BM, C::BN, DW_BAND>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
   ExtPtrs none;
-  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true>(p, t.m0, t.n0, lds, accumulate_dw, none, grp);
+  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, accumulate_dw, none, grp);
 }
 
 // ---- host side -------------------------------------------------------------------------
@@ -747,9 +750,18 @@ void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, co
   hipLaunchKernelGGL(k_split_sum, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s, probs, ext);
 }
 
-void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, const SlotGroup &grp, hipStream_t s) {
+// Gradients of one launch that are stored past the caches: those that a memory-side cache of 256 MB cannot hold until somebody
+// reads them, since what it holds instead -- weights, activations -- is read again.  One mini-batch, one group: eight branches with
+// 358 MB 241 -> 202 us, 220 MB 204 -> 183, seven towers with 1.9 GB 1594 -> 1481; with 92 MB and less 0 - 1 % slower, and 2 %
+// where a second group of the mini-batch adds to them (8 % for that pass alone).  Above the line that second group loses less
+// than the first has gained (two groups: 541 -> 492 us, 460 -> 419, 3450 -> 3320).
+bool gemm_dw_group_streams(int64_t gradient_bytes) { return gradient_bytes >= (int64_t)128 << 20; }
+void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
+                          hipStream_t s) {
   if (total_blocks <= 0 || grp.n <= 0) return;
-  hipLaunchKernelGGL(k_gemm_mid_dw_group, dim3(total_blocks), dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, grp);
+  const dim3 g(total_blocks), b(256);
+  if (stream) hipLaunchKernelGGL(k_gemm_mid_dw_group<true>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
+  else hipLaunchKernelGGL(k_gemm_mid_dw_group<false>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
 }
 
 }  // namespace gpp

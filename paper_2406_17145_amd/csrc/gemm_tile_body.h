@@ -394,9 +394,9 @@ __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout,
     if (FORM == FORM_DW) {
       // fp32 rows: a lane takes FOUR columns, so that one instruction of a wave covers whole rows of the block
       // (256 contiguous bytes of each); with eight columns per lane every store covered every other 16 bytes of a
-      // row, and the L2 had to put the lines together.  STREAM: a gradient that no pass adds to any more goes past
-      // the caches, which keep the operand panels instead (seven [4096 x 4096] gradients over 512 rows: 178 us with
-      // eight columns per lane, 167 with four, 137 streamed; over 2048 rows 454, 440, 410)
+      // row, and the L2 had to put the lines together.  STREAM: gradients that are stored, not added to, go past the
+      // caches, which keep what is read again instead (gemm_dw_group_streams; seven [4096 x 4096] gradients over 512
+      // rows: 178 us with eight columns per lane, 167 with four, 137 streamed; over 2048 rows 454, 440, 410)
       constexpr int LPR4 = COLS / 4, RPI4 = 64 / LPR4, ITS4 = 32 / RPI4;
       const int rl4 = lane / LPR4, c4 = (lane % LPR4) * 4, row4 = wr0 + 32 * i + rl4;
       const bool in4 = !CHECK || wc0 + c4 < p.N, whole4 = !CHECK || wc0 + c4 + 4 <= p.N;

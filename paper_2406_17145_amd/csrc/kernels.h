@@ -227,7 +227,9 @@ struct SlotGroup {
   int32_t first = 0, n = 1, total = 1, pad = 0;
   int64_t stride = 0;
 };
-void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, const SlotGroup &grp, hipStream_t s);
+bool gemm_dw_group_streams(int64_t gradient_bytes);
+void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
+                          hipStream_t s);
 // Workgroups of a launch per output block shape.  Records with a shorter contraction than the launch's longest count
 // for the share of it that they have.
 struct GemmTileCounts {

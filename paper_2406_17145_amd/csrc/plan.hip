@@ -1893,13 +1893,16 @@ void Emitter::backward() {
   if (!dw_group.empty()) {
     // (one launch lets the co-resident tiles of all layers fill each other's tails)
     int blocks = 0;
+    int64_t bytes = 0;
     for (auto &r : dw_group) {
       r.blk_begin = blocks;
       r.split_k = 1;
+      bytes += r.M * r.ldc * 4;
       blocks += gemm_big_tiles_for(64, r.M, r.N, &r.tiles_n);
     }
     // (contraction-major operands: staged through registers, see emit_gemms)
-    add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
+    Step &sg = add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
+    sg.a0 = gemm_dw_group_streams(bytes) ? 1 : 0;
   }
   steps = &pl.bwd;
 }

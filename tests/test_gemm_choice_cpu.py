@@ -109,3 +109,10 @@ def test_activation_of_a_copied_gradient_costs_no_launch():
         # output gradients in; two copies, and in place the other two; input gradients that no GEMM stored itself
         assert elt[:2] == [1, 4 if act == "gelu" else 2]
         assert len(elt) <= 3
+
+
+@pytest.mark.parametrize("branches,k,n,streams", [(1, 64, 64, 0), (1, 4096, 4096, 0), (1, 4096, 8191, 0), (1, 4096, 8192, 1),
+                                                  (2, 4000, 4096, 0), (2, 4096, 4096, 1), (7, 4096, 4096, 1)])
+def test_gradients_that_exceed_half_the_last_level_cache_are_stored_past_it(branches, k, n, streams):
+    (step,) = [p for p in plan(layers(64, k, n, branches), 64, 1, B.FLAG_GROUPED_DW) if p["pass"] == "weights"]
+    assert step["streams"] == streams
