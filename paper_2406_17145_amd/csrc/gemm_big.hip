@@ -621,14 +621,25 @@ __global__ __launch_bounds__(256, 3) void k_gemm_mid(const GemmProb *__restrict_
 }
 
 // backward-weight over a group of stash slots (see big_tile_body).
+// Eight-wave form for long contractions (gemm_big_dw_tile), in bands of four tile rows: one workgroup per compute unit, 32 tiles
+// in flight per XCD as a 4 x 8 block.
+template <bool STREAM>
+__global__ __launch_bounds__(512) void k_gemm_big_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
+                                                           int accumulate_dw, SlotGroup grp) {
+  typedef BigCfg<FORM_DW, 2, 4, 4, 2, 2> C;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
+  const BigTile t = big_locate<C::BM, C::BN, 4>(probs, n, total_blocks);
+  const GemmProb p = probs[t.pi];
+  ExtPtrs none;
+  big_tile_body<FORM_DW, 2, 4, 4, 2, 2, 2, true, 0, false, STREAM>(p, t.m0, t.n0, lds, accumulate_dw, none, grp);
+}
 // Tile order of the grouped weight gradient: bands of eight tile rows.  Its launch holds thousands of 128 x 128 tiles,
 // 128 of them in flight per XCD; numbered column by column these are 32 rows x 4 columns of a [4096 x 1024] gradient
 // (36 operand panels of 512 KB through a 4 MB L2), in bands 8 x 16 (24 panels).  Measured on the transformer stage's
 // launch of all layers: 497-505 -> 483 us (bands of 4: 497, of 16: 487 scaled to the same box).
 constexpr int DW_BAND = 8;
 // (four workgroups per compute unit: 40 KB of LDS and 128 registers each; with three the transformer stage's launch
-// is 6 % slower.  The tile for every size: 256 x 256 outputs per workgroup of eight waves, alone on its compute unit,
-// exposes its 256 KB of stores -- seven [4096 x 4096] gradients over 256 / 2048 rows 127 / 467 us against 100 / 410)
+// is 6 % slower)
 template <bool STREAM>
 __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
                                                               int accumulate_dw, SlotGroup grp) {
@@ -701,6 +712,18 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
   *us = best;
   return rows;
 }
+// Backward-weight: 64 (128 x 128 tiles, co-resident workgroups) or 256.  An eight-wave workgroup is alone on its compute unit and
+// exposes its 256 KB of stores, so it takes a long contraction and whole rounds of tiles to win.  us with 128 x 128 / 256 x 256,
+// gradients stored and added to:
+//   [4096 x 4096], rows 512: 94 / 87, 85 / 83     1024: 135 / 122, 125 / 113    2048: 207 / 185, 206 / 180    8192: 706 / 645, 693 / 627
+//   four of it:         237 / 234, 247 / 291            376 / 357, 386 / 401          680 / 641, 681 / 684        2669 / 2387, 2719 / 2404
+//   two [3000 x 3000] (288 tiles), rows 8192: 763 / 873
+// grouped (four 128 x 128 workgroups per compute unit): four [4096 x 4096], rows 2048 629 / 631, 628 / 650, 4096 1219 / 1193,
+//   1252 / 1195, 8192 2742 / 2448, 2794 / 2481; four [2048 x 2048], rows 8192 703 / 688, 686 / 674.
+// (and tiles that are mostly filled: of the 128 x 128 tiles four to a tile, seven to two at the least)
+int gemm_big_dw_tile(bool grouped, int min_k, int tiles256, int tiles128) {
+  return min_k >= (grouped ? 4096 : 1024) && tiles256 >= 256 && tiles256 % 256 == 0 && 2 * tiles128 >= 7 * tiles256 ? 256 : 64;
+}
 // Slices of a lone forward record's contraction (0: not split): as many workgroups as compute units, slices of at least 16
 // k-steps, where one round of them and the pass over the slices (written and read once, 4 TB/s, and a launch) take 15 %
 // less than the kernel chosen otherwise, by the estimates above.
@@ -738,6 +761,8 @@ void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumul
     launch_big_form<FORM_FWD>(probs, n, total_blocks, tile_rows, direct, ext, s);
   } else if (form == FORM_DX) {
     launch_big_form<FORM_DX>(probs, n, total_blocks, tile_rows, direct, ext, s);
+  } else if (tile_rows == 256) {
+    hipLaunchKernelGGL((k_gemm_big<FORM_DW, 4, 2, 2, 0, 2>), g, dim3(512), 0, s, probs, n, total_blocks, accumulate_dw, ext);
   } else {
     hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, ext);
   }
@@ -756,10 +781,15 @@ void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, co
 // where a second group of the mini-batch adds to them (8 % for that pass alone).  Above the line that second group loses less
 // than the first has gained (two groups: 541 -> 492 us, 460 -> 419, 3450 -> 3320).
 bool gemm_dw_group_streams(int64_t gradient_bytes) { return gradient_bytes >= (int64_t)128 << 20; }
-void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
-                          hipStream_t s) {
+void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
+                          const SlotGroup &grp, hipStream_t s) {
   if (total_blocks <= 0 || grp.n <= 0) return;
-  const dim3 g(total_blocks), b(256);
+  const dim3 g(total_blocks), b(tile_rows == 256 ? 512 : 256);
+  if (tile_rows == 256) {
+    if (stream) hipLaunchKernelGGL(k_gemm_big_dw_group<true>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
+    else hipLaunchKernelGGL(k_gemm_big_dw_group<false>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
+    return;
+  }
   if (stream) hipLaunchKernelGGL(k_gemm_mid_dw_group<true>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
   else hipLaunchKernelGGL(k_gemm_mid_dw_group<false>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
 }

@@ -215,8 +215,8 @@ int gemm_mfma_group_tile(int form, int maxM, int maxN);
 int gemm_mfma_tiles_for(int tile, int M, int N, int *tiles_n);
 int gemm_mfma_partial_floats(int tile);
 // large-tile kernels: 256 x 256 or (forward) 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
-// 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64; backward-weight
-// has this tile only)
+// 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64); backward-weight
+// has the first and the last
 void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, int direct,
                      const ExtPtrs &ext, hipStream_t s);
 bool gemm_big_supported(const GemmProb &p);
@@ -228,8 +228,9 @@ struct SlotGroup {
   int64_t stride = 0;
 };
 bool gemm_dw_group_streams(int64_t gradient_bytes);
-void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
-                          hipStream_t s);
+void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
+                          const SlotGroup &grp, hipStream_t s);
+int gemm_big_dw_tile(bool grouped, int min_k, int tiles256, int tiles128);
 // Workgroups of a launch per output block shape.  Records with a shorter contraction than the launch's longest count
 // for the share of it that they have.
 struct GemmTileCounts {

@@ -810,9 +810,10 @@ struct Emitter {
             continue;
           }
           if (use_mfma && form == FORM_DW && !(pl.flags & 2)) {
-            int tiles128 = 0, min_k = 1 << 30;
+            int tiles128 = 0, tiles256 = 0, min_k = 1 << 30;
             bool ok = true;
             for (auto &r : g) {
+              tiles256 += gemm_big_tiles_for(256, r.M, r.N, nullptr);
               tiles128 += gemm_mfma_tiles_for(128, r.M, r.N, nullptr);
               min_k = std::min(min_k, r.K);
               ok = ok && gemm_big_supported(r);
@@ -831,10 +832,9 @@ struct Emitter {
               add_step(K_GEMM_DW_KSPLIT, push_table(g), (int)g.size(), blocks);
               continue;
             }
-            // every other one runs on the co-resident 128 x 128 tiles, whatever its size (2 x [1000 x 256] over 300
-            // rows: 7.9 us against 10.4 with the ring-buffered 128 x 128 tiles and 10.7 with 64 x 64; [100 x 64]: 7.2
-            // against 10.0 and 7.1)
-            if (ok) tile_rows = 64;
+            // every other one runs on the large tiles, whatever its size (2 x [1000 x 256] over 300 rows: 7.9 us against
+            // 10.4 with the ring-buffered 128 x 128 tiles and 10.7 with 64 x 64; [100 x 64]: 7.2 against 10.0 and 7.1)
+            if (ok) tile_rows = gemm_big_dw_tile(false, min_k, tiles256, tiles128);
           }
           // the large-tile kernels
           if (tile_rows > 0) {
@@ -1892,17 +1892,24 @@ void Emitter::backward() {
   steps->clear();
   if (!dw_group.empty()) {
     // (one launch lets the co-resident tiles of all layers fill each other's tails)
-    int blocks = 0;
+    int blocks = 0, tiles256 = 0, tiles128 = 0, min_k = 1 << 30;
     int64_t bytes = 0;
+    for (auto &r : dw_group) {
+      bytes += r.M * r.ldc * 4;
+      tiles256 += gemm_big_tiles_for(256, r.M, r.N, nullptr);
+      tiles128 += gemm_big_tiles_for(64, r.M, r.N, nullptr);
+      min_k = std::min(min_k, r.K);
+    }
+    const int tile_rows = gemm_big_dw_tile(true, min_k, tiles256, tiles128);
     for (auto &r : dw_group) {
       r.blk_begin = blocks;
       r.split_k = 1;
-      bytes += r.M * r.ldc * 4;
-      blocks += gemm_big_tiles_for(64, r.M, r.N, &r.tiles_n);
+      blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
     }
     // (contraction-major operands: staged through registers, see emit_gemms)
     Step &sg = add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
     sg.a0 = gemm_dw_group_streams(bytes) ? 1 : 0;
+    sg.a2 = tile_rows;
   }
   steps = &pl.bwd;
 }

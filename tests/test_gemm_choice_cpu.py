@@ -116,3 +116,11 @@ def test_activation_of_a_copied_gradient_costs_no_launch():
 def test_gradients_that_exceed_half_the_last_level_cache_are_stored_past_it(branches, k, n, streams):
     (step,) = [p for p in plan(layers(64, k, n, branches), 64, 1, B.FLAG_GROUPED_DW) if p["pass"] == "weights"]
     assert step["streams"] == streams
+
+
+@pytest.mark.parametrize("rows,k,n,branches,flags,tile", [
+    (1023, 4096, 4096, 1, 0, 64), (1024, 4096, 4096, 1, 0, 256), (4096, 300, 4096, 8, 0, 64), (4096, 64, 64, 256, B.FLAG_GROUPED_DW, 64), (2048, 4096, 4096, 1, 0, 256), (2048, 4090, 4084, 1, 0, 256), (2048, 3840, 4096, 1, 0, 64),
+    (4095, 2048, 2048, 4, B.FLAG_GROUPED_DW, 64), (4096, 2048, 2048, 4, B.FLAG_GROUPED_DW, 256), (4096, 2048, 2048, 5, B.FLAG_GROUPED_DW, 64)])
+def test_weight_gradients_take_the_large_tile_for_long_contractions(rows, k, n, branches, flags, tile):
+    (step,) = [p for p in plan(layers(rows, k, n, branches), rows, 1, flags) if p["kernel"] == "gemm_big_dw"]
+    assert step["tile"] == tile

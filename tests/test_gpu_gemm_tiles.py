@@ -120,6 +120,17 @@ def test_merge_off_16_bytes_without_room_for_the_copies(act, slots, flags, monke
         compare(wl, res, grads, stage, ref, label="gemm_tiles merge off 16 bytes")
 
 
+# The eight-wave weight gradient: one round of 256 x 256 tiles over a long contraction, ragged in all three directions.
+@pytest.mark.parametrize("rows,n_micro,flags", [(2050, 2, 0), (4100, 1, B.FLAG_GROUPED_DW)])
+def test_weight_gradient_on_large_tiles(rows, n_micro, flags):
+    wl = _chain(rows, (4090, 4084), ("none",), 1, n_micro)
+    print(f"[case] eight-wave weight gradient rows={rows} flags={flags}", flush=True)
+    assert [p["tile"] for p in _plan(wl, 1, flags) if p["kernel"] == "gemm_big_dw"] == [256]
+    _, res, grads = _run(wl, 1, 1, False, flags=flags)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="gemm_tiles")
+
+
 # fp32: the small tiles (32 x 32, contraction in steps of 64, split over four waves) around their edges, and the first launch that
 # is large enough for the 64 x 64 ones.  The bar is that of the fp32 path; a sum of 1100 products in another order is far below it.
 @pytest.mark.parametrize("rows,widths,branches", [
