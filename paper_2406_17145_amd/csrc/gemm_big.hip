@@ -509,7 +509,10 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   if (Cout == nullptr) return;
   // ---- epilogue.  Where all rows are 16-byte aligned it goes through LDS and touches memory in whole 16-byte
   // pieces of rows (each wave has a private block; the operand tiles are dead: the k-loop and the bias sums ended
-  // with a barrier); other results (fp32 outputs among them) keep the accumulator layout.
+  // with a barrier); other results (fp32 outputs among them) keep the accumulator layout, and so do weight-gradient
+  // tiles that stick out of their matrix where nothing is read: their predicated stores wait for nothing, while the row-wise
+  // ones each wait for their LDS read (grouped gradients, backward pass of [425 x 85] 17.8 against 19.4 us, 4 x [299 x 26]
+  // over 466 rows 39.0 against 41.4; added to, the row-wise form is ahead: 19.5 against 24.5, 36.7 against 37.3).
   static_assert(C::NW * epi_lds_floats<WTN>() * 4 <= C::LDS_ELEMS * 2, "epilogue blocks do not fit the operand LDS");
   const bool inside = m0 + BM <= p.M && n0 + BN <= p.N;
   if constexpr (PARTIAL) {      // fp32 rows as a gradient's (the planner's buffer has whole, aligned rows)
@@ -522,7 +525,7 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   // sixteen rows apart -- 4 x [2048 x 4096 x 1024] forward 78 -> 75.5 us, a one-k-step launch of the same output
   // 29 -> 26 us.  While the stores were flat instructions, which count on the LDS wait counter as well, it
   // was the other way round: 87 against 95 us)
-  if (epi_lds_ok(p, Cout, FORM)) {
+  if (FORM == FORM_DW ? inside || accumulate_dw : epi_lds_ok(p, Cout, FORM)) {      // (gradients have aligned rows)
     if (FORM == FORM_DW && do_bias) __syncthreads();   // the bias sums were read from LDS after the last barrier
     float *stage = (float *)lds + wave * epi_lds_floats<WTN>();
     if (inside) epilogue_wave_lds<FORM, false, WTM, WTN, STREAM>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
@@ -640,15 +643,16 @@ __global__ __launch_bounds__(512) void k_gemm_big_dw_group(const GemmProb *__res
 constexpr int DW_BAND = 8;
 // (four workgroups per compute unit: 40 KB of LDS and 128 registers each; with three the transformer stage's launch
 // is 6 % slower)
-template <bool STREAM>
+// (ADD, gradients are added to, at compile time: with both epilogues in one kernel three registers are spilled)
+template <bool STREAM, bool ADD>
 __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
-                                                              int accumulate_dw, SlotGroup grp) {
+                                                              SlotGroup grp) {
   typedef BigCfg<FORM_DW, 2, 2, 2, 2, 1> C;
   __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
   const BigTile t = big_locate<C::BM, C::BN, DW_BAND>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
   ExtPtrs none;
-  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, accumulate_dw, none, grp);
+  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp);
 }
 
 // ---- host side -------------------------------------------------------------------------
@@ -790,8 +794,9 @@ void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int ac
     else hipLaunchKernelGGL(k_gemm_big_dw_group<false>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
     return;
   }
-  if (stream) hipLaunchKernelGGL(k_gemm_mid_dw_group<true>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
-  else hipLaunchKernelGGL(k_gemm_mid_dw_group<false>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
+  if (accumulate_dw) hipLaunchKernelGGL((k_gemm_mid_dw_group<false, true>), g, b, 0, s, probs, n, total_blocks, grp);
+  else if (stream) hipLaunchKernelGGL((k_gemm_mid_dw_group<true, false>), g, b, 0, s, probs, n, total_blocks, grp);
+  else hipLaunchKernelGGL((k_gemm_mid_dw_group<false, false>), g, b, 0, s, probs, n, total_blocks, grp);
 }
 
 }  // namespace gpp

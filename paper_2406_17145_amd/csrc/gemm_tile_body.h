@@ -320,9 +320,8 @@ constexpr int EPI_LDS_PAD = 4;   // floats: keeps rows 16-byte aligned and sprea
 template <int TJ>
 constexpr int epi_lds_floats() { return 32 * (32 * TJ + EPI_LDS_PAD); }
 
-__device__ __forceinline__ bool epi_lds_ok(const GemmProb &p, const void *Cout, int form) {
+__device__ __forceinline__ bool epi_lds_ok(const GemmProb &p, const void *Cout, int form) {      // FORM_FWD, FORM_DX
   if ((p.ldc & 7) || ((uintptr_t)Cout & 15)) return false;
-  if (form == FORM_DW) return true;                       // fp32 result, no optional operands
   if (p.c_dtype != DT_BF16) return false;
   if (p.res && (p.res_dtype != DT_BF16 || (p.ldres & 7) || ((uintptr_t)p.res & 15))) return false;
   if (p.aux && (p.aux_dtype != DT_BF16 || (p.ldaux & 7) || ((uintptr_t)p.aux & 15))) return false;
