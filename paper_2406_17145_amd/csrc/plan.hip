@@ -810,9 +810,10 @@ struct Emitter {
             continue;
           }
           if (use_mfma && form == FORM_DW && !(pl.flags & 2)) {
-            int tiles128 = 0, tiles256 = 0, min_k = 1 << 30;
+            int tiles64 = 0, tiles128 = 0, tiles256 = 0, min_k = 1 << 30;
             bool ok = true;
             for (auto &r : g) {
+              tiles64 += gemm_mfma_tiles_for(64, r.M, r.N, nullptr);
               tiles256 += gemm_big_tiles_for(256, r.M, r.N, nullptr);
               tiles128 += gemm_mfma_tiles_for(128, r.M, r.N, nullptr);
               min_k = std::min(min_k, r.K);
@@ -821,8 +822,10 @@ struct Emitter {
             // backward-weight with a long contraction and too few 128 x 128 tiles to fill the chip: small tiles, the
             // contraction split over the waves of each workgroup; the longer the contraction, the more tiles it takes
             // to fill in otherwise (2 x [1000 x 256] over 512 / 1200 rows: 9.5 / 13.0 us against 10.1 / 18.1 with
-            // 128 x 128 tiles; 4 x [1000 x 1000]: 35.9 / 53.5 against 16.4 / 28.1)
-            if (min_k >= 512 && tiles128 < std::min(192, 32 + min_k / 16)) {
+            // 128 x 128 tiles; 4 x [1000 x 1000]: 35.9 / 53.5 against 16.4 / 28.1).  Counted in 64 x 64 tiles, four for one:
+            // a matrix of at most 64 rows or columns fills half of every larger tile (a backward pass of 4 x [16 x 4096] over
+            // 800 rows 32 us against 37, of 7 x [9 x 1899] over 921 rows 47 against 51)
+            if (min_k >= 512 && tiles64 < 4 * std::min(192, 32 + min_k / 16)) {
               int blocks = 0;
               for (auto &r : g) {
                 r.blk_begin = blocks;

@@ -124,3 +124,10 @@ def test_gradients_that_exceed_half_the_last_level_cache_are_stored_past_it(bran
 def test_weight_gradients_take_the_large_tile_for_long_contractions(rows, k, n, branches, flags, tile):
     (step,) = [p for p in plan(layers(rows, k, n, branches), rows, 1, flags) if p["kernel"] == "gemm_big_dw"]
     assert step["tile"] == tile
+
+
+def test_narrow_weight_gradients_are_split_over_the_rows():
+    for rows, k, n, branches, kernel in ((800, 4096, 16, 4, "gemm_dw_ksplit"), (921, 1899, 9, 7, "gemm_dw_ksplit"), (800, 4096, 65, 4, "gemm_big_dw"),
+                                         (2000, 1000, 1000, 2, "gemm_dw_ksplit"), (1200, 1000, 1000, 4, "gemm_big_dw")):
+        ops = layers(rows, k, n, branches, grad=False)
+        assert [p["kernel"] for p in plan(ops, rows) if p["kernel"] in ("gemm_dw_ksplit", "gemm_big_dw")] == [kernel], (rows, k, n)
