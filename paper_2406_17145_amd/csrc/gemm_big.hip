@@ -680,6 +680,13 @@ bool gemm_big_supported(const GemmProb &p) {
 //   64 x 64:   at a few workgroups per compute unit.                4 x [512 x 1000 x 3820] 48 (256: 96, 128: 65, 64: 72)
 // 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218; a lone [512 x 4096 x 4096]: 95, 62, 72, 45.
 // `whole_chunks`: every contraction length is a multiple of 8.
+// Behind a short contraction the estimate of the 256 x 256 tiles is too low (their prologue and epilogue are all that such a
+// launch is), so there they are left out unless the launch is whole rounds of them, or in forward from K 768 on at least half
+// of its last one.  us with 256 / 64, forward from K 1024 down, backward-data from K 256 down:
+//   4 x [9679 x 1000 x K], 608 tiles: K 16 117 / 82, 128 124 / 95, 512 170 / 144, 768 195 / 175, 1024 219 / 208, 1536 the same
+//   [3000 x 4096 x K], 192 tiles:     K 512 56 / 50, 768 60 / 52, 1024 66 / 60;     4 x [2048 x 4096 x 512], 512 tiles: 105 / 110
+//   4 x [9679 x 4096 x K], 2432 tiles: K 512 481 / 465, 768 430 / 453
+//   backward-data, 4 x [9679 x 4096 x K], 2432 tiles: K 64 269 / 250, 128 294 / 282;   4 x [5000 x 768 x 200], 240 tiles: 76 / 72
 // The estimates are within 20 % of what was measured, so the 64 x 64 blocks, whose time depends least on the rest of
 // the shape, are left only for an estimate 10 % below theirs.
 int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, bool whole_chunks, float *us) {
@@ -711,7 +718,9 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
     }
   };
   take(64, mid(c.t128));
-  if (whole_chunks) take(256, rounds(c.t256, t256));
+  const float rest256 = c.t256 / CUS - floorf(c.t256 / CUS);
+  const bool whole_rounds = c.t256 >= CUS && (rest256 < 0.01f || (fwd && max_k >= 768 && rest256 >= 0.5f));
+  if (whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256));
   if (whole_chunks && fwd) take(128, rounds(c.t128x256, t128));
   *us = best;
   return rows;

@@ -921,14 +921,19 @@ struct Emitter {
   // have their sums in the memory that a forward pass may overwrite: a stage needs no workspace for them).
   int large_tile(const std::vector<GemmProb> &g, int form, int few, int *slices = nullptr) const {
     if (pl.flags & 2) return 0;
-    int max_m = 0, max_k = 0;
+    int max_m = 0, max_n = 0, max_k = 0;
     bool whole = true;
     for (auto &r : g) {
       if (!gemm_big_supported(r)) return 0;
       max_m = std::max(max_m, r.M);
+      max_n = std::max(max_n, r.N);
       max_k = std::max(max_k, r.K);
       whole = whole && r.K % 8 == 0;
     }
+    // many rows of a few columns each behind a short contraction: half of every tile would be padding, and the launch is
+    // nothing but its result (4 x [40000 x 64 x K] on 64 x 64 / 128 x 128 tiles: K 64 47 / 52 us, 128 59 / 61, 200 89 / 89,
+    // 512 159 / 137)
+    if (form == FORM_FWD && few == 0 && max_n <= 64 && max_k <= 128) return 0;
     if (few > 0 && (max_m <= 64 || (pl.flags & 16) || pl.group_lanes > 0)) return 0;
     GemmTileCounts c;
     auto tiles = [](const GemmProb &r, int bm, int bn) { return (float)(((r.M + bm - 1) / bm) * ((r.N + bn - 1) / bn)); };

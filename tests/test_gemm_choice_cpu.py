@@ -126,6 +126,27 @@ def test_weight_gradients_take_the_large_tile_for_long_contractions(rows, k, n, 
     assert step["tile"] == tile
 
 
+def tiles(rows, k, n, branches, kernel):
+    return [p["tile"] for p in plan(layers(rows, k, n, branches), rows) if p["kernel"] == kernel]
+
+
+def test_large_tiles_behind_a_short_contraction_take_whole_rounds():
+    for k, want in ((16, 64), (1000, 64), (1024, 64), (1032, 256), (2000, 256)):          # 608 tiles of 256 x 256
+        assert tiles(9679, k, 1000, 4, "gemm_big_fwd") == [want], k
+    for k, want in ((16, 256), (512, 256), (1024, 256)):                                  # 512
+        assert tiles(2048, k, 4096, 4, "gemm_big_fwd") == [want], k
+    for k, want in ((512, 64), (768, 256)):                                               # 2432
+        assert tiles(9679, k, 4096, 4, "gemm_big_fwd") == [want], k
+    for n, want in ((64, 64), (256, 64), (264, 256), (1000, 256)):                        # 2432, backward-data
+        assert tiles(9679, 4096, n, 4, "gemm_big_dx") == [want], n
+
+
+def test_narrow_results_of_many_rows():
+    for k, n, kernel in ((64, 64, "gemm_mfma_fwd"), (128, 64, "gemm_mfma_fwd"), (136, 64, "gemm_big_fwd"), (128, 72, "gemm_big_fwd")):
+        fwd = [p["kernel"] for p in plan(layers(40000, k, n, 4), 40000) if p["pass"] == "forward"]
+        assert kernel in fwd, (k, n, fwd)
+
+
 def test_narrow_weight_gradients_are_split_over_the_rows():
     for rows, k, n, branches, kernel in ((800, 4096, 16, 4, "gemm_dw_ksplit"), (921, 1899, 9, 7, "gemm_dw_ksplit"), (800, 4096, 65, 4, "gemm_big_dw"),
                                          (2000, 1000, 1000, 2, "gemm_dw_ksplit"), (1200, 1000, 1000, 4, "gemm_big_dw")):
