@@ -17,9 +17,11 @@ int gemm_generic_tiles(int tile, int M, int N, int *tiles_n) {
   if (tiles_n) *tiles_n = tn;
   return tm * tn;
 }
-// Tile of a launch with this many 64 x 64 tiles: below one workgroup per compute unit the launch is one chain of memory
-// round trips, which the small tiles shorten, and they spread it over four times the compute units.
-int gemm_generic_tile(int tiles64) { return tiles64 < 256 ? GS : GT; }
+// Tile of a launch with this many 64 x 64 tiles: up to two workgroups per compute unit the launch is one chain of memory
+// round trips, which the small tiles shorten, and they spread it over four times the compute units.  Forward, small / large tiles:
+// 1 to 255 tiles of 64 x 64 behind K 8 .. 16 0.8 - 0.9 of the time, 64 0.65, 256 0.4, 1000 0.25; 256 to 511 behind K 8 0.95,
+// 64 0.77, 256 0.6, 1000 0.4; from 512 on, where the small tiles take several rounds, between 0.6 and 1.7 (2048 tiles: 2.1).
+int gemm_generic_tile(int tiles64) { return tiles64 < 512 ? GS : GT; }
 
 // element strides of the logical operands A(i, kk) [M x K] and B(kk, j) [K x N]
 struct GenericStrides {
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_generic_small(const GemmProb *_
     }
     __syncthreads();
     if (k0 + GSK < p.K) fetch(k0 + GSK);
-#pragma unroll
+#pragma unroll 4        // (all sixteen at once take 256 registers and spill 53: twice the time at any size)
     for (int u = 0; u < GSK / 4; ++u) {
       const int kk = wave * (GSK / 4) + u;
       const float4 a = *(const float4 *)(As + kk * ST + ti), b = *(const float4 *)(Bs + kk * ST + tj);

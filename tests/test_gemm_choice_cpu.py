@@ -152,3 +152,10 @@ def test_narrow_weight_gradients_are_split_over_the_rows():
                                          (2000, 1000, 1000, 2, "gemm_dw_ksplit"), (1200, 1000, 1000, 4, "gemm_big_dw")):
         ops = layers(rows, k, n, branches, grad=False)
         assert [p["kernel"] for p in plan(ops, rows) if p["kernel"] in ("gemm_dw_ksplit", "gemm_big_dw")] == [kernel], (rows, k, n)
+
+
+def test_fp32_launches_below_512_tiles_take_the_small_ones():
+    def of(rows, k, n, which):
+        return [p["tile"] for p in plan(layers(rows, k, n, dtype=W.F32), rows) if p["pass"] == which and p["kernel"].startswith("gemm")]
+    assert of(64 * 511, 64, 64, "forward") == [32] and of(64 * 511 + 1, 64, 64, "forward") == [64]
+    assert of(8, 64, 64, "backward") == [32] and of(1100, 1000, 2050, "backward") == [64]

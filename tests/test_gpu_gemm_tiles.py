@@ -131,10 +131,11 @@ def test_weight_gradient_on_large_tiles(rows, n_micro, flags):
     compare(wl, res, grads, stage, ref, label="gemm_tiles")
 
 
-# fp32: the small tiles (32 x 32, contraction in steps of 64, split over four waves) around their edges, and the first launch that
-# is large enough for the 64 x 64 ones.  The bar is that of the fp32 path; a sum of 1100 products in another order is far below it.
+# fp32: the small tiles (32 x 32, contraction in steps of 64, split over four waves) around their edges, and launches that are
+# large enough for the 64 x 64 ones (forward; backward, whose first column of tiles also sums the bias gradient).  The bar is that of the fp32 path; a sum of 1100 products in another order is far below it.
 @pytest.mark.parametrize("rows,widths,branches", [
-    (1, (1, 1), 1), (8, (64, 128, 64), 2), (33, (65, 31, 97), 3), (64, (300, 32, 129), 2), (31, (400, 63, 1), 4), (1100, (1024, 1000), 1)])
+    (1, (1, 1), 1), (8, (64, 128, 64), 2), (33, (65, 31, 97), 3), (64, (300, 32, 129), 2), (31, (400, 63, 1), 4), (1100, (1024, 1000), 1),
+    (2100, (65, 1000), 1), (1100, (1000, 2050), 1)])
 def test_fp32_tiles(rows, widths, branches):
     wl = _chain(rows, widths, ("relu", "none")[2 - len(widths) + 1:], branches, 2, dtype=W.F32)
     print(f"[case] fp32 rows={rows} widths={widths} branches={branches}", flush=True)
