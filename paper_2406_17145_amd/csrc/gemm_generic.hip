@@ -163,8 +163,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_generic_small(const GemmProb *_
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_gemm_generic(const GemmProb *__restrict__ probs, int n,
+// BIAS: the launch holds weight gradients with a bias gradient (without them, eight waves per SIMD need no bound and a
+// forward launch of [8192 x 1000 x 1000] takes 383 us instead of 391)
+template <typename T, bool BIAS>
+__global__ __launch_bounds__(256, BIAS ? 8 : 1) void k_gemm_generic(const GemmProb *__restrict__ probs, int n,
                                                        int accumulate_dw) {
   __shared__ float As[GK][GT + 4];
   __shared__ float Bs[GK][GT + 4];
@@ -178,6 +180,26 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const GemmProb *__restrict
   const int64_t sai = sd.ai, sak = sd.ak, sbk = sd.bk, sbj = sd.bj;
   const T *A = (const T *)p.A;
   const T *B = (const T *)p.B;
+
+  // backward-weight tiles of the first column block also sum the columns of dZ, the bias gradient: four row groups, in
+  // a loop of its own (a test for it inside the contraction loop doubled the time of every launch) and in front of that
+  // loop (behind it, next to the sixteen sums, it takes two registers more than eight waves per SIMD leave: forward of
+  // [8192 x 1000 x 1000] 375 -> 467 us with seven)
+  if (BIAS && p.form == FORM_DW && p.bias != nullptr && n0 == 0) {
+    float bsum = 0.0f;
+    const int bi = min(m0 + (t & (GT - 1)), p.M - 1);
+#pragma unroll 4
+    for (int k = t / GT; k < p.K; k += 256 / GT) bsum += to_f32<T>(A[(int64_t)k * sak + bi]);
+    float *red = &As[0][0];
+    red[t] = bsum;
+    __syncthreads();
+    if (t < GT && m0 + t < p.M) {
+      const float total = (red[t] + red[GT + t]) + (red[2 * GT + t] + red[3 * GT + t]);
+      GPP_G float *db = (GPP_G float *)p.bias + m0 + t;
+      *db = accumulate_dw ? *db + total : total;
+    }
+    __syncthreads();
+  }
 
   float acc[4][4];
 #pragma unroll
@@ -214,23 +236,6 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const GemmProb *__restrict
     }
     __syncthreads();
   }
-  // backward-weight tiles of the first column block also sum the columns of dZ, the bias gradient: four row groups, in
-  // a loop of its own (a test for it inside the loop above doubled the time of every launch)
-  if (p.form == FORM_DW && p.bias != nullptr && n0 == 0) {
-    float bsum = 0.0f;
-    const int bi = min(m0 + (t & (GT - 1)), p.M - 1);
-#pragma unroll 4
-    for (int k = t / GT; k < p.K; k += 256 / GT) bsum += to_f32<T>(A[(int64_t)k * sak + bi]);
-    float *red = &As[0][0];
-    red[t] = bsum;
-    __syncthreads();
-    if (t < GT && m0 + t < p.M) {
-      const float total = (red[t] + red[GT + t]) + (red[2 * GT + t] + red[3 * GT + t]);
-      GPP_G float *db = (GPP_G float *)p.bias + m0 + t;
-      *db = accumulate_dw ? *db + total : total;
-    }
-  }
-
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = m0 + ty + 16 * i;
@@ -259,16 +264,19 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const GemmProb *__restrict
   }
 }
 
-void launch_gemm_generic(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int in_dtype, int tile, hipStream_t s) {
+template <typename T>
+static void launch_generic_type(const GemmProb *probs, int n, int blocks, int accumulate_dw, int tile, bool bias, hipStream_t s) {
+  const dim3 g(blocks), b(256);
+  if (tile == GS) hipLaunchKernelGGL(k_gemm_generic_small<T>, g, b, 0, s, probs, n, accumulate_dw);
+  else if (bias) hipLaunchKernelGGL((k_gemm_generic<T, true>), g, b, 0, s, probs, n, accumulate_dw);
+  else hipLaunchKernelGGL((k_gemm_generic<T, false>), g, b, 0, s, probs, n, accumulate_dw);
+}
+// bias: some weight-gradient record has a bias gradient
+void launch_gemm_generic(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int in_dtype, int tile, bool bias,
+                         hipStream_t s) {
   if (total_blocks <= 0) return;
-  const dim3 g(total_blocks), b(256);
-  if (in_dtype == DT_BF16) {
-    if (tile == GS) hipLaunchKernelGGL(k_gemm_generic_small<uint16_t>, g, b, 0, s, probs, n, accumulate_dw);
-    else hipLaunchKernelGGL(k_gemm_generic<uint16_t>, g, b, 0, s, probs, n, accumulate_dw);
-  } else {
-    if (tile == GS) hipLaunchKernelGGL(k_gemm_generic_small<float>, g, b, 0, s, probs, n, accumulate_dw);
-    else hipLaunchKernelGGL(k_gemm_generic<float>, g, b, 0, s, probs, n, accumulate_dw);
-  }
+  if (in_dtype == DT_BF16) launch_generic_type<uint16_t>(probs, n, total_blocks, accumulate_dw, tile, bias, s);
+  else launch_generic_type<float>(probs, n, total_blocks, accumulate_dw, tile, bias, s);
 }
 
 }  // namespace gpp

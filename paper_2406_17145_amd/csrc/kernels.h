@@ -205,7 +205,8 @@ struct StageFlags {
 };
 
 // ---- launch entry points (defined next to the kernels) -------------------------
-void launch_gemm_generic(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int in_dtype, int tile, hipStream_t s);
+void launch_gemm_generic(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int in_dtype, int tile, bool bias,
+                         hipStream_t s);
 void launch_gemm_mfma(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile,
                       const ExtPtrs &ext, hipStream_t s);
 // tile geometry used by the planner to count workgroups

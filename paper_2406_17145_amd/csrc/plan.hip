@@ -894,6 +894,8 @@ struct Emitter {
           s.a0 = dt;
           s.a1 = form;
           s.a2 = tile;
+          if (!use_mfma)
+            for (auto &r : g) s.a3 |= r.form == FORM_DW && r.bias;
           if (use_mfma && wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
         }
     recs.clear();

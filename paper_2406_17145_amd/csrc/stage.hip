@@ -474,7 +474,7 @@ static gpp_status_t run_steps(gpp_stage *st, const std::vector<Step> &steps, int
     for (int rep = 0; rep < reps; ++rep)
     switch (sp.kern) {
       case K_ELT: launch_elt((const EltProb *)tab, sp.n, sp.blocks, ext, s); break;
-      case K_GEMM_GENERIC: launch_gemm_generic((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a0, sp.a2, s); break;
+      case K_GEMM_GENERIC: launch_gemm_generic((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a0, sp.a2, sp.a3 != 0, s); break;
       case K_GEMM_MFMA: launch_gemm_mfma((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a1, sp.a2, ext, s); break;
       case K_GEMM_BIG: launch_gemm_big((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a1, sp.a2, sp.a0, ext, s); break;
       case K_GEMM_DW_KSPLIT: launch_gemm_dw_ksplit((const GemmProb *)tab, sp.n, sp.blocks, accumulate, s); break;
