@@ -94,10 +94,21 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmProb &pin, int local,
     // backward-data with 32 columns reads 64-byte pieces of W's rows, half a cache line: the two column blocks that share
     // a line get ids 8 apart as well (eight [1 x 2048 x 2048] 27.9 -> 24.2 us, four [32 x 1000 x 1000] 7.4 -> 6.3)
     constexpr int PAIR = FORM == FORM_DX && TJ == 1 ? 2 : 1, GROUP_COLS = 8 * PAIR;
-    const int grp = local / (GROUP_COLS * m_blocks), r = local - grp * GROUP_COLS * m_blocks;
-    const int cols_here = min(GROUP_COLS, n_blocks - GROUP_COLS * grp);     // the last group may hold fewer column blocks
+    const int grp = local / (GROUP_COLS * m_blocks);
+    int r = local - grp * GROUP_COLS * m_blocks, first = GROUP_COLS * grp;
+    int cols_here = min(GROUP_COLS, n_blocks - first);           // the last group may hold fewer column blocks
+    const bool paired = PAIR == 2 && cols_here == GROUP_COLS;
+    if (PAIR == 2 && !paired && cols_here > 8) {                 // eight of them, whose row blocks stay 8 apart, and the rest
+      if (r >= 8 * m_blocks) {
+        r -= 8 * m_blocks;
+        first += 8;
+        cols_here -= 8;
+      } else {
+        cols_here = 8;
+      }
+    }
     const int c = r % cols_here;
-    cb = GROUP_COLS * grp + (PAIR == 2 && cols_here == GROUP_COLS ? 2 * (c & 7) + (c >> 3) : c);
+    cb = first + (paired ? 2 * (c & 7) + (c >> 3) : c);
     rb = r / cols_here;
   }
   GemmProb p = pin;

@@ -91,6 +91,8 @@ def test_sums_over_slices_in_the_static_workspace():
     (700, (600, 2000, 72), ("gelu", "none"), 1),
     (130, (20008, 523, 64), ("gelu", "none"), 1),         # sums over 16 slices of the contraction, the last one shorter
     (100, (9000, 1000), ("none",), 1),                    # the same into an output of the stage
+    (200, (352, 2000), ("gelu",), 1),                     # few rows: 4 row blocks, 11 column blocks of 32
+    (100, (800, 300, 470), ("gelu", "none"), 1),          # 2 row blocks, 25 (a group of 16 and one of 9) and 10
 ])
 @pytest.mark.parametrize("grouped", [False, True])
 def test_tiles_of_every_shape(rows, widths, acts, branches, grouped):
