@@ -1,7 +1,7 @@
 // Branch-grouped bf16 GEMM for problems with many rows AND many columns (the transformer and MLP
 // stacks at full micro-batch), on v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Two kernels:
 //
-// k_gemm_big   eight waves (512 threads) share a 256 x 256 (or 128 x 256) output tile as a 2 x 4 grid
+// k_gemm_big   eight waves (512 threads) share a 256 x 256 (forward also 128 x 256) output tile as a 2 x 4 grid
 //              of wave tiles of 128 x 64 (64 x 64) elements.  Per 16-wide contraction chunk a wave reads
 //              6 KB (4 KB) of operand fragments from LDS for 8 (4) MFMAs.  One workgroup per compute
 //              unit (the double-buffered tiles fill the LDS), so prologue and epilogue of a tile are
@@ -209,10 +209,10 @@ __device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs
   return t;
 }
 
-// k-loop + bias gradient + epilogue of one output tile.  BUFS = 2: LDS double buffer and a ring of NS
-// k-steps in registers (one barrier per step).  BUFS = 1: one LDS buffer, the next k-step waits in
-// registers while the current one is multiplied (two barriers per step; other workgroups on the
-// compute unit fill the gaps).
+// k-loop + bias gradient + epilogue of one output tile.  PIPE: operands copied straight into BUFS LDS buffers (forward and
+// backward-data; whole chunks of k-contiguous rows).  Otherwise staged through registers: BUFS = 2 (backward-weight), LDS
+// double buffer and a ring of NS k-steps in registers (one barrier per step); BUFS = 1, one LDS buffer, the next k-step waits
+// in registers while the current one is multiplied (two barriers per step; other workgroups on the compute unit fill the gaps).
 //
 // GROUP (backward-weight only): the contraction runs over the rows of SEVERAL stash slots, one after
 // the other -- the weight gradient of a group of backward passes in one pass over the accumulator.
@@ -451,6 +451,7 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies of the k-steps beyond the end
     __syncthreads();      // the epilogue reuses the operand LDS
   } else if (BUFS == 2) {
+    static_assert(BUFS == 1 || DIRECT || FORM == FORM_DW, "this loop clears no ragged tail of a k-contiguous row");
 #pragma unroll
     for (int u = 0; u < NS - 1; ++u)
       if (u < nk) fetch(ra[u], rb[u], u);
@@ -562,16 +563,13 @@ __global__ __launch_bounds__(512) void k_gemm_big_split(const GemmProb *__restri
   p.K = min(slice, p.K - k0);
   p.ldc = split_sum_ld(p.N);
   p.C = p.partial + (int64_t)split * p.M * p.ldc;
-  p.c_ext = 0;
   ExtPtrs none;
   big_tile_body<FORM_FWD, 2, 4, 2, 2, 3, 2, false, 1, true>(p, (tile % tiles_m) * C::BM, (tile / tiles_m) * C::BN, lds, 0, none);
 }
 // sum of the slices in order, then what the forward epilogue does; a thread takes four columns of a row
-__global__ __launch_bounds__(256) void k_split_sum(const GemmProb *__restrict__ probs, ExtPtrs ext) {
+__global__ __launch_bounds__(256) void k_split_sum(const GemmProb *__restrict__ probs) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   const GemmProb p = probs[0];
-  void *Cout = result_ptr(p, ext);
-  if (Cout == nullptr) return;
   const int ld = (int)split_sum_ld(p.N), quads = ld / 4;
   const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int row = (int)(at / quads), col = (int)(at - (int64_t)row * quads) * 4;
@@ -609,7 +607,7 @@ __global__ __launch_bounds__(256) void k_split_sum(const GemmProb *__restrict__ 
       if (col + e < p.N) store_from_f32(dst, dtype, i + e, o[e]);
   };
   if (p.act == ACT_GELU && p.aux) put((void *)p.aux, p.aux_dtype, p.ldaux, d);
-  put(Cout, p.c_dtype, p.ldc, v);
+  put((void *)p.C, p.c_dtype, p.ldc, v);
 }
 
 // 128 x 128 tile, 2 x 2 waves of 64 x 64, one LDS buffer, three waves per SIMD
@@ -657,12 +655,8 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
 
 // ---- host side -------------------------------------------------------------------------
 // The kernels take a problem when its matrices fit the 32-bit buffer offsets; the eight-wave ones also need whole chunks
-// of k-contiguous operands (contraction length a multiple of 8).
-// Direct loads move whole, aligned 16-byte chunks: rows and base pointers of both operands must be 16-byte
-// aligned (the planner pads leading dimensions to 64 elements, so only unusual callers fail this).
-bool gemm_big_direct_ok(const GemmProb &p) {
-  return (p.lda & 7) == 0 && (p.ldb & 7) == 0 && ((uintptr_t)p.A & 15) == 0 && ((uintptr_t)p.B & 15) == 0;
-}
+// of k-contiguous operands (contraction length a multiple of 8).  Rows and base pointers on 16 bytes are gemm_mfma_supported's
+// condition, so the eight-wave forward and backward-data kernels can always copy operands straight into LDS.
 bool gemm_big_supported(const GemmProb &p) {
   if (!gemm_mfma_supported(p)) return false;
   const int64_t a_rows = p.form == FORM_DW ? p.K : p.M, b_rows = p.form == FORM_FWD ? p.N : p.K;
@@ -754,38 +748,30 @@ int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n) {
   return cdiv(M, bm) * cdiv(N, bn);
 }
 
-// direct != 0: operands straight into LDS where the form has such a loop (every record must pass
-// gemm_big_direct_ok); the other launches stage through registers
-template <int FORM>
-static void launch_big_form(const GemmProb *probs, int n, int blocks, int tile_rows, int direct, const ExtPtrs &ext, hipStream_t s) {
-  const dim3 g(blocks), b(512);
-  if (tile_rows == 256 && direct) hipLaunchKernelGGL((k_gemm_big<FORM, 4, 2, 2, 2, 2>), g, b, 0, s, probs, n, blocks, 0, ext);
-  else if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM, 4, 2, 2, 0, 2>), g, b, 0, s, probs, n, blocks, 0, ext);
-  else hipLaunchKernelGGL((k_gemm_mid<FORM>), g, dim3(256), 0, s, probs, n, blocks, 0, ext);
-}
-void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, int direct,
-                     const ExtPtrs &ext, hipStream_t s) {
+void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, const ExtPtrs &ext,
+                     hipStream_t s) {
   if (total_blocks <= 0) return;
-  const dim3 g(total_blocks);
-  if (form == FORM_FWD && tile_rows == 128) {
-    if (direct) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 2, 1, 3>), g, dim3(512), 0, s, probs, n, total_blocks, 0, ext);
-    else hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 2, 0, 2>), g, dim3(512), 0, s, probs, n, total_blocks, 0, ext);
-  } else if (form == FORM_FWD) {
-    launch_big_form<FORM_FWD>(probs, n, total_blocks, tile_rows, direct, ext, s);
+  const dim3 g(total_blocks), b8(512), b4(256);
+  // operands straight into LDS where they can be and it pays (4 x [2048 x 4096 x 1024] forward cold: 83 us staged, 78 direct;
+  // 4 x [2048 x 4096 x 4096] backward-data: 336 and 297); backward-weight operands are contraction-major, staged
+  if (form == FORM_FWD) {
+    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 4, 2, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
+    else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
+    else hipLaunchKernelGGL((k_gemm_mid<FORM_FWD>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else if (form == FORM_DX) {
-    launch_big_form<FORM_DX>(probs, n, total_blocks, tile_rows, direct, ext, s);
-  } else if (tile_rows == 256) {
-    hipLaunchKernelGGL((k_gemm_big<FORM_DW, 4, 2, 2, 0, 2>), g, dim3(512), 0, s, probs, n, total_blocks, accumulate_dw, ext);
+    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 4, 2, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
+    else hipLaunchKernelGGL((k_gemm_mid<FORM_DX>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else {
-    hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, dim3(256), 0, s, probs, n, total_blocks, accumulate_dw, ext);
+    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DW, 4, 2, 2, 0, 2>), g, b8, 0, s, probs, n, total_blocks, accumulate_dw, ext);
+    else hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, b4, 0, s, probs, n, total_blocks, accumulate_dw, ext);
   }
 }
 
-void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, const ExtPtrs &ext, hipStream_t s) {
+void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, hipStream_t s) {
   if (total_blocks <= 0) return;
   hipLaunchKernelGGL(k_gemm_big_split, dim3(total_blocks), dim3(512), 0, s, probs, total_blocks);
   const int64_t threads = (int64_t)M * (split_sum_ld(N) / 4);
-  hipLaunchKernelGGL(k_split_sum, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s, probs, ext);
+  hipLaunchKernelGGL(k_split_sum, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s, probs);
 }
 
 // Gradients of one launch that are stored past the caches: those that a memory-side cache of 256 MB cannot hold until somebody

@@ -218,10 +218,9 @@ int gemm_mfma_partial_floats(int tile);
 // large-tile kernels: 256 x 256 or (forward) 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
 // 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64); backward-weight
 // has the first and the last
-void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, int direct,
-                     const ExtPtrs &ext, hipStream_t s);
+void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, const ExtPtrs &ext,
+                     hipStream_t s);
 bool gemm_big_supported(const GemmProb &p);
-bool gemm_big_direct_ok(const GemmProb &p);
 // Backward-weight whose contraction runs over the rows of `n` stash slots, starting at slot `first` and
 // wrapping at `total`; slot s lies s * stride bytes behind slot 0, whose addresses the records hold.
 struct SlotGroup {
@@ -243,7 +242,7 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
 // forward over slices of the contraction: slices (0: none; at most `most`), row stride of their fp32 sums [slices][M][ld], and the two launches
 int gemm_big_split(int M, int N, int K, int64_t most, float us);
 inline __host__ __device__ int64_t split_sum_ld(int N) { return (N + 63) / 64 * 64; }
-void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, const ExtPtrs &ext, hipStream_t s);
+void launch_gemm_split(const GemmProb *probs, int total_blocks, int M, int N, hipStream_t s);
 int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n);
 // backward-weight for small weight matrices and many rows: 64 x 64 tiles, the contraction split over the waves
 void launch_gemm_dw_ksplit(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, hipStream_t s);

@@ -785,7 +785,6 @@ struct Emitter {
             s.a1 = r.M;
             s.a2 = r.N;
             s.launches = 2;
-            if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
             continue;
           }
           if (row_tiles > 0) {
@@ -841,12 +840,6 @@ struct Emitter {
           }
           // the large-tile kernels
           if (tile_rows > 0) {
-            // operands copied straight into LDS (software-pipelined loops of the eight-wave tiles) where the
-            // a operand is k-contiguous and the tile has such a loop: forward on both tiles (4 x [2048 x 4096 x
-            // 1024] cold: 83 staged, 82 plain direct loop, 78 pipelined), backward-data on the 256 x 256 tile
-            // (4 x [2048 x 4096 x 4096]: 336 staged, 297 pipelined)
-            bool direct = form == FORM_FWD || (form == FORM_DX && tile_rows == 256);
-            for (auto &r : g) direct = direct && gemm_big_direct_ok(r);
             int blocks = 0;
             for (auto &r : g) {
               r.blk_begin = blocks;
@@ -854,7 +847,6 @@ struct Emitter {
               blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
             }
             Step &s = add_step(K_GEMM_BIG, push_table(g), (int)g.size(), blocks);
-            s.a0 = direct ? 1 : 0;
             s.a1 = form;
             s.a2 = tile_rows;
             if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
@@ -948,7 +940,7 @@ struct Emitter {
     }
     float us = 0.0f;
     int rows = gemm_big_tile_rows(form, max_k, c, few > 0, whole, &us);
-    if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16) && gemm_big_direct_ok(g[0]))
+    if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16))
       *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, pl.fwd_scratch_bytes / (g[0].M * split_sum_ld(g[0].N) * 4), us);
     // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source) behind a short
     // contraction: the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident

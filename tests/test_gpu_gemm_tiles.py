@@ -80,24 +80,38 @@ def test_sums_over_slices_in_the_static_workspace():
 
 # The bar is that of bf16 storage with fp32 accumulation: the oracle rounds at the same places, so what is left is the order of
 # fp32 sums and results that fall on the other side of a rounding boundary.
-@pytest.mark.parametrize("rows,widths,acts,branches", [
-    (2000, (128, 2056, 136), ("gelu", "none"), 2),        # 256 x 256 forward, ragged in both directions
-    (1900, (1904, 136, 2000), ("none", "gelu"), 2),       # 256 x 256 backward-data into 1904 columns
-    (250, (520, 2056, 520), ("gelu", "gelu"), 9),         # 128 x 256 forward, a last row tile of 122 rows
-    (129, (1000, 1500, 1000), ("gelu", "gelu"), 7),       # one row more than a tile
-    (300, (203, 333, 70), ("gelu", "none"), 3),           # columns that end inside a 16-byte chunk
-    (700, (1203, 333, 1207), ("gelu", "gelu"), 4),        # contractions that end inside a chunk, slices of a merge off 16 bytes
-    (65, (64, 128, 8), ("gelu", "none"), 1),              # smallest launch with a choice of kernels
-    (700, (600, 2000, 72), ("gelu", "none"), 1),
-    (130, (20008, 523, 64), ("gelu", "none"), 1),         # sums over 16 slices of the contraction, the last one shorter
-    (100, (9000, 1000), ("none",), 1),                    # the same into an output of the stage
-    (200, (352, 2000), ("gelu",), 1),                     # few rows: 4 row blocks, 11 column blocks of 32
-    (100, (800, 300, 470), ("gelu", "none"), 1),          # 2 row blocks, 25 (a group of 16 and one of 9) and 10
+# `want`: kernel and tile that the plan must hold, or the case has lost what it is here for.
+@pytest.mark.parametrize("rows,widths,acts,branches,want", [
+    # 128 x 128: ragged in both directions, in rows only, contractions and slices of a merge that end inside a 16-byte chunk
+    (2000, (128, 2056, 136), ("gelu", "none"), 2, ("big_fwd 64", "big_dx 64", "dw_ksplit 0")),
+    (1900, (1904, 136, 2000), ("none", "gelu"), 2, ("big_dx 64", "bwd_merged_dx_dw 0")),
+    (700, (1203, 333, 1207), ("gelu", "gelu"), 4, ("big_fwd 64", "big_dx 64", "big_dw 64")),
+    # 256 x 256 with a last column inside a chunk: forward with the stash, backward-data with the derivative
+    (1000, (2000, 4003), ("gelu",), 4, ("big_fwd 256",)),
+    (1000, (64, 4003, 2000), ("gelu", "none"), 4, ("big_dx 256",)),
+    # 128 x 256: a last row tile of 122 rows; the same with columns that end inside a chunk
+    (250, (520, 2056, 520), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
+    (250, (520, 2051, 520), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
+    # few-row kernel: one row more than two row blocks, columns that end inside a chunk, the smallest and an ordinary launch
+    # with a choice, a contraction of 141 steps, 11 and 25 column blocks (a group of 16 and one of 9) in several row blocks
+    (129, (1000, 1500, 1000), ("gelu", "gelu"), 7, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
+    (300, (203, 333, 70), ("gelu", "none"), 3, ("skinny_fwd 0", "skinny_dx 0", "big_dw 64")),
+    (65, (64, 128, 8), ("gelu", "none"), 1, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
+    (700, (600, 2000, 72), ("gelu", "none"), 1, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
+    (100, (9000, 1000), ("none",), 1, ("skinny_fwd 0",)),
+    (200, (352, 2000), ("gelu",), 1, ("bwd_merged_dx_dw 0",)),
+    (100, (800, 300, 470), ("gelu", "none"), 1, ("bwd_merged_dx_dw 0",)),
+    # narrow results of many rows on the ring-buffered 64 x 64 tiles
+    (9000, (64, 60), ("gelu",), 16, ("mfma_fwd 64",)),
+    # sums over 16 slices of the contraction, the last one shorter
+    (130, (20008, 523, 64), ("gelu", "none"), 1, ("big_fwd 0 of 16",)),
 ])
 @pytest.mark.parametrize("grouped", [False, True])
-def test_tiles_of_every_shape(rows, widths, acts, branches, grouped):
+def test_tiles_of_every_shape(rows, widths, acts, branches, want, grouped):
     wl = _chain(rows, widths, acts, branches, 2)          # (ungrouped: the second micro-batch adds to the gradients of the first)
     print(f"[case] rows={rows} widths={widths} branches={branches} grouped={grouped}", flush=True)
+    held = {p["kernel"].replace("gemm_", "") + f" {p['tile']}" + (f" of {p['slices']}" if p["slices"] else "") for p in _plan(wl)}
+    assert grouped or held.issuperset(want), held
     if grouped:
         _, res, grads = _run(wl, 2, 2, False, flags=B.FLAG_GROUPED_DW)
     else:
