@@ -224,7 +224,7 @@ __device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs
 template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, int NS, bool GROUP = false, int PIPE = 0, bool PARTIAL = false,
           bool STREAM = false>
 __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0, uint16_t *lds, int accumulate_dw,
-                                              const ExtPtrs &ext, const SlotGroup grp = SlotGroup()) {
+                                              const ExtPtrs &ext, const SlotGroup grp = SlotGroup(), int total_blocks = 1 << 30) {
   static_assert(!GROUP || FORM == FORM_DW, "only the weight gradient contracts over a group of slots");
   constexpr bool DIRECT = PIPE != 0;     // operands copied straight into LDS, software-pipelined loop 1 or 2 (below)
   static_assert(!DIRECT || BUFS >= 2, "direct loads fill the other LDS buffers while one is multiplied");
@@ -511,9 +511,10 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   // ---- epilogue.  Where all rows are 16-byte aligned it goes through LDS and touches memory in whole 16-byte
   // pieces of rows (each wave has a private block; the operand tiles are dead: the k-loop and the bias sums ended
   // with a barrier); other results (fp32 outputs among them) keep the accumulator layout, and so do weight-gradient
-  // tiles that stick out of their matrix where nothing is read: their predicated stores wait for nothing, while the row-wise
-  // ones each wait for their LDS read (grouped gradients, backward pass of [425 x 85] 17.8 against 19.4 us, 4 x [299 x 26]
-  // over 466 rows 39.0 against 41.4; added to, the row-wise form is ahead: 19.5 against 24.5, 36.7 against 37.3).
+  // tiles that stick out of their matrix where nothing is read and the launch is small: their predicated stores wait for
+  // nothing, while the row-wise ones each wait for their LDS read (grouped gradients, backward pass of [425 x 85] 17.8 against
+  // 19.4 us, 4 x [299 x 26] over 466 rows 39.0 against 41.4; added to, the row-wise form is ahead: 19.5 against 24.5, 36.7
+  // against 37.3, and so it is in launches of more tiles than run at once, whose stores pile up: 4 x [999 x 1001] 27.2, 26.5).
   static_assert(C::NW * epi_lds_floats<WTN>() * 4 <= C::LDS_ELEMS * 2, "epilogue blocks do not fit the operand LDS");
   const bool inside = m0 + BM <= p.M && n0 + BN <= p.N;
   if constexpr (PARTIAL) {      // fp32 rows as a gradient's (the planner's buffer has whole, aligned rows)
@@ -526,7 +527,7 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   // sixteen rows apart -- 4 x [2048 x 4096 x 1024] forward 78 -> 75.5 us, a one-k-step launch of the same output
   // 29 -> 26 us.  While the stores were flat instructions, which count on the LDS wait counter as well, it
   // was the other way round: 87 against 95 us)
-  if (FORM == FORM_DW ? inside || accumulate_dw : epi_lds_ok(p, Cout, FORM)) {      // (gradients have aligned rows)
+  if (FORM == FORM_DW ? inside || accumulate_dw || total_blocks > 256 : epi_lds_ok(p, Cout, FORM)) {      // (gradients have aligned rows)
     if (FORM == FORM_DW && do_bias) __syncthreads();   // the bias sums were read from LDS after the last barrier
     float *stage = (float *)lds + wave * epi_lds_floats<WTN>();
     if (inside) epilogue_wave_lds<FORM, false, WTM, WTN, STREAM>(p, Cout, acc, m0 + wi0, n0 + wj0, lane, accumulate_dw, stage);
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_mid(const GemmProb *__restrict_
   __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
   const BigTile t = big_locate<C::BM, C::BN>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
-  big_tile_body<FORM, 2, 2, 2, 2, 1, 1>(p, t.m0, t.n0, lds, accumulate_dw, ext);
+  big_tile_body<FORM, 2, 2, 2, 2, 1, 1>(p, t.m0, t.n0, lds, accumulate_dw, ext, SlotGroup(), total_blocks);
 }
 
 // backward-weight over a group of stash slots (see big_tile_body).
@@ -650,7 +651,7 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
   const BigTile t = big_locate<C::BM, C::BN, DW_BAND>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
   ExtPtrs none;
-  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp);
+  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp, total_blocks);
 }
 
 // ---- host side -------------------------------------------------------------------------
