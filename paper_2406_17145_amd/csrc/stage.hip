@@ -42,6 +42,7 @@ struct gpp_stage {
   std::deque<int> fifo;          // slots in the order their forwards were issued
   std::deque<int> pending;       // grouped weight gradients: backpropagated slots whose operands are still needed
   bool fresh = true;             // no backward since the last grad_reset: next one overwrites dense accumulators
+  bool one_group = false;        // the task list being run holds one run of backward passes: one group
   bool fresh_w = true;           // no grouped weight-gradient launch since the last grad_reset
   bool emb_clear_pending = true; // table accumulators not yet cleared since create
   int64_t emb_table_off = -1;    // table of all embedding records (slot 0) for the clear kernel
@@ -480,7 +481,7 @@ static gpp_status_t run_steps(gpp_stage *st, const std::vector<Step> &steps, int
       case K_GEMM_DW_KSPLIT: launch_gemm_dw_ksplit((const GemmProb *)tab, sp.n, sp.blocks, accumulate, s); break;
       case K_GEMM_DW_GROUP:
         if (!grp) return fail(GPP_ERR_UNSUPPORTED, "internal: group launch without a group");
-        launch_gemm_dw_group((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a2, sp.a0 != 0, *grp, s);
+        launch_gemm_dw_group((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a2, sp.a0 != 0 || st->one_group, *grp, s);
         break;
       case K_GEMM_SPLIT: launch_gemm_split((const GemmProb *)tab, sp.blocks, sp.a1, sp.a2, s); break;
       case K_GEMM_SKINNY: launch_gemm_skinny((const GemmProb *)tab, sp.n, sp.blocks, sp.a1, sp.a2, sp.a0, sp.a3, ext, s); break;
@@ -798,6 +799,13 @@ static gpp_status_t run_schedule_lanes(gpp_stage_t *st, const int32_t *tasks, in
   }
   gpp_status_t rc = gpp_stage_grad_reset(st, streams_backward[0]);
   if (rc != GPP_OK) return rc;
+  struct OneGroup {            // for the length of this call
+    gpp_stage *st;
+    ~OneGroup() { st->one_group = false; }
+  } one_group{st};
+  int64_t runs = 0;
+  for (int64_t t = 0; t < n_tasks; ++t) runs += tasks[t] < 0 && (t == 0 || tasks[t - 1] > 0);
+  st->one_group = runs == 1;
   int64_t last_group = -1;   // micro-batch whose slot-free event follows the latest group launch of weight gradients
   hipError_t he = hipSuccess;
   const int L = pl.group_lanes;
