@@ -32,7 +32,7 @@ CAL_MIB = 256
 # kernel name (as rocprofv3 prints it, namespace stripped) -> kernel family of bench.py's `kernels` table
 FAMILIES = [
     (r"k_gemm_(big|mid)_dw_group|k_gemm_(big|mid)<2", "gemm_big_dw"),
-    (r"k_gemm_(big|mid)<0", "gemm_big_fwd"),
+    (r"k_gemm_(big|mid)<0|k_gemm_big_split|k_split_sum", "gemm_big_fwd"),
     (r"k_gemm_(big|mid)<1", "gemm_big_dx"),
     (r"k_gemm_skinny<0", "gemm_skinny_fwd"),
     (r"k_gemm_skinny<1", "gemm_skinny_dx"),
