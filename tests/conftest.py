@@ -12,8 +12,8 @@ def pytest_configure(config):
 
 def pytest_sessionfinish(session, exitstatus):
     """After a run that compared GPU results with the oracle: write the worst error per
-    workload and tensor class to gpurun_out/parity_errors.txt (the tracked copy lives in
-    profiles/)."""
+    workload and tensor class to parity_errors.txt in the scratch output folder (the tracked
+    copy lives in profiles/)."""
     try:
         from tests import parity_util
     except Exception:
