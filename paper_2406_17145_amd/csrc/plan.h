@@ -74,6 +74,9 @@ struct Plan {
   // Linear layers merged at a column off 16 bytes: their gradient is copied out of the merge's (gout_copies: the stage has
   // some), or read in place (no_copies, set before analyse(): the workspace is too small for the copies)
   bool gout_copies = false, no_copies = false;
+  // Launch tables start on a cache line; on 16 bytes where only that fits the workspace (0 - 512 bytes less per copy of them for
+  // a chain of 13 layers)
+  int table_align = 64;
   // Memory that no forward pass of a slot has a use for: the gradient buffers that the backward pass writes (space, offset,
   // bytes).  The fp32 sums of a forward GEMM over slices of its contraction live there, see Emitter::forward_scratch.
   Buf fwd_scratch;

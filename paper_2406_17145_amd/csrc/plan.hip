@@ -452,7 +452,7 @@ struct Emitter {
   }
   template <typename T>
   int64_t push_table(const std::vector<T> &recs) {
-    int64_t off = align_up((int64_t)pl.blob.size(), 16);
+    int64_t off = align_up((int64_t)pl.blob.size(), pl.table_align);
     pl.blob.resize(off + recs.size() * sizeof(T));
     if (!recs.empty()) memcpy(pl.blob.data() + off, recs.data(), recs.size() * sizeof(T));
     return off;

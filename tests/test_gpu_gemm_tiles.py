@@ -136,6 +136,20 @@ def test_merge_off_16_bytes_without_room_for_the_copies(act, slots, flags, monke
         compare(wl, res, grads, stage, ref, label="gemm_tiles merge off 16 bytes")
 
 
+# Launch tables on 16 bytes, where on cache lines they would not fit: 256 bytes less in every copy of them.
+@pytest.mark.parametrize("slots,flags", [(1, 0), (2, B.FLAG_GROUPED_DW)])
+def test_launch_tables_that_fit_on_16_bytes_only(slots, flags, monkeypatch):
+    wl = _chain(33, (64,) * 14, ("relu",) * 13, 1, 2)
+    room = least_workspace(wl.ops, wl.micro_batch, slots, flags) - 256 * slots
+    print(f"[case] launch tables slots={slots} flags={flags}", flush=True)
+    results = [_run(wl, slots, 1, slots > 1, slots=slots, flags=flags)[1:]]
+    monkeypatch.setattr(B, "gpp_stage_workspace_bytes", lambda d: room)
+    results.append(_run(wl, slots, 1, slots > 1, slots=slots, flags=flags)[1:])
+    stage, ref = run_oracle(wl)
+    for res, grads in results:
+        compare(wl, res, grads, stage, ref, label="gemm_tiles launch tables")
+
+
 # The eight-wave weight gradient: one round of 256 x 256 tiles over a long contraction, ragged in all three directions.
 @pytest.mark.parametrize("rows,n_micro,flags", [(2050, 2, 0), (4100, 1, B.FLAG_GROUPED_DW)])
 def test_weight_gradient_on_large_tiles(rows, n_micro, flags):
