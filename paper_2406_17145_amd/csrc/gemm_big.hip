@@ -1,7 +1,7 @@
 // Branch-grouped bf16 GEMM for problems with many rows AND many columns (the transformer and MLP
 // stacks at full micro-batch), on v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Two kernels:
 //
-// k_gemm_big   eight waves (512 threads) share a 256 x 256 (forward also 128 x 256) output tile as a 2 x 4 grid
+// k_gemm_big   eight waves (512 threads) share a 256 x 256 or 128 x 256 output tile as a 2 x 4 grid
 //              of wave tiles of 128 x 64 (64 x 64) elements.  Per 16-wide contraction chunk a wave reads
 //              6 KB (4 KB) of operand fragments from LDS for 8 (4) MFMAs.  One workgroup per compute
 //              unit (the double-buffered tiles fill the LDS), so prologue and epilogue of a tile are
@@ -20,11 +20,10 @@
 // those of the smaller tile kernel.
 #include <algorithm>
 
-#include "gemm_tile_body.h"
+#include "gemm_direct.h"
 
 namespace gpp {
 
-constexpr int GB_BK = 64;           // contraction elements per k-step
 constexpr int GB_KST = GB_BK + 8;   // LDS row stride of k-contiguous tiles: 144-byte rows, conflict-free b128 reads
 
 // tile geometry: WGM x WGN waves, each WTM x WTN MFMA tiles of 32 x 32; LDS buffers (1 or 2)
@@ -95,78 +94,6 @@ __device__ __forceinline__ bf16x8 big_frag_kmajor(const uint16_t *lds, int row0,
   return *(const bf16x8 *)(lds + (row0 + (l & 31)) * GB_KST + k0 + 8 * (l >> 5));
 }
 
-// ---- direct loads: memory -> LDS without passing through registers.  One load instruction of a wave
-// fills 1 KB of consecutive LDS (lane l writes 16 bytes at 16 l behind the wave-uniform destination), so
-// the layout of a tile in LDS is the order of its 16-byte chunks, and the padding that keeps the operand
-// reads free of bank conflicts in the staged path is replaced by a swizzle: WHICH chunk of memory a lane
-// loads.  The asynchronous copy runs while the previous k-step is multiplied; nothing waits in registers.
-typedef __attribute__((address_space(3))) void lds_void_t;
-// The LDS moves 256 bytes per cycle (64 banks of 4 bytes), so what must not collide is:
-// k-contiguous operand, tile [EXT][64]: 128-byte rows, two per bank line; a 16-byte operand read serves 16
-// lanes per cycle, the same chunk column of 16 consecutive rows.  Chunk c of row r sits at chunk position
-// c ^ ((r / 2) % 8): the two rows of a bank line keep their halves, the eight row pairs take eight positions
-template <int EXT, int THREADS>
-__device__ __forceinline__ void big_direct_kmajor(__amdgpu_buffer_rsrc_t rs, int64_t ld, int r0, int k0, int k_lim,
-                                                  uint16_t *tile, int tid) {
-  constexpr int NW = THREADS / 64, ROWS_PER_WAVE = EXT / NW, INSTR = ROWS_PER_WAVE / 8;
-  static_assert(EXT % (8 * NW) == 0, "a wave loads whole groups of eight rows");
-  const int wave = tid >> 6, l = tid & 63;
-#pragma unroll
-  for (int q = 0; q < INSTR; ++q) {
-    const int row = wave * ROWS_PER_WAVE + 8 * q + (l >> 3);
-    const int k = k0 + (((l & 7) ^ ((row >> 1) & 7)) << 3);
-    const uint32_t oob = (uint32_t)-(int32_t)(k >= k_lim) & OOB_OFFSET;
-    const uint32_t off = (uint32_t)(((int64_t)(r0 + row) * ld + k) * 2) | oob;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t *)(tile + (wave * ROWS_PER_WAVE + 8 * q) * GB_BK), 16, off, 0, 0, 0);
-  }
-}
-__device__ __forceinline__ bf16x8 big_direct_frag_kmajor(const uint16_t *tile, int row0, int k0) {
-  const int l = threadIdx.x & 63;
-  const int row = row0 + (l & 31), c = (k0 >> 3) + (l >> 5);
-  return *(const bf16x8 *)(tile + row * GB_BK + ((c ^ ((row >> 1) & 7)) << 3));
-}
-// contraction-major operand, tile [64][EXT]: rows of EXT elements (a multiple of 256 bytes).  The transposing
-// 8-byte read serves 32 lanes per cycle: 64 bytes in each of four consecutive rows.  Chunk c of row k sits at
-// chunk position c ^ (4 (k % 4)), which spreads the four rows over the four 64-byte quarters of a bank line
-template <int EXT, int THREADS>
-__device__ __forceinline__ void big_direct_tr(__amdgpu_buffer_rsrc_t rs, int64_t ld, int k0, int c0, uint16_t *tile, int tid) {
-  constexpr int CPR = EXT / 8;                         // chunks per row
-  constexpr int NW = THREADS / 64, INSTR = GB_BK * CPR / 64 / NW;
-  static_assert((GB_BK * CPR) % (64 * NW) == 0, "whole load instructions per wave");
-  const int wave = tid >> 6, l = tid & 63;
-#pragma unroll
-  for (int q = 0; q < INSTR; ++q) {
-    const int first = (wave * INSTR + q) * 64;         // first chunk (in LDS order) of this instruction
-    const int row = (first + l) / CPR, pos = (first + l) % CPR;
-    const int col = c0 + ((pos ^ ((row & 3) << 2)) << 3);
-    // the whole address in the vector offset: the descriptor's range check (rows at or beyond the contraction
-    // length read zero) does not cover a scalar offset
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t *)(tile + first * 8), 16,
-                                             (uint32_t)(((int64_t)(k0 + row) * ld + col) * 2), 0, 0, 0);
-  }
-}
-template <int COLS>
-__device__ __forceinline__ bf16x8 big_direct_frag_tr(const uint16_t *tile, int col0, int k0) {
-  const int l = threadIdx.x & 63;
-  const int blk = l >> 4, q = l & 15;
-  const int row = k0 + 8 * (blk >> 1) + (q >> 2), col = col0 + 16 * (blk & 1) + 4 * (q & 3);
-  const uint16_t *p = tile + row * COLS + ((((col >> 3) ^ ((row & 3) << 2)) << 3) | (col & 7));
-  typedef __attribute__((address_space(3))) s16x4 lds_v4;
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)p);
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p + 4 * COLS));     // row + 4: same swizzle
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// End of a k-step of the direct path: wait until at most VM of this wave's copy instructions are outstanding
-// (they land in issue order, so the older k-steps are in LDS) and until its LDS reads have returned, then the
-// workgroup barrier.  Written out instead of __syncthreads(): the fence in front of that barrier waits for ALL
-// outstanding copies, which would keep only one k-step in flight whatever the number of LDS buffers.  The
-// "memory" clobber keeps the compiler from moving LDS accesses across it.
-template <int VM>
-__device__ __forceinline__ void copies_landed_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
-}
-
 // Order for the scheduler: one LDS read behind each of the next MF MFMAs (the last MFMA takes the reads left over)
 template <int MF, int READS, int Q = 0>
 __device__ __forceinline__ void big_mix() {
@@ -235,7 +162,8 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   static_assert(DIRECT || BUFS <= 2, "the staged path has one or two LDS buffers");
   uint16_t *lds_a[2] = {lds, lds + (BUFS > 1 ? 1 : 0) * C::A_ELEMS};
   uint16_t *lds_b[2] = {lds + BUFS * C::A_ELEMS, lds + BUFS * C::A_ELEMS + (BUFS > 1 ? 1 : 0) * C::B_ELEMS};
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = DIRECT ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;      // (copy destinations are scalar)
   const int wi0 = (wave / WGN) * (32 * WTM), wj0 = (wave % WGN) * (32 * WTN);
 
   // operand buffers: rows beyond the matrix read as zero
@@ -243,6 +171,8 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   //   DW:  A = dZ [K x M], B = X [K x N]      (K = contraction length in every form)
   const __amdgpu_buffer_rsrc_t rs_a = matrix_rsrc(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);
   const __amdgpu_buffer_rsrc_t rs_b = matrix_rsrc(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
+  const rsrc4 ra4 = matrix_rsrc4(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);     // (the same for the copies)
+  const rsrc4 rb4 = matrix_rsrc4(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
 
   f32x16 acc[WTM][WTN];
 #pragma unroll
@@ -281,14 +211,17 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   // of pointers loses its address space, and the operand reads then turn into generic (flat) loads
   auto da = [&](int b) { return lds + b * C::A_ELEMS; };
   auto db = [&](int b) { return lds + BUFS * C::A_ELEMS + b * C::B_ELEMS; };
+  const uint32_t lds0 = lds_address(lds);
+  auto to_a = [&](int b) { return lds0 + b * C::A_ELEMS * 2; };                       // copy destinations
+  auto to_b = [&](int b) { return lds0 + (BUFS * C::A_ELEMS + b * C::B_ELEMS) * 2; };
   // the same k-step straight into LDS buffer `buf` (a k-step beyond the contraction copies zeros: its rows or
   // chunks lie outside the buffer range)
   auto fetch_direct = [&](int kt, int buf) {
     const int k0 = kt * GB_BK;
-    if (A_TR) big_direct_tr<BM, THREADS>(rs_a, p.lda, k0, m0, da(buf), tid);
-    else      big_direct_kmajor<BM, THREADS>(rs_a, p.lda, m0, k0, p.K, da(buf), tid);
-    if (B_TR) big_direct_tr<BN, THREADS>(rs_b, p.ldb, k0, n0, db(buf), tid);
-    else      big_direct_kmajor<BN, THREADS>(rs_b, p.ldb, n0, k0, p.K, db(buf), tid);
+    if (A_TR) direct_tr<BM, C::NW>(ra4, p.lda, k0, m0, to_a(buf), wave, lane);
+    else      direct_kmajor<BM, C::NW>(ra4, p.lda, m0, k0, p.K, to_a(buf), wave, lane);
+    if (B_TR) direct_tr<BN, C::NW>(rb4, p.ldb, k0, n0, to_b(buf), wave, lane);
+    else      direct_kmajor<BN, C::NW>(rb4, p.ldb, n0, k0, p.K, to_b(buf), wave, lane);
   };
   auto to_lds = [&](const RegsA &xa, const RegsB &xb, int buf) {
     if (A_TR) big_store_tr<BM, THREADS>(xa, lds_a[buf], tid);
@@ -337,10 +270,10 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
     auto frags = [&](int set, int buf, int kc) {
 #pragma unroll
       for (int j = 0; j < WTN; ++j)
-        fb[set][j] = B_TR ? big_direct_frag_tr<BN>(db(buf), wj0 + 32 * j, kc) : big_direct_frag_kmajor(db(buf), wj0 + 32 * j, kc);
+        fb[set][j] = B_TR ? direct_frag_tr<BN>(db(buf), wj0 + 32 * j, kc) : direct_frag_kmajor(db(buf), wj0 + 32 * j, kc);
 #pragma unroll
       for (int i = 0; i < WTM; ++i)
-        fa[set][i] = A_TR ? big_direct_frag_tr<BM>(da(buf), wi0 + 32 * i, kc) : big_direct_frag_kmajor(da(buf), wi0 + 32 * i, kc);
+        fa[set][i] = A_TR ? direct_frag_tr<BM>(da(buf), wi0 + 32 * i, kc) : direct_frag_kmajor(da(buf), wi0 + 32 * i, kc);
     };
     auto mfmas = [&](int set) {
 #pragma unroll
@@ -399,23 +332,22 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
         const int base = wr * 32 * WTM + h * RB + sub * 8, row = base + (lane >> 3);
         const int k = k0 + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
         const uint32_t oob = (uint32_t)-(int32_t)(k >= p.K) & OOB_OFFSET;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_void_t *)(da(buf) + base * GB_BK), 16,
-                                                 (uint32_t)(((int64_t)(m0 + row) * p.lda + k) * 2) | oob, 0, 0, 0);
+        lds_copy16(ra4, to_a(buf) + base * GB_BK * 2, (uint32_t)(((int64_t)(m0 + row) * p.lda + k) * 2) | oob);
       }
     };
     auto copy_b = [&](int kt, int buf) {
-      if (B_TR) big_direct_tr<BN, THREADS>(rs_b, p.ldb, kt * GB_BK, n0, db(buf), tid);
-      else big_direct_kmajor<BN, THREADS>(rs_b, p.ldb, n0, kt * GB_BK, p.K, db(buf), tid);
+      if (B_TR) direct_tr<BN, C::NW>(rb4, p.ldb, kt * GB_BK, n0, to_b(buf), wave, lane);
+      else direct_kmajor<BN, C::NW>(rb4, p.ldb, n0, kt * GB_BK, p.K, to_b(buf), wave, lane);
     };
     bf16x8 fa[2][HM], fb[4][WTN];
     auto read_b = [&](int buf, int c) {
 #pragma unroll
       for (int j = 0; j < WTN; ++j)
-        fb[c][j] = B_TR ? big_direct_frag_tr<BN>(db(buf), wj0 + 32 * j, 16 * c) : big_direct_frag_kmajor(db(buf), wj0 + 32 * j, 16 * c);
+        fb[c][j] = B_TR ? direct_frag_tr<BN>(db(buf), wj0 + 32 * j, 16 * c) : direct_frag_kmajor(db(buf), wj0 + 32 * j, 16 * c);
     };
     auto read_a = [&](int set, int buf, int h, int c) {
 #pragma unroll
-      for (int i = 0; i < HM; ++i) fa[set][i] = big_direct_frag_kmajor(da(buf), wi0 + 32 * (h * HM + i), 16 * c);
+      for (int i = 0; i < HM; ++i) fa[set][i] = direct_frag_kmajor(da(buf), wi0 + 32 * (h * HM + i), 16 * c);
     };
     auto mf = [&](int set, int h, int c) {
 #pragma unroll
@@ -437,7 +369,6 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
       copies_landed_barrier<N1 + N2>();        // the bottom halves of this k-step have landed; top halves and b are free
       copy_a(kt + 2, cur, 0); copy_b(kt + 2, cur);
       read_a(0, cur, 1, 0); mf(1, 0, 3);
-      __builtin_amdgcn_sched_group_barrier(0x010, N1, 0);      // the copies first: they have the longest way
       big_mix<MF, R2>();
       read_a(1, cur, 1, 1); mf(0, 1, 0); big_mix<MF, R2>();
       read_a(0, cur, 1, 2); mf(1, 1, 1); big_mix<MF, R2>();
@@ -445,7 +376,6 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
       copies_landed_barrier<N1 + N2>();        // top halves and b of the next k-step have landed; bottom halves are free
       copy_a(kt + 2, cur, 1);
       read_b(nxt, 0); read_a(0, nxt, 0, 0); mf(1, 1, 3);
-      __builtin_amdgcn_sched_group_barrier(0x010, N2, 0);
       big_mix<MF, R1>();
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies of the k-steps beyond the end
@@ -664,14 +594,15 @@ bool gemm_big_supported(const GemmProb &p) {
   if (a_rows * p.lda * 2 >= 0xffffff00ll || b_rows * p.ldb * 2 >= 0xffffff00ll) return false;
   return true;
 }
-// Tile shape for a launch: 256 (256 x 256, eight waves), 128 (128 x 256, eight waves; forward only), 64 (128 x 128,
+// Tile shape for a launch: 256 (256 x 256, eight waves), 128 (128 x 256, eight waves), 64 (128 x 128,
 // four waves, three workgroups per compute unit), or 0 for the kernel whose waves split the contraction over 64 x 64
 // blocks.  Whatever takes least by the estimates below, which are microseconds fitted to launches with operands from
 // memory, 1 to 7 records of M 64 .. 2048, N and K 1000 .. 4096: K / 64 k-steps, workgroups as counted in `c`.
-//   256 x 256: one workgroup per compute unit, rounds of 256.       4 x [2048 x 4096 x 1024] 87 forward, 91 backward-data
+//   256 x 256: one workgroup per compute unit, rounds of 256.       4 x [2048 x 4096 x 1024] 87 forward, 84 backward-data
 //   128 x 256: the same with half the work in a workgroup.          7 x [256 x 4096 x 4096] forward 81 (256: 104, 64: 92, 0: 151)
+//                                                                   the same backward-data 76 (256: 91, 64: 89, 0: 159)
 //   128 x 128: 1, 2 or 3 per compute unit; a partial round is partly hidden under the full ones.
-//                                                                   7 x [256 x 4096 x 4096] backward-data 87 (256: 127, 0: 159)
+//                                                                   4 x [700 x 1200 x 600] backward-data 17.0 (256: 26.7, 128: 18.6)
 //   64 x 64:   at a few workgroups per compute unit.                4 x [512 x 1000 x 3820] 48 (256: 96, 128: 65, 64: 72)
 // 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218; a lone [512 x 4096 x 4096]: 95, 62, 72, 45.
 // `whole_chunks`: every contraction length is a multiple of 8.
@@ -681,7 +612,9 @@ bool gemm_big_supported(const GemmProb &p) {
 //   4 x [9679 x 1000 x K], 608 tiles: K 16 117 / 82, 128 124 / 95, 512 170 / 144, 768 195 / 175, 1024 219 / 208, 1536 the same
 //   [3000 x 4096 x K], 192 tiles:     K 512 56 / 50, 768 60 / 52, 1024 66 / 60;     4 x [2048 x 4096 x 512], 512 tiles: 105 / 110
 //   4 x [9679 x 4096 x K], 2432 tiles: K 512 481 / 465, 768 430 / 453
-//   backward-data, 4 x [9679 x 4096 x K], 2432 tiles: K 64 269 / 250, 128 294 / 282;   4 x [5000 x 768 x 200], 240 tiles: 76 / 72
+//   backward-data, 4 x [9679 x 1000 x K], 608 tiles: K 256 64 / 57, 1000 112 / 127;   4 x [2048 x 4096 x K], 512 tiles: K 64 44 / 41,
+//     256 47 / 48, 512 58 / 62.  The 128 x 256 tiles from K 768: 4 x [2048 x 1024 x K], 256 tiles, with 128 / 64: K 256 15.7 / 15.3,
+//     512 18.8 / 19.4, 1024 24.0 / 27.5;   4 x [2048 x 4096 x 512], 1024 tiles: 70 / 62
 // The estimates are within 20 % of what was measured, so the 64 x 64 blocks, whose time depends least on the rest of
 // the shape, are left only for an estimate 10 % below theirs.
 int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, bool whole_chunks, float *us) {
@@ -692,8 +625,8 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
     const float full = floorf(tiles / CUS), part = tiles / CUS - full;
     return full * cost(1.0f) + (full == 0.0f || part > 0.01f ? cost(part) : 0.0f);
   };
-  auto t256 = [&](float fill) { return fwd ? 10.0f + 8.0f * fill + (1.35f + 0.2f * fill) * nk : 12.0f + 4.0f * fill + 1.82f * nk; };
-  auto t128 = [&](float fill) { return 9.0f + 4.0f * fill + 0.95f * nk; };
+  auto t256 = [&](float fill) { return fwd ? 10.0f + 8.0f * fill + (1.35f + 0.2f * fill) * nk : 9.0f + 8.0f * fill + (0.85f + 0.65f * fill) * nk; };
+  auto t128 = [&](float fill) { return fwd ? 9.0f + 4.0f * fill + 0.95f * nk : 7.0f + 2.0f * fill + 0.97f * nk; };
   auto mid = [&](float tiles) {
     auto level = [&](float per_cu) {                   // workgroups that share a compute unit
       const float fixed = per_cu <= 1.0f ? 9.0f : (per_cu <= 2.0f ? 13.5f : 16.0f);
@@ -716,7 +649,7 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
   const float rest256 = c.t256 / CUS - floorf(c.t256 / CUS);
   const bool whole_rounds = c.t256 >= CUS && (rest256 < 0.01f || (fwd && max_k >= 768 && rest256 >= 0.5f));
   if (whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256));
-  if (whole_chunks && fwd) take(128, rounds(c.t128x256, t128));
+  if (whole_chunks && (fwd || max_k >= 768)) take(128, rounds(c.t128x256, t128));
   *us = best;
   return rows;
 }
@@ -761,6 +694,7 @@ void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumul
     else hipLaunchKernelGGL((k_gemm_mid<FORM_FWD>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else if (form == FORM_DX) {
     if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 4, 2, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
+    else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 2, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
     else hipLaunchKernelGGL((k_gemm_mid<FORM_DX>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else {
     if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DW, 4, 2, 2, 0, 2>), g, b8, 0, s, probs, n, total_blocks, accumulate_dw, ext);

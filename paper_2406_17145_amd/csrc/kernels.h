@@ -215,7 +215,7 @@ int gemm_generic_tile(int tiles64);
 int gemm_mfma_group_tile(int form, int maxM, int maxN);
 int gemm_mfma_tiles_for(int tile, int M, int N, int *tiles_n);
 int gemm_mfma_partial_floats(int tile);
-// large-tile kernels: 256 x 256 or (forward) 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
+// large-tile kernels: 256 x 256 or (forward, backward-data) 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
 // 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64); backward-weight
 // has the first and the last
 void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, const ExtPtrs &ext,

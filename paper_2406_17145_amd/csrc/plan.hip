@@ -939,18 +939,9 @@ struct Emitter {
       c.t64 += share * tiles(r, 64, 64);
     }
     float us = 0.0f;
-    int rows = gemm_big_tile_rows(form, max_k, c, few > 0, whole, &us);
+    const int rows = gemm_big_tile_rows(form, max_k, c, few > 0, whole, &us);
     if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16))
       *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, pl.fwd_scratch_bytes / (g[0].M * split_sum_ld(g[0].N) * 4), us);
-    // backward-data whose epilogue streams a second matrix (the stashed derivative or the mask source) behind a short
-    // contraction: the 256 x 256 tiles' epilogues all fall together at the end of a round of tiles; three co-resident
-    // 128 x 128 workgroups hide them behind each other's k-loops (4 x [2048 x 4096 x 1024] with the GELU derivative
-    // inside a step: 119 -> 106 us; with a contraction of 4096 the large tile stays ahead, 260 against 296 us)
-    if (form == FORM_DX && rows == 256 && max_k <= 1024) {
-      bool second = true;
-      for (auto &r : g) second = second && r.act != ACT_NONE;
-      if (second) rows = 64;
-    }
     return rows;
   }
 
