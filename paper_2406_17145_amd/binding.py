@@ -440,7 +440,7 @@ def gpp_partition_search(n_ops, edges, b_values, t, w, a, k_values, n_devices, m
 
 
 def gpp_stage_describe(desc):
-    """The launches of a stage: one dict each with pass, kernel (its profile tag), records, blocks, tile, slices and streams."""
+    """The launches of a stage: one dict each with pass, kernel (its profile tag), records, blocks, tile, slices, streams and ring."""
     buf = C.create_string_buffer(1 << 20)
     _check(load().gpp_stage_describe(C.byref(desc), buf, len(buf)))
     out = []

@@ -94,51 +94,8 @@ __device__ __forceinline__ bf16x8 big_frag_kmajor(const uint16_t *lds, int row0,
   return *(const bf16x8 *)(lds + (row0 + (l & 31)) * GB_KST + k0 + 8 * (l >> 5));
 }
 
-// Order for the scheduler: one LDS read behind each of the next MF MFMAs (the last MFMA takes the reads left over)
-template <int MF, int READS, int Q = 0>
-__device__ __forceinline__ void big_mix() {
-  if constexpr (Q < MF) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if constexpr (Q < READS) __builtin_amdgcn_sched_group_barrier(0x100, (Q + 1 == MF && READS > MF) ? READS - MF + 1 : 1, 0);
-    big_mix<MF, READS, Q + 1>();
-  }
-}
-
-// what every tile kernel of this file does first: XCD-aware spreading (consecutive workgroup ids go
-// round-robin over the 8 XCDs; give each XCD one contiguous range of tiles instead, so that
-// neighbours share operand panels in one L2), then (record, tile) from the records' prefix sums
-struct BigTile {
-  int pi, m0, n0;
-};
-// GM > 0: the tiles of a record are numbered in bands of GM tile rows, column by column inside a band, so that
-// the tiles in flight on an XCD form a block that is about as wide as it is high (fewest distinct operand panels
-// per tile); GM = 0: whole columns of tiles one after the other.
-__device__ __forceinline__ int big_spread(int total_blocks) {
-  const int bid = blockIdx.x, xcd = bid & 7, idx = bid >> 3, per = total_blocks >> 3, rem = total_blocks & 7;
-  return xcd * per + min(xcd, rem) + idx;
-}
-template <int BM, int BN, int GM = 0>
-__device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs, int n, int total_blocks) {
-  const int bid = big_spread(total_blocks);
-  BigTile t;
-  t.pi = find_prob(probs, n, bid);
-  const int tile = bid - probs[t.pi].blk_begin;
-  const int tiles_m = cdiv(probs[t.pi].M, BM);
-  if constexpr (GM > 0) {
-    const int tiles_n = cdiv(probs[t.pi].N, BN), band = tile / (GM * tiles_n), first = band * GM;
-    const int rows = min(GM, tiles_m - first), in_band = tile - band * GM * tiles_n;
-    t.m0 = (first + in_band % rows) * BM;
-    t.n0 = (in_band / rows) * BN;
-    return t;
-  }
-  t.m0 = (tile % tiles_m) * BM;          // consecutive tiles share the B panel
-  t.n0 = (tile / tiles_m) * BN;
-  return t;
-}
-
 // k-loop + bias gradient + epilogue of one output tile.  PIPE: operands copied straight into BUFS LDS buffers (forward and
-// backward-data; whole chunks of k-contiguous rows).  Otherwise staged through registers: BUFS = 2 (backward-weight), LDS
-// double buffer and a ring of NS k-steps in registers (one barrier per step); BUFS = 1, one LDS buffer, the next k-step waits
+// backward-data; whole chunks of k-contiguous rows).  Otherwise staged through registers: one LDS buffer, the next k-step waits
 // in registers while the current one is multiplied (two barriers per step; other workgroups on the compute unit fill the gaps).
 //
 // GROUP (backward-weight only): the contraction runs over the rows of SEVERAL stash slots, one after
@@ -148,8 +105,7 @@ __device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs
 //
 // STREAM (backward-weight): stored gradients go past the caches, see epilogue_wave_lds.
 // PARTIAL (forward): the record covers a slice of a contraction; its result is that slice's sum, stored as plain fp32.
-template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, int NS, bool GROUP = false, int PIPE = 0, bool PARTIAL = false,
-          bool STREAM = false>
+template <int FORM, int WGM, int WGN, int WTM, int WTN, int BUFS, bool GROUP = false, int PIPE = 0, bool PARTIAL = false, bool STREAM = false>
 __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0, uint16_t *lds, int accumulate_dw,
                                               const ExtPtrs &ext, const SlotGroup grp = SlotGroup(), int total_blocks = 1 << 30) {
   static_assert(!GROUP || FORM == FORM_DW, "only the weight gradient contracts over a group of slots");
@@ -158,10 +114,8 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   typedef BigCfg<FORM, WGM, WGN, WTM, WTN, BUFS, DIRECT> C;
   constexpr int BM = C::BM, BN = C::BN, THREADS = C::THREADS;
   constexpr bool A_TR = C::A_TR, B_TR = C::B_TR;
-  static_assert(BUFS == 1 || NS % 2 == 0, "the LDS double buffer alternates with the ring slot");
-  static_assert(DIRECT || BUFS <= 2, "the staged path has one or two LDS buffers");
-  uint16_t *lds_a[2] = {lds, lds + (BUFS > 1 ? 1 : 0) * C::A_ELEMS};
-  uint16_t *lds_b[2] = {lds + BUFS * C::A_ELEMS, lds + BUFS * C::A_ELEMS + (BUFS > 1 ? 1 : 0) * C::B_ELEMS};
+  static_assert(DIRECT || BUFS == 1, "the staged path has one LDS buffer");
+  uint16_t *lds_a = lds, *lds_b = lds + C::A_ELEMS;      // staged path
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = DIRECT ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;      // (copy destinations are scalar)
   const int wi0 = (wave / WGN) * (32 * WTM), wj0 = (wave % WGN) * (32 * WTN);
@@ -184,8 +138,8 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
 
   typedef BigRegs<BM, THREADS> RegsA;
   typedef BigRegs<BN, THREADS> RegsB;
-  RegsA ra[DIRECT ? 1 : NS];       // unused (and removed by the compiler) with direct loads
-  RegsB rb[DIRECT ? 1 : NS];
+  RegsA ra;       // unused (and removed by the compiler) with direct loads
+  RegsB rb;
   const int nk_slot = cdiv(p.K, GB_BK);              // k-steps of one slot (of the whole contraction without a group)
   const int nk = GROUP ? nk_slot * grp.n : nk_slot;
   // k-step `kt` of the tile: without a group, contraction elements [64 kt, 64 kt + 64)
@@ -223,20 +177,20 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
     if (B_TR) direct_tr<BN, C::NW>(rb4, p.ldb, k0, n0, to_b(buf), wave, lane);
     else      direct_kmajor<BN, C::NW>(rb4, p.ldb, n0, k0, p.K, to_b(buf), wave, lane);
   };
-  auto to_lds = [&](const RegsA &xa, const RegsB &xb, int buf) {
-    if (A_TR) big_store_tr<BM, THREADS>(xa, lds_a[buf], tid);
-    else      big_store_kmajor<BM, THREADS>(xa, lds_a[buf], tid);
-    if (B_TR) big_store_tr<BN, THREADS>(xb, lds_b[buf], tid);
-    else      big_store_kmajor<BN, THREADS>(xb, lds_b[buf], tid);
+  auto to_lds = [&](const RegsA &xa, const RegsB &xb) {
+    if (A_TR) big_store_tr<BM, THREADS>(xa, lds_a, tid);
+    else      big_store_kmajor<BM, THREADS>(xa, lds_a, tid);
+    if (B_TR) big_store_tr<BN, THREADS>(xb, lds_b, tid);
+    else      big_store_kmajor<BN, THREADS>(xb, lds_b, tid);
   };
-  auto multiply = [&](int buf) {       // staged loops
+  auto multiply = [&]() {       // staged loop
 #pragma unroll
     for (int kc = 0; kc < GB_BK; kc += 16) {
       bf16x8 a[WTM], b[WTN];
 #pragma unroll
-      for (int i = 0; i < WTM; ++i) a[i] = A_TR ? frag_tr<BM>(lds_a[buf], wi0 + 32 * i, kc) : big_frag_kmajor(lds_a[buf], wi0 + 32 * i, kc);
+      for (int i = 0; i < WTM; ++i) a[i] = A_TR ? frag_tr<BM>(lds_a, wi0 + 32 * i, kc) : big_frag_kmajor(lds_a, wi0 + 32 * i, kc);
 #pragma unroll
-      for (int j = 0; j < WTN; ++j) b[j] = B_TR ? frag_tr<BN>(lds_b[buf], wj0 + 32 * j, kc) : big_frag_kmajor(lds_b[buf], wj0 + 32 * j, kc);
+      for (int j = 0; j < WTN; ++j) b[j] = B_TR ? frag_tr<BN>(lds_b, wj0 + 32 * j, kc) : big_frag_kmajor(lds_b, wj0 + 32 * j, kc);
 #pragma unroll
       for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -249,9 +203,9 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   constexpr int BGROUPS = THREADS / BM, BROWS = GB_BK / BGROUPS;
   const bool do_bias = FORM == FORM_DW && p.bias != nullptr && n0 == 0;
   float bsum = 0.0f;
-  auto bias_rows = [&](int buf) {
+  auto bias_rows = [&]() {
     if (FORM == FORM_DW && do_bias) {
-      const uint16_t *la = lds_a[buf] + (tid / BM) * BROWS * (BM + PAD_TR) + (tid % BM);
+      const uint16_t *la = lds_a + (tid / BM) * BROWS * (BM + PAD_TR) + (tid % BM);
 #pragma unroll
       for (int rr = 0; rr < BROWS; ++rr) bsum += bf16_bits_to_f32(la[rr * (BM + PAD_TR)]);
     }
@@ -380,45 +334,24 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies of the k-steps beyond the end
     __syncthreads();      // the epilogue reuses the operand LDS
-  } else if (BUFS == 2) {
-    static_assert(BUFS == 1 || DIRECT || FORM == FORM_DW, "this loop clears no ragged tail of a k-contiguous row");
-#pragma unroll
-    for (int u = 0; u < NS - 1; ++u)
-      if (u < nk) fetch(ra[u], rb[u], u);
-    to_lds(ra[0], rb[0], 0);
-    __syncthreads();
-    for (int kt0 = 0; kt0 < nk; kt0 += NS) {
-#pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        const int kt = kt0 + u;
-        if (kt >= nk) break;
-        const int cur = u & 1;   // NS is even: the LDS buffer of step kt is kt & 1 = u & 1
-        // ring slot (u + NS - 1) % NS was copied to LDS one step ago: refill it with step kt + NS - 1
-        if (kt + NS - 1 < nk) fetch(ra[(u + NS - 1) % NS], rb[(u + NS - 1) % NS], kt + NS - 1);
-        multiply(cur);
-        bias_rows(cur);
-        if (kt + 1 < nk) to_lds(ra[(u + 1) % NS], rb[(u + 1) % NS], cur ^ 1);
-        __syncthreads();
-      }
-    }
   } else {
-    fetch(ra[0], rb[0], 0);
+    fetch(ra, rb, 0);
     const bool ragged = FORM != FORM_DW && (p.K & 7) != 0;     // the contraction ends inside a chunk of k-contiguous rows
     for (int kt = 0; kt < nk; ++kt) {
       if (ragged && kt + 1 == nk) {                            // clear what lies beyond it (row padding)
         const int k = kt * GB_BK + (tid & 7) * 8;
 #pragma unroll
-        for (int q = 0; q < RegsA::PER_THREAD; ++q) ra[0].v[q] = chunk_clear_tail(ra[0].v[q], k, p.K);
+        for (int q = 0; q < RegsA::PER_THREAD; ++q) ra.v[q] = chunk_clear_tail(ra.v[q], k, p.K);
         if (!B_TR) {
 #pragma unroll
-          for (int q = 0; q < RegsB::PER_THREAD; ++q) rb[0].v[q] = chunk_clear_tail(rb[0].v[q], k, p.K);
+          for (int q = 0; q < RegsB::PER_THREAD; ++q) rb.v[q] = chunk_clear_tail(rb.v[q], k, p.K);
         }
       }
-      to_lds(ra[0], rb[0], 0);
+      to_lds(ra, rb);
       __syncthreads();
-      if (kt + 1 < nk) fetch(ra[0], rb[0], kt + 1);
-      multiply(0);
-      bias_rows(0);
+      if (kt + 1 < nk) fetch(ra, rb, kt + 1);
+      multiply();
+      bias_rows();
       __syncthreads();
     }
   }
@@ -467,14 +400,14 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   }
 }
 
-template <int FORM, int WTM, int WTN, int NS, int PIPE, int BUFS = 2>
+template <int FORM, int WTM, int WTN, int PIPE, int BUFS>
 __global__ __launch_bounds__(512) void k_gemm_big(const GemmProb *__restrict__ probs, int n, int total_blocks,
-                                                  int accumulate_dw, ExtPtrs ext) {
-  typedef BigCfg<FORM, 2, 4, WTM, WTN, BUFS, PIPE != 0> C;
+                                                  ExtPtrs ext) {
+  typedef BigCfg<FORM, 2, 4, WTM, WTN, BUFS, true> C;
   __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
   const BigTile t = big_locate<C::BM, C::BN>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
-  big_tile_body<FORM, 2, 4, WTM, WTN, BUFS, NS, false, PIPE>(p, t.m0, t.n0, lds, accumulate_dw, ext);
+  big_tile_body<FORM, 2, 4, WTM, WTN, BUFS, false, PIPE>(p, t.m0, t.n0, lds, 0, ext);
 }
 
 // Forward with a long contraction and few output tiles (the layer behind a merge of many branches): `split_k` workgroups
@@ -495,7 +428,7 @@ __global__ __launch_bounds__(512) void k_gemm_big_split(const GemmProb *__restri
   p.ldc = split_sum_ld(p.N);
   p.C = p.partial + (int64_t)split * p.M * p.ldc;
   ExtPtrs none;
-  big_tile_body<FORM_FWD, 2, 4, 2, 2, 3, 2, false, 1, true>(p, (tile % tiles_m) * C::BM, (tile / tiles_m) * C::BN, lds, 0, none);
+  big_tile_body<FORM_FWD, 2, 4, 2, 2, 3, false, 1, true>(p, (tile % tiles_m) * C::BM, (tile / tiles_m) * C::BN, lds, 0, none);
 }
 // sum of the slices in order, then what the forward epilogue does; a thread takes four columns of a row
 __global__ __launch_bounds__(256) void k_split_sum(const GemmProb *__restrict__ probs) {
@@ -549,22 +482,10 @@ __global__ __launch_bounds__(256, 3) void k_gemm_mid(const GemmProb *__restrict_
   __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
   const BigTile t = big_locate<C::BM, C::BN>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
-  big_tile_body<FORM, 2, 2, 2, 2, 1, 1>(p, t.m0, t.n0, lds, accumulate_dw, ext, SlotGroup(), total_blocks);
+  big_tile_body<FORM, 2, 2, 2, 2, 1>(p, t.m0, t.n0, lds, accumulate_dw, ext, SlotGroup(), total_blocks);
 }
 
 // backward-weight over a group of stash slots (see big_tile_body).
-// Eight-wave form for long contractions (gemm_big_dw_tile), in bands of four tile rows: one workgroup per compute unit, 32 tiles
-// in flight per XCD as a 4 x 8 block.
-template <bool STREAM>
-__global__ __launch_bounds__(512) void k_gemm_big_dw_group(const GemmProb *__restrict__ probs, int n, int total_blocks,
-                                                           int accumulate_dw, SlotGroup grp) {
-  typedef BigCfg<FORM_DW, 2, 4, 4, 2, 2> C;
-  __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_ELEMS];
-  const BigTile t = big_locate<C::BM, C::BN, 4>(probs, n, total_blocks);
-  const GemmProb p = probs[t.pi];
-  ExtPtrs none;
-  big_tile_body<FORM_DW, 2, 4, 4, 2, 2, 2, true, 0, false, STREAM>(p, t.m0, t.n0, lds, accumulate_dw, none, grp);
-}
 // Tile order of the grouped weight gradient: bands of eight tile rows.  Its launch holds thousands of 128 x 128 tiles,
 // 128 of them in flight per XCD; numbered column by column these are 32 rows x 4 columns of a [4096 x 1024] gradient
 // (36 operand panels of 512 KB through a 4 MB L2), in bands 8 x 16 (24 panels).  Measured on the transformer stage's
@@ -581,7 +502,7 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
   const BigTile t = big_locate<C::BM, C::BN, DW_BAND>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
   ExtPtrs none;
-  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp, total_blocks);
+  big_tile_body<FORM_DW, 2, 2, 2, 2, 1, true, 0, false, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp, total_blocks);
 }
 
 // ---- host side -------------------------------------------------------------------------
@@ -594,17 +515,21 @@ bool gemm_big_supported(const GemmProb &p) {
   if (a_rows * p.lda * 2 >= 0xffffff00ll || b_rows * p.ldb * 2 >= 0xffffff00ll) return false;
   return true;
 }
-// Tile shape for a launch: 256 (256 x 256, eight waves), 128 (128 x 256, eight waves), 64 (128 x 128,
-// four waves, three workgroups per compute unit), or 0 for the kernel whose waves split the contraction over 64 x 64
-// blocks.  Whatever takes least by the estimates below, which are microseconds fitted to launches with operands from
-// memory, 1 to 7 records of M 64 .. 2048, N and K 1000 .. 4096: K / 64 k-steps, workgroups as counted in `c`.
+// Kernel of a forward / backward-data launch: tiles of 256 x 256 or 128 x 256 (256, 128: eight waves), of 128 x 128 (64: four waves,
+// three workgroups per compute unit), of 128 x 64 or 64 x 64 out of a ring of LDS buffers (GEMM_RING + 128, + 64: two and three
+// workgroups per compute unit), or the kernel whose waves split the contraction (0).  Whatever takes least by the estimates below,
+// which are microseconds fitted to launches with operands from memory: 1 to 7 records of M 64 .. 4096, N 64 .. 4096 and K 64 ..
+// 4096, K / 64 k-steps, workgroups as counted in `c`.
 //   256 x 256: one workgroup per compute unit, rounds of 256.       4 x [2048 x 4096 x 1024] 87 forward, 84 backward-data
 //   128 x 256: the same with half the work in a workgroup.          7 x [256 x 4096 x 4096] forward 81 (256: 104, 64: 92, 0: 151)
 //                                                                   the same backward-data 76 (256: 91, 64: 89, 0: 159)
 //   128 x 128: 1, 2 or 3 per compute unit; a partial round is partly hidden under the full ones.
-//                                                                   4 x [700 x 1200 x 600] backward-data 17.0 (256: 26.7, 128: 18.6)
-//   64 x 64:   at a few workgroups per compute unit.                4 x [512 x 1000 x 3820] 48 (256: 96, 128: 65, 64: 72)
-// 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218; a lone [512 x 4096 x 4096]: 95, 62, 72, 45.
+//                                                                   2 x [2000 x 2056 x 136] backward-data 16.0 (256: 19.6, ring 18.1)
+//   ring: a chain of k-steps and a share of the chip's rate.        4 x [512 x 1000 x 1000] forward 13.6, backward-data 12.5 with
+//                                                                   128 x 64 (0: 22.5, 20.5; 64: 25.3, 20.9); 7 x [129 x 1500 x 1000]
+//                                                                   forward 14.4 with 64 x 64 (128 x 64: 18.2, 0: 22.4)
+//   0:         few tiles and a long contraction, whose chain it cuts to an eighth.     [300 x 1000 x 4096] 15.1 (ring 19.5)
+// 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218.
 // `whole_chunks`: every contraction length is a multiple of 8.
 // Behind a short contraction the estimate of the 256 x 256 tiles is too low (their prologue and epilogue are all that such a
 // launch is), so there they are left out unless the launch is whole rounds of them, or in forward from K 768 on at least half
@@ -615,9 +540,11 @@ bool gemm_big_supported(const GemmProb &p) {
 //   backward-data, 4 x [9679 x 1000 x K], 608 tiles: K 256 64 / 57, 1000 112 / 127;   4 x [2048 x 4096 x K], 512 tiles: K 64 44 / 41,
 //     256 47 / 48, 512 58 / 62.  The 128 x 256 tiles from K 768: 4 x [2048 x 1024 x K], 256 tiles, with 128 / 64: K 256 15.7 / 15.3,
 //     512 18.8 / 19.4, 1024 24.0 / 27.5;   4 x [2048 x 4096 x 512], 1024 tiles: 70 / 62
-// The estimates are within 20 % of what was measured, so the 64 x 64 blocks, whose time depends least on the rest of
-// the shape, are left only for an estimate 10 % below theirs.
-int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, bool whole_chunks, float *us) {
+// The estimates are within 20 % of what was measured, so a ring kernel has to be ahead of the large tiles by 8 %, behind ragged
+// contractions, which the fit has none of, by 20 %; the few-row kernel is credited 5 %, and 15 % where it has fewer tiles than
+// compute units behind at least 30 k-steps (over 1342 launches: 17 % faster than with the large tiles and the few-row kernel
+// alone, 1.1 % of them more than 3 % slower).
+int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool whole_chunks, float *us) {
   constexpr float CUS = 256.0f;
   const float nk = (float)cdiv(max_k, GB_BK);
   const bool fwd = form == FORM_FWD;
@@ -626,7 +553,7 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
     return full * cost(1.0f) + (full == 0.0f || part > 0.01f ? cost(part) : 0.0f);
   };
   auto t256 = [&](float fill) { return fwd ? 10.0f + 8.0f * fill + (1.35f + 0.2f * fill) * nk : 9.0f + 8.0f * fill + (0.85f + 0.65f * fill) * nk; };
-  auto t128 = [&](float fill) { return fwd ? 9.0f + 4.0f * fill + 0.95f * nk : 7.0f + 2.0f * fill + 0.97f * nk; };
+  auto t128 = [&](float fill) { return fwd ? 9.8f + 4.2f * fill + (0.62f + 0.31f * fill) * nk : 6.2f + 5.3f * fill + (0.67f + 0.21f * fill) * nk; };
   auto mid = [&](float tiles) {
     auto level = [&](float per_cu) {                   // workgroups that share a compute unit
       const float fixed = per_cu <= 1.0f ? 9.0f : (per_cu <= 2.0f ? 13.5f : 16.0f);
@@ -637,33 +564,53 @@ int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks
     if (full == 0.0f) return level(rest);
     return full * level(3.0f) + (rest > 0.01f ? 0.6f * level(rest) : 0.0f);
   };
-  float best = blocks64 ? 0.9f * (3.0f + fmaxf(1.0f, c.t64 / CUS) * (3.2f + 0.30f * nk)) : 1e30f;
-  int rows = blocks64 ? 0 : 64;
-  auto take = [&](int r, float t) {
-    if (t < best) {
-      best = t;
+  // workgroups that share compute units: fixed part and chain of k-steps, what every workgroup adds, and what each beyond one per
+  // compute unit adds
+  auto shared = [&](float blocks, float a, float ak, float b, float bk, float d, float dk) {
+    const float w = blocks / CUS;
+    return a + ak * nk + w * (b + bk * nk) + fmaxf(1.0f, w) * (d + dk * nk);
+  };
+  float best = 1e30f;
+  int rows = 64;
+  auto take = [&](int r, float t, float handicap) {
+    if (t * handicap < best) {
+      best = t * handicap;
       rows = r;
     }
   };
-  take(64, mid(c.t128));
+  take(64, mid(c.t128), 1.0f);
   const float rest256 = c.t256 / CUS - floorf(c.t256 / CUS);
   const bool whole_rounds = c.t256 >= CUS && (rest256 < 0.01f || (fwd && max_k >= 768 && rest256 >= 0.5f));
-  if (whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256));
-  if (whole_chunks && (fwd || max_k >= 768)) take(128, rounds(c.t128x256, t128));
+  if (whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256), 1.0f);
+  if (whole_chunks && (fwd || max_k >= 768)) take(128, rounds(c.t128x256, t128), 1.0f);
+  const float large = best, r128 = fwd ? shared(c.t128x64, 2.14f, 0.18f, 1.36f, 0.181f, 2.0f, 0.138f) : shared(c.t128x64, 2.04f, 0.179f, 1.27f, 0.219f, 1.16f, 0.104f);
+  const float r64 = fwd ? shared(c.t64, 2.51f, 0.153f, 0.64f, 0.122f, 0.95f, 0.092f) : shared(c.t64, 2.35f, 0.134f, 0.63f, 0.155f, 0.62f, 0.074f);
+  if (ring && fminf(r128, r64) < (whole_chunks ? 0.92f : 0.8f) * large) {
+    take(GEMM_RING + 128, r128, 1.0f);
+    take(GEMM_RING + 64, r64, 1.0f);
+  }
   *us = best;
+  if (c.few > 0.0f) {
+    // (for slices of a contraction, of 64 k-steps and more, which the fit does not reach: the few-row kernel's own line there)
+    *us = fminf(*us, 0.9f * (3.0f + fmaxf(1.0f, c.t64 / CUS) * (3.2f + 0.30f * nk)));
+    const float t = fwd ? shared(c.few, 1.06f, 0.028f, 2.06f, 0.184f, 3.45f, 0.109f) : shared(c.few, 1.18f, 0.032f, 1.63f, 0.179f, 2.55f, 0.134f);
+    take(0, t, nk >= 30.0f && c.t64 <= CUS ? 0.85f : 0.95f);
+  }
   return rows;
 }
-// Backward-weight: 64 (128 x 128 tiles, co-resident workgroups) or 256.  An eight-wave workgroup is alone on its compute unit and
-// exposes its 256 KB of stores, so it takes a long contraction and whole rounds of tiles to win.  us with 128 x 128 / 256 x 256,
-// gradients stored and added to:
-//   [4096 x 4096], rows 512: 94 / 87, 85 / 83     1024: 135 / 122, 125 / 113    2048: 207 / 185, 206 / 180    8192: 706 / 645, 693 / 627
-//   four of it:         237 / 234, 247 / 291            376 / 357, 386 / 401          680 / 641, 681 / 684        2669 / 2387, 2719 / 2404
-//   two [3000 x 3000] (288 tiles), rows 8192: 763 / 873
-// grouped (four 128 x 128 workgroups per compute unit): four [4096 x 4096], rows 2048 629 / 631, 628 / 650, 4096 1219 / 1193,
-//   1252 / 1195, 8192 2742 / 2448, 2794 / 2481; four [2048 x 2048], rows 8192 703 / 688, 686 / 674.
-// (and tiles that are mostly filled: of the 128 x 128 tiles four to a tile, seven to two at the least)
-int gemm_big_dw_tile(bool grouped, int min_k, int tiles256, int tiles128) {
-  return min_k >= (grouped ? 4096 : 1024) && tiles256 >= 256 && tiles256 % 256 == 0 && 2 * tiles128 >= 7 * tiles256 ? 256 : 64;
+// Backward-weight: 64 (128 x 128 tiles staged through registers, three or four workgroups per compute unit) or 256 (256 x 128 tiles
+// out of LDS buffers filled by copies, two).  The larger tile moves a quarter less through the LDS for a product and keeps its copies
+// in flight across k-steps, but has fewer workgroups to hide its prologue and its stores.  us with 64 / 256, gradients stored and
+// added to:
+//   four [4096 x 4096], rows 256: 61 / 64, 116 / 120     512: 88 / 87, 130 / 137     1024: 136 / 132, 180 / 178
+//                       2048: 242 / 222, 288 / 263       4096: 465 / 399, 525 / 439  8192: 1514 / 768, 1554 / 810
+//   the sixteen gradients of four transformer layers (768 x 2 tiles), rows 512: 78 / 76, 109 / 107    2048: 196 / 182, 221 / 204
+//   four [2048 x 2048] (512 tiles), rows 512: 26 / 23, 42 / 40;   six [1536 x 3000] (864), rows 1024: 70 / 70, 87 / 91
+//   four [1000 x 1000] (128 tiles), rows 2048: 38 / 42, 43 / 50
+// (a grouped launch mostly stores, a launch per backward pass mostly adds; ragged matrices that leave the larger tiles more than a
+// tenth emptier stay)
+int gemm_big_dw_tile(bool grouped, int k, int tiles256x128, int tiles128) {
+  return k >= (grouped ? 512 : 1024) && tiles256x128 >= 512 && 20 * tiles256x128 <= 11 * tiles128 ? 256 : 64;
 }
 // Slices of a lone forward record's contraction (0: not split): as many workgroups as compute units, slices of at least 16
 // k-steps, where one round of them and the pass over the slices (written and read once, 4 TB/s, and a launch) take 15 %
@@ -675,6 +622,11 @@ int gemm_big_split(int M, int N, int K, int64_t most, float us) {
   s = cdiv(nk, cdiv(nk, s));                            // no slice without k-steps
   const float t = 13.0f + 0.95f * (float)cdiv(nk, s) + 8.0f + (float)M * (float)N * 8.0f * (float)s / 4e6f;
   return s >= 2 && t < 0.85f * us ? s : 0;
+}
+// (backward-weight: the columns of a tile are always 128)
+int gemm_big_dw_tiles(int tile_rows, int M, int N, int *tiles_n) {
+  if (tiles_n) *tiles_n = cdiv(N, 128);
+  return cdiv(M, tile_rows == 64 ? 128 : tile_rows) * cdiv(N, 128);
 }
 int gemm_big_tiles_for(int tile_rows, int M, int N, int *tiles_n) {
   const int bn = tile_rows == 64 ? 128 : 256, bm = tile_rows == 64 ? 128 : tile_rows;
@@ -689,15 +641,15 @@ void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumul
   // operands straight into LDS where they can be and it pays (4 x [2048 x 4096 x 1024] forward cold: 83 us staged, 78 direct;
   // 4 x [2048 x 4096 x 4096] backward-data: 336 and 297); backward-weight operands are contraction-major, staged
   if (form == FORM_FWD) {
-    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 4, 2, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
-    else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
+    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 4, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, ext);
+    else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_FWD, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, ext);
     else hipLaunchKernelGGL((k_gemm_mid<FORM_FWD>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else if (form == FORM_DX) {
-    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 4, 2, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
-    else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 2, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, 0, ext);
+    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 4, 2, 2, 2>), g, b8, 0, s, probs, n, total_blocks, ext);
+    else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, ext);
     else hipLaunchKernelGGL((k_gemm_mid<FORM_DX>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else {
-    if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_big<FORM_DW, 4, 2, 2, 0, 2>), g, b8, 0, s, probs, n, total_blocks, accumulate_dw, ext);
+    if (tile_rows == 256) launch_gemm_ring_dw(probs, n, total_blocks, accumulate_dw, false, SlotGroup(), s);
     else hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, b4, 0, s, probs, n, total_blocks, accumulate_dw, ext);
   }
 }
@@ -720,10 +672,9 @@ bool gemm_dw_group_streams(int64_t gradient_bytes) { return gradient_bytes >= (i
 void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
                           const SlotGroup &grp, hipStream_t s) {
   if (total_blocks <= 0 || grp.n <= 0) return;
-  const dim3 g(total_blocks), b(tile_rows == 256 ? 512 : 256);
+  const dim3 g(total_blocks), b(256);
   if (tile_rows == 256) {
-    if (stream) hipLaunchKernelGGL(k_gemm_big_dw_group<true>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
-    else hipLaunchKernelGGL(k_gemm_big_dw_group<false>, g, b, 0, s, probs, n, total_blocks, accumulate_dw, grp);
+    launch_gemm_ring_dw(probs, n, total_blocks, accumulate_dw, stream, grp, s);
     return;
   }
   if (accumulate_dw) hipLaunchKernelGGL((k_gemm_mid_dw_group<false, true>), g, b, 0, s, probs, n, total_blocks, grp);

@@ -60,7 +60,7 @@ __device__ __forceinline__ bf16x8 direct_frag_kmajor(const uint16_t *tile, int r
   const int row = row0 + (l & 31), c = (k0 >> 3) + (l >> 5);
   return *(const bf16x8 *)(tile + row * GB_BK + ((c ^ ((row >> 1) & 7)) << 3));
 }
-// contraction-major operand, tile [64][EXT].  The transposing 8-byte read serves 32 lanes per cycle: 64 bytes in each of
+// contraction-major operand, tile [BK][EXT].  The transposing 8-byte read serves 32 lanes per cycle: 64 bytes in each of
 // four consecutive rows.  Chunk c of row k sits at chunk position c ^ swizzle(k), which spreads the four rows over the
 // four 64-byte quarters of a bank line: of whole lines (EXT 128 and more) by k % 4, of 128-byte rows, which alternate
 // between the halves of a line by themselves, by (k / 2) % 2
@@ -69,11 +69,11 @@ __device__ __forceinline__ int direct_tr_swizzle(int row) {
   static_assert(EXT == 64 || EXT % 128 == 0, "rows of 128 bytes or whole bank lines");
   return EXT >= 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2;
 }
-template <int EXT, int NW>
+template <int EXT, int NW, int BK = GB_BK>
 __device__ __forceinline__ void direct_tr(rsrc4 rs, int64_t ld, int k0, int c0, uint32_t tile, int wave, int l) {
   constexpr int CPR = EXT / 8;                         // chunks per row
-  constexpr int INSTR = GB_BK * CPR / 64 / NW;
-  static_assert((GB_BK * CPR) % (64 * NW) == 0, "whole load instructions per wave");
+  constexpr int INSTR = BK * CPR / 64 / NW;
+  static_assert((BK * CPR) % (64 * NW) == 0, "whole load instructions per wave");
 #pragma unroll
   for (int q = 0; q < INSTR; ++q) {
     const int first = (wave * INSTR + q) * 64;         // first chunk (in LDS order) of this instruction
@@ -104,6 +104,48 @@ __device__ __forceinline__ bf16x8 direct_frag_tr(const uint16_t *tile, int col0,
 template <int VM>
 __device__ __forceinline__ void copies_landed_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
+}
+
+// Order for the scheduler: one LDS read behind each of the next MF MFMAs (the last MFMA takes the reads left over)
+template <int MF, int READS, int Q = 0>
+__device__ __forceinline__ void big_mix() {
+  if constexpr (Q < MF) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if constexpr (Q < READS) __builtin_amdgcn_sched_group_barrier(0x100, (Q + 1 == MF && READS > MF) ? READS - MF + 1 : 1, 0);
+    big_mix<MF, READS, Q + 1>();
+  }
+}
+
+// what every tile kernel does first: XCD-aware spreading (consecutive workgroup ids go
+// round-robin over the 8 XCDs; give each XCD one contiguous range of tiles instead, so that
+// neighbours share operand panels in one L2), then (record, tile) from the records' prefix sums
+struct BigTile {
+  int pi, m0, n0;
+};
+// GM > 0: the tiles of a record are numbered in bands of GM tile rows, column by column inside a band, so that
+// the tiles in flight on an XCD form a block that is about as wide as it is high (fewest distinct operand panels
+// per tile); GM = 0: whole columns of tiles one after the other.
+__device__ __forceinline__ int big_spread(int total_blocks) {
+  const int bid = blockIdx.x, xcd = bid & 7, idx = bid >> 3, per = total_blocks >> 3, rem = total_blocks & 7;
+  return xcd * per + min(xcd, rem) + idx;
+}
+template <int BM, int BN, int GM = 0>
+__device__ __forceinline__ BigTile big_locate(const GemmProb *__restrict__ probs, int n, int total_blocks) {
+  const int bid = big_spread(total_blocks);
+  BigTile t;
+  t.pi = find_prob(probs, n, bid);
+  const int tile = bid - probs[t.pi].blk_begin;
+  const int tiles_m = cdiv(probs[t.pi].M, BM);
+  if constexpr (GM > 0) {
+    const int tiles_n = cdiv(probs[t.pi].N, BN), band = tile / (GM * tiles_n), first = band * GM;
+    const int rows = min(GM, tiles_m - first), in_band = tile - band * GM * tiles_n;
+    t.m0 = (first + in_band % rows) * BM;
+    t.n0 = (in_band / rows) * BN;
+    return t;
+  }
+  t.m0 = (tile % tiles_m) * BM;          // consecutive tiles share the B panel
+  t.n0 = (tile / tiles_m) * BN;
+  return t;
 }
 
 }  // namespace gpp

@@ -217,7 +217,7 @@ int gemm_mfma_tiles_for(int tile, int M, int N, int *tiles_n);
 int gemm_mfma_partial_floats(int tile);
 // large-tile kernels: 256 x 256 or (forward, backward-data) 128 x 256 outputs per workgroup of eight waves (tile_rows 256 / 128),
 // 128 x 128 outputs per workgroup of four waves, three workgroups per compute unit (tile_rows 64); backward-weight
-// has the first and the last
+// has the last, and 256 x 128 by four waves (tile_rows 256)
 void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int form, int tile_rows, const ExtPtrs &ext,
                      hipStream_t s);
 bool gemm_big_supported(const GemmProb &p);
@@ -230,15 +230,25 @@ struct SlotGroup {
 bool gemm_dw_group_streams(int64_t gradient_bytes);
 void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
                           const SlotGroup &grp, hipStream_t s);
-int gemm_big_dw_tile(bool grouped, int min_k, int tiles256, int tiles128);
+int gemm_big_dw_tile(bool grouped, int k, int tiles256x128, int tiles128);
+int gemm_big_dw_tiles(int tile_rows, int M, int N, int *tiles_n);
+// small workgroups out of a ring of LDS buffers: forward / backward-data with tile_rows x 64 outputs (tile_rows 128 or 64), and the
+// 256 x 128 backward-weight tiles
+bool gemm_ring_supported(const GemmProb &p);
+int gemm_ring_blocks(int tile_rows, int M, int N);
+void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, int tile_rows, const ExtPtrs &ext, hipStream_t s);
+void launch_gemm_ring_dw(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
+                         hipStream_t s);
 // Workgroups of a launch per output block shape.  Records with a shorter contraction than the launch's longest count
 // for the share of it that they have.
 struct GemmTileCounts {
-  float t256 = 0, t128x256 = 0, t128 = 0, t64 = 0;     // 256 x 256, 128 x 256, 128 x 128, 64 x 64
+  float t256 = 0, t128x256 = 0, t128 = 0, t128x64 = 0, t64 = 0;     // 256 x 256, 128 x 256, 128 x 128, 128 x 64, 64 x 64
+  float few = 0;                                                    // workgroups of the few-row kernel; 0: not a choice
 };
-// forward / backward-data; `blocks64`: the 64 x 64 kernel (0) is a choice
-// (*us: the estimate of the choice)
-int gemm_big_tile_rows(int form, int max_k, const GemmTileCounts &c, bool blocks64, bool whole_chunks, float *us);
+// kernel of a forward / backward-data launch: rows of a large tile (256, 128, 64), GEMM_RING + rows of a ring-buffered one (128, 64),
+// or 0 for the few-row kernel.  (*us: what gemm_big_split compares with)
+constexpr int GEMM_RING = 1024;
+int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool whole_chunks, float *us);
 // forward over slices of the contraction: slices (0: none; at most `most`), row stride of their fp32 sums [slices][M][ld], and the two launches
 int gemm_big_split(int M, int N, int K, int64_t most, float us);
 inline __host__ __device__ int64_t split_sum_ld(int N) { return (N + 63) / 64 * 64; }

@@ -726,7 +726,7 @@ struct Emitter {
         }
       }
       // (not where backward-data alone is a launch for the large tiles)
-      if (!dx.empty() && !dw.empty() && row_tiles > 0 && !(pl.flags & 2) && large_tile(dx, FORM_DX, row_tiles) == 0) {
+      if (!dx.empty() && !dw.empty() && row_tiles > 0 && !(pl.flags & 2) && tile_choice(dx, FORM_DX, row_tiles, false) == 0) {
         int blocks = 0, col_tiles = 2;
         skinny_pick_tiles(dx, row_tiles, col_tiles, false);
         for (auto &r : dx) {
@@ -774,7 +774,7 @@ struct Emitter {
           // few rows: the weight-streaming kernel (forward and backward-data only)
           int row_tiles = (use_mfma && form != FORM_DW) ? few_rows(g) : 0;
           int slices = 0;
-          int tile_rows = (use_mfma && form != FORM_DW) ? large_tile(g, form, row_tiles, &slices) : 0;
+          int tile_rows = (use_mfma && form != FORM_DW) ? tile_choice(g, form, row_tiles, true, &slices) : 0;
           if (tile_rows > 0) row_tiles = 0;
           if (slices > 1) {
             GemmProb &r = g[0];
@@ -810,13 +810,14 @@ struct Emitter {
           }
           if (use_mfma && form == FORM_DW && !(pl.flags & 2)) {
             int tiles64 = 0, tiles128 = 0, tiles256 = 0, min_k = 1 << 30;
-            bool ok = true;
+            bool ok = true, ring = true;
             for (auto &r : g) {
               tiles64 += gemm_mfma_tiles_for(64, r.M, r.N, nullptr);
-              tiles256 += gemm_big_tiles_for(256, r.M, r.N, nullptr);
+              tiles256 += gemm_big_dw_tiles(256, r.M, r.N, nullptr);
               tiles128 += gemm_mfma_tiles_for(128, r.M, r.N, nullptr);
               min_k = std::min(min_k, r.K);
               ok = ok && gemm_big_supported(r);
+              ring = ring && gemm_ring_supported(r);
             }
             // backward-weight with a long contraction and too few 128 x 128 tiles to fill the chip: small tiles, the
             // contraction split over the waves of each workgroup; the longer the contraction, the more tiles it takes
@@ -836,7 +837,21 @@ struct Emitter {
             }
             // every other one runs on the large tiles, whatever its size (2 x [1000 x 256] over 300 rows: 7.9 us against
             // 10.4 with the ring-buffered 128 x 128 tiles and 10.7 with 64 x 64; [100 x 64]: 7.2 against 10.0 and 7.1)
-            if (ok) tile_rows = gemm_big_dw_tile(false, min_k, tiles256, tiles128);
+            if (ok) tile_rows = ring ? gemm_big_dw_tile(false, min_k, tiles256, tiles128) : 64;
+          }
+          if (tile_rows > GEMM_RING) {
+            const int rows = tile_rows - GEMM_RING;
+            int blocks = 0;
+            for (auto &r : g) {
+              r.blk_begin = blocks;
+              r.split_k = 1;
+              blocks += gemm_ring_blocks(rows, r.M, r.N);
+            }
+            Step &s = add_step(K_GEMM_RING, push_table(g), (int)g.size(), blocks);
+            s.a1 = form;
+            s.a2 = rows;
+            if (wants_ext(g)) s.ext_kind = EXT_GRAD_INPUTS;
+            continue;
           }
           // the large-tile kernels
           if (tile_rows > 0) {
@@ -844,7 +859,7 @@ struct Emitter {
             for (auto &r : g) {
               r.blk_begin = blocks;
               r.split_k = 1;
-              blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
+              blocks += form == FORM_DW ? gemm_big_dw_tiles(tile_rows, r.M, r.N, &r.tiles_n) : gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
             }
             Step &s = add_step(K_GEMM_BIG, push_table(g), (int)g.size(), blocks);
             s.a1 = form;
@@ -907,18 +922,20 @@ struct Emitter {
     const int row_tiles = gemm_skinny_row_tiles(max_m);
     return row_tiles == 0 && !(pl.flags & 2) && elems < (int64_t)128 * 128 * 256 ? 2 : row_tiles;
   }
-  // Large-tile kernel of a forward / backward-data launch (rows of its tile), or 0: the kernel above, or where that is
+  // Kernel of a forward / backward-data launch as gemm_tile_choice names it, 0 for the kernel above or, where that is
   // not meant for the launch either, the small tiles.  Up to 64 rows a tile would be half padding.  Where launches
   // share the GPU (flag bit 4) the few-row kernel stays wherever it is meant to run: its workgroups fit beside those of
   // another stream, and group launches, which give the same results bit by bit as single ones, know no other kernel.
+  // `ring`: the ring-buffered tiles are a choice.
   // *slices: > 1 when a lone forward record had better be summed over that many slices of its contraction (no more than
   // have their sums in the memory that a forward pass may overwrite: a stage needs no workspace for them).
-  int large_tile(const std::vector<GemmProb> &g, int form, int few, int *slices = nullptr) const {
+  int tile_choice(const std::vector<GemmProb> &g, int form, int few, bool ring, int *slices = nullptr) const {
     if (pl.flags & 2) return 0;
     int max_m = 0, max_n = 0, max_k = 0;
     bool whole = true;
     for (auto &r : g) {
       if (!gemm_big_supported(r)) return 0;
+      ring = ring && gemm_ring_supported(r);
       max_m = std::max(max_m, r.M);
       max_n = std::max(max_n, r.N);
       max_k = std::max(max_k, r.K);
@@ -931,18 +948,22 @@ struct Emitter {
     if (few > 0 && (max_m <= 64 || (pl.flags & 16) || pl.group_lanes > 0)) return 0;
     GemmTileCounts c;
     auto tiles = [](const GemmProb &r, int bm, int bn) { return (float)(((r.M + bm - 1) / bm) * ((r.N + bn - 1) / bn)); };
+    int row_tiles = few, col_tiles = 2;
+    if (few > 0) skinny_pick_tiles(g, row_tiles, col_tiles, false);
     for (auto &r : g) {
       const float share = (float)r.K / (float)max_k;
       c.t256 += share * tiles(r, 256, 256);
       c.t128x256 += share * tiles(r, 128, 256);
       c.t128 += share * tiles(r, 128, 128);
+      c.t128x64 += share * tiles(r, 128, 64);
       c.t64 += share * tiles(r, 64, 64);
+      if (few > 0) c.few += share * tiles(r, 32 * row_tiles, 32 * col_tiles);
     }
     float us = 0.0f;
-    const int rows = gemm_big_tile_rows(form, max_k, c, few > 0, whole, &us);
+    const int choice = gemm_tile_choice(form, max_k, c, ring, whole, &us);
     if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16))
       *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, pl.fwd_scratch_bytes / (g[0].M * split_sum_ld(g[0].N) * 4), us);
-    return rows;
+    return choice;
   }
 
   // Tile shape of a few-row launch: `row_tiles` comes in as the largest row tile the rows allow.  The
@@ -1885,21 +1906,24 @@ void Emitter::backward() {
   steps->clear();
   if (!dw_group.empty()) {
     // (one launch lets the co-resident tiles of all layers fill each other's tails)
-    int blocks = 0, tiles256 = 0, tiles128 = 0, min_k = 1 << 30;
-    int64_t bytes = 0;
+    int blocks = 0, tiles256 = 0, tiles128 = 0;
+    int64_t bytes = 0, steps256 = 0;
+    bool ring = true;
     for (auto &r : dw_group) {
       bytes += r.M * r.ldc * 4;
-      tiles256 += gemm_big_tiles_for(256, r.M, r.N, nullptr);
-      tiles128 += gemm_big_tiles_for(64, r.M, r.N, nullptr);
-      min_k = std::min(min_k, r.K);
+      const int t = gemm_big_dw_tiles(256, r.M, r.N, nullptr);
+      tiles256 += t;
+      steps256 += (int64_t)t * r.K;
+      tiles128 += gemm_big_dw_tiles(64, r.M, r.N, nullptr);
+      ring = ring && gemm_ring_supported(r);
     }
-    const int tile_rows = gemm_big_dw_tile(true, min_k, tiles256, tiles128);
+    // (the mean over the tiles: the layers behind a pool have a handful of rows)
+    const int tile_rows = ring ? gemm_big_dw_tile(true, (int)(steps256 / tiles256), tiles256, tiles128) : 64;
     for (auto &r : dw_group) {
       r.blk_begin = blocks;
       r.split_k = 1;
-      blocks += gemm_big_tiles_for(tile_rows, r.M, r.N, &r.tiles_n);
+      blocks += gemm_big_dw_tiles(tile_rows, r.M, r.N, &r.tiles_n);
     }
-    // (contraction-major operands: staged through registers, see emit_gemms)
     Step &sg = add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
     sg.a0 = gemm_dw_group_streams(bytes) ? 1 : 0;
     sg.a2 = tile_rows;

@@ -81,7 +81,7 @@ static void *g_static_ptr[STATIC_MAX_DEVICES] = {nullptr};          // per devic
 static const gpp_stage *g_static_owner[STATIC_MAX_DEVICES] = {nullptr};   // per device: the stage that holds it
 
 static bool gemm_step(const Step &sp) {
-  return sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_SPLIT || sp.kern == K_GEMM_SKINNY || sp.kern == K_GEMM_BWD_MERGED ||
+  return sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_SPLIT || sp.kern == K_GEMM_SKINNY || sp.kern == K_GEMM_RING || sp.kern == K_GEMM_BWD_MERGED ||
          sp.kern == K_GEMM_DW_KSPLIT || sp.kern == K_GEMM_DW_GROUP;
 }
 
@@ -91,6 +91,7 @@ static int step_tag(const Step &sp, bool backward) {
     case K_GEMM_MFMA: return 1 + sp.a1;                    // 1 fwd, 2 dx, 3 dw
     case K_GEMM_SPLIT: return 28;
     case K_GEMM_BIG: return 28 + sp.a1;                    // 28 fwd, 29 dx, 30 dw
+    case K_GEMM_RING:                                      // (the same family: launches too small for the large tiles)
     case K_GEMM_SKINNY: return 25 + sp.a1;                 // 25 fwd, 26 dx
     case K_GEMM_BWD_MERGED: return 27;
     case K_GEMM_DW_KSPLIT: return 31;
@@ -201,8 +202,8 @@ gpp_status_t gpp_stage_describe(const gpp_stage_desc_t *desc, char *text, size_t
       const int streams = sp.kern == K_GEMM_DW_GROUP && sp.a0;
       if (sp.kern == K_GEMM_GENERIC || sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_DW_GROUP) tile = sp.a2;
       if (sp.kern == K_GEMM_SPLIT) slices = ((const GemmProb *)(pl.blob.data() + sp.table_off))->split_k;
-      snprintf(line, sizeof(line), "%s %s records=%d blocks=%d tile=%d slices=%d streams=%d\n", names[l], kTagNames[step_tag(sp, l == 1)],
-               sp.n, sp.blocks, tile, slices, streams);
+      snprintf(line, sizeof(line), "%s %s records=%d blocks=%d tile=%d slices=%d streams=%d ring=%d\n", names[l], kTagNames[step_tag(sp, l == 1)],
+               sp.n, sp.blocks, tile, slices, streams, sp.kern == K_GEMM_RING ? sp.a2 : 0);
       out += line;
     }
   if (out.size() + 1 > capacity) return fail(GPP_ERR_INVALID_ARG, "text needs " + std::to_string(out.size() + 1) + " bytes");
@@ -495,6 +496,7 @@ static gpp_status_t run_steps(gpp_stage *st, const std::vector<Step> &steps, int
         break;
       case K_GEMM_SPLIT: launch_gemm_split((const GemmProb *)tab, sp.blocks, sp.a1, sp.a2, s); break;
       case K_GEMM_SKINNY: launch_gemm_skinny((const GemmProb *)tab, sp.n, sp.blocks, sp.a1, sp.a2, sp.a0, sp.a3, ext, s); break;
+      case K_GEMM_RING: launch_gemm_ring((const GemmProb *)tab, sp.n, sp.blocks, sp.a1, sp.a2, ext, s); break;
       case K_GEMM_BWD_MERGED: launch_gemm_bwd_merged((const GemmProb *)tab, sp.n, sp.blocks, sp.a2, sp.a1, accumulate, ext, s); break;
       case K_HEAD_LOSS: {   // always runs: it also writes the prediction and two gradients
         float *sink = loss_out ? loss_out : (float *)(st->ws + pl.off_slots + (int64_t)slot * pl.slot_bytes + pl.loss_scalars.off);

@@ -120,7 +120,7 @@ def test_gradients_that_exceed_half_the_last_level_cache_are_stored_past_it(bran
 
 @pytest.mark.parametrize("rows,k,n,branches,flags,tile", [
     (1023, 4096, 4096, 1, 0, 64), (1024, 4096, 4096, 1, 0, 256), (4096, 300, 4096, 8, 0, 64), (4096, 64, 64, 256, B.FLAG_GROUPED_DW, 64), (2048, 4096, 4096, 1, 0, 256), (2048, 4090, 4084, 1, 0, 256), (2048, 3840, 4096, 1, 0, 64),
-    (4095, 2048, 2048, 4, B.FLAG_GROUPED_DW, 64), (4096, 2048, 2048, 4, B.FLAG_GROUPED_DW, 256), (4096, 2048, 2048, 5, B.FLAG_GROUPED_DW, 64)])
+    (511, 2048, 2048, 4, B.FLAG_GROUPED_DW, 64), (4096, 2048, 2048, 4, B.FLAG_GROUPED_DW, 256), (4096, 2048, 1792, 4, B.FLAG_GROUPED_DW, 64)])
 def test_weight_gradients_take_the_large_tile_for_long_contractions(rows, k, n, branches, flags, tile):
     (step,) = [p for p in plan(layers(rows, k, n, branches), rows, 1, flags) if p["kernel"] == "gemm_big_dw"]
     assert step["tile"] == tile
@@ -142,7 +142,7 @@ def test_large_tiles_behind_a_short_contraction_take_whole_rounds():
 
 
 def test_narrow_results_of_many_rows():
-    for k, n, kernel in ((64, 64, "gemm_mfma_fwd"), (128, 64, "gemm_mfma_fwd"), (136, 64, "gemm_big_fwd"), (128, 72, "gemm_big_fwd")):
+    for k, n, kernel in ((64, 64, "gemm_mfma_fwd"), (128, 64, "gemm_mfma_fwd"), (136, 64, "gemm_skinny_fwd"), (128, 72, "gemm_big_fwd")):
         fwd = [p["kernel"] for p in plan(layers(40000, k, n, 4), 40000) if p["pass"] == "forward"]
         assert kernel in fwd, (k, n, fwd)
 

@@ -2,8 +2,10 @@
 is only partly inside the matrix."""
 import pytest
 
+from paper_2406_17145_amd import binding as B
 from tests.parity_util import compare, run_gpu, run_oracle
 from tests.test_gpu_gemm_tiles import _chain, _plan
+from tests.test_gpu_schedule import _run
 
 pytestmark = pytest.mark.gpu
 
@@ -23,3 +25,38 @@ def test_backward_data_on_128_x_256_tiles(rows, widths, acts, branches):
     res, grads = run_gpu(wl)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="gemm_direct")
+
+
+# Ring-buffered tiles: a contraction of one k-step and of less than the buffers hold, one that ends inside a k-step and inside a
+# chunk, a last row tile of one row, columns that end inside a tile and inside a chunk, one row block; every activation, and a
+# result that is stored as fp32.  `want`: tile rows of the ring launches, forward and backward-data.
+@pytest.mark.parametrize("rows,widths,acts,branches,want", [
+    (513, (1000, 1000, 1000), ("gelu", "gelu"), 4, {("fwd", 128), ("dx", 128)}),
+    (300, (203, 333, 70), ("gelu", "none"), 3, {("fwd", 64), ("dx", 64)}),
+    (129, (1000, 1500, 1003), ("relu", "gelu"), 7, {("fwd", 64), ("dx", 64)}),
+    (700, (130, 603, 132), ("gelu", "relu"), 3, {("fwd", 64), ("dx", 64)}),
+    (2047, (64, 65, 128), ("gelu", "none"), 1, {("fwd", 64), ("dx", 64)}),
+    (300, (1, 200, 9), ("relu", "none"), 2, {("fwd", 64), ("dx", 64)}),
+])
+def test_ring_buffered_tiles(rows, widths, acts, branches, want):
+    wl = _chain(rows, widths, acts, branches, 2)
+    print(f"[case] ring rows={rows} widths={widths} branches={branches}", flush=True)
+    held = {(p["kernel"].split("_")[2], p["ring"]) for p in _plan(wl, 2, B.FLAG_GROUPED_DW) if p["ring"]}
+    assert held >= want, held
+    stage, ref = run_oracle(wl)
+    _, res, grads = _run(wl, 2, 2, False, flags=B.FLAG_GROUPED_DW)
+    compare(wl, res, grads, stage, ref, label="gemm_direct ring")
+    res, grads = run_gpu(wl)
+    compare(wl, res, grads, stage, ref, label="gemm_direct ring")
+
+
+# Weight gradients on 256 x 128 tiles: rows that end inside a k-step, slots one behind the other and around the end of the stash,
+# a second group that adds, matrices that end inside a tile in both directions and inside a chunk.
+@pytest.mark.parametrize("rows,n_micro,slots", [(515, 4, 2), (543, 3, 3), (577, 3, 2)])
+def test_grouped_weight_gradients_on_256_x_128_tiles(rows, n_micro, slots):
+    wl = _chain(rows, (2034, 2051), ("gelu",), 4, n_micro)
+    print(f"[case] 256 x 128 weight gradients rows={rows} micro-batches={n_micro} slots={slots}", flush=True)
+    assert [p["tile"] for p in _plan(wl, slots, B.FLAG_GROUPED_DW) if p["pass"] == "weights"] == [256]
+    _, res, grads = _run(wl, slots, slots, False, flags=B.FLAG_GROUPED_DW)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="gemm_direct dw")

@@ -89,9 +89,12 @@ def test_sums_over_slices_in_the_static_workspace():
     # 256 x 256 with a last column inside a chunk: forward with the stash, backward-data with the derivative
     (1000, (2000, 4003), ("gelu",), 4, ("big_fwd 256",)),
     (1000, (64, 4003, 2000), ("gelu", "none"), 4, ("big_dx 256",)),
-    # 128 x 256: a last row tile of 122 rows; the same with columns that end inside a chunk
-    (250, (520, 2056, 520), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
-    (250, (520, 2051, 520), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
+    # ring-buffered tiles, a last row tile of 122 rows; the same with columns that end inside a chunk
+    (250, (520, 2056, 520), ("gelu", "gelu"), 9, ("skinny_fwd 0", "skinny_dx 0")),
+    (250, (520, 2051, 520), ("gelu", "gelu"), 9, ("skinny_fwd 0", "skinny_dx 0")),
+    # 128 x 256: the same two
+    (378, (1032, 2056, 200), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
+    (378, (2056, 2051, 200), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
     # few-row kernel: one row more than two row blocks, columns that end inside a chunk, the smallest and an ordinary launch
     # with a choice, a contraction of 141 steps, 11 and 25 column blocks (a group of 16 and one of 9) in several row blocks
     (129, (1000, 1500, 1000), ("gelu", "gelu"), 7, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
