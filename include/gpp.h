@@ -427,8 +427,8 @@ int32_t gpp_stage_output_op(const gpp_stage_t *stage, int32_t i);
 /* The grouped launches that a stage of this descriptor consists of, one line each in the order of issue: the pass
  * (forward, backward, weights), the profile tag of the kernel, its records and workgroups, and for GEMM kernels that
  * have a choice the rows of their output tile and the slices of their contraction (0: none), and whether grouped weight
- * gradients are stored past the caches; ring: rows of the output tile where a launch of the few-row family runs the
- * ring-buffered kernel (0: it does not), as
+ * gradients are stored past the caches; ring: rows of the output tile where a launch of the few-row family, or of the
+ * weight gradients of all layers, runs the ring-buffered kernel with small tiles (0: it does not), as
  *   forward gemm_big_fwd records=7 blocks=224 tile=256 slices=0 streams=0 ring=0
  * Host-only: needs no GPU, parameter pointers are not looked at.  text: HOST, zero-terminated; GPP_ERR_INVALID_ARG if
  * `capacity` bytes do not hold it. */

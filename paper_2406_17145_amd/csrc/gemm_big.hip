@@ -612,6 +612,22 @@ int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bo
 int gemm_big_dw_tile(bool grouped, int k, int tiles256x128, int tiles128) {
   return k >= (grouped ? 512 : 1024) && tiles256x128 >= 512 && 20 * tiles256x128 <= 11 * tiles128 ? 256 : 64;
 }
+// The launch that holds the weight gradients of all layers, where 256 x 128 tiles are not for it: 128 x 128 (64), or 128 x 64 or
+// 64 x 64 out of a ring of LDS buffers (GEMM_RING + 128, + 64), by estimates fitted to 1298 launches of 1 to 40 gradients of 64 ..
+// 4096 rows and columns over 64 .. 4096 rows, stored and added to (48 % faster than 128 x 128 alone, the ring kernels mostly ahead
+// below a few hundred tiles: [504 x 256] over 4096 rows 55 us with 64, 26 with 128 x 64, 19 with 64 x 64; 12 x [64 x 256] 72, 30,
+// 28; 4 x [2048 x 2048] over 512 rows 32, 43, 43).
+int gemm_dw_small_tile(int k, const GemmTileCounts &c) {
+  const float nk = (float)cdiv(k, GB_BK);
+  auto est = [&](float blocks, float a, float ak, float b, float bk, float d, float dk) {
+    const float w = blocks / 256.0f;
+    return a + ak * nk + w * (b + bk * nk) + fmaxf(1.0f, w) * (d + dk * nk);
+  };
+  const float mid = est(c.t128, 3.8f, 0.834f, 4.3f, 0.319f, -0.21f, -0.012f), r128 = est(c.t128x64, 2.5f, 0.172f, 2.34f, 0.136f, 0.67f, 0.187f);
+  const float r64 = est(c.t64, 2.46f, 0.189f, 1.36f, 0.129f, 0.17f, 0.073f);
+  if (fminf(r128, r64) >= 0.97f * mid) return 64;
+  return GEMM_RING + (r64 <= r128 ? 64 : 128);
+}
 // Slices of a lone forward record's contraction (0: not split): as many workgroups as compute units, slices of at least 16
 // k-steps, where one round of them and the pass over the slices (written and read once, 4 TB/s, and a launch) take 15 %
 // less than the kernel chosen otherwise, by the estimates above.
@@ -649,7 +665,7 @@ void launch_gemm_big(const GemmProb *probs, int n, int total_blocks, int accumul
     else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_big<FORM_DX, 2, 2, 1, 3>), g, b8, 0, s, probs, n, total_blocks, ext);
     else hipLaunchKernelGGL((k_gemm_mid<FORM_DX>), g, b4, 0, s, probs, n, total_blocks, 0, ext);
   } else {
-    if (tile_rows == 256) launch_gemm_ring_dw(probs, n, total_blocks, accumulate_dw, false, SlotGroup(), s);
+    if (tile_rows == 256) launch_gemm_ring_dw(probs, n, total_blocks, accumulate_dw, 256, false, SlotGroup(), s);
     else hipLaunchKernelGGL((k_gemm_mid<FORM_DW>), g, b4, 0, s, probs, n, total_blocks, accumulate_dw, ext);
   }
 }
@@ -673,8 +689,8 @@ void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int ac
                           const SlotGroup &grp, hipStream_t s) {
   if (total_blocks <= 0 || grp.n <= 0) return;
   const dim3 g(total_blocks), b(256);
-  if (tile_rows == 256) {
-    launch_gemm_ring_dw(probs, n, total_blocks, accumulate_dw, stream, grp, s);
+  if (tile_rows == 256 || tile_rows > GEMM_RING) {
+    launch_gemm_ring_dw(probs, n, total_blocks, accumulate_dw, tile_rows > GEMM_RING ? tile_rows - GEMM_RING : tile_rows, stream, grp, s);
     return;
   }
   if (accumulate_dw) hipLaunchKernelGGL((k_gemm_mid_dw_group<false, true>), g, b, 0, s, probs, n, total_blocks, grp);

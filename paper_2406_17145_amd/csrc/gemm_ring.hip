@@ -188,14 +188,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, WGM == 4 ? 4 : 3) void k_gemm_ring(
 }
 
 // (ADD, gradients are added to, at compile time: the other epilogue is not in the kernel)
-template <bool STREAM, bool ADD>
-__global__ __launch_bounds__(256, 2) void k_gemm_ring_dw(const GemmProb *__restrict__ probs, int n, int total_blocks, SlotGroup grp) {
-  typedef RingCfg<FORM_DW, 2, 2, 4, 2, 3, 32> C;
+template <int WGM, int WGN, int TM, int TN, int BK, int OCC, bool STREAM, bool ADD>
+__global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring_dw(const GemmProb *__restrict__ probs, int n, int total_blocks,
+                                                                     SlotGroup grp) {
+  typedef RingCfg<FORM_DW, WGM, WGN, TM, TN, 3, BK> C;
   __shared__ __attribute__((aligned(16))) uint16_t lds[C::ELEMS];
-  const BigTile t = big_locate<C::BM, C::BN, 4>(probs, n, total_blocks);
+  const BigTile t = big_locate<C::BM, C::BN, (C::BM == 256 ? 4 : 8)>(probs, n, total_blocks);
   const GemmProb p = probs[t.pi];
   ExtPtrs none;
-  ring_body<FORM_DW, 2, 2, 4, 2, 3, 32, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp);
+  ring_body<FORM_DW, WGM, WGN, TM, TN, 3, BK, STREAM>(p, t.m0, t.n0, lds, ADD ? 1 : 0, none, grp);
 }
 
 // ---- host side -------------------------------------------------------------------------
@@ -217,13 +218,19 @@ void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, 
     else hipLaunchKernelGGL((k_gemm_ring<FORM_DX, 2, 2>), g, b, 0, s, probs, n, total_blocks, ext);
   }
 }
-void launch_gemm_ring_dw(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
-                         hipStream_t s) {
+template <bool STREAM, bool ADD>
+static void launch_ring_dw(const GemmProb *probs, int n, int blocks, int tile_rows, const SlotGroup &grp, hipStream_t s) {
+  const dim3 g(blocks), b4(256), b8(512);
+  if (tile_rows == 256) hipLaunchKernelGGL((k_gemm_ring_dw<2, 2, 4, 2, 32, 2, STREAM, ADD>), g, b4, 0, s, probs, n, blocks, grp);
+  else if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_ring_dw<4, 2, 1, 1, 64, 4, STREAM, ADD>), g, b8, 0, s, probs, n, blocks, grp);
+  else hipLaunchKernelGGL((k_gemm_ring_dw<2, 2, 1, 1, 64, 3, STREAM, ADD>), g, b4, 0, s, probs, n, blocks, grp);
+}
+void launch_gemm_ring_dw(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
+                         const SlotGroup &grp, hipStream_t s) {
   if (total_blocks <= 0 || grp.n <= 0) return;
-  const dim3 g(total_blocks), b(256);
-  if (accumulate_dw) hipLaunchKernelGGL((k_gemm_ring_dw<false, true>), g, b, 0, s, probs, n, total_blocks, grp);
-  else if (stream) hipLaunchKernelGGL((k_gemm_ring_dw<true, false>), g, b, 0, s, probs, n, total_blocks, grp);
-  else hipLaunchKernelGGL((k_gemm_ring_dw<false, false>), g, b, 0, s, probs, n, total_blocks, grp);
+  if (accumulate_dw) launch_ring_dw<false, true>(probs, n, total_blocks, tile_rows, grp, s);
+  else if (stream) launch_ring_dw<true, false>(probs, n, total_blocks, tile_rows, grp, s);
+  else launch_ring_dw<false, false>(probs, n, total_blocks, tile_rows, grp, s);
 }
 
 }  // namespace gpp

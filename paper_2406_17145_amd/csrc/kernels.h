@@ -228,17 +228,18 @@ struct SlotGroup {
   int64_t stride = 0;
 };
 bool gemm_dw_group_streams(int64_t gradient_bytes);
+// tile_rows: as gemm_big_dw_tile and gemm_dw_small_tile name them
 void launch_gemm_dw_group(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
                           const SlotGroup &grp, hipStream_t s);
 int gemm_big_dw_tile(bool grouped, int k, int tiles256x128, int tiles128);
 int gemm_big_dw_tiles(int tile_rows, int M, int N, int *tiles_n);
 // small workgroups out of a ring of LDS buffers: forward / backward-data with tile_rows x 64 outputs (tile_rows 128 or 64), and the
-// 256 x 128 backward-weight tiles
+// 256 x 128 (tile_rows 256), 128 x 64 and 64 x 64 backward-weight tiles
 bool gemm_ring_supported(const GemmProb &p);
 int gemm_ring_blocks(int tile_rows, int M, int N);
 void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, int tile_rows, const ExtPtrs &ext, hipStream_t s);
-void launch_gemm_ring_dw(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, bool stream, const SlotGroup &grp,
-                         hipStream_t s);
+void launch_gemm_ring_dw(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
+                         const SlotGroup &grp, hipStream_t s);
 // Workgroups of a launch per output block shape.  Records with a shorter contraction than the launch's longest count
 // for the share of it that they have.
 struct GemmTileCounts {
@@ -248,6 +249,7 @@ struct GemmTileCounts {
 // kernel of a forward / backward-data launch: rows of a large tile (256, 128, 64), GEMM_RING + rows of a ring-buffered one (128, 64),
 // or 0 for the few-row kernel.  (*us: what gemm_big_split compares with)
 constexpr int GEMM_RING = 1024;
+int gemm_dw_small_tile(int k, const GemmTileCounts &c);      // the same for the weight gradients of all layers: 64 or a ring's
 int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool whole_chunks, float *us);
 // forward over slices of the contraction: slices (0: none; at most `most`), row stride of their fp32 sums [slices][M][ld], and the two launches
 int gemm_big_split(int M, int N, int K, int64_t most, float us);

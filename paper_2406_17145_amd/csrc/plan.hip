@@ -420,6 +420,7 @@ struct Emitter {
   int64_t part_need = 0, cnt_need = 0;  // split-K scratch high-water marks over all launches
   std::vector<LnProb> ln_fold_later;    // LayerNorm parameter folds of the whole backward pass (see backward())
   std::vector<GemmProb> dw_group;   // backward-weight records left to the launch over a group of slots
+  std::vector<GemmProb> dw_later;   // backward-weight records left to one launch at the end of their own backward pass
   std::vector<char> loss_fused;     // per node: this loss's gradient is written by the forward pass
   std::vector<int> head_loss;       // per LINEAR node: the loss that computes it (one-column head fused into its loss), or -1
   // Embedding bags next to dense branches: the gather (forward) and the sort + segment sums (backward) are long
@@ -989,9 +990,10 @@ struct Emitter {
     if (shrink_rows && col_tiles == 1 && row_tiles == 2 && count(2, 1) <= 256) row_tiles = 1;
   }
 
-  gpp_status_t run();
   void forward();
   void backward();
+  void emit_all_dw(std::vector<GemmProb> &recs, int passes);
+  bool weights_at_the_end() const;
 };
 
 // ---------------------------------------------------------------------------
@@ -1399,12 +1401,32 @@ void Emitter::forward() {
   }
 }
 
+// Weight gradients of a backward pass in one launch behind it instead of one launch (or a share of one) per level: from three
+// levels of them on, where that saves launches and the few tiles of a level no longer run by themselves (fifteen launches of
+// 10 us in three passes of a small recommendation stage: three of 12).  Below, a level's share of its backward-data launch
+// costs no launch at all.  Not where an operator inside a merge that is also added to something multiplies ITS slice of the shared
+// gradient by its derivative: the other operand of that addition reads the same memory as its own gradient.
+bool Emitter::weights_at_the_end() const {
+  const auto &N = pl.nodes;
+  int levels = 0;
+  for (auto &ids : pl.by_level) {
+    bool any = false;
+    for (int i : ids) {
+      if (N[i].d.kind == GPP_OP_CONCAT && N[i].gout_parent >= 0 && N[N[i].gout_parent].d.kind == GPP_OP_ADD) return false;
+      any = any || (N[i].d.kind == GPP_OP_LINEAR && N[i].d.param_dtype == GPP_BF16);
+    }
+    levels += any;
+  }
+  return levels >= 3 && !(pl.flags & 3);
+}
+
 // ---------------------------------------------------------------------------
 void Emitter::backward() {
   steps = &pl.bwd;
   steps->clear();
   auto &N = pl.nodes;
   const int n = (int)N.size();
+  const bool weights_last = weights_at_the_end();
   gstate.assign(n, G_EMPTY);
   gaddend.assign(n, Buf());
   dz_ready.assign(n, 0);
@@ -1551,12 +1573,14 @@ void Emitter::backward() {
                                         (w.in_dtype == DT_F32 && nd.gout.dtype == DT_F32));
           // grouped weight gradients: this record waits for the launch that contracts over every slot of
           // a group of backward passes (both operands sit at the same offsets in every slot)
-          const bool grouped = (pl.flags & 4) && !(pl.flags & 1) && w.in_dtype == DT_BF16 && gemm_big_supported(w) &&
-                               nd.gout.space == SP_SLOT && x.val.space == SP_SLOT;
-          if (grouped) fuse_db = d.has_bias;
+          const bool big = !(pl.flags & 1) && w.in_dtype == DT_BF16 && gemm_big_supported(w);
+          const bool grouped = (pl.flags & 4) && big && nd.gout.space == SP_SLOT && x.val.space == SP_SLOT;
+          const bool later = !(pl.flags & 4) && big && weights_last;
+          if (grouped || later) fuse_db = d.has_bias;
           if (fuse_db) w.bias = (const float *)d.grad[1];
           if (grouped) dw_group.push_back(w);
-          if (!grouped && d.has_bias && !fuse_db) {
+          if (later) dw_later.push_back(w);
+          if (!grouped && !later && d.has_bias && !fuse_db) {
             ColsumProb c;
             memset(&c, 0, sizeof(c));
             c.src = ptr(nd.gout);
@@ -1568,7 +1592,7 @@ void Emitter::backward() {
             colsums.push_back(c);
           }
           if (!grouped) {
-            gemms.push_back(w);
+            if (!later) gemms.push_back(w);
             pl.bwd_shared = true;   // accumulates into the parameter's gradient: backward passes stay in order
           }
           if (head_loss[i] >= 0) {
@@ -1900,35 +1924,52 @@ void Emitter::backward() {
     emit_elt(recs, EXT_GRAD_INPUTS, base);
   }
 
-  // the weight gradients left to the group launch: every layer of the stage in ONE launch (they depend
-  // on nothing but the stashed operands), tiles chosen as for any large-tile launch
+  emit_all_dw(dw_later, 1);
   steps = &pl.dwg;
   steps->clear();
-  if (!dw_group.empty()) {
-    // (one launch lets the co-resident tiles of all layers fill each other's tails)
-    int blocks = 0, tiles256 = 0, tiles128 = 0;
-    int64_t bytes = 0, steps256 = 0;
-    bool ring = true;
-    for (auto &r : dw_group) {
-      bytes += r.M * r.ldc * 4;
-      const int t = gemm_big_dw_tiles(256, r.M, r.N, nullptr);
-      tiles256 += t;
-      steps256 += (int64_t)t * r.K;
-      tiles128 += gemm_big_dw_tiles(64, r.M, r.N, nullptr);
-      ring = ring && gemm_ring_supported(r);
-    }
-    // (the mean over the tiles: the layers behind a pool have a handful of rows)
-    const int tile_rows = ring ? gemm_big_dw_tile(true, (int)(steps256 / tiles256), tiles256, tiles128) : 64;
-    for (auto &r : dw_group) {
-      r.blk_begin = blocks;
-      r.split_k = 1;
-      blocks += gemm_big_dw_tiles(tile_rows, r.M, r.N, &r.tiles_n);
-    }
-    Step &sg = add_step(K_GEMM_DW_GROUP, push_table(dw_group), (int)dw_group.size(), blocks);
-    sg.a0 = gemm_dw_group_streams(bytes) ? 1 : 0;
-    sg.a2 = tile_rows;
-  }
+  emit_all_dw(dw_group, pl.slots);
   steps = &pl.bwd;
+}
+
+// Weight gradients of every layer of the stage in ONE launch (they depend on nothing but the stashed operands and the complete
+// gradients): co-resident tiles of all layers fill each other's tails.  `passes`: backward passes that the contraction runs
+// over at the most, in the slots' order.
+void Emitter::emit_all_dw(std::vector<GemmProb> &recs, int passes) {
+  if (recs.empty()) return;
+  int tiles256 = 0, tiles128 = 0, max_k = 0;
+  int64_t bytes = 0, steps256 = 0;
+  bool ring = true;
+  GemmTileCounts c;
+  for (auto &r : recs) max_k = std::max(max_k, r.K);
+  for (auto &r : recs) {
+    bytes += r.M * r.ldc * 4;
+    const int t = gemm_big_dw_tiles(256, r.M, r.N, nullptr), m = gemm_big_dw_tiles(64, r.M, r.N, nullptr);
+    const float share = (float)r.K / (float)max_k;
+    tiles256 += t;
+    tiles128 += m;
+    steps256 += (int64_t)t * r.K;
+    c.t128 += share * (float)m;
+    c.t128x64 += share * (float)gemm_ring_blocks(128, r.M, r.N);
+    c.t64 += share * (float)gemm_ring_blocks(64, r.M, r.N);
+    ring = ring && gemm_ring_supported(r);
+  }
+  // (the mean contraction over the tiles: the layers behind a pool have a handful of rows; of one pass: eight passes of 64 rows
+  // on the large tiles, whose k-steps then change slots every other time, 43 us against 34)
+  int tile_rows = 64;
+  if (ring) {
+    tile_rows = gemm_big_dw_tile(true, (int)(steps256 / tiles256), tiles256, tiles128);
+    if (tile_rows == 64) tile_rows = gemm_dw_small_tile(passes * max_k, c);
+  }
+  int blocks = 0;
+  for (auto &r : recs) {
+    r.blk_begin = blocks;
+    r.split_k = 1;
+    blocks += tile_rows > GEMM_RING ? gemm_ring_blocks(tile_rows - GEMM_RING, r.M, r.N) : gemm_big_dw_tiles(tile_rows, r.M, r.N, &r.tiles_n);
+  }
+  Step &sg = add_step(K_GEMM_DW_GROUP, push_table(recs), (int)recs.size(), blocks);
+  sg.a0 = gemm_dw_group_streams(bytes) ? 1 : 0;
+
+  sg.a2 = tile_rows;
 }
 
 }  // namespace

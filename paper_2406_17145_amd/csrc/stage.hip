@@ -200,10 +200,10 @@ gpp_status_t gpp_stage_describe(const gpp_stage_desc_t *desc, char *text, size_t
       char line[160];
       int tile = 0, slices = 0;
       const int streams = sp.kern == K_GEMM_DW_GROUP && sp.a0;
-      if (sp.kern == K_GEMM_GENERIC || sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_DW_GROUP) tile = sp.a2;
+      if (sp.kern == K_GEMM_GENERIC || sp.kern == K_GEMM_MFMA || sp.kern == K_GEMM_BIG || sp.kern == K_GEMM_DW_GROUP) tile = sp.a2 & (GEMM_RING - 1);
       if (sp.kern == K_GEMM_SPLIT) slices = ((const GemmProb *)(pl.blob.data() + sp.table_off))->split_k;
       snprintf(line, sizeof(line), "%s %s records=%d blocks=%d tile=%d slices=%d streams=%d ring=%d\n", names[l], kTagNames[step_tag(sp, l == 1)],
-               sp.n, sp.blocks, tile, slices, streams, sp.kern == K_GEMM_RING ? sp.a2 : 0);
+               sp.n, sp.blocks, tile, slices, streams, sp.kern == K_GEMM_RING ? sp.a2 : (sp.kern == K_GEMM_DW_GROUP && sp.a2 > GEMM_RING ? tile : 0));
       out += line;
     }
   if (out.size() + 1 > capacity) return fail(GPP_ERR_INVALID_ARG, "text needs " + std::to_string(out.size() + 1) + " bytes");
@@ -491,8 +491,10 @@ static gpp_status_t run_steps(gpp_stage *st, const std::vector<Step> &steps, int
       case K_GEMM_BIG: launch_gemm_big((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a1, sp.a2, ext, s); break;
       case K_GEMM_DW_KSPLIT: launch_gemm_dw_ksplit((const GemmProb *)tab, sp.n, sp.blocks, accumulate, s); break;
       case K_GEMM_DW_GROUP:
-        if (!grp) return fail(GPP_ERR_UNSUPPORTED, "internal: group launch without a group");
-        launch_gemm_dw_group((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a2, sp.a0 != 0 || st->one_group, *grp, s);
+        if (!grp && !is_bwd) return fail(GPP_ERR_UNSUPPORTED, "internal: group launch without a group");
+        // (in the backward pass: that pass's own weight gradients, whose records hold its slot's addresses)
+        launch_gemm_dw_group((const GemmProb *)tab, sp.n, sp.blocks, accumulate, sp.a2, sp.a0 != 0 || (!is_bwd && st->one_group),
+                             is_bwd ? SlotGroup() : *grp, s);
         break;
       case K_GEMM_SPLIT: launch_gemm_split((const GemmProb *)tab, sp.blocks, sp.a1, sp.a2, s); break;
       case K_GEMM_SKINNY: launch_gemm_skinny((const GemmProb *)tab, sp.n, sp.blocks, sp.a1, sp.a2, sp.a0, sp.a3, ext, s); break;

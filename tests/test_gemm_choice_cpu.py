@@ -159,3 +159,24 @@ def test_fp32_launches_below_512_tiles_take_the_small_ones():
         return [p["tile"] for p in plan(layers(rows, k, n, dtype=W.F32), rows) if p["pass"] == which and p["kernel"].startswith("gemm")]
     assert of(64 * 511, 64, 64, "forward") == [32] and of(64 * 511 + 1, 64, 64, "forward") == [64]
     assert of(8, 64, 64, "backward") == [32] and of(1100, 1000, 2050, "backward") == [64]
+
+
+def test_weight_gradients_of_three_levels_wait_for_the_end_of_the_pass():
+    def weights(depth, flags=0, dtype=W.BF16, added=False):
+        g = W._Graph()
+        outs = []
+        for _ in range(2):
+            x = g.input(64, dtype)
+            for _ in range(depth):
+                x = g.linear(x, 64, 64, "relu", dtype)
+            outs.append(x)
+        y = g.add("concat", outs, out_features=128, dtype=dtype)
+        if added:      # the merge's gradient is also that of the other operand
+            y = g.add("add", (y, g.linear(g.input(128, dtype), 128, 128, "none", dtype)), out_features=128, dtype=dtype)
+        g.linear(y, 128, 64, "none", dtype)
+        steps = [p for p in plan(g.ops, 100, 1, flags) if p["pass"] == "backward"]
+        return [p["records"] for p in steps if p["kernel"] == "gemm_big_dw"], steps[-1]["kernel"]
+    assert weights(1) == ([], "gemm_bwd_merged_dx_dw")            # two levels: each rides along with backward-data
+    assert weights(2) == ([5], "gemm_big_dw") and weights(4)[0] == [9]
+    assert weights(2, B.FLAG_FORCE_GENERIC_GEMM)[0] == [] and weights(3, dtype=W.F32)[0] == []
+    assert weights(3, added=True)[0] == []

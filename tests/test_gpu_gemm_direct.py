@@ -60,3 +60,20 @@ def test_grouped_weight_gradients_on_256_x_128_tiles(rows, n_micro, slots):
     _, res, grads = _run(wl, slots, slots, False, flags=B.FLAG_GROUPED_DW)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="gemm_direct dw")
+
+
+# Weight gradients of three and more levels in one launch behind their own backward pass, stored by the first micro-batch and added
+# to by the others; on 64 x 64, 128 x 64 and 128 x 128 tiles, with matrices that end inside a tile and inside a chunk and rows that
+# end inside a k-step, of which there may be one.
+@pytest.mark.parametrize("rows,widths,branches,want", [
+    (1, (64, 64, 64, 64), 1, (64, 64)), (40, (72, 65, 129, 200), 2, (64, 64)), (300, (203, 333, 70, 129), 3, (64, 64)),
+    (700, (1000, 1000, 263, 520), 2, (128, 128)), (300, (520, 1000, 1003, 520), 4, (64, 0))])
+@pytest.mark.parametrize("slots,two_streams", [(1, False), (2, True)])
+def test_weight_gradients_behind_their_backward_pass(rows, widths, branches, want, slots, two_streams):
+    wl = _chain(rows, widths, ("gelu", "relu", "none"), branches, 3)
+    print(f"[case] weight gradients at the end rows={rows} widths={widths} slots={slots}", flush=True)
+    (step,) = [p for p in _plan(wl, slots, 0) if p["kernel"] in ("gemm_big_dw", "gemm_dw_ksplit", "gemm_bwd_merged_dx_dw")]
+    assert step["pass"] == "backward" and step["records"] == 3 * branches and (step["tile"], step["ring"]) == want
+    _, res, grads = _run(wl, slots, 1, two_streams, slots=slots)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="gemm_direct weights at the end")
