@@ -62,6 +62,8 @@ struct EltProb {
   int32_t src_dtype, dst_dtype, add_dtype;
   int32_t mode, act;
   int32_t ext_src, ext_dst;  // >= 0: pointer comes from the per-call pointer block instead
+  int32_t per_block;         // elements of a workgroup (elt_per_block of the launch's elements)
+  int32_t pieces;            // pieces of 16 bytes of a workgroup; 0: moved by elements
   int32_t blk_begin;
 };
 
@@ -279,7 +281,9 @@ int gemm_mfma_pick_split(int tile, int launch_tiles, int rows_in_tile, int K);
 bool gemm_mfma_supported(const GemmProb &p);
 
 void launch_elt(const EltProb *probs, int n, int total_blocks, const ExtPtrs &ext, hipStream_t s);
-int elt_blocks(int rows, int cols);
+int elt_per_block(int64_t launch_elements);
+int elt_blocks(int rows, int cols, int per_block);
+int elt_pieces_per_block(const EltProb &p);
 void launch_colsum(const ColsumProb *probs, int n, int total_blocks, int accumulate, hipStream_t s);
 int colsum_blocks(int cols);
 

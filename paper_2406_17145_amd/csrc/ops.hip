@@ -7,11 +7,12 @@
 namespace gpp {
 
 // ------------------------------------------------------------------ elt
+// Elements of a workgroup: 2048, so that the copies of a few hundred kilobytes reach all compute units, and four times that
+// in launches of many workgroups, whose threads then have four loads of 16 bytes in flight (7 x [512 x 4096] bf16: 36 us with
+// one load each, 17 with four).
 constexpr int ELT_PER_BLOCK = 2048;
-int elt_blocks(int rows, int cols) {
-  int64_t e = (int64_t)rows * cols;
-  return (int)((e + ELT_PER_BLOCK - 1) / ELT_PER_BLOCK);
-}
+int elt_per_block(int64_t launch_elements) { return launch_elements >= (int64_t)ELT_PER_BLOCK * 2048 ? 4 * ELT_PER_BLOCK : ELT_PER_BLOCK; }
+int elt_blocks(int rows, int cols, int per_block) { return (int)(((int64_t)rows * cols + per_block - 1) / per_block); }
 
 // Plain copy / conversion (no addend, no derivative) with the storage types as template parameters and
 // every load of a thread requested before its first store: a run-time type test or a bounds branch in
@@ -44,46 +45,74 @@ __device__ __forceinline__ void elt_copy_body(const EltProb &p, const void *src,
     }
 }
 
-// Same-type copy whose rows are whole 16-byte chunks (columns, leading dimensions and base addresses multiples
-// of 16 bytes): a thread moves 16 bytes per load instead of one element (the 16 MB input copy of the
-// transformer stage: 59 -> 13 us).  Same block -> element range as the element-wise body.
-template <int ES>
-__device__ __forceinline__ void elt_copy_vec_body(const EltProb &p, const void *src, void *dst, uint32_t base, uint32_t total) {
-  constexpr int EPC = 16 / ES, IT = ELT_PER_BLOCK / EPC / 256;
-  typedef __attribute__((ext_vector_type(4))) uint32_t u4;
-  u4 v[IT];
-  int64_t di[IT];
-#pragma unroll
-  for (int it = 0; it < IT; ++it) {
-    const uint32_t e = min(base + (it * 256 + threadIdx.x) * EPC, total - EPC);
-    const uint32_t r = e / (uint32_t)p.cols, c = e - r * (uint32_t)p.cols;
-    di[it] = ((int64_t)r * p.ld_dst + c) * ES;
-    v[it] = *(const u4 *)((const char *)src + ((int64_t)r * p.ld_src + c) * ES);
-  }
-#pragma unroll
-  for (int it = 0; it < IT; ++it)
-    if (base + (it * 256 + threadIdx.x) * EPC < total) *(u4 *)((char *)dst + di[it]) = v[it];
+// Rows in pieces of 16 bytes, whatever their alignment: same-type copies (MODE 0), dst *= derivative taken from src (MODE 1) and
+// dst = src * derivative taken from addend (MODE 2), both bf16.  The last piece of a row that is no whole number of them
+// starts where it ends with the row; MODE 0 and 2 write what it shares with the piece before twice, the same values, MODE 1 reads what it
+// writes and takes whole pieces only.  The pieces of a record are shared out evenly over its workgroups.  The device
+// reads and writes 16 bytes at any element address: [512 x 3820] bf16 rows, which start on 8 bytes, moved element by element with a
+// division for each took 9 us, whole pieces 5; the 16 MB input copy of the transformer stage 59 -> 9 us.
+typedef __attribute__((ext_vector_type(4))) uint32_t elt_u4;
+__device__ __forceinline__ elt_u4 elt_get16(const void *p) {
+  elt_u4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
 }
-__device__ __forceinline__ bool elt_vec_ok(const EltProb &p, const void *src, const void *dst, int es) {
-  const int epc = 16 / es;
-  return p.cols % epc == 0 && p.ld_src % epc == 0 && p.ld_dst % epc == 0 && (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
+__device__ __forceinline__ void elt_put16(void *p, elt_u4 v) { __builtin_memcpy(p, &v, 16); }
+__device__ __forceinline__ elt_u4 elt_times(elt_u4 g, elt_u4 d, int act) {
+  elt_u4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float lo = __uint_as_float(g[e] << 16) * act_grad(__uint_as_float(d[e] << 16), act);
+    const float hi = __uint_as_float(g[e] & 0xffff0000u) * act_grad(__uint_as_float(d[e] & 0xffff0000u), act);
+    o[e] = (uint32_t)f32_to_bf16_bits(lo) | ((uint32_t)f32_to_bf16_bits(hi) << 16);
+  }
+  return o;
+}
+template <int ES, int MODE, int U>
+__device__ __forceinline__ void elt_pieces(const EltProb &p, const void *src, void *dst, uint32_t first, uint32_t last, uint32_t per_row) {
+  constexpr int EPP = 16 / ES;
+  for (uint32_t c0 = first; c0 < last; c0 += 256 * U) {
+    elt_u4 v[U], m[U];
+    int64_t at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t c = min(c0 + u * 256 + threadIdx.x, last - 1), r = c / per_row;
+      const int64_t col = min((int)(c - r * per_row) * EPP, p.cols - EPP);
+      at[u] = ((int64_t)r * p.ld_dst + col) * ES;
+      v[u] = elt_get16((const char *)src + ((int64_t)r * p.ld_src + col) * ES);
+      if (MODE == 1) m[u] = elt_get16((const char *)dst + at[u]);
+      if (MODE == 2) m[u] = elt_get16((const char *)p.addend + ((int64_t)r * p.ld_add + col) * ES);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c0 + u * 256 + threadIdx.x < last)
+        elt_put16((char *)dst + at[u], MODE == 0 ? v[u] : (MODE == 1 ? elt_times(m[u], v[u], p.act) : elt_times(v[u], m[u], p.act)));
+  }
+}
+template <int ES, int MODE>
+__device__ __forceinline__ void elt_pieces_of_block(const EltProb &p, const void *src, void *dst) {
+  const uint32_t per_row = (uint32_t)(p.cols + 16 / ES - 1) / (16 / ES), total = (uint32_t)p.rows * per_row, share = (uint32_t)p.pieces;
+  const uint32_t first = (blockIdx.x - p.blk_begin) * share, last = min(first + share, total);
+  if (share <= 256) elt_pieces<ES, MODE, 1>(p, src, dst, first, last, per_row);
+  else elt_pieces<ES, MODE, 4>(p, src, dst, first, last, per_row);
+}
+// pieces of a workgroup, 0: the record is not moved in pieces
+int elt_pieces_per_block(const EltProb &p) {
+  if (p.src_dtype != p.dst_dtype || (int64_t)p.rows * p.cols >= (1ll << 31)) return 0;
+  const int epp = p.src_dtype == DT_BF16 ? 8 : 4;
+  if (p.cols < epp || (p.mode == 0 ? p.addend != nullptr : p.src_dtype != DT_BF16)) return 0;
+  if (p.mode == 1 ? p.cols % 8 != 0 : (p.mode == 2 && p.add_dtype != DT_BF16)) return 0;
+  const int64_t total = (int64_t)p.rows * ((p.cols + epp - 1) / epp), blocks = elt_blocks(p.rows, p.cols, p.per_block);
+  return (int)((total + blocks - 1) / blocks);
 }
 
-__global__ __launch_bounds__(256) void k_elt(const EltProb *__restrict__ probs, int n, ExtPtrs ext) {
-  const int pi = find_prob(probs, n, blockIdx.x);
-  const EltProb p = probs[pi];
-  const void *src = p.ext_src >= 0 ? ext.p[p.ext_src] : p.src;
-  void *dst = p.ext_dst >= 0 ? ext.p[p.ext_dst] : p.dst;
-  if (!src || !dst) return;
-  const int64_t total = (int64_t)p.rows * p.cols;
-  const int64_t base = (int64_t)(blockIdx.x - p.blk_begin) * ELT_PER_BLOCK;
+// what is not copied in pieces: conversions, additions, rows shorter than a piece; ELT_PER_BLOCK elements from `base` on
+__device__ __forceinline__ void elt_block(const EltProb &p, const void *src, void *dst, int64_t base, int64_t total) {
   const bool small = total < (1ll << 31) && (int64_t)p.rows * p.ld_dst < (1ll << 32);
   if (p.mode == 2 && small && p.src_dtype == DT_BF16 && p.dst_dtype == DT_BF16 && p.add_dtype == DT_BF16)
     return elt_copy_body<DT_BF16, DT_BF16, true>(p, src, dst, (uint32_t)base, (uint32_t)total);
   if (p.mode == 0 && !p.addend && p.src_dtype != DT_I32 && p.dst_dtype != DT_I32 && small) {
     const bool sb = p.src_dtype == DT_BF16, db = p.dst_dtype == DT_BF16;
-    if (sb && db && elt_vec_ok(p, src, dst, 2)) return elt_copy_vec_body<2>(p, src, dst, (uint32_t)base, (uint32_t)total);
-    if (!sb && !db && elt_vec_ok(p, src, dst, 4)) return elt_copy_vec_body<4>(p, src, dst, (uint32_t)base, (uint32_t)total);
     if (sb && db) return elt_copy_body<DT_BF16, DT_BF16>(p, src, dst, (uint32_t)base, (uint32_t)total);
     if (sb) return elt_copy_body<DT_BF16, DT_F32>(p, src, dst, (uint32_t)base, (uint32_t)total);
     if (db) return elt_copy_body<DT_F32, DT_BF16>(p, src, dst, (uint32_t)base, (uint32_t)total);
@@ -111,6 +140,22 @@ __global__ __launch_bounds__(256) void k_elt(const EltProb *__restrict__ probs, 
   }
 }
 
+__global__ __launch_bounds__(256) void k_elt(const EltProb *__restrict__ probs, int n, ExtPtrs ext) {
+  const int pi = find_prob(probs, n, blockIdx.x);
+  const EltProb p = probs[pi];
+  const void *src = p.ext_src >= 0 ? ext.p[p.ext_src] : p.src;
+  void *dst = p.ext_dst >= 0 ? ext.p[p.ext_dst] : p.dst;
+  if (!src || !dst) return;
+  if (p.pieces > 0) {
+    if (p.mode == 1) return elt_pieces_of_block<2, 1>(p, src, dst);
+    if (p.mode == 2) return elt_pieces_of_block<2, 2>(p, src, dst);
+    if (p.src_dtype == DT_BF16) return elt_pieces_of_block<2, 0>(p, src, dst);
+    return elt_pieces_of_block<4, 0>(p, src, dst);
+  }
+  const int64_t total = (int64_t)p.rows * p.cols;
+  const int64_t end = min(total, (int64_t)(blockIdx.x - p.blk_begin + 1) * p.per_block);
+  for (int64_t base = (int64_t)(blockIdx.x - p.blk_begin) * p.per_block; base < end; base += ELT_PER_BLOCK) elt_block(p, src, dst, base, total);
+}
 void launch_elt(const EltProb *probs, int n, int total_blocks, const ExtPtrs &ext, hipStream_t s) {
   if (total_blocks <= 0) return;
   hipLaunchKernelGGL(k_elt, dim3(total_blocks), dim3(256), 0, s, probs, n, ext);

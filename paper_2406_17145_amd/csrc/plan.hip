@@ -586,9 +586,13 @@ struct Emitter {
   void emit_elt(std::vector<EltProb> &recs, int ext_kind = EXT_NONE, int ext_base = 0) {
     if (recs.empty()) return;
     int blocks = 0;
+    int64_t elements = 0;
+    for (auto &e : recs) elements += (int64_t)e.rows * e.cols;
     for (auto &e : recs) {
       e.blk_begin = blocks;
-      blocks += elt_blocks(e.rows, e.cols);
+      e.per_block = elt_per_block(elements);
+      e.pieces = elt_pieces_per_block(e);
+      blocks += elt_blocks(e.rows, e.cols, e.per_block);
     }
     Step &s = add_step(K_ELT, push_table(recs), (int)recs.size(), blocks);
     s.ext_kind = ext_kind;

@@ -1,9 +1,11 @@
 """GEMM kernels that copy their operands straight into LDS, where the last tile, the last k-step or the last 16-byte chunk of a row
-is only partly inside the matrix."""
+is only partly inside the matrix; copies of rows in 16-byte pieces; what the launches around them leave to each other."""
+import numpy as np
 import pytest
 
 from paper_2406_17145_amd import binding as B
-from tests.parity_util import compare, run_gpu, run_oracle
+from paper_2406_17145_amd import workloads as W
+from tests.parity_util import compare, run_gpu, run_oracle, t2n
 from tests.test_gpu_gemm_tiles import _chain, _plan
 from tests.test_gpu_schedule import _run
 
@@ -77,3 +79,35 @@ def test_weight_gradients_behind_their_backward_pass(rows, widths, branches, wan
     _, res, grads = _run(wl, slots, 1, two_streams, slots=slots)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="gemm_direct weights at the end")
+
+
+# Copies in pieces of 16 bytes: rows of every length around a piece, which therefore start at every element address, into padded rows
+# and out of them; whole values, so nothing may differ.
+@pytest.mark.parametrize("dtype", [W.BF16, W.F32])
+@pytest.mark.parametrize("rows", [1, 3, 700])
+def test_copies_of_rows_at_every_alignment(dtype, rows):
+    widths = (1, 3, 4, 5, 7, 8, 9, 15, 16, 17, 63, 65, 1003)
+    g = W._Graph()
+    ends = [g.add("add", (g.input(w, dtype), g.input(w, dtype)), out_features=w, dtype=dtype) for w in widths]
+    g.linear(g.input(8, dtype), 8, 8, "none", dtype)
+    rng = np.random.Generator(np.random.PCG64(rows))
+    params = W._draw_params(g.ops, rng)
+    ins = {i: W.round_to_bf16(rng.standard_normal((rows, o["out_features"])).astype(np.float32)) for i, o in enumerate(g.ops) if o["kind"] == "input"}
+    st = B.Stage(g.ops, rows, params)
+    outs, gins = st.alloc_outputs(), st.alloc_grad_inputs()
+    gouts = [W.round_to_bf16(rng.standard_normal((rows, g.ops[i]["out_features"])).astype(np.float32)) for i in st.output_ids]
+    print(f"[case] copies dtype={dtype} rows={rows}", flush=True)
+    st.grad_reset()
+    st.forward(0, st.stage_inputs(ins), outs)
+    st.backward(0, [st.to_device(i, x) for i, x in zip(st.output_ids, gouts)], gins)
+    st.sync_status()
+    got_out = {i: t2n(t) for i, t in zip(st.output_ids, outs)}
+    got_gin = {i: t2n(t) for i, t in zip(st.input_ids, gins) if t is not None}
+    st.close()
+    gout = dict(zip(st.output_ids, gouts))
+    for e in ends:
+        a, b = g.ops[e]["inputs"]
+        want = ins[a] + ins[b]
+        assert np.array_equal(got_out[e], W.round_to_bf16(want) if dtype == W.BF16 else want), e
+        assert np.array_equal(got_gin[a], gout[e]) and np.array_equal(got_gin[b], gout[e]), e
+
