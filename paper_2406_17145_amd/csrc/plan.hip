@@ -341,10 +341,28 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
   fwd_scratch.space = slots == 1 && !(flags & 4) ? SP_SHARED : SP_SLOT;
   fwd_scratch.off = fwd_scratch.space == SP_SLOT ? slot_mark : shared_mark;
   fwd_scratch_bytes = (fwd_scratch.space == SP_SLOT ? slot_top : shared_top) - fwd_scratch.off;
+  // a merge of GELU layers stored in place, on 16 bytes each: their stashed derivatives are one matrix like their values, so the
+  // layer behind the merge multiplies all of them in the epilogue of its backward-data launch
+  for (int i = 0; i < n; ++i) {
+    Node &c = nodes[i];
+    if (c.d.kind != GPP_OP_CONCAT || c.d.dtype != DT_BF16 || c.users.size() != 1) continue;
+    bool all = true;
+    for (int m : c.in) {
+      const Node &mm = nodes[m];
+      all = all && mm.d.kind == GPP_OP_LINEAR && mm.d.act == GPP_ACT_GELU_ERF && mm.users.size() == 1 && mm.val_parent == i &&
+            mm.gout_parent == i && mm.fused_add < 0 && mm.val_col % 8 == 0;
+    }
+    if (!all) continue;
+    c.aux = alloc(SP_SLOT, c.rows, c.feat, c.d.dtype);
+    for (int m : c.in) {
+      nodes[m].aux = c.aux;
+      nodes[m].aux.off += nodes[m].val_col * esize(c.aux.dtype);
+    }
+  }
   for (int i = 0; i < n; ++i) {
     Node &nd = nodes[i];
     const gpp_op_desc_t &d = nd.d;
-    if (d.kind == GPP_OP_LINEAR && d.act == GPP_ACT_GELU_ERF) nd.aux = alloc(SP_SLOT, nd.rows, nd.feat, d.dtype);
+    if (d.kind == GPP_OP_LINEAR && d.act == GPP_ACT_GELU_ERF && !nd.aux.valid()) nd.aux = alloc(SP_SLOT, nd.rows, nd.feat, d.dtype);
     if (d.kind == GPP_OP_LAYERNORM) {
       nd.stat0 = alloc(SP_SLOT, 1, nd.rows, DT_F32);
       nd.stat1 = alloc(SP_SLOT, 1, nd.rows, DT_F32);
@@ -445,10 +463,15 @@ struct Emitter {
     else if (steps == &pl.bwd) pl.bwd_shared = true;
     return ws + pl.off_shared + b.off;
   }
-  // (not through ptr(): as shared memory it is used by a stage with one slot only, whose forward passes never overlap
+  // (these not through ptr(): as shared memory it is used by a stage with one slot only, whose forward passes never overlap
   // with anything)
-  char *forward_scratch() const {
-    const Buf &b = pl.fwd_scratch;
+  char *forward_scratch() const { return own_gradient(pl.fwd_scratch); }
+  // A forward launch may write the gradient of a loss, which depends on forward values alone, where the gradient buffers are the
+  // slot's own: per-slot ones, or those of the only slot, whose next forward pass is behind the backward pass that reads them.  The
+  // same numbers, one launch less in every backward pass.  (Not so the one-column heads, whose fused dot products add in another
+  // order: with one slot a stage's losses would not be bit by bit those of the same stage with two.)
+  bool own_gradients() const { return (pl.flags & 4) || pl.slots == 1; }
+  char *own_gradient(const Buf &b) const {
     return ws + (b.space == SP_SLOT ? pl.off_slots + (int64_t)slot * pl.slot_bytes : pl.off_shared) + b.off;
   }
   template <typename T>
@@ -1265,12 +1288,12 @@ void Emitter::forward() {
           l.cols = (int32_t)y.feat;
           l.kind = d.kind;
           l.scale = (float)d.loss_scale;
-          // per-slot gradient buffers (grouped weight gradients): an element-wise loss whose prediction
+          // gradient buffers of the slot's own (grouped weight gradients, or the only slot): an element-wise loss whose prediction
           // has no other consumer writes its gradient in the forward pass, one launch less per backward
           // (the softmax cross-entropy too, where its kernels keep a whole row of logits in registers)
-          if ((pl.flags & 4) && (d.kind != GPP_OP_LOSS_CE || y.feat <= loss_ce_row_limit()) && y.wants_grad && y.users.size() == 1 &&
-              y.gout_parent < 0 && y.fused_add < 0 && y.gout.space == SP_SLOT) {
-            l.dy = ptr(y.gout);
+          if (own_gradients() && (d.kind != GPP_OP_LOSS_CE || y.feat <= loss_ce_row_limit()) && y.wants_grad && y.users.size() == 1 &&
+              y.gout_parent < 0 && y.fused_add < 0 && y.gout.valid()) {
+            l.dy = own_gradient(y.gout);
             l.ld_dy = y.gout.ld;
             l.dy_dtype = y.gout.dtype;
             loss_fused[i] = 1;
@@ -1639,11 +1662,14 @@ void Emitter::backward() {
             }
             // a concat of ReLU layers written in place: the members' activation derivative is one mask
             // over the whole merge buffer (the sign of the stored outputs), applied in this epilogue
-            if (x.d.kind == GPP_OP_CONCAT && x.users.size() == 1 && concat_relu_members(nd.in[0])) {
-              g.act = ACT_RELU;
-              g.aux = ptr(x.val);
-              g.ldaux = x.val.ld;
-              g.aux_dtype = x.val.dtype;
+            // (of GELU layers: their derivatives in one matrix)
+            const bool relu_merge = x.d.kind == GPP_OP_CONCAT && x.users.size() == 1 && concat_relu_members(nd.in[0]);
+            if (relu_merge || (x.d.kind == GPP_OP_CONCAT && x.aux.valid())) {
+              const Buf &ms = relu_merge ? x.val : x.aux;
+              g.act = relu_merge ? ACT_RELU : ACT_GELU;
+              g.aux = ptr(ms);
+              g.ldaux = ms.ld;
+              g.aux_dtype = ms.dtype;
               for (int m : x.in) dz_ready[m] = 1;
             }
             // fold the producer's activation derivative into this epilogue when we are its only consumer

@@ -111,3 +111,28 @@ def test_copies_of_rows_at_every_alignment(dtype, rows):
         assert np.array_equal(got_out[e], W.round_to_bf16(want) if dtype == W.BF16 else want), e
         assert np.array_equal(got_gin[a], gout[e]) and np.array_equal(got_gin[b], gout[e]), e
 
+
+# Activations in front of a merge: all of them GELU on 16 bytes (their derivatives are one matrix), one off 16 bytes, of mixed kinds,
+# and a merge that two operators read.
+@pytest.mark.parametrize("kind", ["gelu", "off", "mixed", "two_readers", "output"])
+@pytest.mark.parametrize("slots,flags", [(1, 0), (2, B.FLAG_GROUPED_DW)])
+def test_merged_activations(kind, slots, flags):
+    rows, widths = 90, (40, 77, 64) if kind == "off" else (40, 72, 64)
+    g = W._Graph()
+    outs = [g.linear(g.input(50, W.BF16), 50, w, "relu" if kind == "mixed" and w == 72 else "gelu", W.BF16) for w in widths]
+    total = sum(widths)
+    y = g.add("concat", outs, out_features=total, dtype=W.BF16)
+    z = g.linear(y, total, 48, "gelu", W.BF16)
+    if kind == "two_readers":
+        z = g.add("concat", (z, g.linear(y, total, 24, "gelu", W.BF16)), out_features=72, dtype=W.BF16)
+    n = 72 if kind == "two_readers" else 48
+    if kind != "output":
+        g.add("loss_mse", (z, g.input(n, W.F32, role="target")), loss_scale=1.0 / (rows * 2 * n))
+    rng = np.random.Generator(np.random.PCG64(len(kind)))
+    params = W._draw_params(g.ops, rng)
+    wl = W.Workload("merged_activations", g.ops, rows, 2, params, W._draw_batches(g.ops, rows, 2, rng, {}), 2e-2)
+    gouts = [{z: W.round_to_bf16(rng.standard_normal((rows, n)).astype(np.float32))} for _ in range(2)] if kind == "output" else None
+    print(f"[case] merged activations {kind} slots={slots} flags={flags}", flush=True)
+    _, res, grads = _run(wl, slots, slots if flags else 1, False, slots=slots, flags=flags, gouts=gouts)
+    stage, ref = run_oracle(wl, gouts)
+    compare(wl, res, grads, stage, ref, label=f"merged activations {kind}")
