@@ -80,6 +80,12 @@ __device__ __forceinline__ float act_grad(float src, int32_t act) {
   return src;
 }
 
+// backward-data epilogue: product times the derivative factor from the mask source
+__device__ __forceinline__ float grad_times(float v, float src, int32_t act) {
+  if (act == ACT_GELU_MERGED) v = bf16_bits_to_f32(f32_to_bf16_bits(v));
+  return v * act_grad(src, act);
+}
+
 // Wave-wide sum / maximum, the same value in every lane, in a fixed order.  Inside a row of 16 lanes the partner
 // values come through the DPP operand path (quad permutations, then the half-row and row mirrors: after each step
 // the lanes of a growing group hold that group's total); the four row totals are read out as scalars and combined.

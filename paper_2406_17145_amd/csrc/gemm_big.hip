@@ -530,7 +530,7 @@ bool gemm_big_supported(const GemmProb &p) {
 //                                                                   forward 14.4 with 64 x 64 (128 x 64: 18.2, 0: 22.4)
 //   0:         few tiles and a long contraction, whose chain it cuts to an eighth.     [300 x 1000 x 4096] 15.1 (ring 19.5)
 // 384 rows (7 x [384 x 4096 x 4096]): 256 106, 128 135, 64 116, 0 218.
-// `whole_chunks`: every contraction length is a multiple of 8.
+// `whole_chunks`: every contraction length is a multiple of 8; `large_tiles`, `ring`: those kernels are choices.
 // Behind a short contraction the estimate of the 256 x 256 tiles is too low (their prologue and epilogue are all that such a
 // launch is), so there they are left out unless the launch is whole rounds of them, or in forward from K 768 on at least half
 // of its last one.  us with 256 / 64, forward from K 1024 down, backward-data from K 256 down:
@@ -544,7 +544,7 @@ bool gemm_big_supported(const GemmProb &p) {
 // contractions, which the fit has none of, by 20 %; the few-row kernel is credited 5 %, and 15 % where it has fewer tiles than
 // compute units behind at least 30 k-steps (over 1342 launches: 17 % faster than with the large tiles and the few-row kernel
 // alone, 1.1 % of them more than 3 % slower).
-int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool whole_chunks, float *us) {
+int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool large_tiles, bool whole_chunks, float *us) {
   constexpr float CUS = 256.0f;
   const float nk = (float)cdiv(max_k, GB_BK);
   const bool fwd = form == FORM_FWD;
@@ -578,11 +578,11 @@ int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bo
       rows = r;
     }
   };
-  take(64, mid(c.t128), 1.0f);
+  if (large_tiles) take(64, mid(c.t128), 1.0f);
   const float rest256 = c.t256 / CUS - floorf(c.t256 / CUS);
   const bool whole_rounds = c.t256 >= CUS && (rest256 < 0.01f || (fwd && max_k >= 768 && rest256 >= 0.5f));
-  if (whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256), 1.0f);
-  if (whole_chunks && (fwd || max_k >= 768)) take(128, rounds(c.t128x256, t128), 1.0f);
+  if (large_tiles && whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256), 1.0f);
+  if (large_tiles && whole_chunks && (fwd || max_k >= 768)) take(128, rounds(c.t128x256, t128), 1.0f);
   const float large = best, r128 = fwd ? shared(c.t128x64, 2.14f, 0.18f, 1.36f, 0.181f, 2.0f, 0.138f) : shared(c.t128x64, 2.04f, 0.179f, 1.27f, 0.219f, 1.16f, 0.104f);
   const float r64 = fwd ? shared(c.t64, 2.51f, 0.153f, 0.64f, 0.122f, 0.95f, 0.092f) : shared(c.t64, 2.35f, 0.134f, 0.63f, 0.155f, 0.62f, 0.074f);
   if (ring && fminf(r128, r64) < (whole_chunks ? 0.92f : 0.8f) * large) {
@@ -594,7 +594,9 @@ int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bo
     // (for slices of a contraction, of 64 k-steps and more, which the fit does not reach: the few-row kernel's own line there)
     *us = fminf(*us, 0.9f * (3.0f + fmaxf(1.0f, c.t64 / CUS) * (3.2f + 0.30f * nk)));
     const float t = fwd ? shared(c.few, 1.06f, 0.028f, 2.06f, 0.184f, 3.45f, 0.109f) : shared(c.few, 1.18f, 0.032f, 1.63f, 0.179f, 2.55f, 0.134f);
-    take(0, t, nk >= 30.0f && c.t64 <= CUS ? 0.85f : 0.95f);
+    // (against the ring alone, for launches that share the GPU with another stream's, the other way round: [4 x 64 x 1000 x 4000] is
+    // 15 us on 128 workgroups and 19 on 64 of the ring, but a step of two such streams 190 and 179)
+    take(0, t, !large_tiles ? 1.15f : nk >= 30.0f && c.t64 <= CUS ? 0.85f : 0.95f);
   }
   return rows;
 }

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_generic_small(const GemmProb *_
       store_from_f32(p.C, p.c_dtype, ci, v);
     } else if (p.form == FORM_DX) {
       v += res[e];
-      if (p.act != ACT_NONE) v *= act_grad(aux[e], p.act);
+      if (p.act != ACT_NONE) v = grad_times(v, aux[e], p.act);
       store_from_f32(p.C, p.c_dtype, ci, v);
     } else {
       ((float *)p.C)[ci] = old[e] + v;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256, BIAS ? 8 : 1) void k_gemm_generic(const GemmPr
         store_from_f32(p.C, p.c_dtype, ci, v);
       } else if (p.form == FORM_DX) {
         if (p.res) v += load_as_f32(p.res, p.res_dtype, (int64_t)row * p.ldres + col);
-        if (p.act != ACT_NONE) v *= act_grad(load_as_f32(p.aux, p.aux_dtype, (int64_t)row * p.ldaux + col), p.act);
+        if (p.act != ACT_NONE) v = grad_times(v, load_as_f32(p.aux, p.aux_dtype, (int64_t)row * p.ldaux + col), p.act);
         store_from_f32(p.C, p.c_dtype, ci, v);
       } else {
         float *c = (float *)p.C;

@@ -28,7 +28,7 @@ struct RingCfg {
   static_assert(ELEMS * 2 <= 160 * 1024, "the buffers do not fit the LDS");
 };
 
-// Order of the sums: one chain per output over the whole contraction, as in the large-tile kernels.
+// Order of the sums: the large tiles' one chain per output over the whole contraction, the small tiles' two, added at the end.
 template <int FORM, int WGM, int WGN, int TM, int TN, int BUFS, int BK, bool STREAM = false>
 __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uint16_t *lds, int accumulate_dw, const ExtPtrs &ext,
                                           const SlotGroup &grp) {
@@ -39,13 +39,18 @@ __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uin
   const int wi0 = (wave / WGN) * (32 * TM), wj0 = (wave % WGN) * (32 * TN);
   rsrc4 rs_a = matrix_rsrc4(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);
   rsrc4 rs_b = matrix_rsrc4(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
-  f32x16 acc[TM][TN];
+  // (a wave with one MFMA tile sums even and odd 16-wide chunks apart: its MFMAs are two chains instead of one)
+  constexpr int CHAINS = TM * TN == 1 ? 2 : 1;
+  f32x16 acc_of[CHAINS][TM][TN];
+  f32x16 (&acc)[TM][TN] = acc_of[0];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int q = 0; q < CHAINS; ++q)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc_of[q][i][j][r] = 0.0f;
   auto da = [&](int b) { return lds + b * C::A_ELEMS; };
   auto db = [&](int b) { return lds + BUFS * C::A_ELEMS + b * C::B_ELEMS; };
   const uint32_t lds0 = lds_address(lds);
@@ -126,7 +131,10 @@ __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uin
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c & 1][i], b[c & 1][j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j) {
+          f32x16 &sum = acc_of[c % CHAINS][i][j];
+          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c & 1][i], b[c & 1][j], sum, 0, 0, 0);
+        }
       if (!TAIL && TM * TN > 1) big_mix<TM * TN, (A_TR ? 2 : 1) * TM + (B_TR ? 2 : 1) * TN>();
     }
   };
@@ -147,6 +155,7 @@ __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uin
     copies_landed_barrier<(BUFS - 2) * C::COPIES>();
     multiply(cur, whole * BK, std::true_type());
   }
+  if constexpr (CHAINS == 2) acc[0][0] += acc_of[1][0][0];
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies of the k-steps beyond the end
   __syncthreads();                                   // the epilogue reuses the operand LDS
 
@@ -177,14 +186,35 @@ __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uin
   }
 }
 
+// A group launch covers the same problems for several micro-batches: the records are member 0's, the members are further row blocks
+// of every column block (whose weight tile they then share in one L2), and everything of a member that lives in a stash slot
+// lies `stride` bytes, its per-call pointers `ext_stride` entries behind the previous member's.
 template <int FORM, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN, WGM == 4 ? 4 : 3) void k_gemm_ring(const GemmProb *__restrict__ probs, int n, int total_blocks,
-                                                                               ExtPtrs ext) {
+                                                                               ExtPtrs ext, MemberGroup group) {
   typedef RingCfg<FORM, WGM, WGN, 1, 1, 3, GB_BK> C;
   __shared__ __attribute__((aligned(16))) uint16_t lds[C::ELEMS];
-  const BigTile t = big_locate<C::BM, C::BN>(probs, n, total_blocks);
-  const GemmProb p = probs[t.pi];
-  ring_body<FORM, WGM, WGN, 1, 1, 3, GB_BK>(p, t.m0, t.n0, lds, 0, ext, SlotGroup());
+  const int bid = big_spread(total_blocks);
+  int lo = 0, hi = n - 1;         // (every record's workgroup range is `members` times the one in its table)
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (probs[mid].blk_begin * group.members <= bid) lo = mid;
+    else hi = mid - 1;
+  }
+  GemmProb p = probs[lo];
+  const int tile = bid - p.blk_begin * group.members, tiles_m = cdiv(p.M, C::BM), row_blocks = tiles_m * group.members;
+  int mt = tile % row_blocks;
+  if (group.members > 1) {
+    const int member = mt / tiles_m;
+    mt -= member * tiles_m;
+    const int64_t off = (int64_t)member * group.stride;
+    p.A = (const GPP_G char *)p.A + off;
+    if (p.C) p.C = (GPP_G char *)p.C + off;
+    if (p.aux) p.aux = (GPP_G char *)p.aux + off;
+    if (p.res) p.res = (const GPP_G char *)p.res + off;
+    if (p.c_ext > 0) p.c_ext += member * group.ext_stride;
+  }
+  ring_body<FORM, WGM, WGN, 1, 1, 3, GB_BK>(p, mt * C::BM, (tile / row_blocks) * C::BN, lds, 0, ext, SlotGroup());
 }
 
 // (ADD, gradients are added to, at compile time: the other epilogue is not in the kernel)
@@ -207,15 +237,17 @@ bool gemm_ring_supported(const GemmProb &p) {
   return (a_rows + 512) * p.lda * 2 < 0xffffff00ll && (b_rows + 512) * p.ldb * 2 < 0xffffff00ll;
 }
 int gemm_ring_blocks(int tile_rows, int M, int N) { return cdiv(M, tile_rows) * cdiv(N, 64); }
-void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, int tile_rows, const ExtPtrs &ext, hipStream_t s) {
+void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, int tile_rows, const ExtPtrs &ext, hipStream_t s,
+                      const MemberGroup &group) {
+  total_blocks *= group.members;
   if (total_blocks <= 0) return;
   const dim3 g(total_blocks), b(tile_rows == 128 ? 512 : 256);
   if (form == FORM_FWD) {
-    if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_ring<FORM_FWD, 4, 2>), g, b, 0, s, probs, n, total_blocks, ext);
-    else hipLaunchKernelGGL((k_gemm_ring<FORM_FWD, 2, 2>), g, b, 0, s, probs, n, total_blocks, ext);
+    if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_ring<FORM_FWD, 4, 2>), g, b, 0, s, probs, n, total_blocks, ext, group);
+    else hipLaunchKernelGGL((k_gemm_ring<FORM_FWD, 2, 2>), g, b, 0, s, probs, n, total_blocks, ext, group);
   } else {
-    if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_ring<FORM_DX, 4, 2>), g, b, 0, s, probs, n, total_blocks, ext);
-    else hipLaunchKernelGGL((k_gemm_ring<FORM_DX, 2, 2>), g, b, 0, s, probs, n, total_blocks, ext);
+    if (tile_rows == 128) hipLaunchKernelGGL((k_gemm_ring<FORM_DX, 4, 2>), g, b, 0, s, probs, n, total_blocks, ext, group);
+    else hipLaunchKernelGGL((k_gemm_ring<FORM_DX, 2, 2>), g, b, 0, s, probs, n, total_blocks, ext, group);
   }
 }
 template <bool STREAM, bool ADD>

@@ -332,7 +332,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmProb &pin, int local,
           if (p.res) v[e] += rs[e];
         } else {
           if (p.res) v[e] += rs[e];
-          if (use_aux_in) v[e] *= act_grad(ax[e], p.act);
+          if (use_aux_in) v[e] = grad_times(v[e], ax[e], p.act);
         }
       }
       u32x4 out;
@@ -365,7 +365,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmProb &pin, int local,
         if (p.res) v += load_as_f32(p.res, p.res_dtype, (int64_t)row * p.ldres + col);
       } else {
         if (p.res) v += load_as_f32(p.res, p.res_dtype, (int64_t)row * p.ldres + col);
-        if (p.act != ACT_NONE) v *= act_grad(load_as_f32(p.aux, p.aux_dtype, (int64_t)row * p.ldaux + col), p.act);
+        if (p.act != ACT_NONE) v = grad_times(v, load_as_f32(p.aux, p.aux_dtype, (int64_t)row * p.ldaux + col), p.act);
       }
       store_from_f32(Cout, p.c_dtype, ci, v);
     }

@@ -251,7 +251,7 @@ __device__ __forceinline__ void epi_finish(const GemmProb &p, void *Cout, const 
       for (int r = 0; r < 16; ++r) v[r] = in.a[r] > 0.0f ? v[r] : 0.0f;
     } else {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) v[r] *= in.a[r];   // stashed derivative
+      for (int r = 0; r < 16; ++r) v[r] = grad_times(v[r], in.a[r], p.act);   // stashed derivative
     }
   }
   if (FORM == FORM_DW) {
@@ -465,7 +465,7 @@ __device__ __forceinline__ void epilogue_wave_lds(const GemmProb &p, void *Cout,
               for (int e = 0; e < 8; ++e) v[e] = ax[e] > 0.0f ? v[e] : 0.0f;
             } else {
 #pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] *= ax[e];
+              for (int e = 0; e < 8; ++e) v[e] = grad_times(v[e], ax[e], p.act);
             }
           }
         }

@@ -22,7 +22,9 @@ enum : int32_t { DT_F32 = 0, DT_BF16 = 1, DT_I32 = 2 };
 #else
 #define GPP_G
 #endif
-enum : int32_t { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2 };
+// ACT_GELU_MERGED (backward-data): the stashed derivatives of several merged layers; the product is rounded to the storage type before
+// it is multiplied, as it is where a launch of its own multiplies the merged gradient
+enum : int32_t { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2, ACT_GELU_MERGED = 3 };
 enum : int32_t { FORM_FWD = 0, FORM_DX = 1, FORM_DW = 2 };
 
 // ---- grouped GEMM -----------------------------------------------------
@@ -239,7 +241,14 @@ int gemm_big_dw_tiles(int tile_rows, int M, int N, int *tiles_n);
 // 256 x 128 (tile_rows 256), 128 x 64 and 64 x 64 backward-weight tiles
 bool gemm_ring_supported(const GemmProb &p);
 int gemm_ring_blocks(int tile_rows, int M, int N);
-void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, int tile_rows, const ExtPtrs &ext, hipStream_t s);
+// micro-batches of a group launch (1: none): slot memory of the next one `stride` bytes, its per-call pointers `ext_stride` entries on
+struct MemberGroup {
+  int32_t members = 1, ext_stride = 0;
+  int64_t stride = 0;
+};
+// (total_blocks counts one member)
+void launch_gemm_ring(const GemmProb *probs, int n, int total_blocks, int form, int tile_rows, const ExtPtrs &ext, hipStream_t s,
+                      const MemberGroup &group = MemberGroup());
 void launch_gemm_ring_dw(const GemmProb *probs, int n, int total_blocks, int accumulate_dw, int tile_rows, bool stream,
                          const SlotGroup &grp, hipStream_t s);
 // Workgroups of a launch per output block shape.  Records with a shorter contraction than the launch's longest count
@@ -252,7 +261,7 @@ struct GemmTileCounts {
 // or 0 for the few-row kernel.  (*us: what gemm_big_split compares with)
 constexpr int GEMM_RING = 1024;
 int gemm_dw_small_tile(int k, const GemmTileCounts &c);      // the same for the weight gradients of all layers: 64 or a ring's
-int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool whole_chunks, float *us);
+int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool large_tiles, bool whole_chunks, float *us);
 // forward over slices of the contraction: slices (0: none; at most `most`), row stride of their fp32 sums [slices][M][ld], and the two launches
 int gemm_big_split(int M, int N, int K, int64_t most, float us);
 inline __host__ __device__ int64_t split_sum_ld(int N) { return (N + 63) / 64 * 64; }

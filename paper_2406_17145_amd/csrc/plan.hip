@@ -951,9 +951,10 @@ struct Emitter {
     return row_tiles == 0 && !(pl.flags & 2) && elems < (int64_t)128 * 128 * 256 ? 2 : row_tiles;
   }
   // Kernel of a forward / backward-data launch as gemm_tile_choice names it, 0 for the kernel above or, where that is
-  // not meant for the launch either, the small tiles.  Up to 64 rows a tile would be half padding.  Where launches
-  // share the GPU (flag bit 4) the few-row kernel stays wherever it is meant to run: its workgroups fit beside those of
-  // another stream, and group launches, which give the same results bit by bit as single ones, know no other kernel.
+  // not meant for the launch either, the small tiles.  Up to 64 rows a large tile would be half padding.  Where launches
+  // share the GPU (flag bit 4) that kernel's meant launches take small workgroups, which fit beside those of another stream.  Group
+  // launches know the few-row kernel and the ring-buffered tiles, and give the same results bit by bit as single ones: the choice is
+  // the one of a single micro-batch's launch.
   // `ring`: the ring-buffered tiles are a choice.
   // *slices: > 1 when a lone forward record had better be summed over that many slices of its contraction (no more than
   // have their sums in the memory that a forward pass may overwrite: a stage needs no workspace for them).
@@ -973,7 +974,9 @@ struct Emitter {
     // nothing but its result (4 x [40000 x 64 x K] on 64 x 64 / 128 x 128 tiles: K 64 47 / 52 us, 128 59 / 61, 200 89 / 89,
     // 512 159 / 137)
     if (form == FORM_FWD && few == 0 && max_n <= 64 && max_k <= 128) return 0;
-    if (few > 0 && (max_m <= 64 || (pl.flags & 16) || pl.group_lanes > 0)) return 0;
+    const bool shared = few > 0 && (pl.flags & 16);
+    if (few > 0 && !shared && pl.group_lanes > 0 && max_m > 64) return 0;
+    if (shared && (!ring || max_k > 8192)) return 0;
     GemmTileCounts c;
     auto tiles = [](const GemmProb &r, int bm, int bn) { return (float)(((r.M + bm - 1) / bm) * ((r.N + bn - 1) / bn)); };
     int row_tiles = few, col_tiles = 2;
@@ -987,8 +990,20 @@ struct Emitter {
       c.t64 += share * tiles(r, 64, 64);
       if (few > 0) c.few += share * tiles(r, 32 * row_tiles, 32 * col_tiles);
     }
+    // Up to 64 rows the ring takes launches whose 64 x 64 tiles fill half of the compute units (up to 32 rows, where half of a tile is
+    // padding, nearly all of them), which the few-row kernel covers with more than one round of workgroups, unless a long
+    // contraction pays for those.  us few-row / ring, forward and backward-data:
+    // 4 x [64 x 2048 x K]: K 512 8.8 / 6.3, 8.3 / 5.9, 1000 12.2 / 10.1, 13.2 / 9.6, 4096 27.6 / 29.3, 36.0 / 29.5;
+    // 7 x [32 x 4096 x 2048] 34.8 / 32.2, 32.3 / 30.6;  4 x [64 x 1000 x 1000] 7.0 / 8.2, 6.3 / 7.4.
+    // Backward-data that shares the GPU takes it always (two streams of four micro-batches of [4 x 64 x 1000 x 1000] a launch:
+    // 13.5 -> 8.8 us); forward there keeps the few-row kernel's eight short chains per sum (12.7 -> 10.2 us with the ring, but ReLU
+    // masks that hang on a last bit fall otherwise than in the runs that share nothing).
+    if (few > 0 && max_m <= 64) {
+      const bool fills = c.t64 >= (max_m > 32 ? 128.0f : 224.0f) && (form == FORM_DX || max_k <= 2048 || c.t64 >= 256.0f);
+      return ring && (fills || (shared && form == FORM_DX)) ? GEMM_RING + 64 : 0;
+    }
     float us = 0.0f;
-    const int choice = gemm_tile_choice(form, max_k, c, ring, whole, &us);
+    const int choice = gemm_tile_choice(form, max_k, c, ring, !shared, whole, &us);
     if (slices && whole && form == FORM_FWD && g.size() == 1 && !(pl.flags & 16))
       *slices = gemm_big_split(g[0].M, g[0].N, g[0].K, pl.fwd_scratch_bytes / (g[0].M * split_sum_ld(g[0].N) * 4), us);
     return choice;
@@ -1666,7 +1681,7 @@ void Emitter::backward() {
             const bool relu_merge = x.d.kind == GPP_OP_CONCAT && x.users.size() == 1 && concat_relu_members(nd.in[0]);
             if (relu_merge || (x.d.kind == GPP_OP_CONCAT && x.aux.valid())) {
               const Buf &ms = relu_merge ? x.val : x.aux;
-              g.act = relu_merge ? ACT_RELU : ACT_GELU;
+              g.act = relu_merge ? ACT_RELU : ACT_GELU_MERGED;
               g.aux = ptr(ms);
               g.ldaux = ms.ld;
               g.aux_dtype = ms.dtype;

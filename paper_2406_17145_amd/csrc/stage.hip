@@ -129,7 +129,7 @@ static const char *const kTagNames[GPP_PROFILE_TAGS] = {
 // other).  Possible where every step is one of the kinds below, runs on the caller's stream, touches slot
 // memory only, and the per-call pointers of all members fit one pointer block.
 static size_t group_record_bytes(int kern) {
-  return kern == K_ELT ? sizeof(EltProb) : kern == K_GEMM_SKINNY ? sizeof(GemmProb) : kern == K_HEAD_LOSS ? sizeof(HeadProb) : 0;
+  return kern == K_ELT ? sizeof(EltProb) : kern == K_GEMM_SKINNY || kern == K_GEMM_RING ? sizeof(GemmProb) : kern == K_HEAD_LOSS ? sizeof(HeadProb) : 0;
 }
 // (the loss sum has no records: one small launch per member adds that member's partial losses)
 static bool group_form(const Step &sp) { return group_record_bytes(sp.kern) != 0 || sp.kern == K_LOSS_SUM; }
@@ -291,7 +291,7 @@ static gpp_status_t stage_create(const gpp_stage_desc_t *desc, void *workspace, 
             uint8_t *dst = gb.data() + (size_t)G * sp.table_off + (size_t)i * sp.n * rec;
             // (few-row GEMM steps need no copy: their group launch reads the first slot's records and reaches the
             // other members by the slot stride, see run_steps_group)
-            if (sp.n <= 0 || rec == 0 || sp.kern == K_GEMM_SKINNY) continue;
+            if (sp.n <= 0 || rec == 0 || sp.kern == K_GEMM_SKINNY || sp.kern == K_GEMM_RING) continue;
             memcpy(dst, src.data() + sp.table_off, (size_t)sp.n * rec);
             const int ext_total = sp.ext_kind == EXT_NONE ? 0
                                   : ((sp.ext_kind == EXT_INPUTS || sp.ext_kind == EXT_GRAD_INPUTS) ? (int)pl.input_ops.size()
@@ -617,6 +617,7 @@ static gpp_status_t run_steps_group(gpp_stage *st, const std::vector<Step> &step
     for (int rep = 0; rep < reps; ++rep)
     switch (sp.kern) {
       case K_ELT: launch_elt((const EltProb *)tab, m * sp.n, m * sp.blocks, ext, s); break;
+      case K_GEMM_RING:
       case K_GEMM_SKINNY: {
         // the records of the lane's first slot; the other members are that many further row blocks, their slot
         // memory L slots further each (the weight tile of a column block then serves all members from one L2)
@@ -624,8 +625,11 @@ static gpp_status_t run_steps_group(gpp_stage *st, const std::vector<Step> &step
         const int ext_total = sp.ext_kind == EXT_NONE ? 0
                               : ((sp.ext_kind == EXT_INPUTS || sp.ext_kind == EXT_GRAD_INPUTS) ? (int)pl.input_ops.size()
                                                                                                : (int)pl.output_ops.size());
-        launch_gemm_skinny((const GemmProb *)tab0, sp.n, sp.blocks, sp.a1, sp.a2, sp.a0, sp.a3, ext, s, m,
-                           (int64_t)pl.group_lanes * pl.slot_bytes, ext_total);
+        if (sp.kern == K_GEMM_RING)
+          launch_gemm_ring((const GemmProb *)tab0, sp.n, sp.blocks, sp.a1, sp.a2, ext, s, MemberGroup{m, ext_total, (int64_t)pl.group_lanes * pl.slot_bytes});
+        else
+          launch_gemm_skinny((const GemmProb *)tab0, sp.n, sp.blocks, sp.a1, sp.a2, sp.a0, sp.a3, ext, s, m,
+                             (int64_t)pl.group_lanes * pl.slot_bytes, ext_total);
         break;
       }
       case K_HEAD_LOSS: {
