@@ -12,6 +12,8 @@ int attn_max_seq();
 int attn_mfma_blocks(int batch, int heads, int seq);
 bool attn_mfma_supported(const AttnProb &p);
 size_t interact_lds_bytes(int F, int d);
+bool interact_mfma_ok(const InteractProb &p, bool backward);
+int interact_mfma_blocks(int batch);
 
 static int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 static int64_t ld_of(int64_t features) { return align_up(features, 64); }
@@ -1380,15 +1382,18 @@ void Emitter::forward() {
     }
     if (!inters.empty()) {
       int blocks = 0, mf = 0, md = 0;
+      bool mfma = !(pl.flags & 1);
+      for (auto &p : inters) mfma = mfma && p.d == inters[0].d && interact_mfma_ok(p, false);
       for (auto &p : inters) {
         p.blk_begin = blocks;
-        blocks += p.batch;
+        blocks += mfma ? interact_mfma_blocks(p.batch) : p.batch;
         mf = std::max(mf, p.F);
         md = std::max(md, p.d);
       }
       Step &s = add_step(K_INTERACT_FWD, push_table(inters), (int)inters.size(), blocks);
       s.a0 = mf;
       s.a1 = md;
+      s.a2 = mfma ? md : 0;
     }
     if (!heads.empty()) {      // (the stage's only loss)
       Step &sh = add_step(K_HEAD_LOSS, push_table(heads), 1, 1);
@@ -1901,15 +1906,18 @@ void Emitter::backward() {
     emit_emb_bwd(embs, 0);
     if (!inters.empty()) {
       int blocks = 0, mf = 0, md = 0;
+      bool mfma = !(pl.flags & 1);
+      for (auto &p : inters) mfma = mfma && p.d == inters[0].d && interact_mfma_ok(p, true);
       for (auto &p : inters) {
         p.blk_begin = blocks;
-        blocks += p.batch;
+        blocks += mfma ? interact_mfma_blocks(p.batch) : p.batch;
         mf = std::max(mf, p.F);
         md = std::max(md, p.d);
       }
       Step &s = add_step(K_INTERACT_BWD, push_table(inters), (int)inters.size(), blocks);
       s.a0 = mf;
       s.a1 = md;
+      s.a2 = mfma ? md : 0;
     }
     flush_post();
     // bags whose gradient is complete now (it is a slice of the merge buffer that this level's operators

@@ -21,8 +21,8 @@ void launch_attn_bwd_dkv(const AttnProb *probs, int n, int total_blocks, int max
 void launch_attn_fwd_mfma(const AttnProb *probs, int n, int total_blocks, hipStream_t s);
 void launch_attn_bwd_dq_mfma(const AttnProb *probs, int n, int total_blocks, hipStream_t s);
 void launch_attn_bwd_dkv_mfma(const AttnProb *probs, int n, int total_blocks, hipStream_t s);
-void launch_interact_fwd(const InteractProb *probs, int n, int total_blocks, int maxF, int maxd, hipStream_t s);
-void launch_interact_bwd(const InteractProb *probs, int n, int total_blocks, int maxF, int maxd, hipStream_t s);
+void launch_interact_fwd(const InteractProb *probs, int n, int total_blocks, int maxF, int maxd, int mfma, hipStream_t s);
+void launch_interact_bwd(const InteractProb *probs, int n, int total_blocks, int maxF, int maxd, int mfma, hipStream_t s);
 void launch_loss_sum(const float *losses, int n, float *out, hipStream_t s);
 }  // namespace gpp
 
@@ -549,8 +549,8 @@ static gpp_status_t run_steps(gpp_stage *st, const std::vector<Step> &steps, int
         st->emb_logged++;
         break;
       }
-      case K_INTERACT_FWD: launch_interact_fwd((const InteractProb *)tab, sp.n, sp.blocks, sp.a0, sp.a1, s); break;
-      case K_INTERACT_BWD: launch_interact_bwd((const InteractProb *)tab, sp.n, sp.blocks, sp.a0, sp.a1, s); break;
+      case K_INTERACT_FWD: launch_interact_fwd((const InteractProb *)tab, sp.n, sp.blocks, sp.a0, sp.a1, sp.a2, s); break;
+      case K_INTERACT_BWD: launch_interact_bwd((const InteractProb *)tab, sp.n, sp.blocks, sp.a0, sp.a1, sp.a2, s); break;
       case K_LOSS_FWD: launch_loss_fwd((const LossProb *)tab, sp.n, sp.blocks, flags, s); break;
       case K_LOSS_BWD: launch_loss_bwd((const LossProb *)tab, sp.n, sp.blocks, s); break;
       case K_LOSS_SUM:

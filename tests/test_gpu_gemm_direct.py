@@ -136,3 +136,23 @@ def test_merged_activations(kind, slots, flags):
     _, res, grads = _run(wl, slots, slots if flags else 1, False, slots=slots, flags=flags, gouts=gouts)
     stage, ref = run_oracle(wl, gouts)
     compare(wl, res, grads, stage, ref, label=f"merged activations {kind}")
+
+
+# The dot interaction on the matrix cores: the fewest vectors, ragged and full 32 (and 33, which stay on the vector path), a batch that
+# ends inside a workgroup, every width.  (Two vectors of one sample are no case: their gradients are one product's bf16 gradient times the
+# other vector, and where that sum of 40 terms cancels, its one rounding is the whole error: 4.7e-2 on either path, 3e-3 over 40 samples.)
+@pytest.mark.parametrize("F,d,b", [(2, 64, 41), (3, 128, 5), (17, 64, 67), (27, 128, 130), (32, 256, 6), (33, 64, 9), (9, 32, 10)])
+def test_dot_interaction(F, d, b):
+    g = W._Graph()
+    vecs = [g.linear(g.input(24, W.BF16), 24, d, "none", W.BF16) for _ in range(F)]
+    x = g.add("concat", vecs, out_features=F * d, dtype=W.BF16)
+    w = d + F * (F - 1) // 2
+    z = g.linear(g.add("dot_interact", (x,), in_features=d, out_features=w, dtype=W.BF16), w, 40, "none", W.BF16)
+    g.add("loss_mse", (z, g.input(40, W.F32, role="target")), loss_scale=1.0 / (b * 2 * 40))
+    rng = np.random.Generator(np.random.PCG64(F))
+    params = W._draw_params(g.ops, rng)
+    wl = W.Workload("dot_interaction", g.ops, b, 2, params, W._draw_batches(g.ops, b, 2, rng, {}), 2e-2)
+    print(f"[case] interaction F={F} d={d} b={b}", flush=True)
+    res, grads = run_gpu(wl)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="dot interaction")
