@@ -31,11 +31,11 @@ CAL_MIB = 256
 
 # kernel name (as rocprofv3 prints it, namespace stripped) -> kernel family of bench.py's `kernels` table
 FAMILIES = [
-    (r"k_gemm_(big|mid)_dw_group|k_gemm_(big|mid)<2", "gemm_big_dw"),
+    (r"k_gemm_mid_dw_group|k_gemm_ring_dw|k_gemm_mid<2", "gemm_big_dw"),
     (r"k_gemm_(big|mid)<0|k_gemm_big_split|k_split_sum", "gemm_big_fwd"),
     (r"k_gemm_(big|mid)<1", "gemm_big_dx"),
-    (r"k_gemm_skinny<0", "gemm_skinny_fwd"),
-    (r"k_gemm_skinny<1", "gemm_skinny_dx"),
+    (r"k_gemm_(skinny|ring)<0", "gemm_skinny_fwd"),
+    (r"k_gemm_(skinny|ring)<1", "gemm_skinny_dx"),
     (r"k_gemm_bwd_merged", "gemm_bwd_merged_dx_dw"),
     (r"k_gemm_dw_ksplit", "gemm_dw_ksplit"),
     (r"k_emb_fwd", "embedding_fwd"),
