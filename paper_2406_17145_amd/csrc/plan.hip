@@ -279,7 +279,12 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
     if (a.d.kind != GPP_OP_ADD || a.in[0] == a.in[1]) continue;
     for (int p : a.in) {
       Node &m = nodes[p];
-      const bool plain = !(m.d.kind == GPP_OP_LINEAR && m.d.act != GPP_ACT_NONE);
+      // (what multiplies a gradient by a derivative in place needs it to itself: a Linear with an activation, and a merge that
+      // such a Linear has its gradient in)
+      auto activated = [](const Node &x) { return x.d.kind == GPP_OP_LINEAR && x.d.act != GPP_ACT_NONE; };
+      bool plain = !activated(m);
+      if (m.d.kind == GPP_OP_CONCAT)
+        for (int q : m.in) plain = plain && !(activated(nodes[q]) && nodes[q].gout_parent == p);
       if (m.users.size() == 1 && plain && m.gdtype == a.gdtype && m.wants_grad && m.d.kind != GPP_OP_INPUT &&
           m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
         m.gout_parent = i;
@@ -1451,17 +1456,13 @@ void Emitter::forward() {
 // Weight gradients of a backward pass in one launch behind it instead of one launch (or a share of one) per level: from three
 // levels of them on, where that saves launches and the few tiles of a level no longer run by themselves (fifteen launches of
 // 10 us in three passes of a small recommendation stage: three of 12).  Below, a level's share of its backward-data launch
-// costs no launch at all.  Not where an operator inside a merge that is also added to something multiplies ITS slice of the shared
-// gradient by its derivative: the other operand of that addition reads the same memory as its own gradient.
+// costs no launch at all.
 bool Emitter::weights_at_the_end() const {
   const auto &N = pl.nodes;
   int levels = 0;
   for (auto &ids : pl.by_level) {
     bool any = false;
-    for (int i : ids) {
-      if (N[i].d.kind == GPP_OP_CONCAT && N[i].gout_parent >= 0 && N[N[i].gout_parent].d.kind == GPP_OP_ADD) return false;
-      any = any || (N[i].d.kind == GPP_OP_LINEAR && N[i].d.param_dtype == GPP_BF16);
-    }
+    for (int i : ids) any = any || (N[i].d.kind == GPP_OP_LINEAR && N[i].d.param_dtype == GPP_BF16);
     levels += any;
   }
   return levels >= 3 && !(pl.flags & 3);

@@ -171,7 +171,7 @@ def test_weight_gradients_of_three_levels_wait_for_the_end_of_the_pass():
                 x = g.linear(x, 64, 64, "relu", dtype)
             outs.append(x)
         y = g.add("concat", outs, out_features=128, dtype=dtype)
-        if added:      # the merge's gradient is also that of the other operand
+        if added:      # (the merge's gradient is a buffer of its own: its layers mask it in place)
             y = g.add("add", (y, g.linear(g.input(128, dtype), 128, 128, "none", dtype)), out_features=128, dtype=dtype)
         g.linear(y, 128, 64, "none", dtype)
         steps = [p for p in plan(g.ops, 100, 1, flags) if p["pass"] == "backward"]
@@ -179,4 +179,4 @@ def test_weight_gradients_of_three_levels_wait_for_the_end_of_the_pass():
     assert weights(1) == ([], "gemm_bwd_merged_dx_dw")            # two levels: each rides along with backward-data
     assert weights(2) == ([5], "gemm_big_dw") and weights(4)[0] == [9]
     assert weights(2, B.FLAG_FORCE_GENERIC_GEMM)[0] == [] and weights(3, dtype=W.F32)[0] == []
-    assert weights(3, added=True)[0] == []
+    assert weights(3, added=True)[0] == [8]

@@ -156,3 +156,28 @@ def test_dot_interaction(F, d, b):
     res, grads = run_gpu(wl)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="dot interaction")
+
+
+# A merge of layers that is also an addend: layers with an activation multiply their slice of its gradient in place, so the other
+# addend must not read the same buffer (it did, and got their masks); without one the two share it.
+@pytest.mark.parametrize("act", ["relu", "gelu", "none"])
+@pytest.mark.parametrize("layers", [1, 2])
+def test_merge_added_to_a_layer(layers, act):
+    g, outs = W._Graph(), []
+    for _ in range(2):
+        x = g.input(64, W.BF16)
+        for _ in range(2):
+            x = g.linear(x, 64, 64, act, W.BF16)
+        outs.append(x)
+    y, z = g.add("concat", outs, out_features=128, dtype=W.BF16), g.input(128, W.BF16)
+    for _ in range(layers):
+        z = g.linear(z, 128, 128, "none", W.BF16)
+    y = g.linear(g.add("add", (y, z), out_features=128, dtype=W.BF16), 128, 64, "none", W.BF16)
+    g.add("loss_mse", (y, g.input(64, W.F32, role="target")), loss_scale=1.0 / 6400)
+    rng = np.random.Generator(np.random.PCG64(3))
+    params = W._draw_params(g.ops, rng)
+    wl = W.Workload("merge_added", g.ops, 100, 2, params, W._draw_batches(g.ops, 100, 2, rng, {}), 2e-2)
+    print(f"[case] merge added layers={layers} act={act}", flush=True)
+    res, grads = run_gpu(wl)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="merge added to a layer")
