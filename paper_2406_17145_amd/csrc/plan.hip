@@ -274,17 +274,22 @@ gpp_status_t Plan::analyse(const gpp_stage_desc_t *desc) {
       col += m.feat;
     }
   }
+  // (what multiplies a gradient by a derivative in place needs it to itself: a Linear with an activation, and a merge that
+  // such a Linear has its gradient in, directly or inside merges of merges; an ADD in between holds none, by this rule)
+  auto activated = [](const Node &x) { return x.d.kind == GPP_OP_LINEAR && x.d.act != GPP_ACT_NONE; };
+  std::function<bool(int)> multiplied = [&](int p) {
+    if (activated(nodes[p])) return true;
+    if (nodes[p].d.kind == GPP_OP_CONCAT)
+      for (int q : nodes[p].in)
+        if (nodes[q].gout_parent == p && multiplied(q)) return true;
+    return false;
+  };
   for (int i = 0; i < n; ++i) {
     Node &a = nodes[i];
     if (a.d.kind != GPP_OP_ADD || a.in[0] == a.in[1]) continue;
     for (int p : a.in) {
       Node &m = nodes[p];
-      // (what multiplies a gradient by a derivative in place needs it to itself: a Linear with an activation, and a merge that
-      // such a Linear has its gradient in)
-      auto activated = [](const Node &x) { return x.d.kind == GPP_OP_LINEAR && x.d.act != GPP_ACT_NONE; };
-      bool plain = !activated(m);
-      if (m.d.kind == GPP_OP_CONCAT)
-        for (int q : m.in) plain = plain && !(activated(nodes[q]) && nodes[q].gout_parent == p);
+      const bool plain = !multiplied(p);
       if (m.users.size() == 1 && plain && m.gdtype == a.gdtype && m.wants_grad && m.d.kind != GPP_OP_INPUT &&
           m.d.kind != GPP_OP_EMBEDDING_BAG_CONCAT) {
         m.gout_parent = i;

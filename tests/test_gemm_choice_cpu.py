@@ -46,6 +46,21 @@ def merged(rows, widths, act="gelu"):
     return g.ops
 
 
+def nested_merge(act, layers, depth):
+    """ADD of a merge, whose layers with an activation sit `depth` merges further in, and `layers` plain layers; a layer and a loss."""
+    g = W._Graph()
+    y = g.add("concat", [g.linear(g.input(64, W.BF16), 64, 64, act, W.BF16) for _ in range(2)], out_features=128, dtype=W.BF16)
+    for d in range(depth):
+        y = g.add("concat", (y, g.linear(g.input(64, W.BF16), 64, 64, "none", W.BF16)), out_features=192 + 64 * d, dtype=W.BF16)
+    n = 128 + 64 * depth
+    z = g.input(n, W.BF16)
+    for _ in range(layers):
+        z = g.linear(z, n, n, "none", W.BF16)
+    y = g.linear(g.add("add", (y, z), out_features=n, dtype=W.BF16), n, 64, "none", W.BF16)
+    g.add("loss_mse", (y, g.input(64, W.F32, role="target")), loss_scale=1.0 / 6400)
+    return g.ops
+
+
 def line(n):
     return -(-n // 256) * 256
 
@@ -180,3 +195,21 @@ def test_weight_gradients_of_three_levels_wait_for_the_end_of_the_pass():
     assert weights(2) == ([5], "gemm_big_dw") and weights(4)[0] == [9]
     assert weights(2, B.FLAG_FORCE_GENERIC_GEMM)[0] == [] and weights(3, dtype=W.F32)[0] == []
     assert weights(3, added=True)[0] == [8]
+
+
+@pytest.mark.parametrize("layers", [1, 2, 3])
+@pytest.mark.parametrize("depth", [0, 1, 2, 3])
+@pytest.mark.parametrize("flags", [0, B.FLAG_GROUPED_DW])
+def test_a_merge_with_masked_layers_anywhere_inside_shares_no_gradient(layers, depth, flags):
+    """Layers with an activation multiply their columns of a merge's gradient in place: the merge has it to itself, and takes a copy
+    of what the addition passes on; without an activation merge and addend read one buffer."""
+    def of(act):
+        ops = nested_merge(act, layers, depth)
+        d, keep = desc(ops, 100, 1, flags)
+        copies = [p["records"] for p in plan(ops, 100, 1, flags) if p["pass"] == "backward" and p["kernel"] == "elt_bwd"]
+        return B.gpp_stage_workspace_bytes(d), copies
+    (masked, m), (plain, p) = of("relu"), of("none")
+    n = 128 + 64 * depth
+    extra = line(100 * n * 2)
+    assert extra <= masked - plain <= extra + 4096, (masked, plain)          # (launch tables)
+    assert m[:1] == [1] and 2 in m and sum(m) == sum(p) + 3

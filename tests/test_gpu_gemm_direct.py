@@ -6,6 +6,7 @@ import pytest
 from paper_2406_17145_amd import binding as B
 from paper_2406_17145_amd import workloads as W
 from tests.parity_util import compare, run_gpu, run_oracle, t2n
+from tests.test_gemm_choice_cpu import nested_merge
 from tests.test_gpu_gemm_tiles import _chain, _plan
 from tests.test_gpu_schedule import _run
 
@@ -181,3 +182,19 @@ def test_merge_added_to_a_layer(layers, act):
     res, grads = run_gpu(wl)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="merge added to a layer")
+
+
+# The same with the activated layers in a merge inside the merge (and one further in), weight gradients per level, at the end of the
+# pass and in one launch over the slots; the other addend reads its gradient at its own level or behind the masks of the layers.
+@pytest.mark.parametrize("act", ["relu", "gelu", "none"])
+@pytest.mark.parametrize("layers,depth,slots,flags", [
+    (1, 1, 1, 0), (2, 1, 1, 0), (3, 2, 2, 0), (1, 1, 2, B.FLAG_GROUPED_DW), (2, 2, 2, B.FLAG_GROUPED_DW)])
+def test_nested_merge_added_to_a_layer(layers, depth, slots, flags, act):
+    wl = W.Workload("merge_nested", nested_merge(act, layers, depth), 100, 2, {}, [], 2e-2)
+    rng = np.random.Generator(np.random.PCG64(depth))
+    wl.params = W._draw_params(wl.ops, rng)
+    wl.batches = W._draw_batches(wl.ops, 100, 2, rng, {})
+    print(f"[case] nested merge added layers={layers} depth={depth} slots={slots} flags={flags} act={act}", flush=True)
+    _, res, grads = _run(wl, slots, slots if flags else 1, False, slots=slots, flags=flags)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="nested merge added to a layer")
