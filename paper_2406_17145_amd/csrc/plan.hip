@@ -461,6 +461,7 @@ struct Emitter {
   bool fork_open = false;
   std::vector<char> emb_hoisted;    // per node: its backward was issued early, on the side stream
   std::vector<int> written_level;   // level whose launches first wrote the node's gradient
+  std::vector<int> added_level[3];  // per kind of launch: the last level whose launch added to it in place
   int cur_level = 0;
   int64_t shared_tmp_top;
 
@@ -658,8 +659,11 @@ struct Emitter {
     r.push_back(e);
     emit_elt(r);
   }
-  Target acquire(int p, bool can_addend) {
+  // `adds`: the launch of this level that the kernel is part of, if it can add to what is there
+  enum { ADDS_NOT = 0, ADDS_GEMM, ADDS_NORM };
+  Target acquire(int p, int adds) {
     Node &nd = pl.nodes[p];
+    const bool can_addend = adds != ADDS_NOT;
     Target t;
     t.dst = nd.gout;
     if (gstate[p] == G_ADDEND && !can_addend) {
@@ -674,8 +678,9 @@ struct Emitter {
       t.addend = gaddend[p];
       gstate[p] = G_WRITTEN;
       written_level[p] = cur_level;
-    } else if (can_addend && written_level[p] != cur_level) {
-      t.addend = nd.gout;   // accumulate in place: every earlier writer ran in an earlier launch
+    } else if (can_addend && written_level[p] != cur_level && added_level[adds][p] != cur_level) {
+      t.addend = nd.gout;   // accumulate in place: every earlier writer ran in an earlier launch (one record of a launch, then)
+      added_level[adds][p] = cur_level;
     } else {                // a launch of this same level also writes it: go through a temporary
       t.post = true;
       t.final_dst = nd.gout;
@@ -1484,6 +1489,7 @@ void Emitter::backward() {
   gaddend.assign(n, Buf());
   dz_ready.assign(n, 0);
   written_level.assign(n, -1);
+  for (auto &v : added_level) v.assign(n, -1);
   post_copies.clear();
   emb_hoisted.assign(n, 0);
   fork_open = false;
@@ -1542,7 +1548,7 @@ void Emitter::backward() {
         if (!y.wants_grad) continue;
         const Node &t = N[nd.in[1]];
         const Buf &yv = y.fused_add >= 0 ? N[y.fused_add].val : y.val;
-        Target tg = acquire(nd.in[0], false);
+        Target tg = acquire(nd.in[0], ADDS_NOT);
         // written by the forward pass already (the prediction's only consumer is this loss, so the
         // gradient buffer itself is the target and nothing is added to it)
         if (loss_fused[i] && !tg.post && !tg.addend.valid() && tg.dst.space == y.gout.space && tg.dst.off == y.gout.off) continue;
@@ -1651,12 +1657,12 @@ void Emitter::backward() {
           if (head_loss[i] >= 0) {
             // the forward pass wrote the input's gradient, activation derivative included (its only consumer
             // is this head, so the gradient buffer itself was the target)
-            (void)acquire(nd.in[0], true);
+            (void)acquire(nd.in[0], ADDS_GEMM);
             if (x.d.act != GPP_ACT_NONE) dz_ready[nd.in[0]] = 1;
             break;
           }
           if (x.wants_grad) {
-            Target tg = acquire(nd.in[0], true);
+            Target tg = acquire(nd.in[0], ADDS_GEMM);
             GemmProb g;
             memset(&g, 0, sizeof(g));
             g.form = FORM_DX;
@@ -1731,7 +1737,7 @@ void Emitter::backward() {
           l.d = (int32_t)nd.feat;
           l.eps = (float)d.eps;
           if (x.wants_grad) {
-            Target tg = acquire(nd.in[0], true);
+            Target tg = acquire(nd.in[0], ADDS_NORM);
             l.y = ptr(tg.dst);
             l.ldy = tg.dst.ld;
             l.y_dtype = tg.dst.dtype;
@@ -1747,7 +1753,7 @@ void Emitter::backward() {
         case GPP_OP_ATTENTION: {
           const Node &x = N[nd.in[0]];
           if (!x.wants_grad) break;
-          Target tg = acquire(nd.in[0], false);
+          Target tg = acquire(nd.in[0], ADDS_NOT);
           AttnProb a;
           memset(&a, 0, sizeof(a));
           a.qkv = ptr(x.val);
@@ -1787,7 +1793,7 @@ void Emitter::backward() {
         case GPP_OP_MEANPOOL_SEQ: {
           const Node &x = N[nd.in[0]];
           if (!x.wants_grad) break;
-          Target tg = acquire(nd.in[0], false);
+          Target tg = acquire(nd.in[0], ADDS_NOT);
           PoolProb p;
           memset(&p, 0, sizeof(p));
           p.backward = 1;
@@ -1812,7 +1818,7 @@ void Emitter::backward() {
         case GPP_OP_DOT_INTERACT: {
           const Node &x = N[nd.in[0]];
           if (!x.wants_grad) break;
-          Target tg = acquire(nd.in[0], false);
+          Target tg = acquire(nd.in[0], ADDS_NOT);
           InteractProb p;
           memset(&p, 0, sizeof(p));
           p.x = ptr(x.val);

@@ -61,6 +61,23 @@ def nested_merge(act, layers, depth):
     return g.ops
 
 
+def skipped(kinds, hidden):
+    """An operator with one consumer per entry of `kinds`, all of a level, each of them added to it again: its gradient arrives through
+    the additions first, then from that level."""
+    g = W._Graph()
+    x = g.input(64, W.BF16)
+    if hidden:
+        x = g.linear(x, 64, 64, "gelu", W.BF16)
+    ends = []
+    for k in kinds:
+        y = (g.linear(x, 64, 64, k, W.BF16) if k != "norm" else
+             g.add("layernorm", (x,), in_features=64, out_features=64, dtype=W.BF16, eps=1e-5))
+        ends.append(g.add("add", (y, x), out_features=64, dtype=W.BF16))
+    n = 64 * len(ends)
+    g.add("loss_mse", (g.add("concat", ends, out_features=n, dtype=W.BF16), g.input(n, W.F32, role="target")), loss_scale=1.0 / (100 * n))
+    return g.ops
+
+
 def line(n):
     return -(-n // 256) * 256
 
@@ -213,3 +230,17 @@ def test_a_merge_with_masked_layers_anywhere_inside_shares_no_gradient(layers, d
     extra = line(100 * n * 2)
     assert extra <= masked - plain <= extra + 4096, (masked, plain)          # (launch tables)
     assert m[:1] == [1] and 2 in m and sum(m) == sum(p) + 3
+
+
+@pytest.mark.parametrize("hidden", [False, True])
+@pytest.mark.parametrize("kinds,copies", [
+    (("none", "none"), 1), (("gelu", "none", "gelu"), 2), (("none", "norm"), 0), (("norm", "gelu", "norm"), 1)])
+def test_one_record_of_a_launch_adds_to_a_gradient_in_place(kinds, copies, hidden):
+    """What is already written is read and written by one record of a level's launch; the others, whose workgroups run beside it,
+    write buffers of their own, which copies behind the level's launches add one by one."""
+    steps = [p for p in plan(skipped(kinds, hidden), 100) if p["pass"] == "backward"]
+    of_level = [i for i, p in enumerate(steps) if p["kernel"] in ("gemm_skinny_dx", "gemm_bwd_merged_dx_dw", "layernorm_bwd_dx")]
+    behind = [p["kernel"] for p in steps[of_level[-2 if hidden else -1] + 1:]]       # (the last launch: of the layer in front)
+    behind = behind[:behind.index("gemm_bwd_merged_dx_dw")] if hidden else behind
+    # (without a layer in front the input's gradient is copied out; hidden layers multiply by their derivative in place)
+    assert [k for k in behind if k == "elt_bwd"] == ["elt_bwd"] * (copies + 1), steps

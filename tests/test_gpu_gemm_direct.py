@@ -6,7 +6,7 @@ import pytest
 from paper_2406_17145_amd import binding as B
 from paper_2406_17145_amd import workloads as W
 from tests.parity_util import compare, run_gpu, run_oracle, t2n
-from tests.test_gemm_choice_cpu import nested_merge
+from tests.test_gemm_choice_cpu import nested_merge, skipped
 from tests.test_gpu_gemm_tiles import _chain, _plan
 from tests.test_gpu_schedule import _run
 
@@ -198,3 +198,17 @@ def test_nested_merge_added_to_a_layer(layers, depth, slots, flags, act):
     _, res, grads = _run(wl, slots, slots if flags else 1, False, slots=slots, flags=flags)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="nested merge added to a layer")
+
+
+# An operator whose gradient arrives through two and three additions and then from as many operators of one level.
+@pytest.mark.parametrize("hidden", [False, True])
+@pytest.mark.parametrize("kinds", [("none", "none"), ("gelu", "none", "gelu"), ("none", "norm"), ("norm", "gelu", "norm")])
+@pytest.mark.parametrize("slots,flags", [(1, 0), (2, B.FLAG_GROUPED_DW)])
+def test_several_consumers_behind_additions(kinds, hidden, slots, flags):
+    ops = skipped(kinds, hidden)
+    rng = np.random.Generator(np.random.PCG64(len(kinds)))
+    wl = W.Workload("several_consumers", ops, 100, 2, W._draw_params(ops, rng), W._draw_batches(ops, 100, 2, rng, {}), 2e-2)
+    print(f"[case] several consumers {kinds} hidden={hidden} slots={slots} flags={flags}", flush=True)
+    _, res, grads = _run(wl, slots, slots if flags else 1, False, slots=slots, flags=flags)
+    stage, ref = run_oracle(wl)
+    compare(wl, res, grads, stage, ref, label="several consumers behind additions")
