@@ -125,8 +125,9 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
   //   DW:  A = dZ [K x M], B = X [K x N]      (K = contraction length in every form)
   const __amdgpu_buffer_rsrc_t rs_a = matrix_rsrc(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);
   const __amdgpu_buffer_rsrc_t rs_b = matrix_rsrc(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
-  const rsrc4 ra4 = matrix_rsrc4(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);     // (the same for the copies)
-  const rsrc4 rb4 = matrix_rsrc4(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
+  rsrc4 ra4 = matrix_rsrc4(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);           // (the same for the copies)
+  rsrc4 rb4 = matrix_rsrc4(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
+  if (DIRECT) settle(ra4, rb4);
 
   f32x16 acc[WTM][WTN];
 #pragma unroll

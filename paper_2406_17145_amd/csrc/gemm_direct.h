@@ -13,6 +13,11 @@ constexpr int GB_BK = 64;           // contraction elements per k-step
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t rsrc4;   // buffer descriptor as the four scalar registers it is
 
+// A memory instruction may read a scalar register that a vector instruction (the readfirstlanes below) has written five wait states
+// later at the earliest.  A tile's two descriptors pass through here behind every such write and before any copy can read them, so that
+// no copy has to wait by itself (in each of them the wait cost the passes with ring-buffered GEMMs 0.4 - 1.6 %, here at most 0.1).  What the compiler could still put in
+// between, a register reloaded from a vector register, tests/test_device_code_cpu.py looks for in the built code.
+__device__ __forceinline__ void settle(rsrc4 &a, rsrc4 &b) { asm("s_nop 4" : "+s"(a), "+s"(b)); }
 // what matrix_rsrc describes: rows beyond the matrix, and chunks steered to OOB_OFFSET, read zero
 __device__ __forceinline__ rsrc4 matrix_rsrc4(const void *base, int rows, int64_t ld, int width) {
   const uint64_t a = (uint64_t)base;
@@ -31,7 +36,8 @@ __device__ __forceinline__ uint32_t lds_address(const uint16_t *p) {
 // 4 x [512 x 1000 x 1000] on 128 x 64 tiles 18.9 us with the builtin, 12.7 without that wait).  The instruction has no register
 // result; what waits for it is copies_landed_barrier, and the compiler's own counted waits, which do not know of it,
 // can only become longer (copies and loads finish in issue order).
-// (m0 holds the destination; one wait state between its write and the copy)
+// Wait states, which the compiler does not add in front of what it does not know to be a memory instruction: one between the write
+// of m0, which holds the destination, and the copy; the five behind a vector write of the descriptor are in settle().
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_copy16(rsrc4 rs, uint32_t dst, uint32_t off) {

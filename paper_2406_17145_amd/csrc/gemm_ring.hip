@@ -39,6 +39,7 @@ __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uin
   const int wi0 = (wave / WGN) * (32 * TM), wj0 = (wave % WGN) * (32 * TN);
   rsrc4 rs_a = matrix_rsrc4(p.A, A_TR ? p.K : p.M, p.lda, A_TR ? p.M : p.K);
   rsrc4 rs_b = matrix_rsrc4(p.B, B_TR ? p.K : p.N, p.ldb, B_TR ? p.N : p.K);
+  settle(rs_a, rs_b);
   // (a wave with one MFMA tile sums even and odd 16-wide chunks apart: its MFMAs are two chains instead of one)
   constexpr int CHAINS = TM * TN == 1 ? 2 : 1;
   f32x16 acc_of[CHAINS][TM][TN];
@@ -66,6 +67,7 @@ __device__ __forceinline__ void ring_body(const GemmProb &p, int m0, int n0, uin
     rs_a[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
     rs_b[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
     rs_b[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xffffu));
+    settle(rs_a, rs_b);
   };
   if constexpr (FORM == FORM_DW) point_at_slot();
   auto copy_next = [&](int buf) {
