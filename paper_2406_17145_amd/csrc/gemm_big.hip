@@ -510,11 +510,13 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
 // The kernels take a problem when its matrices fit the 32-bit buffer offsets; the eight-wave ones also need whole chunks
 // of k-contiguous operands (contraction length a multiple of 8).  Rows and base pointers on 16 bytes are gemm_mfma_supported's
 // condition, so the eight-wave forward and backward-data kernels can always copy operands straight into LDS.
+// 32-bit offsets into both operands.  Of an operand whose rows run along the contraction whole k-steps are fetched, and rows beyond
+// the matrix read zero by lying beyond its bytes: those of the last k-step must not wrap around to the first rows
 bool gemm_big_supported(const GemmProb &p) {
   if (!gemm_mfma_supported(p)) return false;
-  const int64_t a_rows = p.form == FORM_DW ? p.K : p.M, b_rows = p.form == FORM_FWD ? p.N : p.K;
-  if (a_rows * p.lda * 2 >= 0xffffff00ll || b_rows * p.ldb * 2 >= 0xffffff00ll) return false;
-  return true;
+  const int64_t k_rows = (int64_t)cdiv(p.K, GB_BK) * GB_BK;
+  const int64_t a_rows = p.form == FORM_DW ? k_rows : p.M, b_rows = p.form == FORM_FWD ? p.N : k_rows;
+  return a_rows * p.lda * 2 < 0xffffff00ll && b_rows * p.ldb * 2 < 0xffffff00ll;
 }
 // Kernel of a forward / backward-data launch: tiles of 256 x 256 or 128 x 256 (256, 128: eight waves), of 128 x 128 (64: four waves,
 // three workgroups per compute unit), of 128 x 64 or 64 x 64 out of a ring of LDS buffers (GEMM_RING + 128, + 64: two and three

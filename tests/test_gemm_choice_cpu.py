@@ -244,3 +244,12 @@ def test_one_record_of_a_launch_adds_to_a_gradient_in_place(kinds, copies, hidde
     behind = behind[:behind.index("gemm_bwd_merged_dx_dw")] if hidden else behind
     # (without a layer in front the input's gradient is copied out; hidden layers multiply by their derivative in place)
     assert [k for k in behind if k == "elt_bwd"] == ["elt_bwd"] * (copies + 1), steps
+
+
+@pytest.mark.parametrize("rows,kernel", [(1048512, "gemm_big_dw"), (1048513, "gemm_mfma_dw"), (1048575, "gemm_mfma_dw")])
+@pytest.mark.parametrize("flags", [0, B.FLAG_GROUPED_DW])
+def test_weight_gradients_whose_last_k_step_would_wrap_its_offsets(rows, kernel, flags):
+    """Rows of 4 KiB: 1048576 of them are 2^32 bytes.  The large tiles fetch whole k-steps of 64 rows by 32-bit offsets and rely on rows
+    beyond the matrix lying beyond its bytes; where the last k-step passes 2^32 they would read the first rows instead of zeros."""
+    steps = [p for p in plan(layers(rows, 2048, 2048), rows, 1, flags) if p["kernel"].endswith("dw")]
+    assert [p["kernel"] for p in steps] == [kernel]
