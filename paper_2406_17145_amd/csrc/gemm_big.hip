@@ -510,7 +510,7 @@ __global__ __launch_bounds__(256, 4) void k_gemm_mid_dw_group(const GemmProb *__
 // The kernels take a problem when its matrices fit the 32-bit buffer offsets; the eight-wave ones also need whole chunks
 // of k-contiguous operands (contraction length a multiple of 8).  Rows and base pointers on 16 bytes are gemm_mfma_supported's
 // condition, so the eight-wave forward and backward-data kernels can always copy operands straight into LDS.
-// 32-bit offsets into both operands.  Of an operand whose rows run along the contraction whole k-steps are fetched, and rows beyond
+// Of an operand whose rows run along the contraction whole k-steps are fetched, and rows beyond
 // the matrix read zero by lying beyond its bytes: those of the last k-step must not wrap around to the first rows
 bool gemm_big_supported(const GemmProb &p) {
   if (!gemm_mfma_supported(p)) return false;

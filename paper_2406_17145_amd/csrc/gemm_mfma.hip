@@ -41,7 +41,9 @@ bool gemm_mfma_supported(const GemmProb &p) {
   if (((uintptr_t)p.A | (uintptr_t)p.B) & 15) return false;
   if ((p.lda | p.ldb) & 7) return false;
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return false;
-  return true;
+  // 32-bit offsets into both operands (larger ones: the generic kernel)
+  const int64_t a_rows = p.form == FORM_DW ? p.K : p.M, b_rows = p.form == FORM_FWD ? p.N : p.K;
+  return a_rows * p.lda * 2 < 0xffffff00ll && b_rows * p.ldb * 2 < 0xffffff00ll;
 }
 
 // A launch uses one tile shape for all of its problems: the planner asks for it with the largest

@@ -253,3 +253,15 @@ def test_weight_gradients_whose_last_k_step_would_wrap_its_offsets(rows, kernel,
     beyond the matrix lying beyond its bytes; where the last k-step passes 2^32 they would read the first rows instead of zeros."""
     steps = [p for p in plan(layers(rows, 2048, 2048), rows, 1, flags) if p["kernel"].endswith("dw")]
     assert [p["kernel"] for p in steps] == [kernel]
+
+
+def test_operands_of_four_gib_run_on_the_kernel_with_64_bit_addresses():
+    """The matrix-core kernels form 32-bit offsets into an operand: its rows behind 2^32 bytes would be read from its start."""
+    def kernels(rows, flags=0):
+        steps = [p for p in plan(layers(rows, 2048, 64), rows, 1, flags) if p["kernel"].startswith("gemm")]
+        return {(p["pass"], p["kernel"]) for p in steps}
+    assert all("generic" not in k for _, k in kernels(1048575))
+    for flags in (0, B.FLAG_GROUPED_DW):
+        assert {("forward", "gemm_generic_fwd"), ("backward", "gemm_generic_bwd")} <= kernels(1048576, flags)
+    weights = [p["kernel"] for p in plan(layers(300, 131072, 16384), 300) if p["kernel"].startswith("gemm")]       # (a 4 GiB weight matrix)
+    assert weights[0] == "gemm_generic_fwd" and "gemm_generic_bwd" in weights

@@ -212,3 +212,32 @@ def test_several_consumers_behind_additions(kinds, hidden, slots, flags):
     _, res, grads = _run(wl, slots, slots if flags else 1, False, slots=slots, flags=flags)
     stage, ref = run_oracle(wl)
     compare(wl, res, grads, stage, ref, label="several consumers behind additions")
+
+
+# Operands around 2^32 bytes: the last matrix whose offsets fit 32 bits (whose last k-step of a weight gradient passes them) and a
+# larger one.  Bars: bf16 storage of the results, and sums of a million products in fp32.
+@pytest.mark.parametrize("rows", [1048575, 1048640])
+def test_operands_of_four_gib(rows):
+    import torch
+    g = W._Graph()
+    g.linear(g.input(2048, W.BF16), 2048, 64, "none", W.BF16)
+    params = W._draw_params(g.ops, np.random.Generator(np.random.PCG64(1)))
+    print(f"[case] operands of 4 GiB rows={rows}", flush=True)
+    st = B.Stage(g.ops, rows, params)
+    gen = torch.Generator(device=st.dev).manual_seed(rows)
+    x = torch.randn(rows, 2048, device=st.dev, dtype=torch.bfloat16, generator=gen)
+    dy = torch.randn(rows, 64, device=st.dev, dtype=torch.bfloat16, generator=gen)
+    outs, gins, w = st.alloc_outputs(), st.alloc_grad_inputs(), torch.from_numpy(params[1]["W"]).to(st.dev)
+    st.grad_reset()
+    st.forward(0, [x], outs)
+    st.backward(0, [dy], gins)
+    st.sync_status()
+    dw = torch.zeros(64, 2048, device=st.dev, dtype=torch.float64)
+    for a in range(0, rows, 1 << 16):
+        xs, ds = x[a:a + (1 << 16)].float(), dy[a:a + (1 << 16)].float()
+        for got, want in ((outs[0][a:a + (1 << 16)], xs @ w.T), (gins[0][a:a + (1 << 16)], ds @ w)):
+            assert ((got.float() - want).norm() / want.norm()).item() < 4e-3, a
+        dw += (ds.T @ xs).double()
+    got = torch.from_numpy(st.grads_numpy()[1]["W"]).to(st.dev).double()
+    st.close()
+    assert ((got - dw).norm() / dw.norm()).item() < 1e-4
