@@ -573,6 +573,16 @@ int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bo
     const float w = blocks / CUS;
     return a + ak * nk + w * (b + bk * nk) + fmaxf(1.0f, w) * (d + dk * nk);
   };
+  // The ring's workgroups all run at once up to two (128 x 64) or three (64 x 64) on a compute unit.  In forward the first ones behind that
+  // cost as much as half a round of them, which the fit, with no launch there, does not show; a handful of them hides behind the others.
+  // n x [250 x 2056 x 520], 66 n workgroups, ring 128 x 64 / large tiles: n 7 17.8 / 19.8, 8 22.4 / 21.4, 9 23.8 / 22.1, 11 25.3 / 22.6;
+  // 9 x [512 x 1000 x 512], 576: 21.0 / 19.8;  3 x [590 x 2304 x 576] with GELU in a transformer stage, 540: 1.5 us the other way.  64 x 64:
+  // 12 x [130 x 1500 x 1000], 864: 28.0 / 26.5;  4 x [288 x 2688 x 896], 840: 4 us over the 504 of 128 x 64.
+  // (Backward-data of the first six: 13.2 / 15.1, 17.0 / 16.8, 17.4 / 17.2, 17.8 / 17.7;  16.4 / 16.4;  19.3 / 23.0)
+  auto ring_blocks = [&](float blocks, float per_cu) {
+    const float rounds_of = blocks / (per_cu * CUS);
+    return fwd && rounds_of > 1.07f && rounds_of < 1.5f ? 1.5f * per_cu * CUS : blocks;
+  };
   float best = 1e30f;
   int rows = 64;
   auto take = [&](int r, float t, float handicap) {
@@ -586,8 +596,9 @@ int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bo
   const bool whole_rounds = c.t256 >= CUS && (rest256 < 0.01f || (fwd && max_k >= 768 && rest256 >= 0.5f));
   if (large_tiles && whole_chunks && (max_k > (fwd ? 1024 : 256) || whole_rounds)) take(256, rounds(c.t256, t256), 1.0f);
   if (large_tiles && whole_chunks && (fwd || max_k >= 768)) take(128, rounds(c.t128x256, t128), 1.0f);
-  const float large = best, r128 = fwd ? shared(c.t128x64, 2.14f, 0.18f, 1.36f, 0.181f, 2.0f, 0.138f) : shared(c.t128x64, 2.04f, 0.179f, 1.27f, 0.219f, 1.16f, 0.104f);
-  const float r64 = fwd ? shared(c.t64, 2.51f, 0.153f, 0.64f, 0.122f, 0.95f, 0.092f) : shared(c.t64, 2.35f, 0.134f, 0.63f, 0.155f, 0.62f, 0.074f);
+  const float n128x64 = ring_blocks(c.t128x64, 2.0f), n64 = ring_blocks(c.t64, 3.0f);
+  const float large = best, r128 = fwd ? shared(n128x64, 2.14f, 0.18f, 1.36f, 0.181f, 2.0f, 0.138f) : shared(n128x64, 2.04f, 0.179f, 1.27f, 0.219f, 1.16f, 0.104f);
+  const float r64 = fwd ? shared(n64, 2.51f, 0.153f, 0.64f, 0.122f, 0.95f, 0.092f) : shared(n64, 2.35f, 0.134f, 0.63f, 0.155f, 0.62f, 0.074f);
   if (ring && fminf(r128, r64) < (whole_chunks ? 0.92f : 0.8f) * large) {
     take(GEMM_RING + 128, r128, 1.0f);
     take(GEMM_RING + 64, r64, 1.0f);

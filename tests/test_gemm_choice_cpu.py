@@ -265,3 +265,13 @@ def test_operands_of_four_gib_run_on_the_kernel_with_64_bit_addresses():
         assert {("forward", "gemm_generic_fwd"), ("backward", "gemm_generic_bwd")} <= kernels(1048576, flags)
     weights = [p["kernel"] for p in plan(layers(300, 131072, 16384), 300) if p["kernel"].startswith("gemm")]       # (a 4 GiB weight matrix)
     assert weights[0] == "gemm_generic_fwd" and "gemm_generic_bwd" in weights
+
+
+@pytest.mark.parametrize("rows,k,n,branches,kernel,tile", [
+    (250, 520, 2056, 7, "gemm_skinny_fwd", 128), (250, 520, 2056, 8, "gemm_skinny_fwd", 128), (250, 520, 2056, 9, "gemm_big_fwd", 128),
+    (250, 520, 2051, 9, "gemm_big_fwd", 128), (512, 512, 1000, 8, "gemm_skinny_fwd", 128), (512, 512, 1000, 9, "gemm_big_fwd", 128),
+    (130, 1000, 1500, 10, "gemm_skinny_fwd", 64), (130, 1000, 1500, 12, "gemm_big_fwd", 128)])
+def test_ring_tiles_that_begin_a_second_round(rows, k, n, branches, kernel, tile):
+    """512 workgroups of 128 x 64 or 768 of 64 x 64 run at once; launches of up to half as many again go to the larger tiles."""
+    (step,) = [p for p in plan(layers(rows, k, n, branches, act="relu", grad=False), rows) if p["kernel"].endswith("fwd") and "gemm" in p["kernel"]]
+    assert (step["kernel"], step["ring"] or step["tile"]) == (kernel, tile)
