@@ -78,6 +78,14 @@ def test_sums_over_slices_in_the_static_workspace():
     st.close()
 
 
+def _label(p):
+    """Kernel and tile of a launch, as the cases below name it (launches of the few-row family that run on ring-buffered tiles: ring)."""
+    name = p["kernel"].replace("gemm_", "")
+    if name.startswith("skinny") and p["ring"]:
+        return name.replace("skinny", "ring") + f" {p['ring']}"
+    return name + f" {p['tile']}" + (f" of {p['slices']}" if p["slices"] else "")
+
+
 # The bar is that of bf16 storage with fp32 accumulation: the oracle rounds at the same places, so what is left is the order of
 # fp32 sums and results that fall on the other side of a rounding boundary.
 # `want`: kernel and tile that the plan must hold, or the case has lost what it is here for.
@@ -89,31 +97,38 @@ def test_sums_over_slices_in_the_static_workspace():
     # 256 x 256 with a last column inside a chunk: forward with the stash, backward-data with the derivative
     (1000, (2000, 4003), ("gelu",), 4, ("big_fwd 256",)),
     (1000, (64, 4003, 2000), ("gelu", "none"), 4, ("big_dx 256",)),
-    # ring-buffered tiles, a last row tile of 122 rows; the same with columns that end inside a chunk
-    (250, (520, 2056, 520), ("gelu", "gelu"), 9, ("skinny_fwd 0", "skinny_dx 0")),
-    (250, (520, 2051, 520), ("gelu", "gelu"), 9, ("skinny_fwd 0", "skinny_dx 0")),
-    # 128 x 256: the same two
+    # 128 x 256 forward, a last row tile of 122 rows, and ring-buffered tiles; the same with columns that end inside a chunk
+    (250, (520, 2056, 520), ("gelu", "gelu"), 9, ("big_fwd 128", "ring_fwd 64", "ring_dx 128")),
+    (250, (520, 2051, 520), ("gelu", "gelu"), 9, ("big_fwd 128", "ring_fwd 64", "ring_dx 128")),
+    # 128 x 256 forward next to 128 x 128 backward-data: the same two
     (378, (1032, 2056, 200), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
     (378, (2056, 2051, 200), ("gelu", "gelu"), 9, ("big_fwd 128", "big_dx 64")),
-    # few-row kernel: one row more than two row blocks, columns that end inside a chunk, the smallest and an ordinary launch
-    # with a choice, a contraction of 141 steps, 11 and 25 column blocks (a group of 16 and one of 9) in several row blocks
-    (129, (1000, 1500, 1000), ("gelu", "gelu"), 7, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
-    (300, (203, 333, 70), ("gelu", "none"), 3, ("skinny_fwd 0", "skinny_dx 0", "big_dw 64")),
-    (65, (64, 128, 8), ("gelu", "none"), 1, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
-    (700, (600, 2000, 72), ("gelu", "none"), 1, ("skinny_fwd 0", "bwd_merged_dx_dw 0")),
+    # ring-buffered 64 x 64 tiles forward: one row more than two row blocks, columns that end inside a chunk, the smallest and an
+    # ordinary launch with a choice; backward-data of these with the weight gradients, by the few-row body
+    (129, (1000, 1500, 1000), ("gelu", "gelu"), 7, ("ring_fwd 64", "bwd_merged_dx_dw 0")),
+    (300, (203, 333, 70), ("gelu", "none"), 3, ("ring_fwd 64", "ring_dx 64", "big_dw 64")),
+    (65, (64, 128, 8), ("gelu", "none"), 1, ("ring_fwd 64", "bwd_merged_dx_dw 0")),
+    (700, (600, 2000, 72), ("gelu", "none"), 1, ("ring_fwd 64", "skinny_fwd 0", "bwd_merged_dx_dw 0")),
+    # few-row kernel: a contraction of 141 steps; backward-data of 11 and 25 column blocks (a group of 16 and one of 9) in several row blocks
     (100, (9000, 1000), ("none",), 1, ("skinny_fwd 0",)),
-    (200, (352, 2000), ("gelu",), 1, ("bwd_merged_dx_dw 0",)),
-    (100, (800, 300, 470), ("gelu", "none"), 1, ("bwd_merged_dx_dw 0",)),
-    # narrow results of many rows on the ring-buffered 64 x 64 tiles
+    (200, (352, 2000), ("gelu",), 1, ("ring_fwd 64", "bwd_merged_dx_dw 0")),
+    (100, (800, 300, 470), ("gelu", "none"), 1, ("skinny_fwd 0", "ring_fwd 64", "bwd_merged_dx_dw 0")),
+    # narrow results of many rows on the tiled kernel (64 x 64)
     (9000, (64, 60), ("gelu",), 16, ("mfma_fwd 64",)),
     # sums over 16 slices of the contraction, the last one shorter
     (130, (20008, 523, 64), ("gelu", "none"), 1, ("big_fwd 0 of 16",)),
+    # few-row kernel, forward and backward-data each in a launch of its own: one row more than one and than two row blocks, a last
+    # row block of 8 and of 44 rows, columns and contractions that end inside a chunk, a mask and a derivative in the epilogue
+    (65, (2051, 131, 2051, 77), ("gelu", "relu", "none"), 1, ("skinny_fwd 0", "skinny_dx 0", "big_dw 64")),
+    (129, (1000, 203, 4099, 70), ("gelu", "gelu", "none"), 2, ("skinny_fwd 0", "skinny_dx 0", "big_dw 128")),
+    (200, (2051, 203, 3003, 70), ("gelu", "gelu", "none"), 2, ("skinny_fwd 0", "skinny_dx 0", "ring_dx 128")),
+    (300, (2051, 333), ("gelu",), 3, ("skinny_fwd 0", "ring_dx 128")),
 ])
 @pytest.mark.parametrize("grouped", [False, True])
 def test_tiles_of_every_shape(rows, widths, acts, branches, want, grouped):
     wl = _chain(rows, widths, acts, branches, 2)          # (ungrouped: the second micro-batch adds to the gradients of the first)
     print(f"[case] rows={rows} widths={widths} branches={branches} grouped={grouped}", flush=True)
-    held = {p["kernel"].replace("gemm_", "") + f" {p['tile']}" + (f" of {p['slices']}" if p["slices"] else "") for p in _plan(wl)}
+    held = {_label(p) for p in _plan(wl)}
     assert grouped or held.issuperset(want), held
     if grouped:
         _, res, grads = _run(wl, 2, 2, False, flags=B.FLAG_GROUPED_DW)
@@ -153,11 +168,11 @@ def test_launch_tables_that_fit_on_16_bytes_only(slots, flags, monkeypatch):
         compare(wl, res, grads, stage, ref, label="gemm_tiles launch tables")
 
 
-# The eight-wave weight gradient: one round of 256 x 256 tiles over a long contraction, ragged in all three directions.
+# Weight gradients on one round of 256 x 128 tiles over a long contraction, ragged in all three directions.
 @pytest.mark.parametrize("rows,n_micro,flags", [(2050, 2, 0), (4100, 1, B.FLAG_GROUPED_DW)])
 def test_weight_gradient_on_large_tiles(rows, n_micro, flags):
     wl = _chain(rows, (4090, 4084), ("none",), 1, n_micro)
-    print(f"[case] eight-wave weight gradient rows={rows} flags={flags}", flush=True)
+    print(f"[case] 256 x 128 weight gradient rows={rows} flags={flags}", flush=True)
     assert [p["tile"] for p in _plan(wl, 1, flags) if p["kernel"] == "gemm_big_dw"] == [256]
     _, res, grads = _run(wl, 1, 1, False, flags=flags)
     stage, ref = run_oracle(wl)

@@ -535,6 +535,27 @@ def test_group_launches_give_the_one_stream_results_bit_for_bit():
             compare(wl, res, grads, ora_stage, ora_res, label="group launches vs oracle")
 
 
+# The few-row kernel's group form with several row blocks of 64 and 32 rows per member: where the launches have the GPU to themselves, and
+# where they share it behind a contraction that the ring-buffered tiles are not for.  One micro-batch a launch and two: the same bits.
+@pytest.mark.parametrize("mb,widths,hidden,shared_gpu", [(200, (70, 131, 9, 33), 1000, False), (130, (2051, 131, 9), 200, False), (130, (70, 8200, 9), 200, True)])
+def test_group_launches_of_several_row_blocks_on_the_few_row_kernel(mb, widths, hidden, shared_gpu):
+    wl = W.candle_uno(micro_batch=mb, n_micro=4, widths=widths, hidden=hidden, act="gelu")
+    flags = B.FLAG_GROUPED_DW | (B.FLAG_SHARED_GPU if shared_gpu else 0) | B.flag_group_launches(2)
+    desc, keep = B.build_desc(wl.ops, mb, 4, flags)
+    few = [p["kernel"] for p in B.gpp_stage_describe(desc) if p["kernel"].startswith("gemm_skinny") and not p["ring"]]
+    assert few[0] == "gemm_skinny_fwd" and (shared_gpu or "gemm_skinny_dx" in few), few
+    st = B.Stage(wl.ops, wl.micro_batch, wl.params, slots=4, flags=flags)
+    assert B.gpp_stage_group_launches(st.handle) == (2, 2)
+    st.close()
+    print(f"[case] {wl.name} b={mb} widths={widths} few-row group launches shared={shared_gpu}", flush=True)
+    _, res1, grads1 = _run(wl, 4, 4, False, reps=2, flags=flags)
+    for lanes in (True, False):
+        _, res, grads = _run(wl, 4, 4, True, reps=2, flags=flags, lanes=(2, 2), shared_lanes=lanes)
+        _same(res, grads, res1, grads1, f"few-row group launches shared lanes={lanes}")
+    ora_stage, ora_res = run_oracle(wl)
+    compare(wl, res, grads, ora_stage, ora_res, label="few-row group launches")
+
+
 def test_group_launches_on_a_mid_pipeline_stage_and_where_they_do_not_apply():
     # a stage with outputs: the group launches carry the output, output-gradient and input-gradient pointers of all
     # their micro-batches
