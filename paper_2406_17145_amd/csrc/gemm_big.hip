@@ -243,9 +243,6 @@ __device__ __forceinline__ void big_tile_body(const GemmProb &p, int m0, int n0,
     // beyond the contraction are copied like the others -- their rows lie outside the operand's buffer range and
     // read zero -- into buffers nobody multiplies any more, and the fragments read for a k-step that does not
     // exist are dropped.  The number of outstanding copies is then the same in every iteration.
-    // L2 prefetch PD k-steps ahead of the copies, issued BEHIND the copies of its iteration: the loads of a wave
-    // complete in order, so a wait for copies never includes the prefetch issued after them, only the one of the
-    // iteration before, which has had a whole k-step more
 #pragma unroll
     for (int u = 0; u < BUFS; ++u) fetch_direct(u, u);
     copies_landed_barrier<(BUFS - 1) * LPF>();
@@ -547,6 +544,9 @@ bool gemm_big_supported(const GemmProb &p) {
 // contractions, which the fit has none of, by 20 %; the few-row kernel is credited 5 %, and 15 % where it has fewer tiles than
 // compute units behind at least 30 k-steps (over 1342 launches: 17 % faster than with the large tiles and the few-row kernel
 // alone, 1.1 % of them more than 3 % slower).
+// Both rules meet in 4 x [512 x 1000] over contractions of 942, 3820, 2048 and 1, operands from memory: few-row 33.1, which it takes, ring 128 x 64
+// 36.4, 64 x 64 43.2, 128 x 128 69.3.  Ragged ones of one length on ring 128 x 64, which they take / the next best: 942 16.1 / 17.7,
+// 2042 25.2 / 29.0, 3820 41.5 / 48.4;  7 x [512 x 4096 x 2042] stays on 128 x 128: 108 / 121.
 int gemm_tile_choice(int form, int max_k, const GemmTileCounts &c, bool ring, bool large_tiles, bool whole_chunks, float *us) {
   constexpr float CUS = 256.0f;
   const float nk = (float)cdiv(max_k, GB_BK);

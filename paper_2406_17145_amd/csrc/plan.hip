@@ -2033,7 +2033,6 @@ void Emitter::emit_all_dw(std::vector<GemmProb> &recs, int passes) {
   }
   Step &sg = add_step(K_GEMM_DW_GROUP, push_table(recs), (int)recs.size(), blocks);
   sg.a0 = gemm_dw_group_streams(bytes) ? 1 : 0;
-
   sg.a2 = tile_rows;
 }
 
