@@ -449,7 +449,8 @@ gpp_status_t gpp_stage_embedding_sort_result(gpp_stage_t *stage, int32_t op, con
  * with a pair of HIP events on the caller's stream (events are created on first use: the only
  * allocation these calls ever make, and only in this mode).  profile_read waits for the recorded
  * events and returns, per tag, the accumulated milliseconds and kernel launches since the last
- * reset; ms and launches are HOST arrays of GPP_PROFILE_TAGS entries.  enable = R > 1 (at most 64) is a
+ * reset; ms and launches are HOST arrays of GPP_PROFILE_TAGS entries.  The tags gemm_skinny_fwd and gemm_skinny_dx hold
+ * the launches of the few-row family on either of its kernels (gpp_stage_describe tells them apart).  enable = R > 1 (at most 64) is a
  * TIMING-ONLY mode: every grouped GEMM launch is issued R times back to back inside its bracket, so that the
  * bracket's own dispatch latency (about two microseconds) is spread over R launches; accumulated gradients
  * and in-place sums of such a pass are meaningless. */

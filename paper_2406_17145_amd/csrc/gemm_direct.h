@@ -14,9 +14,10 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t rsrc4;   // buffer descriptor as the four scalar registers it is
 
 // A memory instruction may read a scalar register that a vector instruction (the readfirstlanes below) has written five wait states
-// later at the earliest.  A tile's two descriptors pass through here behind every such write and before any copy can read them, so that
-// no copy has to wait by itself (in each of them the wait cost the passes with ring-buffered GEMMs 0.4 - 1.6 %, here at most 0.1).  What the compiler could still put in
-// between, a register reloaded from a vector register, tests/test_device_code_cpu.py looks for in the built code.
+// later at the earliest.  A tile's two descriptors pass through here behind every such write and before any copy can read them, so
+// that no copy has to wait by itself (in each of them the wait cost the passes with ring-buffered GEMMs 0.4 - 1.6 %, here at most 0.3).
+// What the compiler could still put in between, a register reloaded from a vector register, tests/test_device_code_cpu.py looks for
+// in the built code.
 __device__ __forceinline__ void settle(rsrc4 &a, rsrc4 &b) { asm("s_nop 4" : "+s"(a), "+s"(b)); }
 // what matrix_rsrc describes: rows beyond the matrix, and chunks steered to OOB_OFFSET, read zero
 __device__ __forceinline__ rsrc4 matrix_rsrc4(const void *base, int rows, int64_t ld, int width) {
