@@ -461,7 +461,7 @@ struct Emitter {
   bool fork_open = false;
   std::vector<char> emb_hoisted;    // per node: its backward was issued early, on the side stream
   std::vector<int> written_level;   // level whose launches first wrote the node's gradient
-  std::vector<int> added_level[3];  // per kind of launch: the last level whose launch added to it in place
+  std::vector<int> added_level[3], added[3];  // per kind of launch: the last level that added to it in place, and how many of its records
   int cur_level = 0;
   int64_t shared_tmp_top;
 
@@ -640,6 +640,7 @@ struct Emitter {
   struct Target {
     Buf dst, addend;      // addend valid: kernel must add it (may equal dst)
     bool post = false;    // kernel wrote into a temporary `dst`; accumulate into `final` afterwards
+    int turn = 0;         // records of the level that add to `dst` in place before this one, each in a launch in front of this one's
     Buf final_dst;
   };
   std::vector<EltProb> post_copies;
@@ -678,9 +679,11 @@ struct Emitter {
       t.addend = gaddend[p];
       gstate[p] = G_WRITTEN;
       written_level[p] = cur_level;
-    } else if (can_addend && written_level[p] != cur_level && added_level[adds][p] != cur_level) {
-      t.addend = nd.gout;   // accumulate in place: every earlier writer ran in an earlier launch (one record of a launch, then)
+    } else if (can_addend && written_level[p] != cur_level) {
+      t.addend = nd.gout;   // accumulate in place: every earlier writer runs in an earlier launch, those of this level too
+      if (added_level[adds][p] != cur_level) added[adds][p] = 0;
       added_level[adds][p] = cur_level;
+      t.turn = added[adds][p]++;
     } else {                // a launch of this same level also writes it: go through a temporary
       t.post = true;
       t.final_dst = nd.gout;
@@ -1490,6 +1493,7 @@ void Emitter::backward() {
   dz_ready.assign(n, 0);
   written_level.assign(n, -1);
   for (auto &v : added_level) v.assign(n, -1);
+  for (auto &v : added) v.assign(n, 0);
   post_copies.clear();
   emb_hoisted.assign(n, 0);
   fork_open = false;
@@ -1599,8 +1603,12 @@ void Emitter::backward() {
 
     // 3. per-kind grouped backward launches
     std::vector<ColsumProb> colsums;
-    std::vector<GemmProb> gemms;
-    std::vector<LnProb> lns;
+    std::vector<std::vector<GemmProb>> gemms(1);      // per turn (Target::turn)
+    std::vector<std::vector<LnProb>> lns(1);
+    auto of_turn = [](auto &turns, int t) -> auto & {
+      if ((int)turns.size() <= t) turns.resize(t + 1);
+      return turns[t];
+    };
     std::vector<AttnProb> attns;
     std::vector<PoolProb> pools;
     std::vector<EmbProb> embs;
@@ -1651,7 +1659,7 @@ void Emitter::backward() {
             colsums.push_back(c);
           }
           if (!grouped) {
-            if (!later) gemms.push_back(w);
+            if (!later) gemms[0].push_back(w);
             pl.bwd_shared = true;   // accumulates into the parameter's gradient: backward passes stay in order
           }
           if (head_loss[i] >= 0) {
@@ -1713,7 +1721,7 @@ void Emitter::backward() {
               g.aux_dtype = ms.dtype;
               dz_ready[nd.in[0]] = 1;
             }
-            gemms.push_back(g);
+            of_turn(gemms, tg.turn).push_back(g);
           }
           break;
         }
@@ -1736,8 +1744,10 @@ void Emitter::backward() {
           l.rows = (int32_t)nd.rows;
           l.d = (int32_t)nd.feat;
           l.eps = (float)d.eps;
+          int turn = 0;
           if (x.wants_grad) {
             Target tg = acquire(nd.in[0], ADDS_NORM);
+            turn = tg.turn;
             l.y = ptr(tg.dst);
             l.ldy = tg.dst.ld;
             l.y_dtype = tg.dst.dtype;
@@ -1747,7 +1757,7 @@ void Emitter::backward() {
               l.add_dtype = tg.addend.dtype;
             }
           }
-          lns.push_back(l);
+          of_turn(lns, turn).push_back(l);
           break;
         }
         case GPP_OP_ATTENTION: {
@@ -1848,13 +1858,14 @@ void Emitter::backward() {
       pl.bwd_shared = true;   // accumulates parameter gradients in the order of the backward passes
       add_step(K_COLSUM, push_table(colsums), (int)colsums.size(), blocks);
     }
-    emit_gemms(gemms);
-    if (!lns.empty()) {
+    for (auto &turn : gemms) emit_gemms(turn);
+    for (auto &turn : lns) {
+      if (turn.empty()) continue;
       // first kernel: dx rows and per-row-block partial parameter sums; operators without partial
       // scratch and without a dx consumer skip it
       std::vector<LnProb> dx;
       int blocks = 0, max_d = 0;
-      for (auto &l : lns)
+      for (auto &l : turn)
         if (l.y || l.partial) {
           l.row_blocks = (l.rows + ln_bwd_rows_per_block() - 1) / ln_bwd_rows_per_block();
           LnProb c = l;
@@ -1879,7 +1890,7 @@ void Emitter::backward() {
       // pass instead of one per level (four launches of 6 us in the two-layer transformer stage); the others read
       // x and dy, which later levels may overwrite, and are folded here.
       std::vector<LnProb> now;
-      for (auto &l : lns) (l.partial ? ln_fold_later : now).push_back(l);
+      for (auto &l : turn) (l.partial ? ln_fold_later : now).push_back(l);
       pl.bwd_shared = true;   // accumulates parameter gradients in the order of the backward passes
       if (!now.empty()) {
         blocks = 0;

@@ -233,17 +233,18 @@ def test_a_merge_with_masked_layers_anywhere_inside_shares_no_gradient(layers, d
 
 
 @pytest.mark.parametrize("hidden", [False, True])
-@pytest.mark.parametrize("kinds,copies", [
-    (("none", "none"), 1), (("gelu", "none", "gelu"), 2), (("none", "norm"), 0), (("norm", "gelu", "norm"), 1)])
-def test_one_record_of_a_launch_adds_to_a_gradient_in_place(kinds, copies, hidden):
-    """What is already written is read and written by one record of a level's launch; the others, whose workgroups run beside it,
-    write buffers of their own, which copies behind the level's launches add one by one."""
+@pytest.mark.parametrize("kinds", [("none", "none"), ("gelu", "none", "gelu"), ("none", "norm"), ("norm", "gelu", "norm")])
+def test_one_record_of_a_launch_adds_to_a_gradient_in_place(kinds, hidden):
+    """What is already written is read and written by one record of a launch; the next one of the level, whose workgroups would run
+    beside it, is in a launch behind it.  Nothing else than that is launched more."""
     steps = [p for p in plan(skipped(kinds, hidden), 100) if p["pass"] == "backward"]
-    of_level = [i for i, p in enumerate(steps) if p["kernel"] in ("gemm_skinny_dx", "gemm_bwd_merged_dx_dw", "layernorm_bwd_dx")]
-    behind = [p["kernel"] for p in steps[of_level[-2 if hidden else -1] + 1:]]       # (the last launch: of the layer in front)
-    behind = behind[:behind.index("gemm_bwd_merged_dx_dw")] if hidden else behind
-    # (without a layer in front the input's gradient is copied out; hidden layers multiply by their derivative in place)
-    assert [k for k in behind if k == "elt_bwd"] == ["elt_bwd"] * (copies + 1), steps
+    gemms = [p["records"] for p in steps if p["kernel"] in ("gemm_skinny_dx", "gemm_bwd_merged_dx_dw")]
+    norms = [p["records"] for p in steps if p["kernel"] == "layernorm_bwd_dx"]
+    n = sum(k != "norm" for k in kinds)
+    assert gemms == [n + 1] + [1] * (n - 1) + [2] * hidden and norms == [1] * (len(kinds) - n)      # (weight gradients with the first)
+    # a copy of the first addition's gradient, the others added to it, the level's derivatives (in copies of their own); then the
+    # derivative of the layer in front, or the input's gradient on its way to the caller
+    assert sum(p["kernel"] == "elt_bwd" for p in steps) == len(kinds) + ("gelu" in kinds) + 1, steps
 
 
 @pytest.mark.parametrize("rows,kernel", [(1048512, "gemm_big_dw"), (1048513, "gemm_mfma_dw"), (1048575, "gemm_mfma_dw")])
