@@ -232,12 +232,12 @@ def test_operands_of_four_gib(rows):
     st.forward(0, [x], outs)
     st.backward(0, [dy], gins)
     st.sync_status()
-    dw = torch.zeros(64, 2048, device=st.dev, dtype=torch.float64)
+    dw, db = torch.zeros(64, 2048, device=st.dev, dtype=torch.float64), dy.double().sum(0)
     for a in range(0, rows, 1 << 16):
         xs, ds = x[a:a + (1 << 16)].float(), dy[a:a + (1 << 16)].float()
         for got, want in ((outs[0][a:a + (1 << 16)], xs @ w.T), (gins[0][a:a + (1 << 16)], ds @ w)):
             assert ((got.float() - want).norm() / want.norm()).item() < 4e-3, a
         dw += (ds.T @ xs).double()
-    got = torch.from_numpy(st.grads_numpy()[1]["W"]).to(st.dev).double()
+    grads = {k: torch.from_numpy(v).to(st.dev).double() for k, v in st.grads_numpy()[1].items()}
     st.close()
-    assert ((got - dw).norm() / dw.norm()).item() < 1e-4
+    assert ((grads["W"] - dw).norm() / dw.norm()).item() < 1e-4 and ((grads["b"] - db).norm() / db.norm()).item() < 1e-4
